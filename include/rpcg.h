@@ -104,11 +104,14 @@ typedef struct {
                               events in the loop; 0: none (default). Other values:
                               RPCG_ERR_INVALID */
     int32_t xcd_parts;     /* SpMV work split into this many contiguous row ranges, one per
-                              XCD (0 = auto = 1, no split). Results do not depend on it. */
+                              XCD (0 = auto: one per XCD where the rows of the matrix
+                              line up by their column offsets, else 1). Results do not
+                              depend on it. */
     int32_t spmv_block_size; /* solver SpMV kernel: threads per workgroup (0 = auto) */
     int32_t spmv_grid_size;  /* solver SpMV kernel: workgroups (0 = auto) */
     int32_t no_col16;        /* 1: keep 32-bit column indices in the solver's matrix copy even
-                                when every |column - row| fits 16 bits (default 0) */
+                                where the columns fit 16-bit codes or need no storage
+                                (default 0) */
     double *tau_history;   /* optional DEVICE array of maxit+1 doubles: tau^(0..L) */
 } rpcg_opts;
 
@@ -187,11 +190,14 @@ int rpcg_spmv(rpcg_ctx *ctx, const rpcg_csr *A /* host struct */, const double *
               void *stream);
 
 /* A matrix prepared for repeated products (Section 4.3 SpMV): a device copy
- * in the solver's sliced-ELL layout (binary64 values, 16-bit column codes
- * where the columns allow them; about 10 bytes per stored entry plus 9 bytes
- * per row), owned by the handle. Products with it are the same fma chains as
- * rpcg_spmv, so y is bit-identical to rpcg_spmv on the matrix it was made
- * from, at the streaming rate of the solver's own SpMV. */
+ * in the solver's layout, owned by the handle. Where the rows line up by their
+ * column offsets (stencils, bands) it holds 8 bytes per stored entry, or next
+ * to nothing where the entries are also constant along the offsets; else a
+ * sliced-ELL copy (binary64 values, 16-bit column codes where the columns
+ * allow them; about 10 bytes per stored entry plus 9 bytes per row). Products
+ * with it are the same fma chains as rpcg_spmv, so y is bit-identical to
+ * rpcg_spmv on the matrix it was made from, at the rate of the solver's own
+ * SpMV. */
 typedef struct rpcg_smat rpcg_smat;
 
 /* Builds the copy of A (device CSR; its structure is checked on the device,

@@ -52,7 +52,7 @@ static LaunchCfg make_cfg(const rpcg_ctx *c, const rpcg_opts &o, long long work_
     cfg.early_exit = o.early_exit != 0;
     cfg.fpe_size = o.fpe_size;
     cfg.fallback = o.fpe_fallback != 0;
-    cfg.xcd_parts = o.xcd_parts ? o.xcd_parts : 1;
+    cfg.xcd_parts = o.xcd_parts;
     cfg.stream = s;
     return cfg;
 }
@@ -66,17 +66,19 @@ static LaunchCfg make_vec_cfg(const rpcg_ctx *c, const rpcg_opts &o, long long n
     return cfg;
 }
 
-// SpMV kernel: one wavefront per 64-row slice at a time; own overrides. The
-// binary32 kernel keeps fewer bytes in flight per wavefront and wants twice
-// the workgroups of the binary64 one.
-static LaunchCfg make_spmv_cfg(const rpcg_ctx *c, const rpcg_opts &o, long long nslices, hipStream_t s,
+// SpMV kernel: one wavefront per slice at a time; own overrides. The binary32
+// kernel keeps fewer bytes in flight per wavefront and wants twice the
+// workgroups of the binary64 one. Over diagonal-aligned slices the loop waits
+// on gathers, not on the matrix stream, and wants every wavefront the
+// registers allow (16 per CU).
+static LaunchCfg make_spmv_cfg(const rpcg_ctx *c, const rpcg_opts &o, long long nslices, bool diag, hipStream_t s,
                                bool f32 = false)
 {
     rpcg_opts q = o;
     q.block_size = o.spmv_block_size;
     q.grid_size = o.spmv_grid_size;
-    LaunchCfg cfg = make_cfg(c, q, std::max(1ll, nslices * 64), 256, s);
-    const long long cap = (f32 ? 4ll : 2ll) * c->num_cus;
+    LaunchCfg cfg = make_cfg(c, q, std::max(1ll, nslices * 64), diag && nslices > 4ll * c->num_cus ? 512 : 256, s);
+    const long long cap = (!diag && f32 ? 4ll : 2ll) * c->num_cus;
     if (!q.grid_size) cfg.grid = (int)std::max(1ll, std::min((nslices * 64 + cfg.block - 1) / cfg.block, cap));
     return cfg;
 }
@@ -134,6 +136,8 @@ int rpcg_create(rpcg_ctx **out, int device)
     if (rc == RPCG_OK) rc = hip_status(hipHostMalloc((void **)&c->host_done, 64 * sizeof(int), hipHostMallocDefault));
     if (rc == RPCG_OK) rc = hip_status(hipHostMalloc((void **)&c->host_state, sizeof(PcgState), hipHostMallocDefault));
     if (rc == RPCG_OK) rc = hip_status(hipHostMalloc((void **)&c->host_ir, sizeof(IrState), hipHostMallocDefault));
+    if (rc == RPCG_OK)
+        rc = hip_status(hipHostMalloc((void **)&c->host_info, sizeof(DotInfo) + sizeof(long long), hipHostMallocDefault));
     if (rc == RPCG_OK) rc = hip_status(hipEventCreateWithFlags(&c->poll_ev[0], hipEventDisableTiming));
     if (rc == RPCG_OK) rc = hip_status(hipEventCreateWithFlags(&c->poll_ev[1], hipEventDisableTiming));
     if (rc == RPCG_OK) rc = ensure_ws(c, 8 * c->num_cus);
@@ -155,13 +159,16 @@ void rpcg_destroy(rpcg_ctx *c)
     c->sell_col.release();
     c->sell_cfirst.release();
     c->sell_len.release();
-    c->scan_scratch.release();
+    c->diag_ds.release();
+    c->diag_de.release();
+    c->widths.release();
     c->vecs.release();
     c->ir_vecs.release();
     c->beta_hist.release();
     if (c->host_done) (void)hipHostFree(c->host_done);
     if (c->host_state) (void)hipHostFree(c->host_state);
     if (c->host_ir) (void)hipHostFree(c->host_ir);
+    if (c->host_info) (void)hipHostFree(c->host_info);
     for (hipEvent_t e : c->events) (void)hipEventDestroy(e);
     for (hipEvent_t e : c->ir_events) (void)hipEventDestroy(e);
     for (hipEvent_t e : c->poll_ev) if (e) (void)hipEventDestroy(e);
@@ -290,41 +297,83 @@ struct SellBuilt {
     const unsigned short *col16p = nullptr;
     const int *cfirst = nullptr;
     const unsigned char *len8 = nullptr;
+    const DiagSlice *ds = nullptr; // diagonal-aligned slices instead of off, col, ...
+    const DiagEnt *de = nullptr;
 };
 
 // Device buffers a sliced-ELL copy is built into (the context's for the
 // solver, a rpcg_smat's own for prepared matrices).
 struct SellBufs {
-    rpcg_host::Buffer *off, *val, *val32, *col, *cfirst, *len;
+    rpcg_host::Buffer *off, *val, *val32, *col, *cfirst, *len, *ds, *de;
 };
 
 static SellBufs ctx_sell_bufs(rpcg_ctx *c)
 {
-    return {&c->sell_off, &c->sell_val, &c->sell_val32, &c->sell_col, &c->sell_cfirst, &c->sell_len};
+    return {&c->sell_off, &c->sell_val, &c->sell_val32, &c->sell_col, &c->sell_cfirst, &c->sell_len,
+            &c->diag_ds, &c->diag_de};
 }
 
-// One pass over the CSR checks its structure and measures the slices
-// (nothing indexes through the matrix before the check has passed), then the
-// copy is filled. Source values: v64 or v32; kept as binary64 (out64) and/or
-// rounded to binary32 (out32). The interleave is that of the solver's value
-// type: two entries for a binary64-only copy, one when binary32 values are
-// kept. Waits for the stream.
+// Builds the copy of a CSR matrix. The row pointers are checked and the slices
+// measured first (nothing indexes through the matrix before that). Rows that
+// line up give diagonal-aligned slices (no column data, and no values either
+// where the coefficients are constant along them) as far as diag_worth_it. Otherwise one pass over the entries checks the columns and
+// measures the 16-bit codes and the general sliced-ELL copy is filled. Source
+// values: v64 or v32; kept as binary64 (out64) and/or rounded to binary32
+// (out32). The general copy's interleave is that of the solver's value type:
+// two entries for a binary64-only copy, one when binary32 values are kept.
+// no_col16 asks for 32-bit columns, that is the general copy. Waits for the stream.
 static int build_sell(rpcg_ctx *c, const SellBufs &bf, int n, int nnz, const int *rp, const int *col,
                       const double *v64, const float *v32, bool out64, bool out32, bool no_col16, hipStream_t s,
                       SellBuilt *out)
 {
     const int nslices = (n + 63) / 64;
     const int vec = out32 ? sell_vec<float>() : sell_vec<double>();
+    DotInfo &scan_info = *c->host_info;
+    long long &padded = *(long long *)(c->host_info + 1);
+    out->nslices = nslices;
     RPCG_TRY(hipMemsetAsync(c->info, 0, sizeof(DotInfo), s));
-    RPCG_TRY(bf.off->ensure(sizeof(long long) * (nslices + 1)));
+    const int nd = (n + DIAG_ROWS - 1) / DIAG_ROWS, nw = 2 * nd; // 128-row slices, widths
+    RPCG_TRY(bf.off->ensure(sizeof(long long) * (nw + 1)));
+    RPCG_TRY(c->widths.ensure(sizeof(int) * ((size_t)nw + DIAG_TABLE)));
     long long *off = (long long *)bf.off->p;
-    RPCG_TRY(hipMemsetAsync(off, 0, sizeof(long long) * (nslices + 1), s));
-    RPCG_TRY(launch_csr_scan(n, nnz, rp, col, vec, off + 1, &c->info->flags, &c->info->max_len,
-                             &c->info->max_delta, s));
-    RPCG_TRY(launch_sell_scan(off, nslices, s));
-    long long padded = 0;
-    DotInfo scan_info;
-    RPCG_TRY(hipMemcpyAsync(&padded, off + nslices, sizeof padded, hipMemcpyDeviceToHost, s));
+    int *table = (int *)c->widths.p, *w = table + DIAG_TABLE;
+    RPCG_TRY(launch_row_widths(n, nnz, rp, w, &c->info->flags, &c->info->max_len, s));
+    RPCG_TRY(launch_scan_len(w, nw, off, 1, true, s));
+    padded = 0;
+    if (nw > 0) RPCG_TRY(hipMemcpyAsync(&padded, off + nw, sizeof padded, hipMemcpyDeviceToHost, s));
+    RPCG_TRY(hipMemcpyAsync(&scan_info, c->info, sizeof scan_info, hipMemcpyDeviceToHost, s));
+    RPCG_TRY(hipStreamSynchronize(s));
+    if (scan_info.flags) return RPCG_ERR_INVALID;
+    if (!no_col16 && padded > 0 && scan_info.max_len <= DIAG_MAX_ROW) {
+        RPCG_TRY(bf.ds->ensure(sizeof(DiagSlice) * nd));
+        RPCG_TRY(bf.de->ensure(sizeof(DiagEnt) * (size_t)diag_mpos(padded, nd)));
+        DiagSlice *ds = (DiagSlice *)bf.ds->p;
+        DiagEnt *de = (DiagEnt *)bf.de->p;
+        RPCG_TRY(hipMemsetAsync(table, 0xFF, sizeof(int) * DIAG_TABLE, s));
+        RPCG_TRY(launch_diag_align(n, 0, rp, col, v64, v32, off, de, ds, w, table, c->info, s));
+        RPCG_TRY(hipMemcpyAsync(&scan_info, c->info, sizeof scan_info, hipMemcpyDeviceToHost, s));
+        RPCG_TRY(hipStreamSynchronize(s));
+        if (!scan_info.diag_fail && diag_worth_it(scan_info.diag_total, scan_info.diag_values, nnz)) {
+            if (scan_info.flags) return RPCG_ERR_INVALID;
+            RPCG_TRY(launch_diag_share(nd, de, ds, table, s));
+            double *s64 = nullptr;
+            float *s32 = nullptr;
+            const size_t nv = DIAG_ROWS * (size_t)scan_info.diag_values;
+            if (nv > 0) {
+                if (out64) { RPCG_TRY(bf.val->ensure(sizeof(double) * nv)); s64 = (double *)bf.val->p; }
+                if (out32) { RPCG_TRY(bf.val32->ensure(sizeof(float) * nv)); s32 = (float *)bf.val32->p; }
+                RPCG_TRY(launch_scan_len(w, nd, &ds->vpos, sizeof(DiagSlice) / sizeof(long long), false, s));
+                RPCG_TRY(launch_diag_fill(n, rp, v64, v32, de, ds, s64, s32, s));
+            }
+            out->nslices = nd;
+            out->val64 = s64;
+            out->val32 = s32;
+            out->ds = ds;
+            out->de = de;
+            return RPCG_OK;
+        }
+    }
+    RPCG_TRY(launch_csr_scan(n, nnz, rp, col, &c->info->flags, &c->info->max_len, &c->info->max_delta, s));
     RPCG_TRY(hipMemcpyAsync(&scan_info, c->info, sizeof scan_info, hipMemcpyDeviceToHost, s));
     RPCG_TRY(hipStreamSynchronize(s));
     if (scan_info.flags) return RPCG_ERR_INVALID;
@@ -347,7 +396,6 @@ static int build_sell(rpcg_ctx *c, const SellBufs &bf, int n, int nnz, const int
     }
     RPCG_TRY(launch_sell_fill(n, rp, col, v64, v32, vec, off, s64, s32, col16 ? nullptr : (int *)bf.col->p,
                               col16 ? (unsigned short *)bf.col->p : nullptr, cfirst, len8, s));
-    out->nslices = nslices;
     out->col16 = col16;
     out->off = off;
     out->val64 = s64;
@@ -373,6 +421,8 @@ static SellMat<T> sell_mat(const SellBuilt &B, const T *val, int n, const int *r
     M.row_ptr = row_ptr;
     M.len8 = B.len8;
     M.val64 = B.val64;
+    M.ds = B.ds;
+    M.de = B.de;
     return M;
 }
 
@@ -539,12 +589,10 @@ static bool valid_csr_f32(const rpcg_csr_f32 *A)
 // columns in range), with the scan of the sliced-ELL construction.
 static int check_csr(rpcg_ctx *c, const rpcg_csr *E, hipStream_t s)
 {
-    const int nslices = (E->n + 63) / 64;
-    RPCG_TRY(c->scan_scratch.ensure(sizeof(long long) * (nslices + 1)));
     RPCG_TRY(hipMemsetAsync(c->info, 0, sizeof(DotInfo), s));
-    RPCG_TRY(launch_csr_scan(E->n, E->nnz, E->row_ptr, E->col_idx, 1, (long long *)c->scan_scratch.p + 1,
-                             &c->info->flags, &c->info->max_len, &c->info->max_delta, s));
-    DotInfo inf;
+    RPCG_TRY(launch_csr_scan(E->n, E->nnz, E->row_ptr, E->col_idx, &c->info->flags, &c->info->max_len,
+                             &c->info->max_delta, s));
+    DotInfo &inf = *c->host_info;
     RPCG_TRY(hipMemcpyAsync(&inf, c->info, sizeof inf, hipMemcpyDeviceToHost, s));
     RPCG_TRY(hipStreamSynchronize(s));
     return inf.flags ? RPCG_ERR_INVALID : RPCG_OK;
@@ -565,19 +613,18 @@ static int pcg_solve_any(rpcg_ctx *c, int mode, int n, int nnz, const int *rp, c
     RPCG_TRY(hipSetDevice(c->device));
     hipStream_t s = (hipStream_t)stream;
     auto t0 = std::chrono::steady_clock::now();
-    const int nslices = (n + 63) / 64;
     constexpr bool F32 = std::is_same<T, float>::value;
+    SellBuilt B;
+    int rc = build_sell(c, ctx_sell_bufs(c), n, nnz, rp, col, v64, v32, !F32, F32, o.no_col16 != 0, s, &B);
+    if (rc != RPCG_OK) return rc;
     LaunchCfg cfg_rows = make_vec_cfg(c, o, std::max(1, n), s);
-    LaunchCfg cfg_sl = make_spmv_cfg(c, o, nslices, s, F32);
+    LaunchCfg cfg_sl = make_spmv_cfg(c, o, B.nslices, B.ds != nullptr, s, F32);
     // EXBLAS results do not depend on the lane expansion length. With the
     // default, the binary64 SpMV kernel (and the setup) keep four terms: its
     // <d, w> lanes then flush to the long accumulator less often, while the
     // vector kernels' two dots per element are cheapest with three
     if (!F32 && mode == MODE_EXBLAS && (!opts || opts->fpe_size == 0)) cfg_sl.fpe_size = 4;
-    int rc = ensure_ws(c, std::max(cfg_rows.grid, cfg_sl.grid));
-    if (rc != RPCG_OK) return rc;
-    SellBuilt B;
-    rc = build_sell(c, ctx_sell_bufs(c), n, nnz, rp, col, v64, v32, !F32, F32, o.no_col16 != 0, s, &B);
+    rc = ensure_ws(c, std::max(cfg_rows.grid, cfg_sl.grid));
     if (rc != RPCG_OK) return rc;
     for (const rpcg_csr *E : {extra0, extra1}) {
         if (!E) continue;
@@ -677,17 +724,17 @@ static int ir_body(rpcg_ctx *c, int mode, const rpcg_csr *A, const double *b, do
     o.fpe_size = resolve_fpe_size(o.fpe_size, mode);
     const int nslices = (n + 63) / 64;
     LaunchCfg cfg_rows = make_vec_cfg(c, o, std::max(1, n), s);
-    LaunchCfg cfg_sl = make_spmv_cfg(c, o, nslices, s, true);
+    SellBuilt B;
+    int rc = build_sell(c, ctx_sell_bufs(c), n, A->nnz, A->row_ptr, A->col_idx, A->val, nullptr, true, true,
+                        o.no_col16 != 0, s, &B);
+    if (rc != RPCG_OK) return rc;
+    LaunchCfg cfg_sl = make_spmv_cfg(c, o, B.nslices, B.ds != nullptr, s, true);
     LaunchCfg cfg_res = make_res_cfg(c, nslices, s);
     rpcg_opts dflt;
     rpcg_opts_default(&dflt);
     dflt.fpe_size = 3;
     LaunchCfg cfg_dot = make_cfg(c, dflt, std::max(1, (n + 7) / 8), 256, s);
-    int rc = ensure_ws(c, std::max(std::max(cfg_rows.grid, cfg_sl.grid), std::max(cfg_res.grid, cfg_dot.grid)));
-    if (rc != RPCG_OK) return rc;
-    SellBuilt B;
-    rc = build_sell(c, ctx_sell_bufs(c), n, A->nnz, A->row_ptr, A->col_idx, A->val, nullptr, true, true, o.no_col16 != 0, s,
-                    &B);
+    rc = ensure_ws(c, std::max(std::max(cfg_rows.grid, cfg_sl.grid), std::max(cfg_res.grid, cfg_dot.grid)));
     if (rc != RPCG_OK) return rc;
     SellMat<float> M = sell_mat<float>(B, B.val32, n, A->row_ptr);
     const size_t nn = (size_t)std::max(1, n);
@@ -805,16 +852,20 @@ struct rpcg_smat {
     int device = 0;
     int num_cus = 256;
     int n = 0;
-    rpcg_host::Buffer off, val, val32, col, cfirst, len, rp;
+    rpcg_host::Buffer off, val, val32, col, cfirst, len, rp, ds, de;
     SellBuilt B;
 };
 
 static int smat_build(rpcg_ctx *c, const rpcg_csr *A, rpcg_smat *M, hipStream_t s)
 {
-    const SellBufs bf{&M->off, &M->val, &M->val32, &M->col, &M->cfirst, &M->len};
+    const SellBufs bf{&M->off, &M->val, &M->val32, &M->col, &M->cfirst, &M->len, &M->ds, &M->de};
     int rc = build_sell(c, bf, A->n, A->nnz, A->row_ptr, A->col_idx, A->val, nullptr, true, false, false, s, &M->B);
     if (rc != RPCG_OK) return rc;
-    if (!M->B.len8) { // rows of 256 or more entries: the row lengths come from a copy of row_ptr
+    if (!M->B.ds) { // the merge's scratch is not kept
+        M->ds.release();
+        M->de.release();
+    }
+    if (!M->B.len8 && !M->B.ds) { // rows of 256 or more entries: the row lengths come from a copy of row_ptr
         RPCG_TRY(M->rp.ensure(sizeof(int) * ((size_t)A->n + 1)));
         RPCG_TRY(hipMemcpyAsync(M->rp.p, A->row_ptr, sizeof(int) * ((size_t)A->n + 1), hipMemcpyDeviceToDevice, s));
     }
@@ -849,9 +900,10 @@ int rpcg_smat_spmv(rpcg_smat *M, const double *x, double *y, void *stream)
     if (M->n == 0) return RPCG_OK;
     RPCG_TRY(hipSetDevice(M->device));
     const SellMat<double> A = sell_mat<double>(M->B, M->B.val64, M->n, (const int *)M->rp.p);
-    // one workgroup of four wavefronts per four slices, at most two per CU
+    // one workgroup of four wavefronts per four slices; at most two per CU, four
+    // over diagonal-aligned slices (they wait on gathers, not on the matrix stream)
     const long long want = ((long long)M->B.nslices + 3) / 4;
-    const int grid = (int)std::max(1ll, std::min(want, 2ll * M->num_cus));
+    const int grid = (int)std::max(1ll, std::min(want, (M->B.ds ? 4ll : 2ll) * M->num_cus));
     RPCG_TRY(launch_sell_spmv(A, x, y, grid, (hipStream_t)stream));
     return RPCG_OK;
 }
@@ -860,7 +912,8 @@ void rpcg_smat_destroy(rpcg_smat *M)
 {
     if (!M) return;
     (void)hipSetDevice(M->device); // teardown: nothing to report to
-    for (rpcg_host::Buffer *b : {&M->off, &M->val, &M->val32, &M->col, &M->cfirst, &M->len, &M->rp}) b->release();
+    for (rpcg_host::Buffer *b : {&M->off, &M->val, &M->val32, &M->col, &M->cfirst, &M->len, &M->rp, &M->ds, &M->de})
+        b->release();
     delete M;
 }
 

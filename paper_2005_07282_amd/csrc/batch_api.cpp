@@ -25,8 +25,8 @@ struct rpcg_batch {
     std::vector<BatchSys> sys;         // per system (slot ranges follow the schedule)
     std::vector<long long> off_host;   // concatenated slice offsets
     long long total_rows = 0, total_slices = 0;
-    bool col16 = false;
-    Buffer off, val, col, cfirst, len8;
+    int layout = LAY_COL32;
+    Buffer off, val, col, cfirst, len8, ds, de;
     Buffer vecs;                       // b, x, r, z, d, w, dinv
     Buffer st, hist_ptrs, active;
     Buffer dsys, druns, dwg;
@@ -112,6 +112,7 @@ void compute_schedule(rpcg_batch *B, const std::vector<char> *active, std::vecto
 {
     const rpcg_batch_tuning &t = B->tuning;
     const int G = t.grid_size;
+    const int step = B->layout == LAY_DIAG ? 2 : 1; // runs start at whole slices of the layout
     auto on = [&](int q) { return !active || (*active)[q]; };
     std::vector<std::vector<BatchRun>> per_wg(G);
     auto add = [&](int g, int sys, int s) {
@@ -131,14 +132,14 @@ void compute_schedule(rpcg_batch *B, const std::vector<char> *active, std::vecto
             if (!on(q)) continue;
             for (int s = 0; s < B->sys[q].nslices; ++s) {
                 const long long gsl = B->sys[q].slice0 + s;
-                if (acc >= target && g < G - 1) { ++g; acc = 0; }
+                if (acc >= target && g < G - 1 && s % step == 0) { ++g; acc = 0; }
                 add(g, q, s);
                 acc += std::max(64ll, B->off_host[gsl + 1] - B->off_host[gsl]);
             }
         }
     } else {
         // tiles of tile_slices slices, systems interleaved, dealt round-robin
-        const int T = t.tile_slices;
+        const int T = (t.tile_slices + step - 1) / step * step;
         long long i = 0;
         int max_tiles = 0;
         for (int q = 0; q < B->nsys; ++q) max_tiles = std::max(max_tiles, (B->sys[q].nslices + T - 1) / T);
@@ -250,9 +251,11 @@ BatchArgs batch_args(const rpcg_batch *B, bool with_hist)
     a.wg_run = (const int *)B->dwg.p;
     a.off = (const long long *)B->off.p;
     a.val = (const double *)B->val.p;
-    a.col = B->col16 ? nullptr : (const int *)B->col.p;
-    a.col16 = B->col16 ? (const unsigned short *)B->col.p : nullptr;
-    a.cfirst = B->col16 ? (const int *)B->cfirst.p : nullptr;
+    a.col = B->layout == LAY_COL32 ? (const int *)B->col.p : nullptr;
+    a.col16 = B->layout == LAY_COL16 ? (const unsigned short *)B->col.p : nullptr;
+    a.cfirst = B->layout == LAY_COL16 ? (const int *)B->cfirst.p : nullptr;
+    a.ds = B->layout == LAY_DIAG ? (const DiagSlice *)B->ds.p : nullptr;
+    a.de = B->layout == LAY_DIAG ? (const DiagEnt *)B->de.p : nullptr;
     a.len8 = B->len8.p ? (const unsigned char *)B->len8.p : nullptr;
     double *v = (double *)B->vecs.p;
     const size_t T = (size_t)B->total_rows;
@@ -295,7 +298,7 @@ int batch_start(rpcg_batch *B, const double *const *b, double *const *x, bool wi
     }
     if (!x) RPCG_TRY(hipMemsetAsync(v + T, 0, sizeof(double) * T, B->gs));
     const BatchArgs a = batch_args(B, with_hist);
-    RPCG_TRY(launch_batch_setup(B->mode, B->col16, a, B->tuning.grid_size, B->tuning.block_size, B->ws, B->ws_cap,
+    RPCG_TRY(launch_batch_setup(B->mode, B->layout, a, B->tuning.grid_size, B->tuning.block_size, B->ws, B->ws_cap,
                                 B->o.tol, B->o.maxit, batch_cfg(B)));
     return RPCG_OK;
 }
@@ -309,7 +312,7 @@ int capture_graph(rpcg_batch *B, bool with_hist)
     RPCG_TRY(hipStreamBeginCapture(B->gs, hipStreamCaptureModeThreadLocal));
     hipError_t err = hipSuccess;
     for (int i = 0; i < B->tuning.graph_iterations && err == hipSuccess; ++i)
-        err = launch_batch_iteration(B->mode, B->col16, a, B->tuning.grid_size, B->tuning.block_size, B->ws,
+        err = launch_batch_iteration(B->mode, B->layout, a, B->tuning.grid_size, B->tuning.block_size, B->ws,
                                      B->ws_cap, cfg);
     hipGraph_t g = nullptr;
     hipError_t e2 = hipStreamEndCapture(B->gs, &g);
@@ -345,7 +348,7 @@ void rpcg_batch_destroy(rpcg_batch *B)
     (void)hipSetDevice(B->ctx->device); // teardown reports nothing
     if (B->gs) (void)hipStreamSynchronize(B->gs);
     drop_graph(B);
-    for (Buffer *b : {&B->off, &B->val, &B->col, &B->cfirst, &B->len8, &B->vecs, &B->st, &B->hist_ptrs, &B->active,
+    for (Buffer *b : {&B->off, &B->val, &B->col, &B->cfirst, &B->len8, &B->ds, &B->de, &B->vecs, &B->st, &B->hist_ptrs, &B->active,
                       &B->dsys, &B->druns, &B->dwg, &B->ws_mem})
         b->release();
     for (hipEvent_t e : {B->ev_in, B->ev_out, B->poll_ev[0], B->poll_ev[1], B->t_ev[0], B->t_ev[1], B->stage_ev[0],
@@ -371,7 +374,7 @@ static int batch_create_body(rpcg_batch *B, const rpcg_csr *A, hipStream_t calle
     RPCG_TRY(hipHostMalloc((void **)&B->host_poll_st, 2 * sizeof(PcgState) * B->nsys, hipHostMallocDefault));
     RPCG_TRY(hipEventCreateWithFlags(&B->stage_ev[0], hipEventDisableTiming));
     RPCG_TRY(hipEventCreateWithFlags(&B->stage_ev[1], hipEventDisableTiming));
-    // layout: each system's rows start at a multiple of 64, its slices after the previous system's
+    // layout: each system's rows start at a multiple of 128, its slices after the previous system's
     B->sys.resize(B->nsys);
     long long row0 = 0, slice0 = 0;
     for (int q = 0; q < B->nsys; ++q) {
@@ -382,8 +385,8 @@ static int batch_create_body(rpcg_batch *B, const rpcg_csr *A, hipStream_t calle
         S.nslices = (A[q].n + 63) / 64;
         S.slot0 = S.slot1 = 0;
         S.row_ptr = A[q].row_ptr;
-        row0 += 64ll * S.nslices;
-        slice0 += S.nslices;
+        slice0 += (S.nslices + 1) / 2 * 2; // an even number of 64-row slices: whole 128-row slices
+        row0 = 64 * slice0;
     }
     B->total_rows = std::max(64ll, row0);
     B->total_slices = slice0;
@@ -392,13 +395,15 @@ static int batch_create_body(rpcg_batch *B, const rpcg_csr *A, hipStream_t calle
     RPCG_TRY(hipStreamWaitEvent(B->gs, B->ev_in, 0));
     RPCG_TRY(B->off.ensure(sizeof(long long) * (B->total_slices + 1)));
     long long *off = (long long *)B->off.p;
-    RPCG_TRY(hipMemsetAsync(off, 0, sizeof(long long) * (B->total_slices + 1), B->gs));
+    const int ns = (int)B->total_slices;
+    RPCG_TRY(c->widths.ensure(sizeof(int) * ((size_t)ns + DIAG_TABLE)));
+    int *table = (int *)c->widths.p, *w = table + DIAG_TABLE;
+    RPCG_TRY(hipMemsetAsync(off, 0, sizeof(long long), B->gs));
     RPCG_TRY(hipMemsetAsync(c->info, 0, sizeof(DotInfo), B->gs));
-    const int vec = sell_vec<double>();
     for (int q = 0; q < B->nsys; ++q)
-        RPCG_TRY(launch_csr_scan(A[q].n, A[q].nnz, A[q].row_ptr, A[q].col_idx, vec, off + B->sys[q].slice0 + 1,
-                                 &c->info->flags, &c->info->max_len, &c->info->max_delta, B->gs));
-    if (B->total_slices > 0) RPCG_TRY(launch_sell_scan(off, (int)B->total_slices, B->gs));
+        RPCG_TRY(launch_row_widths(A[q].n, A[q].nnz, A[q].row_ptr, w + B->sys[q].slice0, &c->info->flags,
+                                   &c->info->max_len, B->gs));
+    RPCG_TRY(launch_scan_len(w, ns, off, 1, true, B->gs));
     B->off_host.resize(B->total_slices + 1);
     DotInfo inf;
     RPCG_TRY(hipMemcpyAsync(B->off_host.data(), off, sizeof(long long) * (B->total_slices + 1),
@@ -406,19 +411,66 @@ static int batch_create_body(rpcg_batch *B, const rpcg_csr *A, hipStream_t calle
     RPCG_TRY(hipMemcpyAsync(&inf, c->info, sizeof inf, hipMemcpyDeviceToHost, B->gs));
     RPCG_TRY(hipStreamSynchronize(B->gs));
     if (inf.flags) return RPCG_ERR_INVALID;
-    B->col16 = inf.max_delta <= 32767;
-    const size_t np = (size_t)std::max(1ll, B->off_host[B->total_slices]);
-    RPCG_TRY(B->val.ensure(sizeof(double) * np));
-    RPCG_TRY(B->col.ensure((B->col16 ? sizeof(short) : sizeof(int)) * np));
-    if (B->col16) RPCG_TRY(B->cfirst.ensure(sizeof(int) * (size_t)std::max(1ll, B->total_slices)));
-    if (inf.max_len < 256) RPCG_TRY(B->len8.ensure((size_t)B->total_rows));
-    for (int q = 0; q < B->nsys; ++q) {
-        const BatchSys &S = B->sys[q];
-        RPCG_TRY(launch_sell_fill(S.n, A[q].row_ptr, A[q].col_idx, A[q].val, nullptr, vec, off + S.slice0,
-                                  (double *)B->val.p, nullptr, B->col16 ? nullptr : (int *)B->col.p,
-                                  B->col16 ? (unsigned short *)B->col.p : nullptr,
-                                  B->col16 ? (int *)B->cfirst.p + S.slice0 : nullptr,
-                                  B->len8.p ? (unsigned char *)B->len8.p + S.row0 : nullptr, B->gs));
+    const long long padded = B->off_host[B->total_slices];
+    bool aligned = false;
+    if (padded > 0 && inf.max_len <= DIAG_MAX_ROW) { // diagonal-aligned slices, as for a single system
+        const int nd = ns / 2;
+        long long nnz = 0;
+        for (int q = 0; q < B->nsys; ++q) nnz += A[q].nnz;
+        RPCG_TRY(B->ds.ensure(sizeof(DiagSlice) * nd));
+        RPCG_TRY(B->de.ensure(sizeof(DiagEnt) * (size_t)diag_mpos(padded, nd)));
+        DiagSlice *ds = (DiagSlice *)B->ds.p;
+        DiagEnt *de = (DiagEnt *)B->de.p;
+        RPCG_TRY(hipMemsetAsync(table, 0xFF, sizeof(int) * DIAG_TABLE, B->gs));
+        for (int q = 0; q < B->nsys; ++q) {
+            const BatchSys &S = B->sys[q];
+            RPCG_TRY(launch_diag_align(S.n, S.slice0 / 2, A[q].row_ptr, A[q].col_idx, A[q].val, nullptr,
+                                       off + S.slice0, de, ds + S.slice0 / 2, w + S.slice0 / 2, table, c->info, B->gs));
+        }
+        RPCG_TRY(hipMemcpyAsync(&inf, c->info, sizeof inf, hipMemcpyDeviceToHost, B->gs));
+        RPCG_TRY(hipStreamSynchronize(B->gs));
+        aligned = !inf.diag_fail && diag_worth_it(inf.diag_total, inf.diag_values, nnz);
+        if (aligned) {
+            if (inf.flags) return RPCG_ERR_INVALID;
+            B->layout = LAY_DIAG;
+            RPCG_TRY(launch_diag_share(nd, de, ds, table, B->gs));
+            if (inf.diag_values > 0) {
+                RPCG_TRY(B->val.ensure(sizeof(double) * DIAG_ROWS * (size_t)inf.diag_values));
+                RPCG_TRY(launch_scan_len(w, nd, &ds->vpos, sizeof(DiagSlice) / sizeof(long long), false, B->gs));
+                for (int q = 0; q < B->nsys; ++q) {
+                    const BatchSys &S = B->sys[q];
+                    RPCG_TRY(launch_diag_fill(S.n, A[q].row_ptr, A[q].val, nullptr, de, ds + S.slice0 / 2,
+                                              (double *)B->val.p, nullptr, B->gs));
+                }
+            }
+        } else {
+            B->ds.release();
+            B->de.release();
+        }
+    }
+    if (!aligned) {
+        for (int q = 0; q < B->nsys; ++q)
+            RPCG_TRY(launch_csr_scan(A[q].n, A[q].nnz, A[q].row_ptr, A[q].col_idx, &c->info->flags, &c->info->max_len,
+                                     &c->info->max_delta, B->gs));
+        RPCG_TRY(hipMemcpyAsync(&inf, c->info, sizeof inf, hipMemcpyDeviceToHost, B->gs));
+        RPCG_TRY(hipStreamSynchronize(B->gs));
+        if (inf.flags) return RPCG_ERR_INVALID;
+        const bool col16 = inf.max_delta <= 32767;
+        B->layout = col16 ? LAY_COL16 : LAY_COL32;
+        const int vec = sell_vec<double>();
+        const size_t np = (size_t)std::max(1ll, padded);
+        RPCG_TRY(B->val.ensure(sizeof(double) * np));
+        RPCG_TRY(B->col.ensure((col16 ? sizeof(short) : sizeof(int)) * np));
+        if (col16) RPCG_TRY(B->cfirst.ensure(sizeof(int) * (size_t)std::max(1ll, B->total_slices)));
+        if (inf.max_len < 256) RPCG_TRY(B->len8.ensure((size_t)B->total_rows));
+        for (int q = 0; q < B->nsys; ++q) {
+            const BatchSys &S = B->sys[q];
+            RPCG_TRY(launch_sell_fill(S.n, A[q].row_ptr, A[q].col_idx, A[q].val, nullptr, vec, off + S.slice0,
+                                      (double *)B->val.p, nullptr, col16 ? nullptr : (int *)B->col.p,
+                                      col16 ? (unsigned short *)B->col.p : nullptr,
+                                      col16 ? (int *)B->cfirst.p + S.slice0 : nullptr,
+                                      B->len8.p ? (unsigned char *)B->len8.p + S.row0 : nullptr, B->gs));
+        }
     }
     RPCG_TRY(B->vecs.ensure(sizeof(double) * 7 * (size_t)B->total_rows));
     RPCG_TRY(hipMemsetAsync(B->vecs.p, 0, sizeof(double) * 7 * (size_t)B->total_rows, B->gs));
@@ -523,7 +575,7 @@ int rpcg_batch_tune(rpcg_batch *B, const double *const *b, int32_t trial_iterati
                 if (rc != RPCG_OK) return rc;
                 RPCG_TRY(hipEventRecord(B->t_ev[0], B->gs));
                 for (int i = 0; i < trial_iterations; ++i)
-                    RPCG_TRY(launch_batch_iteration(B->mode, B->col16, a, cfg.grid, cfg.block, B->ws, B->ws_cap, cfg));
+                    RPCG_TRY(launch_batch_iteration(B->mode, B->layout, a, cfg.grid, cfg.block, B->ws, B->ws_cap, cfg));
                 RPCG_TRY(hipEventRecord(B->t_ev[1], B->gs));
                 RPCG_TRY(hipEventSynchronize(B->t_ev[1]));
             }

@@ -12,7 +12,7 @@ __device__ __forceinline__ SellMat<double> batch_mat(const BatchArgs &a, const B
 {
     SellMat<double> M;
     M.n = S.n;
-    M.nslices = S.nslices;
+    M.nslices = a.ds ? (S.nslices + 1) / 2 : S.nslices;
     M.off = a.off + S.slice0;
     M.val = a.val;
     M.col = a.col;
@@ -21,7 +21,19 @@ __device__ __forceinline__ SellMat<double> batch_mat(const BatchArgs &a, const B
     M.col16 = a.col16;
     M.cfirst = a.cfirst ? a.cfirst + S.slice0 : nullptr;
     M.val64 = nullptr;
+    M.ds = a.ds ? a.ds + S.slice0 / 2 : nullptr;
+    M.de = a.de;
     return M;
+}
+
+// The slices of wavefront `wave` of W in a run (whose bounds are 64-row slices,
+// even with diagonal-aligned slices but for a system's end).
+template <int LAY>
+__device__ __forceinline__ SliceRange batch_slices(const BatchRun &R, int wave, int W)
+{
+    const int s0 = __builtin_amdgcn_readfirstlane(R.s0), s1 = __builtin_amdgcn_readfirstlane(R.s1);
+    if constexpr (LAY == LAY_DIAG) return {s0 / 2 + wave, (s1 + 1) / 2, W};
+    else return {s0 + wave, s1, W};
 }
 
 // Slots [g0, ...) of a workspace seen as slots [0, ...).

@@ -34,7 +34,7 @@ __device__ __forceinline__ int wg_read_int(const int *p, RedShared &sh)
 }
 
 // K1: S1 + partial of S2 (as k_pcg_spmv_dot, per run).
-template <int MODE, int P, bool COL16>
+template <int MODE, int P, int LAY>
 __global__ void __launch_bounds__(MAX_BLOCK) k_batch_spmv_dot(BatchArgs a, SlotView sv, bool ee, bool capture)
 {
     __shared__ RedShared sh;
@@ -57,17 +57,16 @@ __global__ void __launch_bounds__(MAX_BLOCK) k_batch_spmv_dot(BatchArgs a, SlotV
         __syncthreads();
         LaneDot<MODE, P> L;
         L.init();
-        for (long long s = R.s0 + wave; s < R.s1; s += W) {
-            const long long base = uniform_ll(M.off[s]);
-            const int width = __builtin_amdgcn_readfirstlane((int)((M.off[s + 1] - base) >> 6));
-            const long long i = s * 64 + lane;
-            const int len = sell_len(M, i);
-            const double sum = sell_row<double, COL16, false>(M, base, width, i, len, d, nullptr, nullptr);
-            if (i < M.n) {
-                w[i] = sum;
-                L.add(d[i], sum, sh.acc[0], ee, capture);
-            }
-        }
+        for_slices<double, LAY, false>(M, batch_slices<LAY>(R, wave, W), lane, [&](long long i, auto &&rows) {
+            constexpr int NR = lane_rows<LAY>();
+            double sum[NR], di[NR];
+            rows(d, sum, nullptr, nullptr);
+            load_rows<NR>(di, d, i, M.n);
+            store_rows(w, sum, i, M.n);
+#pragma unroll
+            for (int r = 0; r < NR; ++r)
+                if (i + r < M.n) L.add(di[r], sum[r], sh.acc[0], ee, capture);
+        });
         block_finish<MODE, P>(L, sh.acc[0], sv, R.slot, ee, capture, &st->flags, sh);
     }
 }
@@ -180,14 +179,15 @@ __global__ void __launch_bounds__(MAX_BLOCK) k_batch_direction(BatchArgs a, Slot
     }
 }
 
-hipError_t launch_batch_iteration(int mode, bool col16, const BatchArgs &a, int grid, int block, const DotWs *ws3,
+hipError_t launch_batch_iteration(int mode, int layout, const BatchArgs &a, int grid, int block, const DotWs *ws3,
                                   int stride, const LaunchCfg &c)
 {
     SlotView s0{ws3[0], stride}, s1{ws3[1], stride}, s2{ws3[2], stride};
     dispatch(mode, c.fpe_size, [&](auto m, auto p) {
         constexpr int M = decltype(m)::value, PP = decltype(p)::value;
-        if (col16) k_batch_spmv_dot<M, PP, true><<<grid, block, 0, c.stream>>>(a, s0, c.early_exit, c.fallback);
-        else k_batch_spmv_dot<M, PP, false><<<grid, block, 0, c.stream>>>(a, s0, c.early_exit, c.fallback);
+        dispatch_layout(layout, [&](auto lay) {
+            k_batch_spmv_dot<M, PP, decltype(lay)::value><<<grid, block, 0, c.stream>>>(a, s0, c.early_exit, c.fallback);
+        });
         k_batch_update<M, PP><<<grid, block, 0, c.stream>>>(a, s0, s1, s2, c.early_exit, c.fallback);
         k_batch_direction<M, PP><<<grid, block, 0, c.stream>>>(a, s1, s2, c.early_exit, c.fallback);
     });

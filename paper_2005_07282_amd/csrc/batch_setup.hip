@@ -25,7 +25,7 @@ __device__ __noinline__ void batch_setup_finish(LaneDot<MODE, P> &L, long long *
     block_finish<MODE, P>(L, acc, sv, g, ee, capture, gflags, sh);
 }
 
-template <int MODE, int P, bool COL16>
+template <int MODE, int P, int LAY>
 __global__ void __launch_bounds__(MAX_BLOCK)
 k_batch_setup(BatchArgs a, SlotView w0, SlotView w1, SlotView w2, bool ee, bool capture)
 {
@@ -48,31 +48,33 @@ k_batch_setup(BatchArgs a, SlotView w0, SlotView w1, SlotView w2, bool ee, bool 
         Lt.init();
         Lbb.init();
         int flags = 0;
-        for (long long s = R.s0 + wave; s < R.s1; s += W) {
-            const long long base = uniform_ll(M.off[s]);
-            const int width = __builtin_amdgcn_readfirstlane((int)((M.off[s + 1] - base) >> 6));
-            const long long i = s * 64 + lane;
-            const int len = sell_len(M, i);
-            double aii = 0.0;
-            bool found = false;
-            const double acc = sell_row<double, COL16, true>(M, base, width, i, len, a.x + r0, &aii, &found);
-            if (i < M.n) {
-                const long long g = r0 + i;
-                if (!found || !(aii > 0.0)) flags |= FLAG_NOT_SPD;
-                const double bi = a.b[g];
-                if (!is_finite_bits(bi) || !is_finite_bits(a.x[g])) flags |= FLAG_NONFINITE;
-                const double di = 1.0 / aii;
-                const double ri = bi - acc;
-                const double zi = di * ri;
-                a.dinv[g] = di;
-                a.r[g] = ri;
-                a.z[g] = zi;
-                a.d[g] = zi;
-                Lb.add(zi, ri, sh.acc[0], ee, capture);
-                Lt.add(ri, ri, sh.acc[1], ee, capture);
-                Lbb.add(bi, bi, sh.acc[2], ee, capture);
+        for_slices<double, LAY, true>(M, batch_slices<LAY>(R, wave, W), lane, [&](long long i, auto &&rows) {
+            constexpr int NR = lane_rows<LAY>();
+            double acc[NR], aii[NR], bi[NR], xi[NR], di[NR], ri[NR], zi[NR];
+            bool found[NR];
+#pragma unroll
+            for (int r = 0; r < NR; ++r) { aii[r] = 0.0; found[r] = false; }
+            rows(a.x + r0, acc, aii, found);
+            load_rows<NR>(bi, a.b + r0, i, M.n);
+            load_rows<NR>(xi, (const double *)a.x + r0, i, M.n);
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                di[r] = 1.0 / aii[r];
+                ri[r] = bi[r] - acc[r];
+                zi[r] = di[r] * ri[r];
+                if (i + r < M.n) {
+                    if (!found[r] || !(aii[r] > 0.0)) flags |= FLAG_NOT_SPD;
+                    if (!is_finite_bits(bi[r]) || !is_finite_bits(xi[r])) flags |= FLAG_NONFINITE;
+                    Lb.add(zi[r], ri[r], sh.acc[0], ee, capture);
+                    Lt.add(ri[r], ri[r], sh.acc[1], ee, capture);
+                    Lbb.add(bi[r], bi[r], sh.acc[2], ee, capture);
+                }
             }
-        }
+            store_rows(a.dinv + r0, di, i, M.n);
+            store_rows(a.r + r0, ri, i, M.n);
+            store_rows(a.z + r0, zi, i, M.n);
+            store_rows(a.d + r0, zi, i, M.n);
+        });
         if (flags) atomicOr(&a.st[R.sys].flags, flags);
         int *gf = &a.st[R.sys].flags;
         batch_setup_finish<MODE, P>(Lb, sh.acc[0], w0, R.slot, ee, capture, gf, sh);
@@ -131,15 +133,17 @@ k_batch_fin_setup(BatchArgs a, SlotView w0, SlotView w1, SlotView w2, double tol
     }
 }
 
-hipError_t launch_batch_setup(int mode, bool col16, const BatchArgs &a, int grid, int block, const DotWs *ws3,
+hipError_t launch_batch_setup(int mode, int layout, const BatchArgs &a, int grid, int block, const DotWs *ws3,
                               int stride, double tol, int maxit, const LaunchCfg &c)
 {
     SlotView s0{ws3[0], stride}, s1{ws3[1], stride}, s2{ws3[2], stride};
     k_batch_state_init<<<(a.nsys + 63) / 64, 64, 0, c.stream>>>(a, maxit);
     dispatch(mode, c.fpe_size, [&](auto m, auto p) {
         constexpr int M = decltype(m)::value, PP = decltype(p)::value;
-        if (col16) k_batch_setup<M, PP, true><<<grid, block, 0, c.stream>>>(a, s0, s1, s2, c.early_exit, c.fallback);
-        else k_batch_setup<M, PP, false><<<grid, block, 0, c.stream>>>(a, s0, s1, s2, c.early_exit, c.fallback);
+        dispatch_layout(layout, [&](auto lay) {
+            k_batch_setup<M, PP, decltype(lay)::value><<<grid, block, 0, c.stream>>>(a, s0, s1, s2, c.early_exit,
+                                                                                     c.fallback);
+        });
         k_batch_fin_setup<M, PP><<<a.nsys, 256, 0, c.stream>>>(a, s0, s1, s2, tol, c.early_exit, c.fallback);
     });
     return hipGetLastError();

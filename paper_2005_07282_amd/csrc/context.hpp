@@ -45,14 +45,15 @@ struct rpcg_ctx {
     rpcg::DotInfo *info = nullptr;
     rpcg::PcgState *st = nullptr;
     rpcg::IrState *ist = nullptr;
-    rpcg_host::Buffer sell_off, sell_val, sell_val32, sell_col, sell_cfirst, sell_len;
+    rpcg_host::Buffer sell_off, sell_val, sell_val32, sell_col, sell_cfirst, sell_len, diag_ds, diag_de;
+    rpcg_host::Buffer widths;  // construction scratch: table of record lists, then one int per slice
     rpcg_host::Buffer vecs;    // r, z, d, w, dinv of the solver
     rpcg_host::Buffer ir_vecs; // refinement: r (binary64), rf and c (binary32)
     rpcg_host::Buffer beta_hist; // beta of every iteration
-    rpcg_host::Buffer scan_scratch; // slice widths of structural checks of extra CSR arguments
     int *host_done = nullptr;  // pinned: polled flags
     rpcg::PcgState *host_state = nullptr;
     rpcg::IrState *host_ir = nullptr;
+    rpcg::DotInfo *host_info = nullptr; // and, behind it, one long long (construction total)
     std::vector<hipEvent_t> events;
     std::vector<hipEvent_t> ir_events;
     hipEvent_t poll_ev[2] = {nullptr, nullptr};

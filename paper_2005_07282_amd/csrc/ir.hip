@@ -22,7 +22,7 @@ constexpr int RES_BATCH = 9;              // row entries loaded together
 // not fit goes into the lane's own long accumulator in LDS), then adds the
 // expansion to that accumulator and rounds once. The accumulators are the
 // columns of a [ACC_DIGITS][64] array per wavefront.
-template <bool COL16>
+template <int LAY>
 __global__ void __launch_bounds__(IR_BLOCK)
 k_ir_residual(SellMat<float> A, const double *__restrict__ b, const double *__restrict__ x, double *__restrict__ r,
               IrState *ist, SlotView sv)
@@ -46,15 +46,22 @@ k_ir_residual(SellMat<float> A, const double *__restrict__ b, const double *__re
             else flags |= FLAG_NONFINITE;
         }
     };
+    // one product a x_j subtracted from the row's sum
+    auto term = [&](double (&e)[RES_FPE], double a, double g) {
+        double ph, pl;
+        two_prod(-a, g, ph, pl);
+        if (!is_finite_bits(g) || !is_finite_bits(ph)) flags |= FLAG_NONFINITE;
+        else if (__builtin_fabs(ph) < 0x1p-969 && a != 0.0 && g != 0.0) flags |= FLAG_INEXACT;
+        put(e, ph);
+        put(e, pl);
+    };
     const long long wstride = (long long)gridDim.x * IR_WAVES;
-    for (long long s = (long long)blockIdx.x * IR_WAVES + wave; s < A.nslices; s += wstride) {
-        const long long base = uniform_ll(A.off[s]);
-        const int width = __builtin_amdgcn_readfirstlane((int)((A.off[s + 1] - base) >> 6));
-        const long long i = s * 64 + lane;
-        const int len = sell_len(A, i);
-        const long long p0 = base + lane; // binary32 layout: no interleave
-        int first = 0, cur = 0;
-        if constexpr (COL16) first = (i < A.n ? (int)i : A.n - 1) + A.cfirst[s];
+    // 64 rows at a time: a slice, or the even or odd rows of a 128-row slice
+    const long long units = LAY == LAY_DIAG ? 2ll * A.nslices : A.nslices;
+    for (long long t = (long long)blockIdx.x * IR_WAVES + wave; t < units; t += wstride) {
+        const long long s = LAY == LAY_DIAG ? t >> 1 : t;
+        const int half = (int)(t & 1);
+        const long long i = LAY == LAY_DIAG ? s * DIAG_ROWS + 2 * lane + half : s * 64 + lane;
         double e[RES_FPE];
 #pragma unroll
         for (int j = 0; j < RES_FPE; ++j) e[j] = 0.0;
@@ -63,37 +70,57 @@ k_ir_residual(SellMat<float> A, const double *__restrict__ b, const double *__re
             if (!is_finite_bits(bi)) flags |= FLAG_NONFINITE;
             put(e, bi);
         }
-        for (int k0 = 0; k0 < width; k0 += RES_BATCH) {
-            int c[RES_BATCH];
-            double a[RES_BATCH], g[RES_BATCH];
+        if constexpr (LAY == LAY_DIAG) {
+            const cptr<DiagSlice> S = as_const(A.ds) + s;
+            const cptr<DiagEnt> rec = as_const(A.de) + S->mpos;
+            const bool cst = S->flags & DIAG_CONST;
+            const int width = S->width;
+            for (int k0 = 0; k0 < width; k0 += DIAG_BATCH) {
+                double a[DIAG_BATCH], g[DIAG_BATCH];
 #pragma unroll
-            for (int u = 0; u < RES_BATCH; ++u) {
-                // positions past the width repeat the last entry (its column decodes unchanged: code 0)
-                const int k = min(k0 + u, width - 1);
-                if constexpr (COL16) {
-                    const unsigned code = k0 + u < width ? __builtin_nontemporal_load(&A.col16[p0 + 64ll * k]) : 0u;
-                    cur = (k0 + u == 0) ? first + (int)(short)code : cur + (int)code;
-                    c[u] = cur;
-                } else {
-                    c[u] = __builtin_nontemporal_load(&A.col[p0 + 64ll * k]);
+                for (int u = 0; u < DIAG_BATCH; ++u) {
+                    const long long c = i + rec[k0 + u].off;
+                    g[u] = x[c < 0 ? 0 : (c >= A.n ? A.n - 1 : c)];
+                    a[u] = cst ? rec[k0 + u].v : A.val64[S->vpos + (long long)DIAG_ROWS * min(k0 + u, width - 1) + 2 * lane + half];
                 }
+#pragma unroll
+                for (int u = 0; u < DIAG_BATCH; ++u)
+                    if ((rec[k0 + u].mask[half] >> lane) & 1ull) term(e, a[u], g[u]);
             }
+        } else {
+            const long long base = uniform_ll(A.off[s]);
+            const int width = __builtin_amdgcn_readfirstlane((int)((A.off[s + 1] - base) >> 6));
+            const int len = sell_len(A, i);
+            const long long p0 = base + lane; // binary32 layout: no interleave
+            int first = 0, cur = 0;
+            if constexpr (LAY == LAY_COL16) first = (i < A.n ? (int)i : A.n - 1) + A.cfirst[s];
+            for (int k0 = 0; k0 < width; k0 += RES_BATCH) {
+                int c[RES_BATCH];
+                double a[RES_BATCH], g[RES_BATCH];
 #pragma unroll
-            for (int u = 0; u < RES_BATCH; ++u) {
-                const int k = min(k0 + u, width - 1);
-                a[u] = __builtin_nontemporal_load(&A.val64[p0 + 64ll * k]);
-            }
+                for (int u = 0; u < RES_BATCH; ++u) {
+                    // positions past the width repeat the last entry (its column decodes unchanged: code 0)
+                    const int k = min(k0 + u, width - 1);
+                    if constexpr (LAY == LAY_COL16) {
+                        const unsigned code = k0 + u < width ? __builtin_nontemporal_load(&A.col16[p0 + 64ll * k]) : 0u;
+                        cur = (k0 + u == 0) ? first + (int)(short)code : cur + (int)code;
+                        c[u] = cur;
+                    } else {
+                        c[u] = __builtin_nontemporal_load(&A.col[p0 + 64ll * k]);
+                    }
+                }
 #pragma unroll
-            for (int u = 0; u < RES_BATCH; ++u) g[u] = x[c[u]];
+                for (int u = 0; u < RES_BATCH; ++u) {
+                    const int k = min(k0 + u, width - 1);
+                    a[u] = __builtin_nontemporal_load(&A.val64[p0 + 64ll * k]);
+                }
 #pragma unroll
-            for (int u = 0; u < RES_BATCH; ++u) {
-                if (k0 + u < len) {
-                    double ph, pl;
-                    two_prod(-a[u], g[u], ph, pl);
-                    if (!is_finite_bits(g[u]) || !is_finite_bits(ph)) flags |= FLAG_NONFINITE;
-                    else if (__builtin_fabs(ph) < 0x1p-969 && a[u] != 0.0 && g[u] != 0.0) flags |= FLAG_INEXACT;
-                    put(e, ph);
-                    put(e, pl);
+                for (int u = 0; u < RES_BATCH; ++u) g[u] = x[c[u]];
+#pragma unroll
+                for (int u = 0; u < RES_BATCH; ++u) {
+                    if (k0 + u < len) {
+                        term(e, a[u], g[u]);
+                    }
                 }
             }
         }
@@ -180,10 +207,11 @@ __global__ void k_ir_update(int n, double *__restrict__ x, const float *__restri
 hipError_t launch_ir_residual(const SellMat<float> &A, const double *b, const double *x, double *r, IrState *ist,
                               const DotWs &ws, int stride, const LaunchCfg &c)
 {
-    if (!A.val64 || sell_vec<float>() != 1) return hipErrorInvalidValue;
+    if ((!A.val64 && !A.ds) || sell_vec<float>() != 1) return hipErrorInvalidValue;
     SlotView sv{ws, stride};
-    if (A.col16) k_ir_residual<true><<<c.grid, IR_BLOCK, 0, c.stream>>>(A, b, x, r, ist, sv);
-    else k_ir_residual<false><<<c.grid, IR_BLOCK, 0, c.stream>>>(A, b, x, r, ist, sv);
+    dispatch_layout(A.layout(), [&](auto lay) {
+        k_ir_residual<decltype(lay)::value><<<c.grid, IR_BLOCK, 0, c.stream>>>(A, b, x, r, ist, sv);
+    });
     return hipGetLastError();
 }
 

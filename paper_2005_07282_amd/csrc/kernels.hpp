@@ -20,6 +20,7 @@ enum {
 constexpr int MAX_BLOCK = 1024;
 constexpr int MAX_WAVES = MAX_BLOCK / 64;
 constexpr int MAX_FPE = 8;
+constexpr int NUM_XCDS = 8; // accelerator dies, each with its own L2; workgroups are dealt to them round-robin
 constexpr int ACC_WORDS = 68; // same as ACC_DIGITS in numerics.hpp
 
 // Per-dot reduction workspace for up to `gmax` workgroups (slots).
@@ -39,6 +40,11 @@ struct DotInfo {
     long long max_delta; // column-code range (SELL construction scratch)
     long long escapes;
     long long fallbacks;
+    // construction scratch of the diagonal-aligned copy
+    int diag_fail;                // nonzero: some slice's rows do not line up
+    int pad2;
+    unsigned long long diag_total;  // entry records of all slices
+    unsigned long long diag_values; // those whose values must be stored
 };
 
 // PCG state on the device. Written only by the last workgroup of a kernel
@@ -98,10 +104,60 @@ __host__ __device__ constexpr int sell_vec()
     return sizeof(T) == 8 ? RPCG_SELL_VEC64 : 1;
 }
 
+// Diagonal-aligned slices of 128 rows: the layout of operators whose rows share
+// their column offsets (stencils, bands), used instead of the columns above
+// when the rows of the slices line up. The entries of a slice's rows are
+// merged by offset = column - row into records; a record holds the offset and
+// the masks of the rows that have an entry there (lane j owns the rows 2 j and
+// 2 j + 1: mask[0] and mask[1]), in an order that keeps every row's storage order. So a
+// row's columns cost no memory traffic, its gathers are contiguous runs, and a slice
+// whose entries agree along every record (a constant-coefficient operator) stores one
+// value per record and none per row; other slices store the values of record k
+// of row 2 j + r at vpos + 128 k + 2 j + r. The records are followed by at least
+// 16 empty ones (empty masks, offset 0), so a loop may read whole batches.
+constexpr int DIAG_ROWS = 128;
+struct DiagEnt {
+    double v;                   // constant slices: the value,
+    unsigned long long mask[2]; // rows with an entry
+    int off;                    // column - row
+    float vf;                   // and the value rounded to binary32
+};
+struct DiagSlice {
+    long long mpos; // first record
+    long long vpos; // first value (slices that are not constant)
+    int width;      // records
+    int flags;
+};
+enum {
+    DIAG_CONST = 1, // one value per record
+    DIAG_CLAMP = 2, // masked-out rows may point outside the vector
+    DIAG_TRI = 4,   // records 3 q, 3 q + 1, 3 q + 2 sit at neighbouring offsets
+};
+// Records per batch of loads: a 7-point row is one batch, a 27-point row three
+// (in runs of three neighbours).
+constexpr int DIAG_BATCH = 7, DIAG_TRI_BATCH = 9;
+constexpr int DIAG_PAD = 24; // empty records after a slice's own
+// Records of slice s start here (w64: 64 times the widths, that is the longest
+// rows, of the 64-row slices before it): room for the widths of its two
+// 64-row slices and a few more, and the empty records.
+__host__ __device__ constexpr long long diag_mpos(long long w64, long long s) { return (w64 >> 6) + (DIAG_PAD + 8) * s; }
+// Kept while the values that must be stored stay within 1.25 times the
+// entries (8 bytes against 10 an entry in the general copy) and the records
+// within twice.
+__host__ constexpr bool diag_worth_it(unsigned long long records, unsigned long long values, long long nnz)
+{
+    return 4 * DIAG_ROWS * values <= 5 * (unsigned long long)nnz && DIAG_ROWS * records <= 2 * (unsigned long long)nnz;
+}
+constexpr int DIAG_TABLE = 8192; // hash slots of record lists, a power of two (see k_diag_share)
+constexpr int DIAG_MAX_ROW = 1024; // longer rows keep the general layout (the merge walks a row entry by entry)
+
+// Column layouts of the solvers' matrix copies.
+enum { LAY_COL32 = 0, LAY_COL16 = 1, LAY_DIAG = 2 };
+
 template <typename T>
 struct SellMat {
     int n;
-    int nslices;
+    int nslices;          // of the layout: 64 rows, diagonal-aligned 128
     const long long *off; // [nslices + 1]
     const T *val;
     const int *col;
@@ -110,6 +166,10 @@ struct SellMat {
     const unsigned short *col16; // when non-null: column codes (col unused)
     const int *cfirst;    // with col16: [nslices] first-column offset of each slice
     const double *val64;  // optional binary64 values (same layout), else null
+    const DiagSlice *ds;  // when non-null: diagonal-aligned slices (off, col, col16, cfirst, len8 unused)
+    const DiagEnt *de;
+
+    int layout() const { return ds ? LAY_DIAG : (col16 ? LAY_COL16 : LAY_COL32); }
 };
 
 struct LaunchCfg {
@@ -118,7 +178,7 @@ struct LaunchCfg {
     bool early_exit;
     int fpe_size;
     bool fallback;
-    int xcd_parts; // SpMV: number of contiguous slice ranges (one per XCD)
+    int xcd_parts; // SpMV: number of contiguous slice ranges (one per XCD), 0 = by the layout
     hipStream_t stream;
 };
 
@@ -137,14 +197,29 @@ hipError_t launch_exp_range(long long n, const double *v, int *emin, int *emax, 
 hipError_t launch_spmv_csr(int n, long long nnz, const int *row_ptr, const int *col, const double *val,
                            const double *x, double *y, hipStream_t s);
 
-// CSR structural check (*bad set if malformed), slice sizes (64 times the
-// slice's longest row, into off_plus1), longest row, and the range of the
-// 16-bit column codes (*max_delta <= 32767 iff every code fits), one
+// Slice widths (longest row of each 64 rows, an even number of slices: the
+// last may be empty), longest row, and the check of row_ptr (*bad set if malformed).
+hipError_t launch_row_widths(int n, int nnz, const int *row_ptr, int *w, int *bad, int *max_len, hipStream_t s);
+// out[j stride] = 64 sum(len[0..j)), j < m (and j = m with `total`).
+hipError_t launch_scan_len(const int *len, int m, long long *out, int stride, bool total, hipStream_t s);
+// CSR structural check (*bad set if malformed), longest row, and the range of
+// the 16-bit column codes (*max_delta <= 32767 iff every code fits), one
 // wavefront per 64-row slice.
-hipError_t launch_csr_scan(int n, int nnz, const int *row_ptr, const int *col, int vec, long long *off_plus1,
-                           int *bad, int *max_len, long long *max_delta, hipStream_t s);
+hipError_t launch_csr_scan(int n, int nnz, const int *row_ptr, const int *col, int *bad, int *max_len,
+                           long long *max_delta, hipStream_t s);
+// Diagonal-aligned slices from a CSR whose row_ptr has been checked: the merge
+// (records, DiagSlice without vpos, ulen, column check, totals or diag_fail in
+// info; values from exactly one of val64 and val32; sbase = slices before this
+// matrix in de, in 128-row slices; off: 64 times the widths of the 64-row slices before; table: DIAG_TABLE ints set to -1), the sharing of equal record
+// lists (over all matrices of a table), and the stored values of the slices
+// that need them.
+hipError_t launch_diag_align(int n, long long sbase, const int *row_ptr, const int *col, const double *val64,
+                             const float *val32, const long long *off, DiagEnt *de, DiagSlice *ds, int *ulen,
+                             int *table, DotInfo *info, hipStream_t s);
+hipError_t launch_diag_share(int nslices, const DiagEnt *de, DiagSlice *ds, const int *table, hipStream_t s);
+hipError_t launch_diag_fill(int n, const int *row_ptr, const double *val64, const float *val32, const DiagEnt *de,
+                            const DiagSlice *ds, double *sval64, float *sval32, hipStream_t s);
 
-hipError_t launch_sell_scan(long long *off, int nslices, hipStream_t s);
 // Fill the sliced-ELL arrays from the CSR. The source values are binary64
 // (val64_in) or binary32 (val32_in, exactly one of the two non-null); sval64
 // receives them as binary64, sval32 rounded to nearest binary32; either
@@ -246,10 +321,10 @@ hipError_t launch_fac_update(int mode, int l, int n, const FacPre &P, const PcgV
 // the concatenated sliced-ELL copy (slices never span systems), and its
 // dot partials in slots [slot0, slot1).
 struct BatchSys {
-    long long row0;
-    long long slice0;
+    long long row0;   // multiple of 128
+    long long slice0; // row0 / 64
     int n;
-    int nslices;
+    int nslices;      // 64-row slices
     int slot0;
     int slot1;
     const int *row_ptr; // the caller's CSR row pointers of the system
@@ -276,6 +351,8 @@ struct BatchArgs {
     const unsigned short *col16;
     const int *cfirst;
     const unsigned char *len8; // indexed by concatenated row
+    const DiagSlice *ds;       // when non-null: diagonal-aligned slices (all systems)
+    const DiagEnt *de;
     // concatenated vectors
     const double *b;
     double *x, *r, *z, *d, *w, *dinv;
@@ -286,12 +363,12 @@ struct BatchArgs {
 
 // Setup of every system (state, partials of <z,r>, <r,r>, <b,b> into ws3,
 // one workgroup per system to merge them).
-hipError_t launch_batch_setup(int mode, bool col16, const BatchArgs &a, int grid, int block, const DotWs *ws3,
+hipError_t launch_batch_setup(int mode, int layout, const BatchArgs &a, int grid, int block, const DotWs *ws3,
                               int stride, double tol, int maxit, const LaunchCfg &cfg);
 // One iteration of every system not done: SpMV + <d,w> partials (ws[0]),
 // per-system rho, updates + <z,r>, <r,r> partials (ws[1], ws[2]), per-system
 // stopping test and gamma, direction update.
-hipError_t launch_batch_iteration(int mode, bool col16, const BatchArgs &a, int grid, int block, const DotWs *ws3,
+hipError_t launch_batch_iteration(int mode, int layout, const BatchArgs &a, int grid, int block, const DotWs *ws3,
                                   int stride, const LaunchCfg &cfg);
 
 } // namespace rpcg

@@ -29,7 +29,7 @@ static __global__ void k_fac_state_init(PcgState *st, int maxit)
 }
 
 // r = b - A x0 over the sliced-ELL copy; partials of <r,r> and <b,b>.
-template <int MODE, int P, bool COL16>
+template <int MODE, int P, int LAY>
 __global__ void __launch_bounds__(MAX_BLOCK)
 k_fac_setup_r(SellMat<double> A, PcgVecs<double> v, PcgState *st, SlotView wt, SlotView wbb, bool ee, bool capture)
 {
@@ -42,23 +42,23 @@ k_fac_setup_r(SellMat<double> A, PcgVecs<double> v, PcgState *st, SlotView wt, S
     Lbb.init();
     int flags = 0;
     const int lane = lane_id();
-    const int wave = __builtin_amdgcn_readfirstlane(wave_id());
-    const long long wstride = (long long)gridDim.x * num_waves();
-    for (long long s = (long long)blockIdx.x * num_waves() + wave; s < A.nslices; s += wstride) {
-        const long long base = uniform_ll(A.off[s]);
-        const int width = __builtin_amdgcn_readfirstlane((int)((A.off[s + 1] - base) >> 6));
-        const long long i = s * 64 + lane;
-        const int len = sell_len(A, i);
-        const double acc = sell_row<double, COL16, false>(A, base, width, i, len, v.x, nullptr, nullptr);
-        if (i < A.n) {
-            const double bi = v.b[i];
-            if (!is_finite_bits(bi) || !is_finite_bits(v.x[i])) flags |= FLAG_NONFINITE;
-            const double ri = bi - acc;
-            v.r[i] = ri;
-            Lt.add(ri, ri, sh.acc[1], ee, capture);
-            Lbb.add(bi, bi, sh.acc[2], ee, capture);
+    for_slices<double, LAY, false>(A, wave_slices(A.nslices, 1), lane, [&](long long i, auto &&rows) {
+        constexpr int R = lane_rows<LAY>();
+        double acc[R], bi[R], xi[R], ri[R];
+        rows(v.x, acc, nullptr, nullptr);
+        load_rows<R>(bi, v.b, i, A.n);
+        load_rows<R>(xi, v.x, i, A.n);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            ri[r] = bi[r] - acc[r];
+            if (i + r < A.n) {
+                if (!is_finite_bits(bi[r]) || !is_finite_bits(xi[r])) flags |= FLAG_NONFINITE;
+                Lt.add(ri[r], ri[r], sh.acc[1], ee, capture);
+                Lbb.add(bi[r], bi[r], sh.acc[2], ee, capture);
+            }
         }
-    }
+        store_rows(v.r, ri, i, A.n);
+    });
     if (flags) atomicOr(&st->flags, flags);
     fac_block_finish<MODE, P>(Lt, sh.acc[1], wt, blockIdx.x, ee, capture, &st->flags, sh);
     fac_block_finish<MODE, P>(Lbb, sh.acc[2], wbb, blockIdx.x, ee, capture, &st->flags, sh);
@@ -104,10 +104,10 @@ hipError_t launch_fac_setup(int mode, const SellMat<double> &A, const FacPre &Pr
     k_fac_state_init<<<1, 64, 0, c.stream>>>(st, maxit);
     dispatch(mode, c.fpe_size, [&](auto m, auto p) {
         constexpr int M = decltype(m)::value, PP = decltype(p)::value;
-        if (A.col16)
-            k_fac_setup_r<M, PP, true><<<c.grid, c.block, 0, c.stream>>>(A, v, st, s1, s2, c.early_exit, c.fallback);
-        else
-            k_fac_setup_r<M, PP, false><<<c.grid, c.block, 0, c.stream>>>(A, v, st, s1, s2, c.early_exit, c.fallback);
+        dispatch_layout(A.layout(), [&](auto lay) {
+            k_fac_setup_r<M, PP, decltype(lay)::value><<<c.grid, c.block, 0, c.stream>>>(A, v, st, s1, s2, c.early_exit,
+                                                                                         c.fallback);
+        });
         k_fac_gt<<<c.grid, c.block, 0, c.stream>>>(A.n, Pr, v.r, t, st);
         k_fac_z<M, PP, true><<<c.grid, c.block, 0, c.stream>>>(A.n, Pr, v, t, st, s0, c.early_exit, c.fallback);
         k_fac_fin_setup<M, PP><<<1, MAX_BLOCK, 0, c.stream>>>(c.grid, v, st, s0, s1, s2, tol, c.early_exit,

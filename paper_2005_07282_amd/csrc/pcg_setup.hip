@@ -36,7 +36,7 @@ static __global__ void k_state_init(PcgState *st, int maxit)
 // dinv = RN(1/a_ii), r = RN(b - A x0), z = RN(dinv r), d = z, and the
 // workgroup partials of <z,r>, <r,r>, <b,b>. One wavefront per 64-row slice
 // of the sliced-ELL copy, as in the iteration's SpMV.
-template <int MODE, int P, bool COL16, typename T>
+template <int MODE, int P, int LAY, typename T>
 __global__ void __launch_bounds__(MAX_BLOCK)
 k_pcg_setup(SellMat<T> A, PcgVecs<T> v, PcgState *st, SlotView w0, SlotView w1, SlotView w2, bool ee, bool capture)
 {
@@ -47,32 +47,33 @@ k_pcg_setup(SellMat<T> A, PcgVecs<T> v, PcgState *st, SlotView w0, SlotView w1, 
     Lb.init(); Lt.init(); Lbb.init();
     int flags = 0;
     const int lane = lane_id();
-    const int wave = __builtin_amdgcn_readfirstlane(wave_id());
-    const long long wstride = (long long)gridDim.x * num_waves();
-    for (long long s = (long long)blockIdx.x * num_waves() + wave; s < A.nslices; s += wstride) {
-        const long long base = uniform_ll(A.off[s]);
-        const int width = __builtin_amdgcn_readfirstlane((int)((A.off[s + 1] - base) >> 6));
-        const long long i = s * 64 + lane;
-        const int len = sell_len(A, i);
-        T aii = T(0);
-        bool found = false;
-        const T acc = sell_row<T, COL16, true>(A, base, width, i, len, v.x, &aii, &found);
-        if (i < A.n) {
-            if (!found || !(aii > T(0))) flags |= FLAG_NOT_SPD;
-            const T bi = v.b[i];
-            if (!is_finite_bits((double)bi) || !is_finite_bits((double)v.x[i])) flags |= FLAG_NONFINITE;
-            const T di = T(1) / aii;
-            const T ri = bi - acc;
-            const T zi = di * ri;
-            v.dinv[i] = di;
-            v.r[i] = ri;
-            v.z[i] = zi;
-            v.d[i] = zi;
-            Lb.add(zi, ri, sh.acc[0], ee, capture);
-            Lt.add(ri, ri, sh.acc[1], ee, capture);
-            Lbb.add(bi, bi, sh.acc[2], ee, capture);
+    for_slices<T, LAY, true>(A, wave_slices(A.nslices, 1), lane, [&](long long i, auto &&rows) {
+        constexpr int R = lane_rows<LAY>();
+        T acc[R], aii[R], bi[R], xi[R], di[R], ri[R], zi[R];
+        bool found[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) { aii[r] = T(0); found[r] = false; }
+        rows(v.x, acc, aii, found);
+        load_rows<R>(bi, v.b, i, A.n);
+        load_rows<R>(xi, v.x, i, A.n);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            di[r] = T(1) / aii[r];
+            ri[r] = bi[r] - acc[r];
+            zi[r] = di[r] * ri[r];
+            if (i + r < A.n) {
+                if (!found[r] || !(aii[r] > T(0))) flags |= FLAG_NOT_SPD;
+                if (!is_finite_bits((double)bi[r]) || !is_finite_bits((double)xi[r])) flags |= FLAG_NONFINITE;
+                Lb.add(zi[r], ri[r], sh.acc[0], ee, capture);
+                Lt.add(ri[r], ri[r], sh.acc[1], ee, capture);
+                Lbb.add(bi[r], bi[r], sh.acc[2], ee, capture);
+            }
         }
-    }
+        store_rows(v.dinv, di, i, A.n);
+        store_rows(v.r, ri, i, A.n);
+        store_rows(v.z, zi, i, A.n);
+        store_rows(v.d, zi, i, A.n);
+    });
     if (flags) atomicOr(&st->flags, flags);
     setup_block_finish<MODE, P>(Lb, sh.acc[0], w0, blockIdx.x, ee, capture, &st->flags, sh);
     setup_block_finish<MODE, P>(Lt, sh.acc[1], w1, blockIdx.x, ee, capture, &st->flags, sh);
@@ -124,12 +125,10 @@ hipError_t launch_pcg_setup(int mode, const SellMat<T> &A, const PcgVecs<T> &v, 
     if (e != hipSuccess) return e;
     dispatch(mode, c.fpe_size, [&](auto m, auto p) {
         constexpr int M = decltype(m)::value, PP = decltype(p)::value;
-        if (A.col16)
-            k_pcg_setup<M, PP, true, T><<<c.grid, c.block, 0, c.stream>>>(A, v, st, s0, s1, s2, c.early_exit,
-                                                                         c.fallback);
-        else
-            k_pcg_setup<M, PP, false, T><<<c.grid, c.block, 0, c.stream>>>(A, v, st, s0, s1, s2, c.early_exit,
-                                                                          c.fallback);
+        dispatch_layout(A.layout(), [&](auto lay) {
+            k_pcg_setup<M, PP, decltype(lay)::value, T><<<c.grid, c.block, 0, c.stream>>>(A, v, st, s0, s1, s2,
+                                                                                          c.early_exit, c.fallback);
+        });
         k_pcg_fin_setup<M, PP, T><<<1, MAX_BLOCK, 0, c.stream>>>(c.grid, v, st, s0, s1, s2, tol, c.early_exit,
                                                                  c.fallback);
     });

@@ -73,13 +73,12 @@ __device__ __forceinline__ void max_to(unsigned long long *p, unsigned long long
 
 // Pass 1, one slice at a time per wavefront (grid-stride): structural check
 // of the CSR (row_ptr[0] = 0, row_ptr[n] = nnz, non-decreasing, columns in
-// [0, n)), slice widths (the slice's longest row), the longest row,
-// and whether the 16-bit column codes can represent the slice: *max_delta
+// [0, n)), the longest row, and whether the 16-bit column codes can represent the slice: *max_delta
 // receives the largest |rank-0 code|, or 2^40 if a step between consecutive
 // columns of a row is negative or above 65535. Each wavefront keeps its
 // maxima in registers and publishes them once.
 __global__ void k_csr_scan(int n, int nnz, int nslices, const int *__restrict__ rp, const int *__restrict__ col,
-                           int vec, long long *off_plus1, int *bad, int *max_len, long long *max_delta)
+                           int *bad, int *max_len, long long *max_delta)
 {
     const int lane = lane_of();
     const long long wave0 = ((long long)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
@@ -100,7 +99,6 @@ __global__ void k_csr_scan(int n, int nnz, int nslices, const int *__restrict__ 
         int w = len;
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) w = max(w, __shfl_xor(w, off, 64));
-        if (lane == 0) off_plus1[s] = 64ll * w; // an odd width ends in a single-entry column
         wmax = max(wmax, w);
         if (__ballot(!ok) != 0) { // rows inconsistent: the entries are not read
             failed = true;
@@ -138,28 +136,6 @@ __global__ void k_csr_scan(int n, int nnz, int nslices, const int *__restrict__ 
         max_to(max_len, wmax);
         max_to((unsigned long long *)max_delta, dmax);
     }
-}
-
-// In-place inclusive prefix sum of off[1..nslices] with off[0] = 0, one workgroup of 1024.
-__global__ void __launch_bounds__(1024) k_sell_scan(long long *off, int nslices)
-{
-    __shared__ long long part[1024];
-    int t = threadIdx.x;
-    long long chunk = (nslices + 1023) / 1024;
-    long long b = 1 + t * chunk, e = min((long long)nslices + 1, b + chunk);
-    long long s = 0;
-    for (long long i = b; i < e; ++i) s += off[i];
-    part[t] = s;
-    __syncthreads();
-    for (int d = 1; d < 1024; d <<= 1) {
-        long long v = t >= d ? part[t - d] : 0;
-        __syncthreads();
-        part[t] += v;
-        __syncthreads();
-    }
-    long long run = t ? part[t - 1] : 0;
-    for (long long i = b; i < e; ++i) { run += off[i]; off[i] = run; }
-    if (t == 0) off[0] = 0;
 }
 
 // Pass 2, one workgroup of one wavefront per slice. Padding entries hold the
@@ -250,39 +226,32 @@ __global__ void __launch_bounds__(64) k_sell_fill(int n, int nslices, const int 
     }
 }
 
-// y = A x on a prepared sliced-ELL copy (Section 4.3): lane j of a wavefront
-// computes row 64 s + j as the sequential fma chain of sell_row (the same
-// chain, from +0 in storage order, as the CSR kernel); wavefronts stride over
-// the slices.
-template <bool COL16>
+// y = A x on a prepared copy (Section 4.3): lane j of a wavefront computes row
+// 64 s + j as the sequential fma chain of slice_row (the same chain, from +0 in
+// storage order, as the CSR kernel). Diagonal-aligned slices are cut into
+// `parts` contiguous ranges, one per XCD (see wave_slices).
+template <int LAY>
 __global__ void __launch_bounds__(256) k_sell_spmv(SellMat<double> A, const double *__restrict__ x,
-                                                   double *__restrict__ y)
+                                                   double *__restrict__ y, int parts)
 {
     const int lane = lane_of();
-    const int W = blockDim.x >> 6;
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    for (long long s = (long long)blockIdx.x * W + wave; s < A.nslices; s += (long long)gridDim.x * W) {
-        const long long base = uniform_ll(A.off[s]);
-        const int width = __builtin_amdgcn_readfirstlane((int)((A.off[s + 1] - base) >> 6));
-        const long long i = s * 64 + lane;
-        const int len = sell_len(A, i);
-        const double sum = sell_row<double, COL16, false>(A, base, width, i, len, x, nullptr, nullptr);
-        if (i < A.n) y[i] = sum;
-    }
+    for_slices<double, LAY, false>(A, wave_slices(A.nslices, parts), lane, [&](long long i, auto &&rows) {
+        double sum[lane_rows<LAY>()];
+        rows(x, sum, nullptr, nullptr);
+        store_rows(y, sum, i, A.n);
+    });
 }
 
 // ---------------------------------------------------------------------------
 // Launch functions
 
-hipError_t launch_csr_scan(int n, int nnz, const int *row_ptr, const int *col, int vec, long long *off_plus1,
-                           int *bad, int *max_len, long long *max_delta, hipStream_t s)
+hipError_t launch_csr_scan(int n, int nnz, const int *row_ptr, const int *col, int *bad, int *max_len,
+                           long long *max_delta, hipStream_t s)
 {
     const int nslices = (n + 63) / 64;
     if (nslices == 0) return hipSuccess;
-    if (vec < 1) return hipErrorInvalidValue;
     const int grid = (int)std::min<long long>((nslices + 3) / 4, 4096);
-    hipLaunchKernelGGL(k_csr_scan, dim3(grid), dim3(256), 0, s, n, nnz, nslices, row_ptr, col, vec, off_plus1, bad,
-                       max_len, max_delta);
+    hipLaunchKernelGGL(k_csr_scan, dim3(grid), dim3(256), 0, s, n, nnz, nslices, row_ptr, col, bad, max_len, max_delta);
     return hipGetLastError();
 }
 
@@ -290,14 +259,10 @@ hipError_t launch_sell_spmv(const SellMat<double> &A, const double *x, double *y
 {
     if (A.nslices == 0) return hipSuccess;
     if (grid < 1) return hipErrorInvalidValue;
-    if (A.col16) hipLaunchKernelGGL(k_sell_spmv<true>, dim3(grid), dim3(256), 0, s, A, x, y);
-    else hipLaunchKernelGGL(k_sell_spmv<false>, dim3(grid), dim3(256), 0, s, A, x, y);
-    return hipGetLastError();
-}
-
-hipError_t launch_sell_scan(long long *off, int nslices, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_sell_scan, dim3(1), dim3(1024), 0, s, off, nslices);
+    const int parts = A.ds && grid >= 64 ? NUM_XCDS : 1;
+    dispatch_layout(A.layout(), [&](auto lay) {
+        k_sell_spmv<decltype(lay)::value><<<grid, 256, 0, s>>>(A, x, y, parts);
+    });
     return hipGetLastError();
 }
 

@@ -4,7 +4,10 @@
 // column encoding are described with SellMat.
 #pragma once
 
+#include "diag_row.hpp"
 #include "kernels.hpp"
+
+#include <type_traits>
 
 namespace rpcg {
 
@@ -181,6 +184,95 @@ __device__ __forceinline__ T sell_row(const SellMat<T> &A, long long base, int w
     else
         sell_rest<T, COL16, DIAG, BG - 1, false>(groups - g0, A, p0, g0, first, cur, len, i, x, sum, aii, found, 0, 0);
     return sum;
+}
+
+// Slices of a wavefront when the slices are cut into `parts` contiguous ranges
+// and workgroup b works in range b % parts (workgroups are dealt round-robin
+// over the XCDs, so with one part per XCD the rows an XCD gathers from stay
+// together in its L2). Kept in scalar registers: the division runs on the
+// vector unit, and a slice index left there would turn every uniform load
+// that depends on it into a vector load.
+struct SliceRange {
+    long long begin, end, step;
+};
+__device__ __forceinline__ SliceRange wave_slices(int nslices, int parts)
+{
+    const int W = blockDim.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int idx = __builtin_amdgcn_readfirstlane((int)(blockIdx.x / parts));
+    const int part = (int)blockIdx.x - idx * parts;
+    const int groups = __builtin_amdgcn_readfirstlane((int)((gridDim.x - part + parts - 1) / parts));
+    const long long lo = uniform_ll((long long)nslices * part / parts);
+    return {lo + (long long)idx * W + wave, uniform_ll((long long)nslices * (part + 1) / parts), (long long)groups * W};
+}
+
+// Rows a lane owns per slice.
+template <int LAY>
+constexpr int lane_rows() { return LAY == LAY_DIAG ? 2 : 1; }
+
+// Elements i, .., i + R - 1 of a vector of n (zeros past the end).
+template <int R, typename T>
+__device__ __forceinline__ void load_rows(T (&o)[R], const T *__restrict__ p, long long i, int n)
+{
+    if constexpr (R == 2) {
+        if (i + 1 < n) {
+            const pair_t<T> q = *(const pair_t<T> *)(p + i);
+            o[0] = q.x;
+            o[1] = q.y;
+            return;
+        }
+        o[1] = T(0);
+    }
+    o[0] = i < n ? p[i] : T(0);
+}
+template <int R, typename T>
+__device__ __forceinline__ void store_rows(T *__restrict__ p, const T (&v)[R], long long i, int n)
+{
+    if constexpr (R == 2) {
+        if (i + 1 < n) {
+            *(pair_t<T> *)(p + i) = pair_t<T>{v[0], v[1]};
+            return;
+        }
+    }
+    if (i < n) p[i] = v[0];
+}
+
+// f(i, rows) for every slice of a wavefront's range, in order: i is the lane's
+// first row, and rows(x, sum, aii, found) gives its lane_rows<LAY>() rows of
+// A x in the copy's layout LAY (0 past the last row).
+template <typename T, int LAY, bool DIAG, typename F>
+__device__ __forceinline__ void for_slices(const SellMat<T> &A, const SliceRange &R, int lane, F &&f)
+{
+    if constexpr (LAY == LAY_DIAG) {
+        if (R.begin >= R.end) return;
+        DiagSlice next = A.ds[R.begin];
+        for (long long s = R.begin; s < R.end; s += R.step) {
+            const DiagRec S = diag_scalar(next);
+            next = A.ds[s + R.step < R.end ? s + R.step : s];
+            f(s * DIAG_ROWS + 2 * lane, [&](const T *__restrict__ x, T (&sum)[2], T *aii, bool *found) {
+                diag_rows<T, DIAG>(A, S, s, (unsigned)lane, x, sum, aii, found);
+            });
+        }
+    } else {
+        for (long long s = R.begin; s < R.end; s += R.step) {
+            const long long base = uniform_ll(A.off[s]);
+            const int width = __builtin_amdgcn_readfirstlane((int)((A.off[s + 1] - base) >> 6));
+            const long long i = s * 64 + lane;
+            const int len = sell_len(A, i);
+            f(i, [&](const T *__restrict__ x, T (&sum)[1], T *aii, bool *found) {
+                sum[0] = sell_row<T, LAY == LAY_COL16, DIAG>(A, base, width, i, len, x, aii, found);
+            });
+        }
+    }
+}
+
+// Call f(IC<layout>) for the runtime layout of a copy.
+template <typename F>
+inline void dispatch_layout(int layout, F &&f)
+{
+    if (layout == LAY_DIAG) f(std::integral_constant<int, LAY_DIAG>{});
+    else if (layout == LAY_COL16) f(std::integral_constant<int, LAY_COL16>{});
+    else f(std::integral_constant<int, LAY_COL32>{});
 }
 
 } // namespace rpcg
