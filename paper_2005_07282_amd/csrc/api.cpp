@@ -23,12 +23,16 @@ using namespace rpcg_host;
 static int ensure_ws(rpcg_ctx *c, int groups)
 {
     if (groups <= c->ws_groups) return RPCG_OK;
+    const size_t acc_bytes = DOT_COPIES * DOT_PITCH * sizeof(long long);
     size_t per = (size_t)groups * (ACC_WORDS * sizeof(long long) + 2 * sizeof(int) +
                                    MAX_FPE * sizeof(double) + sizeof(int));
-    RPCG_TRY(c->ws_mem.ensure(3 * per + 256 * 4));
+    per = acc_bytes + (per + 255) / 256 * 256;
+    RPCG_TRY(c->ws_mem.ensure(3 * per));
     char *base = (char *)c->ws_mem.p;
     for (int i = 0; i < 3; ++i) {
         char *b = base + i * per;
+        c->ws[i].acc = (long long *)b;
+        b += acc_bytes;
         c->ws[i].digits = (long long *)b;
         b += (size_t)groups * ACC_WORDS * sizeof(long long);
         c->ws[i].part = (double *)b;
@@ -462,13 +466,12 @@ static int run_pcg(rpcg_ctx *c, int mode, const SellMat<T> &M, const T *b, T *x,
     v.hist = o.tau_history;
     RPCG_TRY(c->beta_hist.ensure(sizeof(double) * ((size_t)o.maxit + 1)));
     v.beta_hist = (double *)c->beta_hist.p;
-    const int stride = c->ws_groups;
     T *t = v.dinv; // the factored preconditioner needs no inverse diagonal: t = G^T r lives there
     if constexpr (F64) {
-        if (fp) RPCG_TRY(launch_fac_setup(mode, M, *fp, v, t, c->st, c->ws, stride, o.tol, o.maxit, cfg_rows));
-        else RPCG_TRY(launch_pcg_setup<T>(mode, M, v, c->st, c->ws, stride, o.tol, o.maxit, cfg_sl));
+        if (fp) RPCG_TRY(launch_fac_setup(mode, M, *fp, v, t, c->st, c->ws, o.tol, o.maxit, cfg_rows));
+        else RPCG_TRY(launch_pcg_setup<T>(mode, M, v, c->st, c->ws, o.tol, o.maxit, cfg_sl));
     } else {
-        RPCG_TRY(launch_pcg_setup<T>(mode, M, v, c->st, c->ws, stride, o.tol, o.maxit, cfg_sl));
+        RPCG_TRY(launch_pcg_setup<T>(mode, M, v, c->st, c->ws, o.tol, o.maxit, cfg_sl));
     }
     RPCG_TRY(hipStreamSynchronize(s));
     out->setup_ms = ms_since(t0);
@@ -491,30 +494,26 @@ static int run_pcg(rpcg_ctx *c, int mode, const SellMat<T> &M, const T *b, T *x,
             const int l = launched + it;
             hipEvent_t *ev = (timing && l % kstride == 0) ? &c->events[(size_t)l * EV_PER_IT] : nullptr;
             if (ev) RPCG_TRY(hipEventRecord(ev[0], s));
-            RPCG_TRY(launch_pcg_spmv_dot<T>(mode, M, v, c->st, c->ws[0], stride, cfg_sl));
+            RPCG_TRY(launch_pcg_spmv_dot<T>(mode, M, v, c->st, c->ws, cfg_sl));
             if (ev) RPCG_TRY(hipEventRecord(ev[1], s));
             if (k1_only) ev = nullptr;
             bool done_fac = false;
             if constexpr (F64) {
                 if (fp) {
-                    // beta partials in ws[0] (the SpMV's are merged first), tau in ws[1];
                     // r alternates between its buffer and r2
                     PcgVecs<T> vl = v;
                     vl.r = (l & 1) ? r2 : v.r;
-                    RPCG_TRY(launch_fac_update(mode, l, n, *fp, vl, (l & 1) ? v.r : r2, t, c->st, c->ws[0],
-                                               cfg_sl.grid, c->ws, stride, cfg_rows));
+                    RPCG_TRY(launch_fac_update(mode, l, n, *fp, vl, (l & 1) ? v.r : r2, t, c->st, c->ws,
+                                               cfg_sl.grid, cfg_rows));
                     if (ev) RPCG_TRY(hipEventRecord(ev[2], s));
-                    RPCG_TRY(launch_pcg_direction<T>(mode, l, n, v, c->st, c->ws, cfg_rows.grid, stride, cfg_rows,
-                                                     false));
+                    RPCG_TRY(launch_pcg_direction<T>(mode, l, n, v, c->st, c->ws, cfg_rows.grid, cfg_rows, false));
                     done_fac = true;
                 }
             }
             if (!done_fac) {
-                RPCG_TRY(launch_pcg_update<T>(mode, l, n, v, c->st, c->ws[0], cfg_sl.grid, c->ws + 1, stride,
-                                              cfg_rows));
+                RPCG_TRY(launch_pcg_update<T>(mode, l, n, v, c->st, c->ws, cfg_sl.grid, cfg_rows));
                 if (ev) RPCG_TRY(hipEventRecord(ev[2], s));
-                RPCG_TRY(launch_pcg_direction<T>(mode, l, n, v, c->st, c->ws + 1, cfg_rows.grid, stride, cfg_rows,
-                                                 true));
+                RPCG_TRY(launch_pcg_direction<T>(mode, l, n, v, c->st, c->ws, cfg_rows.grid, cfg_rows, true));
             }
             if (ev) RPCG_TRY(hipEventRecord(ev[3], s));
         }

@@ -29,7 +29,14 @@ struct DotWs {
     int *range;        // [gmax][2] nonzero word range of each workgroup accumulator
     double *part;      // [gmax][MAX_FPE] workgroup expansions (fpe) or partial sums (plain)
     int *esc;          // [gmax] escape counts (fpe)
+    long long *acc;    // [DOT_COPIES][DOT_PITCH] accumulators the single solver's workgroups add to
 };
+
+// The single solver's exact dots: workgroups add the words of their
+// accumulators into one of DOT_COPIES copies (integers, any order), the next
+// kernel sums the copies. Eight copies keep the adds to one address few
+// enough to drain with the kernel; the escape count sits behind the words of copy 0.
+constexpr int DOT_COPIES = 8, DOT_PITCH = 72, DOT_ESC = 70;
 
 // Scalars of one standalone dot call (device memory).
 struct DotInfo {
@@ -242,23 +249,25 @@ struct PcgVecs {
 // (the binary32 inner solver of the mixed-precision refinement). Scalars in
 // PcgState are held as binary64; binary32 values widen to it exactly.
 
-// Setup (state init, partials, one-workgroup finalize) into ws3[0..2].
+// Setup (state init, partials, one-workgroup finalize) into ws3[0..2], which it leaves empty.
 template <typename T>
 hipError_t launch_pcg_setup(int mode, const SellMat<T> &A, const PcgVecs<T> &v, PcgState *st, const DotWs *ws3,
-                            int stride, double tol, int maxit, const LaunchCfg &cfg);
-// Iteration l: K1 writes its partials to `ws`; K2 merges them (Gd slots) and
-// writes two dots into ws2[0..1]; K3 merges those (G slots).
+                            double tol, int maxit, const LaunchCfg &cfg);
+// Iteration l: K1 adds <d,w> to ws3[0]; K2 merges it (from Gd workgroups) and
+// adds <z,r> to ws3[1] and <r,r> to ws3[2]; K3 merges those (from G
+// workgroups). Each dot is emptied by the kernel after the one that reads it
+// (K3 empties ws3[0], K1 the others).
 template <typename T>
-hipError_t launch_pcg_spmv_dot(int mode, const SellMat<T> &A, const PcgVecs<T> &v, PcgState *st,
-                               const DotWs &ws, int stride, const LaunchCfg &cfg);
+hipError_t launch_pcg_spmv_dot(int mode, const SellMat<T> &A, const PcgVecs<T> &v, PcgState *st, const DotWs *ws3,
+                               const LaunchCfg &cfg);
 template <typename T>
-hipError_t launch_pcg_update(int mode, int l, int n, const PcgVecs<T> &v, PcgState *st, const DotWs &wsd, int Gd,
-                             const DotWs *ws2, int stride, const LaunchCfg &cfg);
+hipError_t launch_pcg_update(int mode, int l, int n, const PcgVecs<T> &v, PcgState *st, const DotWs *ws3, int Gd,
+                             const LaunchCfg &cfg);
 // s3: also apply the iterate update of iteration l (the Jacobi solver; the
 // factored solver's update kernel applies it itself).
 template <typename T>
-hipError_t launch_pcg_direction(int mode, int l, int n, const PcgVecs<T> &v, PcgState *st, const DotWs *ws2, int G,
-                                int stride, const LaunchCfg &cfg, bool s3);
+hipError_t launch_pcg_direction(int mode, int l, int n, const PcgVecs<T> &v, PcgState *st, const DotWs *ws3, int G,
+                                const LaunchCfg &cfg, bool s3);
 
 // ---- mixed-precision refinement (binary64 outer loop) ----
 
@@ -300,19 +309,18 @@ struct FacPre {
     double eps;
 };
 
-// Setup: r = b - A x0, partials of <r,r> (ws3[1]) and <b,b> (ws3[2]); t = G^T r;
-// z = G t + eps r, d = z, partials of <z,r> (ws3[0]); merge of the three.
-// Every step that writes partials runs on cfg.grid workgroups.
+// Setup: r = b - A x0, <r,r> (ws3[1]) and <b,b> (ws3[2]); t = G^T r;
+// z = G t + eps r, d = z, <z,r> (ws3[0]); merge of the three, left empty.
+// Every step that adds to a dot runs on cfg.grid workgroups.
 hipError_t launch_fac_setup(int mode, const SellMat<double> &A, const FacPre &P, const PcgVecs<double> &v, double *t,
-                            PcgState *st, const DotWs *ws3, int stride, double tol, int maxit, const LaunchCfg &cfg);
-// Iteration l after the SpMV kernel (partials of <d,w> in wsd, Gd slots), two
+                            PcgState *st, const DotWs *ws3, double tol, int maxit, const LaunchCfg &cfg);
+// Iteration l after the SpMV kernel (<d,w> in ws3[0], from Gd workgroups), two
 // launches: merge delta, rho; x update; r update read from v.r and written to
-// r_new (the caller alternates the two buffers), partials of <r,r> (ws[1]),
-// t = G^T r; then z = G t + eps r with partials of <z,r> (ws[0]). The
-// direction kernel then merges ws[0] (beta) and ws[1] (tau).
+// r_new (the caller alternates the two buffers), <r,r> added to ws3[2],
+// t = G^T r; then z = G t + eps r with <z,r> added to ws3[1]. The direction
+// kernel then merges those as in the Jacobi solver.
 hipError_t launch_fac_update(int mode, int l, int n, const FacPre &P, const PcgVecs<double> &v, double *r_new,
-                             double *t, PcgState *st, const DotWs &wsd, int Gd, const DotWs *ws, int stride,
-                             const LaunchCfg &cfg);
+                             double *t, PcgState *st, const DotWs *ws3, int Gd, const LaunchCfg &cfg);
 
 // ---- batched solves (many independent systems per launch) ----
 

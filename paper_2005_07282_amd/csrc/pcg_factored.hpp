@@ -22,7 +22,7 @@ __global__ void k_fac_gt(int n, FacPre Pr, const double *__restrict__ r, double 
 // z = G t + eps r (and d = z at setup); partials of <z, r>.
 template <int MODE, int P, bool SETUP>
 __global__ void __launch_bounds__(MAX_BLOCK)
-k_fac_z(int n, FacPre Pr, PcgVecs<double> v, const double *__restrict__ t, PcgState *st, SlotView wb, bool ee,
+k_fac_z(int n, FacPre Pr, PcgVecs<double> v, const double *__restrict__ t, PcgState *st, DotWs wb, bool ee,
         bool capture)
 {
     __shared__ RedShared sh;
@@ -39,7 +39,7 @@ k_fac_z(int n, FacPre Pr, PcgVecs<double> v, const double *__restrict__ t, PcgSt
         if (SETUP) v.d[i] = zi;
         Lb.add(zi, ri, sh.acc[0], ee, capture);
     }
-    block_finish<MODE, P>(Lb, sh.acc[0], wb, blockIdx.x, ee, capture, &st->flags, sh);
+    block_publish<MODE, P, 1, false>({&Lb}, {sh.acc[0]}, {&wb}, ee, capture, &st->flags, sh);
 }
 
 } // namespace rpcg

@@ -26,26 +26,38 @@ __global__ void k_fac_gt(int n, FacPre Pr, const double *__restrict__ r, double 
 template <int MODE, int P>
 __global__ void __launch_bounds__(MAX_BLOCK)
 k_fac_update(int l, int n, FacPre Pr, PcgVecs<double> v, const double *__restrict__ r_old, double *__restrict__ r_new,
-             double *__restrict__ t, PcgState *st, SlotView sd, int Gd, SlotView wt, bool ee, bool capture)
+             double *__restrict__ t, PcgState *st, DotWs wd, int Gd, DotWs wt, bool ee, bool capture)
 {
     __shared__ RedShared sh;
-    if (wg_read_flag(&st->done, sh)) return;
-    long long esc_d = 0;
-    const double delta = merge_slots<MODE, P>(sd, Gd, ee, capture, sh.acc[0], &esc_d, &st->flags, sh, 0);
-    const bool bad = (st->flags & FLAG_NONFINITE) || !is_finite_bits(delta);
+    const double beta = v.beta_hist[l];
+    if (wave_id() == 0) {
+        const int done = coherent_int(&st->done), flags = coherent_int(&st->flags);
+        long long esc;
+        const double d = wave_merge<MODE>(wd, Gd, &esc);
+        if (lane_id() == 0) {
+            sh.flag = done;
+            sh.rng[0] = flags;
+            sh.val[0] = d;
+            sh.red_ll[0] = esc;
+        }
+    }
+    zero_acc(sh.acc[1]);
+    __syncthreads();
+    if (sh.flag) return;
+    const double delta = sh.val[0];
+    const bool bad = (sh.rng[0] & FLAG_NONFINITE) || !is_finite_bits(delta);
     const bool breakdown = !(delta > 0.0);
+    const double rho = beta / delta;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        st->escapes += esc_d;
+        const long long esc_d = sh.red_ll[0];
+        if (esc_d) st->escapes += esc_d;
         if (capture && esc_d > 0) st->fallbacks += 1;
         st->delta = delta;
         if (bad) { st->status = -6; st->done = 1; }
         else if (breakdown) { st->status = -5; st->done = 1; }
+        else st->rho = rho;
     }
     if (bad || breakdown) return;
-    const double rho = v.beta_hist[l] / delta;
-    if (blockIdx.x == 0 && threadIdx.x == 0) st->rho = rho;
-    zero_acc(sh.acc[1]);
-    __syncthreads();
     LaneDot<MODE, P> Lt;
     Lt.init();
     const double *__restrict__ w = v.w;
@@ -63,21 +75,19 @@ k_fac_update(int l, int n, FacPre Pr, PcgVecs<double> v, const double *__restric
         }
         t[i] = ti;
     }
-    block_finish<MODE, P>(Lt, sh.acc[1], wt, blockIdx.x, ee, capture, &st->flags, sh);
+    block_publish<MODE, P, 1, false>({&Lt}, {sh.acc[1]}, {&wt}, ee, capture, &st->flags, sh);
 }
 
 hipError_t launch_fac_update(int mode, int l, int n, const FacPre &Pr, const PcgVecs<double> &v, double *r_new,
-                             double *t, PcgState *st, const DotWs &wsd, int Gd, const DotWs *ws, int stride,
-                             const LaunchCfg &c)
+                             double *t, PcgState *st, const DotWs *ws3, int Gd, const LaunchCfg &c)
 {
-    SlotView sd{wsd, stride}, s0{ws[0], stride}, s1{ws[1], stride};
     PcgVecs<double> vz = v;
     vz.r = r_new;
     dispatch(mode, c.fpe_size, [&](auto m, auto p) {
         constexpr int M = decltype(m)::value, PP = decltype(p)::value;
-        k_fac_update<M, PP><<<c.grid, c.block, 0, c.stream>>>(l, n, Pr, v, v.r, r_new, t, st, sd, Gd, s1,
+        k_fac_update<M, PP><<<c.grid, c.block, 0, c.stream>>>(l, n, Pr, v, v.r, r_new, t, st, ws3[0], Gd, ws3[2],
                                                               c.early_exit, c.fallback);
-        k_fac_z<M, PP, false><<<c.grid, c.block, 0, c.stream>>>(n, Pr, vz, t, st, s0, c.early_exit, c.fallback);
+        k_fac_z<M, PP, false><<<c.grid, c.block, 0, c.stream>>>(n, Pr, vz, t, st, ws3[1], c.early_exit, c.fallback);
     });
     return hipGetLastError();
 }

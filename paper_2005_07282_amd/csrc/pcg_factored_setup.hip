@@ -7,22 +7,18 @@
 namespace rpcg {
 
 template <int MODE, int P>
-__device__ __noinline__ void fac_block_finish(LaneDot<MODE, P> &L, long long *acc, const SlotView &sv, int g, bool ee,
-                                              bool capture, int *gflags, RedShared &sh)
+__device__ __noinline__ void fac_publish(LaneDot<MODE, P> &L, long long *acc, const DotWs &w, bool ee, bool capture,
+                                         int *gflags, RedShared &sh)
 {
-    block_finish<MODE, P>(L, acc, sv, g, ee, capture, gflags, sh);
+    block_publish<MODE, P, 1, false>({&L}, {acc}, {&w}, ee, capture, gflags, sh);
 }
 
-template <int MODE, int P>
-__device__ __noinline__ double fac_merge(const SlotView &sv, int G, bool ee, bool capture, long long *acc,
-                                         long long *esc_out, int *flags_out, RedShared &sh, int slot_val)
+static __global__ void k_fac_state_init(PcgState *st, int maxit, DotWs w0, DotWs w1, DotWs w2)
 {
-    return merge_slots<MODE, P>(sv, G, ee, capture, acc, esc_out, flags_out, sh, slot_val);
-}
-
-static __global__ void k_fac_state_init(PcgState *st, int maxit)
-{
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+    clear_dot(w0);
+    clear_dot(w1);
+    clear_dot(w2);
+    if (threadIdx.x != 0) return;
     PcgState z = {};
     z.maxit = maxit;
     *st = z;
@@ -31,7 +27,7 @@ static __global__ void k_fac_state_init(PcgState *st, int maxit)
 // r = b - A x0 over the sliced-ELL copy; partials of <r,r> and <b,b>.
 template <int MODE, int P, int LAY>
 __global__ void __launch_bounds__(MAX_BLOCK)
-k_fac_setup_r(SellMat<double> A, PcgVecs<double> v, PcgState *st, SlotView wt, SlotView wbb, bool ee, bool capture)
+k_fac_setup_r(SellMat<double> A, PcgVecs<double> v, PcgState *st, DotWs wt, DotWs wbb, bool ee, bool capture)
 {
     __shared__ RedShared sh;
     zero_acc(sh.acc[1]);
@@ -60,21 +56,35 @@ k_fac_setup_r(SellMat<double> A, PcgVecs<double> v, PcgState *st, SlotView wt, S
         store_rows(v.r, ri, i, A.n);
     });
     if (flags) atomicOr(&st->flags, flags);
-    fac_block_finish<MODE, P>(Lt, sh.acc[1], wt, blockIdx.x, ee, capture, &st->flags, sh);
-    fac_block_finish<MODE, P>(Lbb, sh.acc[2], wbb, blockIdx.x, ee, capture, &st->flags, sh);
+    fac_publish<MODE, P>(Lt, sh.acc[1], wt, ee, capture, &st->flags, sh);
+    fac_publish<MODE, P>(Lbb, sh.acc[2], wbb, ee, capture, &st->flags, sh);
 }
 
-// One workgroup: beta0, tau0, <b,b>, threshold, stopping test.
+// One workgroup of FIN_BLOCK threads, a dot per wavefront: beta0, tau0, <b,b>,
+// threshold, stopping test. Leaves the accumulators empty.
+constexpr int FIN_BLOCK = 256;
 template <int MODE, int P>
-__global__ void __launch_bounds__(MAX_BLOCK)
-k_fac_fin_setup(int G, PcgVecs<double> v, PcgState *st, SlotView w0, SlotView w1, SlotView w2, double tol, bool ee,
-                bool capture)
+__global__ void __launch_bounds__(FIN_BLOCK)
+k_fac_fin_setup(int G, PcgVecs<double> v, PcgState *st, DotWs w0, DotWs w1, DotWs w2, double tol, bool ee, bool capture)
 {
     __shared__ RedShared sh;
-    long long e0, e1, e2;
-    const double beta = fac_merge<MODE, P>(w0, G, ee, capture, sh.acc[0], &e0, &st->flags, sh, 0);
-    const double tau = fac_merge<MODE, P>(w1, G, ee, capture, sh.acc[1], &e1, &st->flags, sh, 1);
-    const double bb = fac_merge<MODE, P>(w2, G, ee, capture, sh.acc[2], &e2, &st->flags, sh, 2);
+    const int wv = wave_id();
+    if (wv < 3) {
+        long long esc;
+        const double d = wave_merge<MODE>(wv == 0 ? w0 : (wv == 1 ? w1 : w2), G, &esc);
+        if (lane_id() == 0) {
+            sh.val[wv] = d;
+            sh.red_ll[wv] = esc;
+        }
+    }
+    __syncthreads();
+    if (MODE != MODE_PLAIN) {
+        clear_dot(w0);
+        clear_dot(w1);
+        clear_dot(w2);
+    }
+    const double beta = sh.val[0], tau = sh.val[1], bb = sh.val[2];
+    const long long e0 = sh.red_ll[0], e1 = sh.red_ll[1], e2 = sh.red_ll[2];
     if (threadIdx.x == 0) {
         st->escapes += e0 + e1 + e2;
         if (capture) st->fallbacks += (e0 > 0) + (e1 > 0) + (e2 > 0);
@@ -98,10 +108,10 @@ k_fac_fin_setup(int G, PcgVecs<double> v, PcgState *st, SlotView w0, SlotView w1
 }
 
 hipError_t launch_fac_setup(int mode, const SellMat<double> &A, const FacPre &Pr, const PcgVecs<double> &v, double *t,
-                            PcgState *st, const DotWs *ws3, int stride, double tol, int maxit, const LaunchCfg &c)
+                            PcgState *st, const DotWs *ws3, double tol, int maxit, const LaunchCfg &c)
 {
-    SlotView s0{ws3[0], stride}, s1{ws3[1], stride}, s2{ws3[2], stride};
-    k_fac_state_init<<<1, 64, 0, c.stream>>>(st, maxit);
+    const DotWs &s0 = ws3[0], &s1 = ws3[1], &s2 = ws3[2];
+    k_fac_state_init<<<1, 256, 0, c.stream>>>(st, maxit, s0, s1, s2);
     dispatch(mode, c.fpe_size, [&](auto m, auto p) {
         constexpr int M = decltype(m)::value, PP = decltype(p)::value;
         dispatch_layout(A.layout(), [&](auto lay) {
@@ -110,7 +120,7 @@ hipError_t launch_fac_setup(int mode, const SellMat<double> &A, const FacPre &Pr
         });
         k_fac_gt<<<c.grid, c.block, 0, c.stream>>>(A.n, Pr, v.r, t, st);
         k_fac_z<M, PP, true><<<c.grid, c.block, 0, c.stream>>>(A.n, Pr, v, t, st, s0, c.early_exit, c.fallback);
-        k_fac_fin_setup<M, PP><<<1, MAX_BLOCK, 0, c.stream>>>(c.grid, v, st, s0, s1, s2, tol, c.early_exit,
+        k_fac_fin_setup<M, PP><<<1, FIN_BLOCK, 0, c.stream>>>(c.grid, v, st, s0, s1, s2, tol, c.early_exit,
                                                               c.fallback);
     });
     return hipGetLastError();

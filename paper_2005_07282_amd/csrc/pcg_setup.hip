@@ -7,26 +7,23 @@
 
 namespace rpcg {
 
-// The setup runs once per solve: its three block partials and three merges go
-// through out-of-line calls, which keeps the number of inlined copies (and
-// the compile time over all mode and length variants) down.
+// The setup runs once per solve: its three block partials go through
+// out-of-line calls, which keeps the number of inlined copies (and the
+// compile time over all mode and length variants) down.
 template <int MODE, int P>
-__device__ __noinline__ void setup_block_finish(LaneDot<MODE, P> &L, long long *acc, const SlotView &sv, int g,
-                                                bool ee, bool capture, int *gflags, RedShared &sh)
+__device__ __noinline__ void setup_publish(LaneDot<MODE, P> &L, long long *acc, const DotWs &w, bool ee, bool capture,
+                                           int *gflags, RedShared &sh)
 {
-    block_finish<MODE, P>(L, acc, sv, g, ee, capture, gflags, sh);
+    block_publish<MODE, P, 1, false>({&L}, {acc}, {&w}, ee, capture, gflags, sh);
 }
 
-template <int MODE, int P, typename T>
-__device__ __noinline__ T setup_merge(const SlotView &sv, int G, bool ee, bool capture, long long *acc,
-                                      long long *esc_out, int *flags_out, RedShared &sh, int slot_val)
+// State of a new solve; the dots' accumulators emptied (one workgroup).
+static __global__ void k_state_init(PcgState *st, int maxit, DotWs w0, DotWs w1, DotWs w2)
 {
-    return merge_slots<MODE, P, T>(sv, G, ee, capture, acc, esc_out, flags_out, sh, slot_val);
-}
-
-static __global__ void k_state_init(PcgState *st, int maxit)
-{
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+    clear_dot(w0);
+    clear_dot(w1);
+    clear_dot(w2);
+    if (threadIdx.x != 0) return;
     PcgState z = {};
     z.maxit = maxit;
     z.ended = 0x7FFFFFFF;
@@ -38,7 +35,7 @@ static __global__ void k_state_init(PcgState *st, int maxit)
 // of the sliced-ELL copy, as in the iteration's SpMV.
 template <int MODE, int P, int LAY, typename T>
 __global__ void __launch_bounds__(MAX_BLOCK)
-k_pcg_setup(SellMat<T> A, PcgVecs<T> v, PcgState *st, SlotView w0, SlotView w1, SlotView w2, bool ee, bool capture)
+k_pcg_setup(SellMat<T> A, PcgVecs<T> v, PcgState *st, DotWs w0, DotWs w1, DotWs w2, bool ee, bool capture)
 {
     __shared__ RedShared sh;
     zero_acc(sh.acc[0]); zero_acc(sh.acc[1]); zero_acc(sh.acc[2]);
@@ -75,23 +72,36 @@ k_pcg_setup(SellMat<T> A, PcgVecs<T> v, PcgState *st, SlotView w0, SlotView w1, 
         store_rows(v.d, zi, i, A.n);
     });
     if (flags) atomicOr(&st->flags, flags);
-    setup_block_finish<MODE, P>(Lb, sh.acc[0], w0, blockIdx.x, ee, capture, &st->flags, sh);
-    setup_block_finish<MODE, P>(Lt, sh.acc[1], w1, blockIdx.x, ee, capture, &st->flags, sh);
-    setup_block_finish<MODE, P>(Lbb, sh.acc[2], w2, blockIdx.x, ee, capture, &st->flags, sh);
+    setup_publish<MODE, P>(Lb, sh.acc[0], w0, ee, capture, &st->flags, sh);
+    setup_publish<MODE, P>(Lt, sh.acc[1], w1, ee, capture, &st->flags, sh);
+    setup_publish<MODE, P>(Lbb, sh.acc[2], w2, ee, capture, &st->flags, sh);
 }
 
-// One workgroup: beta0, tau0, <b,b>; thr = RN(RN(tol*tol) <b,b>) in T with
-// tol rounded to T; stopping test.
+// One workgroup of FIN_BLOCK threads, a dot per wavefront: beta0, tau0, <b,b>; thr = RN(RN(tol*tol)
+// <b,b>) in T with tol rounded to T; stopping test. Leaves the accumulators empty.
+constexpr int FIN_BLOCK = 256;
 template <int MODE, int P, typename T>
-__global__ void __launch_bounds__(MAX_BLOCK)
-k_pcg_fin_setup(int G, PcgVecs<T> v, PcgState *st, SlotView w0, SlotView w1, SlotView w2, double tol, bool ee,
-                bool capture)
+__global__ void __launch_bounds__(FIN_BLOCK)
+k_pcg_fin_setup(int G, PcgVecs<T> v, PcgState *st, DotWs w0, DotWs w1, DotWs w2, double tol, bool ee, bool capture)
 {
     __shared__ RedShared sh;
-    long long e0, e1, e2;
-    const T beta = setup_merge<MODE, P, T>(w0, G, ee, capture, sh.acc[0], &e0, &st->flags, sh, 0);
-    const T tau = setup_merge<MODE, P, T>(w1, G, ee, capture, sh.acc[1], &e1, &st->flags, sh, 1);
-    const T bb = setup_merge<MODE, P, T>(w2, G, ee, capture, sh.acc[2], &e2, &st->flags, sh, 2);
+    const int wv = wave_id();
+    if (wv < 3) {
+        long long esc;
+        const T d = wave_merge<MODE, T>(wv == 0 ? w0 : (wv == 1 ? w1 : w2), G, &esc);
+        if (lane_id() == 0) {
+            sh.val[wv] = d;
+            sh.red_ll[wv] = esc;
+        }
+    }
+    __syncthreads();
+    if (MODE != MODE_PLAIN) {
+        clear_dot(w0);
+        clear_dot(w1);
+        clear_dot(w2);
+    }
+    const T beta = (T)sh.val[0], tau = (T)sh.val[1], bb = (T)sh.val[2];
+    const long long e0 = sh.red_ll[0], e1 = sh.red_ll[1], e2 = sh.red_ll[2];
     if (threadIdx.x == 0) {
         st->escapes += e0 + e1 + e2;
         if (capture) st->fallbacks += (e0 > 0) + (e1 > 0) + (e2 > 0);
@@ -117,19 +127,18 @@ k_pcg_fin_setup(int G, PcgVecs<T> v, PcgState *st, SlotView w0, SlotView w1, Slo
 
 template <typename T>
 hipError_t launch_pcg_setup(int mode, const SellMat<T> &A, const PcgVecs<T> &v, PcgState *st, const DotWs *ws3,
-                            int stride, double tol, int maxit, const LaunchCfg &c)
+                            double tol, int maxit, const LaunchCfg &c)
 {
-    SlotView s0{ws3[0], stride}, s1{ws3[1], stride}, s2{ws3[2], stride};
-    hipLaunchKernelGGL(k_state_init, dim3(1), dim3(64), 0, c.stream, st, maxit);
+    hipLaunchKernelGGL(k_state_init, dim3(1), dim3(256), 0, c.stream, st, maxit, ws3[0], ws3[1], ws3[2]);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     dispatch(mode, c.fpe_size, [&](auto m, auto p) {
         constexpr int M = decltype(m)::value, PP = decltype(p)::value;
         dispatch_layout(A.layout(), [&](auto lay) {
-            k_pcg_setup<M, PP, decltype(lay)::value, T><<<c.grid, c.block, 0, c.stream>>>(A, v, st, s0, s1, s2,
+            k_pcg_setup<M, PP, decltype(lay)::value, T><<<c.grid, c.block, 0, c.stream>>>(A, v, st, ws3[0], ws3[1], ws3[2],
                                                                                           c.early_exit, c.fallback);
         });
-        k_pcg_fin_setup<M, PP, T><<<1, MAX_BLOCK, 0, c.stream>>>(c.grid, v, st, s0, s1, s2, tol, c.early_exit,
+        k_pcg_fin_setup<M, PP, T><<<1, FIN_BLOCK, 0, c.stream>>>(c.grid, v, st, ws3[0], ws3[1], ws3[2], tol, c.early_exit,
                                                                  c.fallback);
     });
     return hipGetLastError();
@@ -141,6 +150,6 @@ hipError_t launch_pcg_setup(int mode, const SellMat<T> &A, const PcgVecs<T> &v, 
 #error "define RPCG_VALUE_TYPE (double or float)"
 #endif
 template hipError_t launch_pcg_setup<RPCG_VALUE_TYPE>(int, const SellMat<RPCG_VALUE_TYPE> &, const PcgVecs<RPCG_VALUE_TYPE> &, PcgState *,
-                                             const DotWs *, int, double, int, const LaunchCfg &);
+                                             const DotWs *, double, int, const LaunchCfg &);
 
 } // namespace rpcg

@@ -10,12 +10,17 @@ namespace rpcg {
 // Wavefront -> slice mapping: see wave_slices.
 template <int MODE, int P, int LAY, typename T>
 __global__ void __launch_bounds__(MAX_BLOCK)
-k_pcg_spmv_dot(SellMat<T> A, PcgVecs<T> v, PcgState *st, SlotView sv, bool ee, bool capture, int xcd_parts)
+k_pcg_spmv_dot(SellMat<T> A, PcgVecs<T> v, PcgState *st, DotWs wd, DotWs wb, DotWs wt, bool ee, bool capture,
+               int xcd_parts)
 {
     __shared__ RedShared sh;
     if (st->done) return;
     long long *acc = sh.acc[0];
     zero_acc(acc);
+    if (MODE != MODE_PLAIN && blockIdx.x == 0) { // the direction kernel has read them
+        clear_dot(wb);
+        clear_dot(wt);
+    }
     __syncthreads();
     LaneDot<MODE, P> L;
     L.init();
@@ -31,21 +36,20 @@ k_pcg_spmv_dot(SellMat<T> A, PcgVecs<T> v, PcgState *st, SlotView sv, bool ee, b
         for (int r = 0; r < R; ++r)
             if (i + r < A.n) L.add(di[r], sum[r], acc, ee, capture);
     });
-    block_finish<MODE, P>(L, acc, sv, blockIdx.x, ee, capture, &st->flags, sh);
+    block_publish<MODE, P, 1, false>({&L}, {acc}, {&wd}, ee, capture, &st->flags, sh);
 }
 
 template <typename T>
 hipError_t launch_pcg_spmv_dot(int mode, const SellMat<T> &A, const PcgVecs<T> &v, PcgState *st,
-                               const DotWs &ws, int stride, const LaunchCfg &c)
+                               const DotWs *ws3, const LaunchCfg &c)
 {
     const int want = c.xcd_parts ? c.xcd_parts : (A.ds ? NUM_XCDS : 1);
     const int parts = c.grid >= 64 ? want : 1;
-    SlotView sv{ws, stride};
     dispatch(mode, c.fpe_size, [&](auto m, auto p) {
         constexpr int M = decltype(m)::value, PP = decltype(p)::value;
         dispatch_layout(A.layout(), [&](auto lay) {
-            k_pcg_spmv_dot<M, PP, decltype(lay)::value, T><<<c.grid, c.block, 0, c.stream>>>(A, v, st, sv, c.early_exit,
-                                                                                             c.fallback, parts);
+            k_pcg_spmv_dot<M, PP, decltype(lay)::value, T><<<c.grid, c.block, 0, c.stream>>>(A, v, st, ws3[0], ws3[1], ws3[2],
+                                                                                             c.early_exit, c.fallback, parts);
         });
     });
     return hipGetLastError();
@@ -57,6 +61,6 @@ hipError_t launch_pcg_spmv_dot(int mode, const SellMat<T> &A, const PcgVecs<T> &
 #error "define RPCG_VALUE_TYPE (double or float)"
 #endif
 template hipError_t launch_pcg_spmv_dot<RPCG_VALUE_TYPE>(int, const SellMat<RPCG_VALUE_TYPE> &, const PcgVecs<RPCG_VALUE_TYPE> &, PcgState *,
-                                                const DotWs &, int, const LaunchCfg &);
+                                                const DotWs *, const LaunchCfg &);
 
 } // namespace rpcg

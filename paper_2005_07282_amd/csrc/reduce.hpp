@@ -52,6 +52,12 @@ struct RedShared {
     double val[3];
 };
 
+// A word another workgroup of the same kernel may write, from the coherent level.
+__device__ __forceinline__ int coherent_int(const int *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Workgroup-uniform read of a flag that workgroup 0 of the same kernel may
 // set while this workgroup runs: one thread reads, every thread sees its value.
 __device__ __forceinline__ bool wg_read_flag(const int *p, RedShared &sh)
@@ -329,14 +335,16 @@ __device__ __forceinline__ long long wave_sum_i64_last(long long v)
     return v;
 }
 
-// The same sum in every lane (read from lane 63).
-__device__ __forceinline__ long long wave_sum_i64_all(long long v)
+// Lane l's value in every lane (l wavefront-uniform).
+__device__ __forceinline__ long long wave_i64_of(long long v, int l)
 {
-    v = wave_sum_i64_last(v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)v, 63);
-    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(v >> 32), 63);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)v, l);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(v >> 32), l);
     return (long long)(((unsigned long long)hi << 32) | lo);
 }
+
+// The sum in every lane (read from lane 63).
+__device__ __forceinline__ long long wave_sum_i64_all(long long v) { return wave_i64_of(wave_sum_i64_last(v), 63); }
 
 // Minimum / maximum of an int over the wavefront, in every lane: the same
 // DPP pattern, lanes without a source keeping the identity.
@@ -469,6 +477,38 @@ __device__ __forceinline__ int wave_fpe_merge(double (&a)[P], bool ee, bool capt
     return esc;
 }
 
+// Whether wave_fpe_merge of these expansions cannot leave a remainder
+// anywhere. Every component is a multiple of 2^lsb. With |a[i]| < 2^(e_i + 1)
+// over the lanes, e = max e_i: at level 0 a lane's running sum stays below
+// the sum of all 64 P <= 2^9 components (and of error terms far below them), 2^(e + 12) with
+// room; a level of magnitude below 2^B passes on less than 2^(B - 53), at most 6 P < 2^6
+// times into any one expansion, so level i stays below the larger of its own content
+// and 2^7 times that, doubled. What leaves the last level is a multiple of 2^lsb: below 2^lsb
+// it is zero.
+template <int P>
+__device__ __forceinline__ bool wave_fpe_merge_is_exact(const double (&a)[P])
+{
+    int e[P], lsb = 1 << 20, all = -(1 << 20);
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+        e[i] = -(1 << 20);
+        if (a[i] != 0.0) {
+            const unsigned long long bits = __builtin_bit_cast(unsigned long long, a[i]);
+            const int be = (int)((bits >> 52) & 0x7FF);
+            const unsigned long long m = (bits & 0xFFFFFFFFFFFFFull) | (be ? 1ull << 52 : 0ull);
+            e[i] = be == 0x7FF ? 1 << 20 : (be ? be : 1) - 1023;
+            lsb = min(lsb, (be ? be : 1) - 1075 + (int)__builtin_ctzll(m));
+        }
+        e[i] = wave_minmax_i32_all<true>(e[i]);
+        all = max(all, e[i]);
+    }
+    lsb = wave_minmax_i32_all<false>(lsb);
+    int pass = all + 12 - 53;
+#pragma unroll
+    for (int i = 1; i < P; ++i) pass = max(e[i] + 1, pass + 7) + 1 - 53;
+    return pass < lsb;
+}
+
 // Fixed-order workgroup sum of a double into thread 0.
 __device__ inline double block_sum_d(double v, RedShared &sh)
 {
@@ -493,6 +533,24 @@ __device__ inline long long block_sum_ll(long long v, RedShared &sh)
         for (int w = 0; w < num_waves(); ++w) t += sh.red_ll[w];
     __syncthreads();
     return t;
+}
+
+// FPE: the lanes' expansions of a wavefront into the long accumulator, escapes
+// of the wavefront merge counted. Where the merge provably has none, the
+// expansions go in word by word instead: the same exact sum without the merge's
+// chain of 6 P^2 dependent TwoSums (31 k rows: the update kernel 23.8 -> 15 us).
+template <int P>
+__device__ __forceinline__ void wave_fpe_finish(double (&a)[P], int &esc, bool ee, bool capture, long long *acc, int &flags)
+{
+    if (wave_fpe_merge_is_exact<P>(a)) {
+        wave_flush_exact<P>(a, acc, flags);
+        return;
+    }
+    esc += wave_fpe_merge<P>(a, ee, capture, acc, flags);
+    if (lane_id() == 0) {
+#pragma unroll
+        for (int i = 0; i < P; ++i) acc_add_lds(acc, a[i], flags);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -527,11 +585,7 @@ __device__ __forceinline__ void block_finish(LaneDot<MODE, P, ADAPT> &L, long lo
             // way: the slot is the exact workgroup partial, merged across
             // workgroups like exblas
             L.esc += fpe_sum_capture<P>(L.a, L.e, ee, capture, acc, L.flags);
-            L.esc += wave_fpe_merge<P>(L.a, ee, capture, acc, L.flags);
-            if (lane_id() == 0) {
-#pragma unroll
-                for (int i = 0; i < P; ++i) acc_add_lds(acc, L.a[i], L.flags);
-            }
+            wave_fpe_finish<P>(L.a, L.esc, ee, capture, acc, L.flags);
             const long long esc = block_sum_ll(L.esc, sh);
             if (threadIdx.x == 0) sv.ws.esc[g] = (int)esc;
         }
@@ -614,18 +668,16 @@ __device__ __forceinline__ void wave_normalize(long long &a, long long &b)
         b += ca;
         long long cb = 0;
         if (l != TOP_LANE) { cb = b >> 32; b &= 0xFFFFFFFFll; }
-        long long cin = __shfl_up(cb, 1, 64);
-        if (l == 0) cin = 0;
-        a += cin;
+        a += dpp_i64<0x138>(cb); // wave_shr:1, lane 0 receives 0
         if (__ballot((a >> 32) != 0) == 0) break;
     }
 }
 
+// Word k (wavefront-uniform) of a normalized accumulator.
 __device__ __forceinline__ long long wave_word(long long a, long long b, int k)
 {
     if (k < 0 || k >= ACC_DIGITS) return 0;
-    long long v = __shfl((k & 1) ? b : a, k >> 1, 64);
-    return v;
+    return wave_i64_of((k & 1) ? b : a, k >> 1);
 }
 
 // Rounding format: significand bits, weight of the last bit of the smallest
@@ -635,16 +687,15 @@ template <> struct Fmt<double> { static constexpr int PREC = 53, QMIN = -1074, E
 template <> struct Fmt<float> { static constexpr int PREC = 24, QMIN = -149, EMAX_INF = 128; };
 
 // Correctly rounded (nearest, ties to even) value of the accumulator in
-// format T, computed by one full wavefront; every lane returns it.
-template <typename T = double>
-__device__ inline T wave_acc_round(const long long *acc)
+// format T, computed by one full wavefront from the words 2 l and 2 l + 1 of
+// each lane l (zeros past the top); every lane returns it.
+template <typename T>
+__device__ inline T wave_round(long long a, long long b)
 {
     constexpr int PREC = Fmt<T>::PREC, QMIN = Fmt<T>::QMIN, EMAX_INF = Fmt<T>::EMAX_INF;
     const int l = lane_id();
-    long long a = (2 * l < ACC_DIGITS) ? acc[2 * l] : 0;
-    long long b = (2 * l + 1 < ACC_DIGITS) ? acc[2 * l + 1] : 0;
     wave_normalize(a, b);
-    const bool neg = __shfl(b, TOP_LANE, 64) < 0;
+    const bool neg = __builtin_amdgcn_readlane((int)(b >> 32), TOP_LANE) < 0;
     if (neg) {
         a = -a;
         b = -b;
@@ -690,6 +741,13 @@ __device__ inline T wave_acc_round(const long long *acc)
         if (neg) bits |= 1u << 31;
         return __builtin_bit_cast(float, bits);
     }
+}
+
+template <typename T = double>
+__device__ inline T wave_acc_round(const long long *acc)
+{
+    const int l = lane_id();
+    return wave_round<T>((2 * l < ACC_DIGITS) ? acc[2 * l] : 0, (2 * l + 1 < ACC_DIGITS) ? acc[2 * l + 1] : 0);
 }
 
 // ---------------------------------------------------------------------------
@@ -775,6 +833,99 @@ __device__ __forceinline__ T merge_slots(const SlotView &sv, int G, bool ee, boo
         __syncthreads();
         return r;
     }
+}
+
+// ---------------------------------------------------------------------------
+// The single solver's dots: accumulators in DOT_COPIES copies (DotWs::acc).
+// Workgroups add the words of their LDS accumulators with device-scope
+// integer atomics; the consuming kernel's wavefront reads every copy in one
+// round of loads, sums and rounds. Against one slot per workgroup this saves the
+// consumer the word range and the slots' rows, two dependent rounds of memory
+// latency in every workgroup. PLAIN keeps the slots (its sum order is fixed).
+
+// Add the workgroup accumulators of D dots (LDS) to their global copies, after
+// the lanes' expansions have gone in; escapes and flags too. All threads call.
+template <int MODE, int P, int D, bool ADAPT>
+__device__ __forceinline__ void block_publish(LaneDot<MODE, P, ADAPT> *const (&L)[D], long long *const (&acc)[D],
+                                              const DotWs *const (&w)[D], bool ee, bool capture, int *gflags, RedShared &sh)
+{
+    if constexpr (MODE == MODE_PLAIN) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const double t = block_sum_d(L[d]->s, sh);
+            if (threadIdx.x == 0) w[d]->part[blockIdx.x] = t;
+        }
+    } else {
+        int fl = 0;
+        if constexpr (MODE == MODE_EXBLAS && D == 2) {
+            wave_flush_exact2<P>(L[0]->a, acc[0], L[0]->flags, L[1]->a, acc[1], L[1]->flags);
+        } else {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                if constexpr (MODE == MODE_EXBLAS) {
+                    wave_flush_exact<P>(L[d]->a, acc[d], L[d]->flags);
+                } else {
+                    L[d]->esc += fpe_sum_capture<P>(L[d]->a, L[d]->e, ee, capture, acc[d], L[d]->flags);
+                    wave_fpe_finish<P>(L[d]->a, L[d]->esc, ee, capture, acc[d], L[d]->flags);
+                    const long long esc = wave_sum_i64_all(L[d]->esc);
+                    if (lane_id() == 0 && esc) atomicAdd((unsigned long long *)&w[d]->acc[DOT_ESC], (unsigned long long)esc);
+                }
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < D; ++d) fl |= L[d]->flags;
+        __syncthreads();
+        const int copy = blockIdx.x % DOT_COPIES;
+        for (int q = threadIdx.x; q < D * ACC_DIGITS; q += blockDim.x) {
+            const int d = D == 1 ? 0 : q / ACC_DIGITS, k = q - d * ACC_DIGITS;
+            // one carry step keeps every word below 2^33 in magnitude, so the
+            // integer sum over the workgroups cannot overflow
+            const long long *a = D == 1 || d == 0 ? acc[0] : acc[D - 1];
+            const long long v = a[k];
+            const long long cin = k ? (a[k - 1] >> 32) : 0;
+            const long long o = (k == ACC_DIGITS - 1) ? v + cin : (v & 0xFFFFFFFFll) + cin;
+            long long *dst = (D == 1 || d == 0 ? w[0] : w[D - 1])->acc;
+            if (o != 0) atomicAdd((unsigned long long *)&dst[copy * DOT_PITCH + k], (unsigned long long)o);
+        }
+        if (fl) atomicOr(gflags, fl);
+    }
+}
+
+// The scalar of one dot, by one full wavefront: rounded once (every lane
+// returns it), escapes into *esc. PLAIN: the G workgroup sums in a fixed order.
+template <int MODE, typename T = double>
+__device__ __forceinline__ T wave_merge(const DotWs &w, int G, long long *esc)
+{
+    const int l = lane_id();
+    *esc = 0;
+    if constexpr (MODE == MODE_PLAIN) {
+        double s[4] = {0.0, 0.0, 0.0, 0.0};
+        int g = l;
+        for (; g + 3 * 64 < G; g += 4 * 64) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) s[j] += w.part[g + 64 * j];
+        }
+        for (; g < G; g += 64) s[0] += w.part[g];
+        return (T)__shfl(wave_sum_down((s[0] + s[1]) + (s[2] + s[3])), 0, 64);
+    } else {
+        long long a = 0, b = 0;
+        if (l < DOT_PITCH / 2) {
+            longlong2 q[DOT_COPIES];
+#pragma unroll
+            for (int c = 0; c < DOT_COPIES; ++c) q[c] = ((const longlong2 *)(w.acc + c * DOT_PITCH))[l];
+#pragma unroll
+            for (int c = 0; c < DOT_COPIES; ++c) { a += q[c].x; b += q[c].y; }
+        }
+        if constexpr (MODE == MODE_FPE) *esc = wave_i64_of(a, DOT_ESC / 2);
+        if (l > TOP_LANE) a = b = 0;
+        return wave_round<T>(a, b);
+    }
+}
+
+// Empty a dot's accumulators (one workgroup, for adds of a later kernel).
+__device__ __forceinline__ void clear_dot(const DotWs &w)
+{
+    for (int k = threadIdx.x; k < DOT_COPIES * DOT_PITCH; k += blockDim.x) w.acc[k] = 0;
 }
 
 template <int V>
