@@ -166,7 +166,7 @@ int rpcg_exdot(rpcg_ctx *ctx, rpcg_mode mode, int64_t n, const double *x, const 
  * capture, tight serving loops, harnesses that forbid hipMalloc): the dot
  * product of rpcg_exdot, same arguments, same kernels and same results,
  * without a context. Its workgroup slots and counters live in a static
- * device array of about 1.3 MB per GPU (allocated when the library is
+ * device array of about 20 KB per GPU (allocated when the library is
  * loaded, held until the process ends), so the call allocates nothing; it
  * runs on the current device. It holds at most RPCG_NOALLOC_MAX_GROUPS
  * workgroups: opts->grid_size above that gives RPCG_ERR_INVALID, and the

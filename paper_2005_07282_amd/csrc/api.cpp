@@ -144,6 +144,10 @@ int rpcg_create(rpcg_ctx **out, int device)
         rc = hip_status(hipHostMalloc((void **)&c->host_info, sizeof(DotInfo) + sizeof(long long), hipHostMallocDefault));
     if (rc == RPCG_OK) rc = hip_status(hipEventCreateWithFlags(&c->poll_ev[0], hipEventDisableTiming));
     if (rc == RPCG_OK) rc = hip_status(hipEventCreateWithFlags(&c->poll_ev[1], hipEventDisableTiming));
+    if (rc == RPCG_OK)
+        rc = hip_status(hipHostMalloc((void **)&c->host_dot, DOT_BLOCKS * 2 * sizeof(unsigned long long), hipHostMallocDefault));
+    if (rc == RPCG_OK) rc = hip_status(c->dot_blocks.ensure(sizeof(long long) * DOT_BLOCKS * DOT_COPIES * DOT_PITCH));
+    if (rc == RPCG_OK) rc = hip_status(hipMemset(c->dot_blocks.p, 0, c->dot_blocks.bytes));
     if (rc == RPCG_OK) rc = ensure_ws(c, 8 * c->num_cus);
     if (rc != RPCG_OK) { rpcg_destroy(c); return rc; }
     *out = c;
@@ -166,6 +170,7 @@ void rpcg_destroy(rpcg_ctx *c)
     c->diag_ds.release();
     c->diag_de.release();
     c->widths.release();
+    c->dot_blocks.release();
     c->vecs.release();
     c->ir_vecs.release();
     c->beta_hist.release();
@@ -173,17 +178,25 @@ void rpcg_destroy(rpcg_ctx *c)
     if (c->host_state) (void)hipHostFree(c->host_state);
     if (c->host_ir) (void)hipHostFree(c->host_ir);
     if (c->host_info) (void)hipHostFree(c->host_info);
+    if (c->host_dot) (void)hipHostFree(c->host_dot);
     for (hipEvent_t e : c->events) (void)hipEventDestroy(e);
     for (hipEvent_t e : c->ir_events) (void)hipEventDestroy(e);
     for (hipEvent_t e : c->poll_ev) if (e) (void)hipEventDestroy(e);
     delete c;
 }
 
-static int exdot_status(const DotInfo &inf, int mode, bool fallback)
+// Wait for a dot's record: the kernel writes it as its last action, so the
+// host sees it a few microseconds before the stream reports completion. A record
+// that does not come soon is waited for as any work of the stream.
+static int wait_record(const volatile unsigned long long *rec, unsigned seq, hipStream_t s)
 {
-    if (inf.flags & FLAG_NONFINITE) return RPCG_ERR_NONFINITE;
-    if (inf.flags & FLAG_INEXACT) return RPCG_WARN_FPE_INEXACT;
-    if (mode == MODE_FPE && inf.escapes > 0 && !fallback) return RPCG_WARN_FPE_INEXACT;
+    auto there = [&] { return (unsigned)(__atomic_load_n(&rec[1], __ATOMIC_ACQUIRE) >> 32) == seq; };
+    auto t0 = std::chrono::steady_clock::now();
+    for (unsigned k = 1; !there(); ++k)
+        if ((k & 255) == 0 && ms_since(t0) > 1.0) {
+            RPCG_TRY(hipStreamSynchronize(s));
+            return there() ? RPCG_OK : RPCG_ERR_HIP;
+        }
     return RPCG_OK;
 }
 
@@ -199,36 +212,24 @@ static int run_exdot(rpcg_ctx *c, int mode, int64_t n, const double *x, const do
     o.fpe_size = resolve_fpe_size(o.fpe_size, mode);
     RPCG_TRY(hipSetDevice(c->device));
     hipStream_t s = (hipStream_t)stream;
-    // 1024-thread workgroups; four per CU for the expansion modes, eight for
-    // plain (measured at 2^28 elements: 5.2 / 3.8 TB/s exact on narrow / wide
-    // data against 4.5 / 3.0 with 256-thread workgroups, eight per CU). The
-    // exact modes give a thread at least 256 elements where that still
-    // leaves a workgroup per CU: the workgroup's accumulator setup and
-    // partial and the lanes' overflow windows are then paid over more data
-    // (2^22 to 2^26 elements: 5-25% faster; 2^28 keeps four per CU).
     LaunchCfg cfg = make_cfg(c, o, std::max<int64_t>(1, (n + 7) / 8), 1024, s);
-    if (!o.grid_size) {
-        cfg.grid = (int)std::max<int64_t>(1, std::min<int64_t>((n + 8ll * cfg.block - 1) / (8ll * cfg.block),
-                                                               (mode == MODE_PLAIN ? 8ll : 4ll) * c->num_cus));
-        if (mode != MODE_PLAIN)
-            cfg.grid = (int)std::max<int64_t>(std::min<int64_t>(cfg.grid, c->num_cus),
-                                              std::min<int64_t>(cfg.grid, (n + 256ll * cfg.block - 1) / (256ll * cfg.block)));
-    }
+    if (!o.grid_size) cfg.grid = exdot_grid(mode, n, cfg.block, c->num_cus);
     int rc = ensure_ws(c, cfg.grid);
     if (rc != RPCG_OK) return rc;
-    RPCG_TRY(hipMemsetAsync(c->info, 0, sizeof(DotInfo), s));
-    if (digits) RPCG_TRY(launch_exdot_partial(n, x, y, (long long *)digits, c->ws[0], c->ws_groups, c->info, cfg));
-    else RPCG_TRY(launch_exdot(mode, n, x, y, out, c->ws[0], c->ws_groups, c->info, cfg));
+    // the calls take the context's blocks in turn
+    const unsigned seq = ++c->dot_seq ? c->dot_seq : ++c->dot_seq;
+    const unsigned slot = seq % DOT_BLOCKS;
+    unsigned long long *rec = c->host_dot + 2 * slot;
+    if (res) __atomic_store_n(&rec[1], 0ull, __ATOMIC_RELAXED);
+    const ExdotWs w{(long long *)c->dot_blocks.p + (size_t)slot * DOT_COPIES * DOT_PITCH, c->ws[0].part,
+                    res ? rec : nullptr, seq};
+    if (digits) RPCG_TRY(launch_exdot_partial(n, x, y, (long long *)digits, w, cfg));
+    else RPCG_TRY(launch_exdot(mode, n, x, y, out, w, cfg));
     if (res) {
         std::memset(res, 0, sizeof(*res));
-        DotInfo inf;
-        RPCG_TRY(hipMemcpyAsync(&inf, c->info, sizeof inf, hipMemcpyDeviceToHost, s));
-        RPCG_TRY(hipStreamSynchronize(s));
-        res->fpe_escapes = inf.escapes;
-        res->fallbacks = inf.fallbacks;
-        res->grid_size = cfg.grid;
-        res->block_size = cfg.block;
-        res->status = exdot_status(inf, mode, cfg.fallback);
+        rc = wait_record(rec, seq, s);
+        if (rc != RPCG_OK) return rc;
+        exdot_result(rec[0], rec[1], mode, cfg, res);
         return res->status;
     }
     return RPCG_OK;
@@ -744,8 +745,8 @@ static int ir_body(rpcg_ctx *c, int mode, const rpcg_csr *A, const double *b, do
     const int stride = c->ws_groups;
     IrState *ist = c->ist;
     RPCG_TRY(hipMemsetAsync(ist, 0, sizeof(IrState), s));
-    RPCG_TRY(hipMemsetAsync(c->info, 0, sizeof(DotInfo), s));
-    RPCG_TRY(launch_exdot(MODE_EXBLAS, n, b, b, &ist->bb, c->ws[0], stride, c->info, cfg_dot));
+    const ExdotWs wbb{(long long *)c->dot_blocks.p, c->ws[0].part, nullptr, 0}; // block 0: this call is the context's only one
+    RPCG_TRY(launch_exdot(MODE_EXBLAS, n, b, b, &ist->bb, wbb, cfg_dot));
     RPCG_TRY(hipStreamSynchronize(s));
     const double setup_ms = ms_since(t_start);
     const bool timing = o.timing != 0;

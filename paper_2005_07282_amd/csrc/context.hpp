@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <chrono>
 #include <cstdint>
 #include <map>
@@ -33,6 +34,9 @@ struct Buffer {
     }
 };
 
+// Accumulator blocks of the standalone dot that the calls on a context take in turn.
+constexpr unsigned DOT_BLOCKS = 16;
+
 } // namespace rpcg_host
 
 struct rpcg_ctx {
@@ -53,6 +57,9 @@ struct rpcg_ctx {
     int *host_done = nullptr;  // pinned: polled flags
     rpcg::PcgState *host_state = nullptr;
     rpcg::IrState *host_ir = nullptr;
+    rpcg_host::Buffer dot_blocks; // DOT_BLOCKS accumulator blocks of the standalone dot, empty between calls
+    unsigned long long *host_dot = nullptr; // pinned: a record of two words per block
+    unsigned dot_seq = 0;
     rpcg::DotInfo *host_info = nullptr; // and, behind it, one long long (construction total)
     std::vector<hipEvent_t> events;
     std::vector<hipEvent_t> ir_events;
@@ -107,6 +114,38 @@ inline int resolve_fpe_size(int p, int mode)
 {
     if (p) return p;
     return mode == rpcg::MODE_EXBLAS ? 3 : 4;
+}
+
+// Workgroups (of `block` threads) of a standalone dot. Plain: eight elements a
+// thread, at most eight workgroups per CU. The exact modes: one workgroup up to
+// EXDOT_ALONE elements (it needs no atomics and no tickets); then four elements
+// a thread up to one workgroup per CU, as each costs the accumulator's setup and
+// partial (2^20 pairs: 11.9 us on 256 workgroups, 13.9 us on 128, 14.3 us on 512); two per CU
+// where a thread has 32 elements or more (2^22 pairs in FPE mode: 22.6 us on
+// 256, 29.5 us on 512; 2^24 and up want 512, and no more: the next pairs are prefetched).
+constexpr int64_t EXDOT_ALONE = 8192;
+inline int exdot_grid(int mode, int64_t n, int block, int cus)
+{
+    if (mode == rpcg::MODE_PLAIN)
+        return (int)std::max<int64_t>(1, std::min<int64_t>((n + 8ll * block - 1) / (8ll * block), 8ll * cus));
+    if (n <= EXDOT_ALONE) return 1;
+    const int64_t per_cu = n / ((int64_t)cus * block) >= 32 ? 2 : 1;
+    return (int)std::max<int64_t>(1, std::min<int64_t>((n + 4ll * block - 1) / (4ll * block), per_cu * cus));
+}
+
+// A standalone dot's result record from the kernel's two words.
+inline void exdot_result(unsigned long long rec0, unsigned long long rec1, int mode, const rpcg::LaunchCfg &cfg,
+                         rpcg_result *res)
+{
+    const unsigned flags = (unsigned)rec1;
+    res->fpe_escapes = (int64_t)rec0;
+    res->fallbacks = mode == rpcg::MODE_FPE && rec0 > 0 && cfg.fallback ? 1 : 0;
+    res->grid_size = cfg.grid;
+    res->block_size = cfg.block;
+    if (flags & rpcg::FLAG_NONFINITE) res->status = RPCG_ERR_NONFINITE;
+    else if (flags & rpcg::FLAG_INEXACT) res->status = RPCG_WARN_FPE_INEXACT;
+    else if (mode == rpcg::MODE_FPE && rec0 > 0 && !cfg.fallback) res->status = RPCG_WARN_FPE_INEXACT;
+    else res->status = RPCG_OK;
 }
 
 // Timing events between solver kernels. They carry no system-scope fence:

@@ -1,22 +1,64 @@
 // Standalone dot product kernels (exact, expansion-based and plain), the
 // rounding of a long accumulator, and the CSR SpMV.
 #include "reduce.hpp"
+#include "sell_spmv.hpp"
 
 #include <algorithm>
 
 namespace rpcg {
 
 // ---------------------------------------------------------------------------
-// Standalone dot product: per-workgroup partials, then a one-workgroup
-// finalize that merges them and rounds once.
+// Standalone dot product in one launch. Each workgroup adds the words of its
+// exact partial into one of DOT_COPIES accumulators with device-scope integer
+// atomics and takes a ticket once they are complete; the workgroup that takes
+// the last one sums the copies, rounds and leaves the block empty for the next
+// call. Nothing but those atomics, and loads and stores at their level, passes
+// between workgroups, so no fence writes back a cache (a device-scope fence
+// before each ticket had cost 2 to 14 times the whole dot). The tickets are in two levels: a thousand
+// workgroups that end together would otherwise queue on one address.
+// A call on one workgroup needs neither atomics nor tickets.
+// What bounds it: HBM from about 2^26 pairs on, for narrow and wide exponents
+// alike (2^26 narrow 250 -> 185 us, 5.8 TB/s; FPE on wide data 300 -> 210 us),
+// with the next pairs prefetched and the streamed loads marked non-temporal
+// (199 us without the mark). Short calls are latency: 10007 pairs took a memset, two
+// kernels of 8.3 and 7.2 us and a copy, and take one kernel of 9.6 us.
 
 constexpr int EX_COPIES = 4;
 constexpr int EX_PITCH = ACC_DIGITS; // 136 dwords: copies 8 banks apart
+constexpr int EX_ONE_LEVEL = 64;     // workgroups up to which the tickets take one level (one round trip less)
+constexpr int EX_UNROLL = 2;         // 16-byte pairs of each vector a thread loads together
 
+__device__ __forceinline__ long long coherent_ll(const long long *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Every vector memory operation of this wavefront, atomics included, has completed.
+__device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// Spread (in binades) of the products' exponents over a wavefront's first
+// loads above which a lane starts in the direct mode: the expansions hold about 53 P bits, so
+// most products would leave a remainder. It only moves work between two exact paths.
+constexpr int EX_WIDE = 128;
+
+__device__ __forceinline__ void exponent_span(double x, double y, int &lo, int &hi)
+{
+    const int ex = (int)((__builtin_bit_cast(unsigned long long, x) >> 52) & 0x7FF);
+    const int ey = (int)((__builtin_bit_cast(unsigned long long, y) >> 52) & 0x7FF);
+    if (ex && ey) {
+        lo = min(lo, ex + ey);
+        hi = max(hi, ex + ey);
+    }
+}
+
+// blk: DOT_COPIES x DOT_PITCH words, empty (words 68 and 69: tickets, 70:
+// escapes, 71: flags); part: [gridDim.x] (plain). Writes *out, or with
+// digits_out the exact sum as normalized words; rec (may be null): rec[0]
+// the escapes, then rec[1] = seq << 32 | flags, at system scope, as the last action of the call.
 template <int MODE, int P>
 __global__ void __launch_bounds__(MAX_BLOCK)
-k_exdot_part(long long n, const double *__restrict__ x, const double *__restrict__ y, SlotView sv,
-             DotInfo *info, bool ee, bool capture)
+k_exdot(long long n, const double *__restrict__ x, const double *__restrict__ y, long long *blk, double *part,
+        double *out, long long *digits_out, unsigned long long *rec, unsigned seq, bool ee, bool capture)
 {
     __shared__ RedShared sh;
     // lanes add into one of EX_COPIES copies of the long accumulator by
@@ -25,6 +67,24 @@ k_exdot_part(long long n, const double *__restrict__ x, const double *__restrict
     // apart start in different LDS banks); summed into copy 0 at the end
     __shared__ long long accx[EX_COPIES - 1][EX_PITCH];
     long long *acc = sh.acc[0];
+    const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const long long stride = (long long)gridDim.x * blockDim.x;
+    typedef pair_t<double> pr; // 16-byte loads at any 8-byte alignment
+    const long long n2 = n >> 1;
+    pr a[EX_UNROLL], b[EX_UNROLL];
+    // the loads past the end repeat the thread's first pair or, where it has none, nothing
+    auto load = [&](long long i) {
+#pragma unroll
+        for (int u = 0; u < EX_UNROLL; ++u) {
+            const long long j = i + u * stride;
+            if (j < n2) {
+                a[u] = __builtin_nontemporal_load((const pr *)(x + 2 * j));
+                b[u] = __builtin_nontemporal_load((const pr *)(y + 2 * j));
+            }
+        }
+    };
+    long long i = tid;
+    load(i);
     zero_acc(acc);
     for (int q = threadIdx.x; q < (EX_COPIES - 1) * EX_PITCH; q += blockDim.x) (&accx[0][0])[q] = 0;
     __syncthreads();
@@ -33,24 +93,52 @@ k_exdot_part(long long n, const double *__restrict__ x, const double *__restrict
 
     LaneDot<MODE, P, MODE != MODE_PLAIN> L;
     L.init();
-    const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long long stride = (long long)gridDim.x * blockDim.x;
-    const bool vec = ((((uintptr_t)x) | ((uintptr_t)y)) & 15) == 0;
-    if (vec) {
-        const long long n2 = n >> 1;
-        const double2 *x2 = reinterpret_cast<const double2 *>(x);
-        const double2 *y2 = reinterpret_cast<const double2 *>(y);
-        for (long long i = tid; i < n2; i += stride) {
-            double2 a = x2[i], b = y2[i];
-            L.add(a.x, b.x, accl, ee, capture);
-            L.add(a.y, b.y, accl, ee, capture);
+    if (MODE == MODE_EXBLAS || (MODE == MODE_FPE && capture)) {
+        int lo = 1 << 20, hi = -1;
+        if (i < n2) {
+            exponent_span(a[0].x, b[0].x, lo, hi);
+            exponent_span(a[0].y, b[0].y, lo, hi);
         }
-        if ((n & 1) && tid == 0) L.add(x[n - 1], y[n - 1], accl, ee, capture);
-    } else {
-        for (long long i = tid; i < n; i += stride) L.add(x[i], y[i], accl, ee, capture);
+        if (wave_minmax_i32_all<true>(hi) - wave_minmax_i32_all<false>(lo) > EX_WIDE) L.direct = ADAPT_DIRECT;
     }
-    if constexpr (MODE != MODE_PLAIN) {
+    while (i < n2) {
+        pr ca[EX_UNROLL], cb[EX_UNROLL];
+#pragma unroll
+        for (int u = 0; u < EX_UNROLL; ++u) { ca[u] = a[u]; cb[u] = b[u]; }
+        const long long i0 = i;
+        i += EX_UNROLL * stride;
+        load(i); // in flight while the current pairs are accumulated
+#pragma unroll
+        for (int u = 0; u < EX_UNROLL; ++u)
+            if (u == 0 || i0 + u * stride < n2) {
+                L.add(ca[u].x, cb[u].x, accl, ee, capture);
+                L.add(ca[u].y, cb[u].y, accl, ee, capture);
+            }
+    }
+    if ((n & 1) && tid == 0) L.add(x[n - 1], y[n - 1], accl, ee, capture);
+
+    // the workgroup's partial
+    const bool alone = gridDim.x == 1;
+    if constexpr (MODE == MODE_PLAIN) {
+        const double t = block_sum_d(L.s, sh);
+        if (threadIdx.x == 0) {
+            if (alone) sh.val[0] = t;
+            else __hip_atomic_store(&part[blockIdx.x], t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    } else {
+        if constexpr (MODE == MODE_EXBLAS) {
+            wave_flush_exact<P>(L.a, accl, L.flags);
+        } else {
+            L.esc += fpe_sum_capture<P>(L.a, L.e, ee, capture, accl, L.flags);
+            wave_fpe_finish<P>(L.a, L.esc, ee, capture, accl, L.flags);
+        }
+        if (threadIdx.x == 0) { sh.flag = 0; sh.red_ll[0] = 0; }
         __syncthreads();
+        if (L.flags) atomicOr(&sh.flag, L.flags);
+        if constexpr (MODE == MODE_FPE) {
+            const long long esc = wave_sum_i64_all(L.esc);
+            if (lane_id() == 0 && esc) atomicAdd((unsigned long long *)&sh.red_ll[0], (unsigned long long)esc);
+        }
         for (int q = threadIdx.x; q < ACC_DIGITS; q += blockDim.x) {
             long long v = acc[q];
 #pragma unroll
@@ -58,48 +146,104 @@ k_exdot_part(long long n, const double *__restrict__ x, const double *__restrict
             acc[q] = v;
         }
         __syncthreads();
+        if (!alone) {
+            long long *copy = blk + (blockIdx.x % DOT_COPIES) * DOT_PITCH;
+            auto add = [](long long *p, long long v) {
+                __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            };
+            for (int k = threadIdx.x; k < ACC_DIGITS; k += blockDim.x) {
+                // one carry step keeps every word below 2^33 in magnitude, so the
+                // integer sum over the workgroups cannot overflow
+                const long long v = acc[k], cin = k ? (acc[k - 1] >> 32) : 0;
+                const long long o = (k == ACC_DIGITS - 1) ? v + cin : (v & 0xFFFFFFFFll) + cin;
+                if (o != 0) add(&copy[k], o);
+            }
+            if (threadIdx.x == 0) {
+                if (sh.red_ll[0]) add(&blk[DOT_ESC], sh.red_ll[0]);
+                if (sh.flag) __hip_atomic_fetch_or(&blk[DOT_ESC + 1], (long long)sh.flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
     }
-    block_finish<MODE, P>(L, acc, sv, blockIdx.x, ee, capture, &info->flags, sh);
-}
+    if (!alone) {
+        wait_vmem();
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const int G = gridDim.x, g = blockIdx.x % DOT_COPIES;
+            auto ticket = [](long long *p) { return __hip_atomic_fetch_add(p, 1ll, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+            bool last = true;
+            if (G > EX_ONE_LEVEL) last = ticket(&blk[g * DOT_PITCH + ACC_DIGITS]) == (G - g + DOT_COPIES - 1) / DOT_COPIES - 1;
+            if (last) last = ticket(&blk[ACC_DIGITS + 1]) == (G > EX_ONE_LEVEL ? DOT_COPIES : G) - 1;
+            sh.rng[0] = last;
+        }
+        __syncthreads();
+        if (!sh.rng[0]) return;
+    } else {
+        __syncthreads();
+    }
+    if (wave_id() != 0) return;
 
-// One workgroup: merges the G slots, rounds, writes *out and the counters;
-// or, with digits_out, writes the exact sum as normalized accumulator words.
-template <int MODE, int P>
-__global__ void __launch_bounds__(MAX_BLOCK)
-k_exdot_fin(int G, SlotView sv, DotInfo *info, double *out, long long *digits_out, bool ee, bool capture)
-{
-    __shared__ RedShared sh;
-    long long *acc = sh.acc[0];
-    if (digits_out) {
-        if constexpr (MODE == MODE_EXBLAS) {
-            zero_acc(acc);
-            __syncthreads();
-            for (int k = wave_id(); k < ACC_DIGITS; k += num_waves()) {
-                long long s = sum_row(sv.ws.digits + (long long)k * sv.stride, G);
-                if (lane_id() == 0) acc[k] = s;
+    // the finishing wavefront
+    const int l = lane_id();
+    long long da = 0, db = 0, esc = 0;
+    int flags = 0;
+    double r = 0.0;
+    if constexpr (MODE == MODE_PLAIN) {
+        if (alone) {
+            r = sh.val[0];
+        } else { // fixed order: lane-strided sums of the workgroups, then the tree
+            const int G = gridDim.x;
+            double s[4] = {0.0, 0.0, 0.0, 0.0};
+            auto at = [&](int g) { return __hip_atomic_load(&part[g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+            int g = l;
+            for (; g + 3 * 64 < G; g += 4 * 64) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) s[j] += at(g + 64 * j);
             }
-            __syncthreads();
-            if (wave_id() == 0) {
-                const int l = lane_id();
-                long long a = (2 * l < ACC_DIGITS) ? acc[2 * l] : 0;
-                long long b = (2 * l + 1 < ACC_DIGITS) ? acc[2 * l + 1] : 0;
-                wave_normalize(a, b);
-                if (2 * l < ACC_DIGITS) digits_out[2 * l] = a;
-                if (2 * l + 1 < ACC_DIGITS) digits_out[2 * l + 1] = b;
-            }
+            for (; g < G; g += 64) s[0] += at(g);
+            r = __shfl(wave_sum_down((s[0] + s[1]) + (s[2] + s[3])), 0, 64);
         }
-        return;
+    } else {
+        if (alone) {
+            if (2 * l < ACC_DIGITS) { da = acc[2 * l]; db = acc[2 * l + 1]; }
+            esc = sh.red_ll[0];
+            flags = sh.flag;
+        } else if (l < DOT_PITCH / 2) {
+            long long q[DOT_COPIES][2];
+#pragma unroll
+            for (int c = 0; c < DOT_COPIES; ++c) {
+                q[c][0] = coherent_ll(&blk[c * DOT_PITCH + 2 * l]);
+                q[c][1] = coherent_ll(&blk[c * DOT_PITCH + 2 * l + 1]);
+            }
+#pragma unroll
+            for (int c = 0; c < DOT_COPIES; ++c) { da += q[c][0]; db += q[c][1]; }
+        }
+        if (!alone) {
+            esc = wave_i64_of(da, DOT_ESC / 2);
+            flags = (int)wave_i64_of(db, DOT_ESC / 2);
+            if (l > TOP_LANE) da = db = 0;
+        }
+        if (digits_out) {
+            wave_normalize(da, db);
+            if (2 * l < ACC_DIGITS) {
+                digits_out[2 * l] = da;
+                digits_out[2 * l + 1] = db;
+            }
+        } else {
+            r = wave_round<double>(da, db);
+        }
     }
-    long long esc = 0;
-    int fl = 0;
-    double r = merge_slots<MODE, P>(sv, G, ee, capture, acc, &esc, &info->flags, sh, 0);
-    if (threadIdx.x == 0) {
-        fl = info->flags;
-        *out = (fl & FLAG_NONFINITE) ? __builtin_nan("") : r;
-        if constexpr (MODE == MODE_FPE) {
-            info->escapes += esc;
-            if (esc > 0 && capture) info->fallbacks += 1;
-        }
+    if (!alone) { // empty the block again
+        for (int k = l; k < DOT_COPIES * DOT_PITCH; k += 64)
+            __hip_atomic_store(&blk[k], 0ll, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (l == 0 && out)
+        __hip_atomic_store(out, (flags & FLAG_NONFINITE) ? __builtin_nan("") : r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (rec) {
+        if (l == 0) __hip_atomic_store(&rec[0], (unsigned long long)esc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        wait_vmem(); // the result and the empty block are in place before the caller may go on
+        if (l == 0)
+            __hip_atomic_store(&rec[1], ((unsigned long long)seq << 32) | (unsigned)flags, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
@@ -203,25 +347,21 @@ k_spmv_csr(int n, const int *__restrict__ rp, const int *__restrict__ col, const
 // ---------------------------------------------------------------------------
 // Launch functions
 
-hipError_t launch_exdot(int mode, long long n, const double *x, const double *y, double *out,
-                        const DotWs &ws, int stride, DotInfo *info, const LaunchCfg &c)
+hipError_t launch_exdot(int mode, long long n, const double *x, const double *y, double *out, const ExdotWs &w,
+                        const LaunchCfg &c)
 {
-    SlotView sv{ws, stride};
     dispatch(mode, c.fpe_size, [&](auto m, auto p) {
         constexpr int M = decltype(m)::value, PP = decltype(p)::value;
-        k_exdot_part<M, PP><<<c.grid, c.block, 0, c.stream>>>(n, x, y, sv, info, c.early_exit, c.fallback);
-        k_exdot_fin<M, PP><<<1, MAX_BLOCK, 0, c.stream>>>(c.grid, sv, info, out, nullptr, c.early_exit,
-                                                          c.fallback);
+        k_exdot<M, PP><<<c.grid, c.block, 0, c.stream>>>(n, x, y, w.blk, w.part, out, nullptr, w.rec, w.seq, c.early_exit,
+                                                         c.fallback);
     });
     return hipGetLastError();
 }
 
-hipError_t launch_exdot_partial(long long n, const double *x, const double *y, long long *digits,
-                                const DotWs &ws, int stride, DotInfo *info, const LaunchCfg &c)
+hipError_t launch_exdot_partial(long long n, const double *x, const double *y, long long *digits, const ExdotWs &w,
+                                const LaunchCfg &c)
 {
-    SlotView sv{ws, stride};
-    k_exdot_part<MODE_EXBLAS, 4><<<c.grid, c.block, 0, c.stream>>>(n, x, y, sv, info, true, true);
-    k_exdot_fin<MODE_EXBLAS, 4><<<1, MAX_BLOCK, 0, c.stream>>>(c.grid, sv, info, nullptr, digits, true, true);
+    k_exdot<MODE_EXBLAS, 4><<<c.grid, c.block, 0, c.stream>>>(n, x, y, w.blk, w.part, nullptr, digits, nullptr, 0, true, true);
     return hipGetLastError();
 }
 

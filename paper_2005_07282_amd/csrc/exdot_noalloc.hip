@@ -1,7 +1,7 @@
 // rpcg_exdot_noalloc: the dot product of rpcg_exdot for callers that cannot
-// allocate device memory. The workgroup slots and the call's counters live in
-// a file-scope device array instead of a context workspace; the kernels are
-// those of rpcg_exdot and take the array's device address as their workspace.
+// allocate device memory. The accumulator block, the workgroup sums of the plain
+// mode and the call's record live in a file-scope device array instead of a
+// context workspace; the kernel is that of rpcg_exdot.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -17,11 +17,9 @@ namespace {
 using namespace rpcg;
 
 constexpr int NA_GROUPS = RPCG_NOALLOC_MAX_GROUPS;
-constexpr size_t NA_INFO_BYTES = 256;
-// per slot: accumulator words, range pair, expansion / partial sum, escape count
-constexpr size_t NA_SLOT_BYTES = ACC_WORDS * sizeof(long long) + 2 * sizeof(int) + MAX_FPE * sizeof(double) + sizeof(int);
-constexpr size_t NA_BYTES = NA_INFO_BYTES + (size_t)NA_GROUPS * NA_SLOT_BYTES;
-static_assert(sizeof(DotInfo) <= NA_INFO_BYTES, "counter record fits its reserved bytes");
+constexpr size_t NA_REC_BYTES = 256; // the record
+constexpr int NA_WORDS = DOT_COPIES * DOT_PITCH;
+constexpr size_t NA_BYTES = NA_REC_BYTES + NA_WORDS * sizeof(long long) + (size_t)NA_GROUPS * sizeof(double);
 
 // One copy per GPU, held until the process ends. In host code this name is
 // only a handle for hipGetSymbolAddress: kernels receive the address that
@@ -55,8 +53,9 @@ hipError_t device_scratch(int dev, unsigned char **ptr, int *cus)
     return d.err;
 }
 
-// The counters must start at zero; a fill kernel rather than a memset node,
-// so that a captured graph replays it correctly.
+// The accumulators must start at zero, whatever calls that overlapped have left
+// behind; a fill kernel rather than a memset node, so that a captured graph
+// replays it correctly.
 __global__ void k_zero_words(unsigned long long *p, int words)
 {
     for (int i = threadIdx.x; i < words; i += blockDim.x) p[i] = 0ull;
@@ -85,15 +84,10 @@ extern "C" int rpcg_exdot_noalloc(rpcg_mode mode_in, int64_t n, const double *x,
     RPCG_TRY(device_scratch(dev, &base, &cus));
     hipStream_t s = (hipStream_t)stream;
 
-    // launch shape of rpcg_exdot, with the grid capped by the slot count
+    // launch shape of rpcg_exdot, with the grid capped by the array
     LaunchCfg cfg;
     cfg.block = o.block_size ? o.block_size : 1024;
-    cfg.grid = o.grid_size ? o.grid_size
-                           : (int)std::max<int64_t>(1, std::min<int64_t>((n + 8ll * cfg.block - 1) / (8ll * cfg.block),
-                                                                         (mode == MODE_PLAIN ? 8ll : 4ll) * cus));
-    if (!o.grid_size && mode != MODE_PLAIN)
-        cfg.grid = (int)std::max<int64_t>(std::min<int64_t>(cfg.grid, cus),
-                                          std::min<int64_t>(cfg.grid, (n + 256ll * cfg.block - 1) / (256ll * cfg.block)));
+    cfg.grid = o.grid_size ? o.grid_size : exdot_grid(mode, n, cfg.block, cus);
     cfg.grid = std::min(cfg.grid, NA_GROUPS);
     cfg.early_exit = o.early_exit != 0;
     cfg.fpe_size = o.fpe_size;
@@ -101,37 +95,22 @@ extern "C" int rpcg_exdot_noalloc(rpcg_mode mode_in, int64_t n, const double *x,
     cfg.xcd_parts = 1;
     cfg.stream = s;
 
-    // layout of the array: counters, then the slot arrays for NA_GROUPS workgroups
-    DotInfo *info = (DotInfo *)base;
-    unsigned char *b = base + NA_INFO_BYTES;
-    DotWs ws;
-    ws.digits = (long long *)b;
-    b += (size_t)NA_GROUPS * ACC_WORDS * sizeof(long long);
-    ws.part = (double *)b;
-    b += (size_t)NA_GROUPS * MAX_FPE * sizeof(double);
-    ws.range = (int *)b;
-    b += (size_t)NA_GROUPS * 2 * sizeof(int);
-    ws.esc = (int *)b;
-
-    hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, (unsigned long long *)info,
-                       (int)(sizeof(DotInfo) / sizeof(unsigned long long)));
+    // layout of the array: record, accumulators, workgroup sums
+    ExdotWs w;
+    w.rec = res ? (unsigned long long *)base : nullptr;
+    w.blk = (long long *)(base + NA_REC_BYTES);
+    w.part = (double *)(base + NA_REC_BYTES + NA_WORDS * sizeof(long long));
+    w.seq = 1;
+    hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(256), 0, s, (unsigned long long *)w.blk, NA_WORDS);
     RPCG_TRY(hipGetLastError());
-    RPCG_TRY(launch_exdot(mode, n, x, y, out, ws, NA_GROUPS, info, cfg));
+    RPCG_TRY(launch_exdot(mode, n, x, y, out, w, cfg));
     if (res) {
         std::memset(res, 0, sizeof(*res));
-        DotInfo inf;
-        RPCG_TRY(hipMemcpyAsync(&inf, info, sizeof inf, hipMemcpyDeviceToHost, s));
+        unsigned long long rec[2];
+        RPCG_TRY(hipMemcpyAsync(rec, w.rec, sizeof rec, hipMemcpyDeviceToHost, s));
         RPCG_TRY(hipStreamSynchronize(s));
-        res->fpe_escapes = inf.escapes;
-        res->fallbacks = inf.fallbacks;
-        res->grid_size = cfg.grid;
-        res->block_size = cfg.block;
-        int st = RPCG_OK;
-        if (inf.flags & FLAG_NONFINITE) st = RPCG_ERR_NONFINITE;
-        else if (inf.flags & FLAG_INEXACT) st = RPCG_WARN_FPE_INEXACT;
-        else if (mode == MODE_FPE && inf.escapes > 0 && !cfg.fallback) st = RPCG_WARN_FPE_INEXACT;
-        res->status = st;
-        return st;
+        exdot_result(rec[0], rec[1], mode, cfg, res);
+        return res->status;
     }
     return RPCG_OK;
 }

@@ -38,15 +38,13 @@ struct DotWs {
 // enough to drain with the kernel; the escape count sits behind the words of copy 0.
 constexpr int DOT_COPIES = 8, DOT_PITCH = 72, DOT_ESC = 70;
 
-// Scalars of one standalone dot call (device memory).
+// Scalars of a matrix copy's construction (device memory).
 struct DotInfo {
     unsigned pad0;
     int flags;
     int max_len;         // longest row (SELL construction scratch)
     int pad1;
     long long max_delta; // column-code range (SELL construction scratch)
-    long long escapes;
-    long long fallbacks;
     // construction scratch of the diagonal-aligned copy
     int diag_fail;                // nonzero: some slice's rows do not line up
     int pad2;
@@ -192,10 +190,17 @@ struct LaunchCfg {
 // ---- launch functions (return hipError_t of the launch) ----
 // `stride` is the slot capacity of the dot workspaces (see DotWs).
 
-hipError_t launch_exdot(int mode, long long n, const double *x, const double *y, double *out,
-                        const DotWs &ws, int stride, DotInfo *info, const LaunchCfg &cfg);
-hipError_t launch_exdot_partial(long long n, const double *x, const double *y, long long *digits,
-                                const DotWs &ws, int stride, DotInfo *info, const LaunchCfg &cfg);
+// Workspace of one standalone dot call.
+struct ExdotWs {
+    long long *blk;          // DOT_COPIES x DOT_PITCH words, all zero; left so
+    double *part;            // [grid] (plain)
+    unsigned long long *rec; // optional: the call's record (escapes; seq << 32 | flags), host-visible or device memory
+    unsigned seq;
+};
+hipError_t launch_exdot(int mode, long long n, const double *x, const double *y, double *out, const ExdotWs &w,
+                        const LaunchCfg &cfg);
+hipError_t launch_exdot_partial(long long n, const double *x, const double *y, long long *digits, const ExdotWs &w,
+                                const LaunchCfg &cfg);
 hipError_t launch_acc_round(const long long *digits, double *out, hipStream_t s);
 // Exponent range (floor(log2 |v|)) of the nonzero finite entries of v, merged into *emin, *emax.
 hipError_t launch_exp_range(long long n, const double *v, int *emin, int *emax, hipStream_t s);
