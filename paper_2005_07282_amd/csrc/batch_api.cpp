@@ -30,9 +30,8 @@ struct rpcg_batch {
     Buffer vecs;                       // b, x, r, z, d, w, dinv
     Buffer st, hist_ptrs, active;
     Buffer dsys, druns, dwg;
-    Buffer ws_mem;
-    DotWs ws[3];
-    int ws_cap = 0;
+    Buffer acc, part;                  // dots: accumulators per system; plain sums per slot
+    int part_cap = 0;
     int nruns = 0;
     rpcg_batch_tuning tuning{};
     uint64_t signature = 0;
@@ -63,35 +62,26 @@ bool valid_tuning(const rpcg_batch_tuning &t)
            t.graph_iterations <= 64;
 }
 
-rpcg_batch_tuning default_tuning(const rpcg_ctx *c)
+rpcg_batch_tuning default_tuning(const rpcg_ctx *c, long long slices)
 {
     rpcg_batch_tuning t{};
     t.policy = 0;
     t.tile_slices = 16;
-    t.grid_size = 2 * c->num_cus;
-    t.block_size = 256;
+    // two workgroups of 512 a CU where they have work for it (64 systems of
+    // 16^3 to 96^3: 115 ms; 121 ms with 256 threads; 4 of 60^3 to 70^3: 13.0 ms
+    // against 14.7 ms with one), one for small batches (60 of 16^3 to 30^3: 4.9 ms against 5.3 ms)
+    t.grid_size = (slices >= 32ll * 2 * c->num_cus ? 2 : 1) * c->num_cus;
+    t.block_size = 512;
     t.graph_iterations = 8;
     return t;
 }
 
-int ensure_batch_ws(rpcg_batch *B, int groups)
+// The workgroup sums of the plain mode, by slot (the exact modes' accumulators are per system).
+int ensure_batch_part(rpcg_batch *B, int groups)
 {
-    if (groups <= B->ws_cap) return RPCG_OK;
-    const size_t per = (size_t)groups * (ACC_WORDS * sizeof(long long) + 2 * sizeof(int) + MAX_FPE * sizeof(double) +
-                                         sizeof(int));
-    RPCG_TRY(B->ws_mem.ensure(3 * per + 256 * 4));
-    char *base = (char *)B->ws_mem.p;
-    for (int i = 0; i < 3; ++i) {
-        char *p = base + i * per;
-        B->ws[i].digits = (long long *)p;
-        p += (size_t)groups * ACC_WORDS * sizeof(long long);
-        B->ws[i].part = (double *)p;
-        p += (size_t)groups * MAX_FPE * sizeof(double);
-        B->ws[i].range = (int *)p;
-        p += (size_t)groups * 2 * sizeof(int);
-        B->ws[i].esc = (int *)p;
-    }
-    B->ws_cap = groups;
+    if (groups <= B->part_cap) return RPCG_OK;
+    RPCG_TRY(B->part.ensure(3 * (size_t)groups * sizeof(double)));
+    B->part_cap = groups;
     return RPCG_OK;
 }
 
@@ -114,31 +104,77 @@ void compute_schedule(rpcg_batch *B, const std::vector<char> *active, std::vecto
     const int G = t.grid_size;
     const int step = B->layout == LAY_DIAG ? 2 : 1; // runs start at whole slices of the layout
     auto on = [&](int q) { return !active || (*active)[q]; };
-    std::vector<std::vector<BatchRun>> per_wg(G);
-    auto add = [&](int g, int sys, int s) {
-        std::vector<BatchRun> &v = per_wg[g];
-        if (!v.empty() && v.back().sys == sys && v.back().s1 == s) v.back().s1 = s + 1;
-        else v.push_back(BatchRun{sys, s, s + 1, -1});
-    };
+    runs.clear();
+    wg_run.assign(G + 1, 0);
     if (t.policy == 0) {
-        // contiguous chunks with equal stored entries (at least one slice of work each)
-        long long total = 0;
+        // Contiguous chunks of the concatenated slices, by weight (stored
+        // entries and a slice's own cost). Large chunks are equal and run on
+        // across systems. Where a chunk is under SHARE_SLICES slices, the prologue that
+        // a workgroup would run twice for the end of one system and the
+        // start of the next costs more than an uneven chunk (8 systems of 20^3 to 40^3:
+        // 5.2 ms against 4.0 ms; 64 of 16^3 to 96^3 the other way round, 116 ms against 134 ms): every
+        // system then starts a new workgroup, with the smallest chunk that
+        // takes no more than G of them, and none under MIN_SLICES. A chunk's end is searched in the
+        // offsets, so a schedule costs the host its runs, not the slices.
+        constexpr long long SHARE_SLICES = 64, MIN_SLICES = 16;
+        auto upto = [&](int q, int s) { return B->off_host[B->sys[q].slice0 + s] + 64ll * s; };
+        auto weight = [&](int q) { return on(q) ? upto(q, B->sys[q].nslices) - upto(q, 0) : 0ll; };
+        long long total = 0, slices = 0;
+        int live = 0;
         for (int q = 0; q < B->nsys; ++q)
-            if (on(q)) total += B->off_host[B->sys[q].slice0 + B->sys[q].nslices] - B->off_host[B->sys[q].slice0];
-        const long long target = std::max(1ll, (total + G - 1) / G);
-        int g = 0;
-        long long acc = 0;
+            if (weight(q) > 0) {
+                total += weight(q);
+                slices += B->sys[q].nslices;
+                ++live;
+            }
+        long long target = std::max(1ll, (total + G - 1) / G);
+        const bool own = live <= G && slices < SHARE_SLICES * G;
+        if (own && slices > 0) {
+            auto chunks = [&](long long T) {
+                long long c = 0;
+                for (int q = 0; q < B->nsys; ++q) c += (weight(q) + T - 1) / T;
+                return c;
+            };
+            long long lo = std::max(target, MIN_SLICES * total / slices), hi = std::max(lo, total);
+            while (lo < hi) {
+                const long long mid = lo + (hi - lo) / 2;
+                if (chunks(mid) <= G) hi = mid;
+                else lo = mid + 1;
+            }
+            target = lo;
+        }
+        int g = 0;           // workgroups started
+        long long room = 0;  // weight left in the last one
         for (int q = 0; q < B->nsys; ++q) {
-            if (!on(q)) continue;
-            for (int s = 0; s < B->sys[q].nslices; ++s) {
-                const long long gsl = B->sys[q].slice0 + s;
-                if (acc >= target && g < G - 1 && s % step == 0) { ++g; acc = 0; }
-                add(g, q, s);
-                acc += std::max(64ll, B->off_host[gsl + 1] - B->off_host[gsl]);
+            const int ns = B->sys[q].nslices;
+            if (weight(q) == 0) continue;
+            // this system's chunks: equal ones of its own, or what is left of the last workgroup and full ones
+            const long long share = own ? (weight(q) + (weight(q) + target - 1) / target - 1) / ((weight(q) + target - 1) / target)
+                                        : target;
+            if (own) room = 0;
+            for (int s = 0; s < ns;) {
+                if (room <= 0 && g < G) {
+                    wg_run[g++] = (int)runs.size();
+                    room = share;
+                }
+                // the first whole slices (of the layout) that fill the workgroup; the last one takes the rest
+                int lo = 1, hi = (ns - s + step - 1) / step;
+                if (g == G && !own) lo = hi;
+                while (lo < hi) {
+                    const int mid = (lo + hi) / 2;
+                    if (upto(q, std::min(ns, s + mid * step)) - upto(q, s) >= room) hi = mid;
+                    else lo = mid + 1;
+                }
+                const int e = std::min(ns, s + lo * step);
+                runs.push_back(BatchRun{q, s, e, (int)runs.size()});
+                room -= upto(q, e) - upto(q, s);
+                s = e;
             }
         }
+        for (; g <= G; ++g) wg_run[g] = (int)runs.size();
     } else {
         // tiles of tile_slices slices, systems interleaved, dealt round-robin
+        std::vector<std::vector<BatchRun>> per_wg(G);
         const int T = (t.tile_slices + step - 1) / step * step;
         long long i = 0;
         int max_tiles = 0;
@@ -150,14 +186,12 @@ void compute_schedule(rpcg_batch *B, const std::vector<char> *active, std::vecto
                 const int g = (int)(i++ % G);
                 per_wg[g].push_back(BatchRun{q, s0, s1, -1});
             }
+        for (int g = 0; g < G; ++g) {
+            wg_run[g] = (int)runs.size();
+            runs.insert(runs.end(), per_wg[g].begin(), per_wg[g].end());
+        }
+        wg_run[G] = (int)runs.size();
     }
-    runs.clear();
-    wg_run.assign(G + 1, 0);
-    for (int g = 0; g < G; ++g) {
-        wg_run[g] = (int)runs.size();
-        runs.insert(runs.end(), per_wg[g].begin(), per_wg[g].end());
-    }
-    wg_run[G] = (int)runs.size();
     std::vector<int> order(runs.size());
     for (size_t k = 0; k < order.size(); ++k) order[k] = (int)k;
     std::sort(order.begin(), order.end(), [&](int a, int b) {
@@ -219,7 +253,7 @@ int build_schedule(rpcg_batch *B)
     // a re-partition over a subset never has more runs: policy 0 makes at most
     // grid + nsys runs, policy 1 a subset of the tiles
     B->slot_cap = std::max(1, B->tuning.policy == 0 ? std::max(B->nruns, B->tuning.grid_size + B->nsys) : B->nruns);
-    int rc = ensure_batch_ws(B, B->slot_cap);
+    int rc = ensure_batch_part(B, B->slot_cap);
     if (rc != RPCG_OK) return rc;
     const size_t maxruns = (size_t)B->slot_cap;
     RPCG_TRY(B->dsys.ensure(sizeof(BatchSys) * B->nsys));
@@ -267,6 +301,9 @@ BatchArgs batch_args(const rpcg_batch *B, bool with_hist)
     a.w = v + 5 * T;
     a.dinv = v + 6 * T;
     a.st = (PcgState *)B->st.p;
+    a.acc = (long long *)B->acc.p;
+    a.part = (double *)B->part.p;
+    a.part_cap = B->part_cap;
     a.hist = with_hist ? (double *const *)B->hist_ptrs.p : nullptr;
     a.active = (int *)B->active.p;
     return a;
@@ -298,7 +335,7 @@ int batch_start(rpcg_batch *B, const double *const *b, double *const *x, bool wi
     }
     if (!x) RPCG_TRY(hipMemsetAsync(v + T, 0, sizeof(double) * T, B->gs));
     const BatchArgs a = batch_args(B, with_hist);
-    RPCG_TRY(launch_batch_setup(B->mode, B->layout, a, B->tuning.grid_size, B->tuning.block_size, B->ws, B->ws_cap,
+    RPCG_TRY(launch_batch_setup(B->mode, B->layout, a, B->tuning.grid_size, B->tuning.block_size,
                                 B->o.tol, B->o.maxit, batch_cfg(B)));
     return RPCG_OK;
 }
@@ -312,8 +349,7 @@ int capture_graph(rpcg_batch *B, bool with_hist)
     RPCG_TRY(hipStreamBeginCapture(B->gs, hipStreamCaptureModeThreadLocal));
     hipError_t err = hipSuccess;
     for (int i = 0; i < B->tuning.graph_iterations && err == hipSuccess; ++i)
-        err = launch_batch_iteration(B->mode, B->layout, a, B->tuning.grid_size, B->tuning.block_size, B->ws,
-                                     B->ws_cap, cfg);
+        err = launch_batch_iteration(B->mode, B->layout, a, B->tuning.grid_size, B->tuning.block_size, cfg);
     hipGraph_t g = nullptr;
     hipError_t e2 = hipStreamEndCapture(B->gs, &g);
     if (err != hipSuccess) { if (g) (void)hipGraphDestroy(g); return hip_status(err); }
@@ -349,7 +385,7 @@ void rpcg_batch_destroy(rpcg_batch *B)
     if (B->gs) (void)hipStreamSynchronize(B->gs);
     drop_graph(B);
     for (Buffer *b : {&B->off, &B->val, &B->col, &B->cfirst, &B->len8, &B->ds, &B->de, &B->vecs, &B->st, &B->hist_ptrs, &B->active,
-                      &B->dsys, &B->druns, &B->dwg, &B->ws_mem})
+                      &B->dsys, &B->druns, &B->dwg, &B->acc, &B->part})
         b->release();
     for (hipEvent_t e : {B->ev_in, B->ev_out, B->poll_ev[0], B->poll_ev[1], B->t_ev[0], B->t_ev[1], B->stage_ev[0],
                          B->stage_ev[1]})
@@ -475,11 +511,12 @@ static int batch_create_body(rpcg_batch *B, const rpcg_csr *A, hipStream_t calle
     RPCG_TRY(B->vecs.ensure(sizeof(double) * 7 * (size_t)B->total_rows));
     RPCG_TRY(hipMemsetAsync(B->vecs.p, 0, sizeof(double) * 7 * (size_t)B->total_rows, B->gs));
     RPCG_TRY(B->st.ensure(sizeof(PcgState) * B->nsys));
+    RPCG_TRY(B->acc.ensure(sizeof(long long) * 3 * DOT_COPIES * DOT_PITCH * (size_t)B->nsys));
     RPCG_TRY(B->hist_ptrs.ensure(sizeof(double *) * B->nsys));
     RPCG_TRY(B->active.ensure(sizeof(int)));
     B->host_st.resize(B->nsys);
     auto it = c->batch_tunings.find(B->signature);
-    B->tuning = it != c->batch_tunings.end() ? it->second : default_tuning(c);
+    B->tuning = it != c->batch_tunings.end() ? it->second : default_tuning(c, B->total_slices);
     int rc = build_schedule(B);
     if (rc != RPCG_OK) return rc;
     RPCG_TRY(hipStreamSynchronize(B->gs));
@@ -575,7 +612,7 @@ int rpcg_batch_tune(rpcg_batch *B, const double *const *b, int32_t trial_iterati
                 if (rc != RPCG_OK) return rc;
                 RPCG_TRY(hipEventRecord(B->t_ev[0], B->gs));
                 for (int i = 0; i < trial_iterations; ++i)
-                    RPCG_TRY(launch_batch_iteration(B->mode, B->layout, a, cfg.grid, cfg.block, B->ws, B->ws_cap, cfg));
+                    RPCG_TRY(launch_batch_iteration(B->mode, B->layout, a, cfg.grid, cfg.block, cfg));
                 RPCG_TRY(hipEventRecord(B->t_ev[1], B->gs));
                 RPCG_TRY(hipEventSynchronize(B->t_ev[1]));
             }

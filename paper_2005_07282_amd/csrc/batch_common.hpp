@@ -48,11 +48,13 @@ __device__ __forceinline__ SlotView batch_slots(const SlotView &v, int g0)
     return o;
 }
 
-// Flags of a system after this workgroup's merges (read from the coherent
-// level, not a possibly stale cached copy).
-__device__ __forceinline__ int batch_flags(const PcgState *st)
+// Dot d of system `sys` (S its record).
+__device__ __forceinline__ DotWs batch_dot(const BatchArgs &a, int sys, const BatchSys &S, int d)
 {
-    return __hip_atomic_load(&st->flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    DotWs w{};
+    w.acc = a.acc + ((long long)sys * 3 + d) * (DOT_COPIES * DOT_PITCH);
+    w.part = a.part + (long long)d * a.part_cap + S.slot0;
+    return w;
 }
 
 } // namespace rpcg

@@ -23,19 +23,9 @@
 
 namespace rpcg {
 
-// Workgroup-uniform read of an int another workgroup of the same kernel may
-// write (one thread reads, every thread sees its value).
-__device__ __forceinline__ int wg_read_int(const int *p, RedShared &sh)
-{
-    __syncthreads(); // the previous reader's value has been used
-    if (threadIdx.x == 0) sh.flag = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
-    return sh.flag;
-}
-
 // K1: S1 + partial of S2 (as k_pcg_spmv_dot, per run).
 template <int MODE, int P, int LAY>
-__global__ void __launch_bounds__(MAX_BLOCK) k_batch_spmv_dot(BatchArgs a, SlotView sv, bool ee, bool capture)
+__global__ void __launch_bounds__(MAX_BLOCK) k_batch_spmv_dot(BatchArgs a, bool ee, bool capture)
 {
     __shared__ RedShared sh;
     const int lane = lane_id();
@@ -52,7 +42,12 @@ __global__ void __launch_bounds__(MAX_BLOCK) k_batch_spmv_dot(BatchArgs a, SlotV
         const SellMat<double> M = batch_mat(a, S);
         const double *__restrict__ d = a.d + S.row0;
         double *__restrict__ w = a.w + S.row0;
-        __syncthreads(); // the previous run's partial is written before the accumulator is reused
+        const DotWs wd = batch_dot(a, R.sys, S, 0);
+        if (MODE != MODE_PLAIN && R.s0 == 0) { // the direction kernel has read them
+            clear_dot(batch_dot(a, R.sys, S, 1));
+            clear_dot(batch_dot(a, R.sys, S, 2));
+        }
+        __syncthreads(); // the previous run's accumulator has been published before it is reused
         zero_acc(sh.acc[0]);
         __syncthreads();
         LaneDot<MODE, P> L;
@@ -67,31 +62,55 @@ __global__ void __launch_bounds__(MAX_BLOCK) k_batch_spmv_dot(BatchArgs a, SlotV
             for (int r = 0; r < NR; ++r)
                 if (i + r < M.n) L.add(di[r], sum[r], sh.acc[0], ee, capture);
         });
-        block_finish<MODE, P>(L, sh.acc[0], sv, R.slot, ee, capture, &st->flags, sh);
+        block_publish<MODE, P, 1, false>({&L}, {sh.acc[0]}, {&wd}, R.slot - S.slot0, ee, capture, &st->flags, sh);
     }
 }
 
-// K2: delta = <d, w> of the run's system merged (every run alike), rho =
-// beta / delta; S4, S5 and the partials of S6, S8.
+// K2: delta = <d, w> of the run's system merged (every run alike, by its first
+// wavefront), rho = beta / delta; S4, S5 and the partials of S6, S8. Two rows per
+// thread and step (16-byte accesses), the next two loaded ahead.
 template <int MODE, int P>
-__global__ void __launch_bounds__(MAX_BLOCK) k_batch_update(BatchArgs a, SlotView sd, SlotView wb, SlotView wt,
-                                                            bool ee, bool capture)
+__global__ void __launch_bounds__(MAX_BLOCK) k_batch_update(BatchArgs a, bool ee, bool capture)
 {
     __shared__ RedShared sh;
     for (int ri = a.wg_run[blockIdx.x]; ri < a.wg_run[blockIdx.x + 1]; ++ri) {
         const BatchRun R = a.runs[ri];
         PcgState *st = a.st + R.sys;
-        if (wg_read_int(&st->done, sh)) continue; // set in this kernel only by a breakdown every run sees
         const BatchSys S = a.sys[R.sys];
         const bool lead = R.s0 == 0;
+        const int i1 = (int)min((long long)R.s1 * 64, (long long)S.n);
+        long long i = (long long)R.s0 * 64 + 2 * threadIdx.x;
+        const double *__restrict__ wp = a.w + S.row0, *__restrict__ qp = a.dinv + S.row0;
+        double *__restrict__ rp = a.r + S.row0, *__restrict__ zp = a.z + S.row0;
+        double wn[2], rn[2], qn[2];
+        load_rows<2>(wn, wp, i, i1);
+        load_rows<2>(rn, (const double *)rp, i, i1);
+        load_rows<2>(qn, qp, i, i1);
         const int it = st->it_cur;
-        long long esc = 0;
-        const double delta = merge_slots<MODE, P>(batch_slots<MODE>(sd, S.slot0), S.slot1 - S.slot0, ee, capture,
-                                                  sh.acc[0], &esc, &st->flags, sh, 0);
-        const bool bad = (batch_flags(st) & FLAG_NONFINITE) || !is_finite_bits(delta);
+        const double beta = st->beta_par[it & 1];
+        __syncthreads(); // the previous run has read sh
+        if (wave_id() == 0) {
+            const int done = coherent_int(&st->done), flags = coherent_int(&st->flags);
+            long long esc;
+            const double d = wave_merge<MODE>(batch_dot(a, R.sys, S, 0), S.slot1 - S.slot0, &esc);
+            if (lane_id() == 0) {
+                sh.flag = done; // set in this kernel only by a breakdown every run sees
+                sh.rng[0] = flags;
+                sh.val[0] = d;
+                sh.red_ll[0] = esc;
+            }
+        }
+        zero_acc(sh.acc[0]);
+        zero_acc(sh.acc[1]);
+        __syncthreads();
+        if (sh.flag) continue;
+        const double delta = sh.val[0];
+        const bool bad = (sh.rng[0] & FLAG_NONFINITE) || !is_finite_bits(delta);
         const bool breakdown = !(delta > 0.0);
+        const double rho = beta / delta;
         if (lead && threadIdx.x == 0) {
-            st->escapes += esc;
+            const long long esc = sh.red_ll[0];
+            if (esc) st->escapes += esc;
             if (capture && esc > 0) st->fallbacks += 1;
             st->delta = delta;
             if (bad || breakdown) {
@@ -99,62 +118,110 @@ __global__ void __launch_bounds__(MAX_BLOCK) k_batch_update(BatchArgs a, SlotVie
                 st->ended = it;
                 st->done = 1;
                 atomicSub(a.active, 1);
+            } else {
+                st->rho = rho;
             }
         }
         if (bad || breakdown) continue;
-        const double rho = st->beta_par[it & 1] / delta;
-        if (lead && threadIdx.x == 0) st->rho = rho;
-        const long long r0 = S.row0;
-        const long long i1 = min((long long)R.s1 * 64, (long long)S.n);
-        zero_acc(sh.acc[0]);
-        zero_acc(sh.acc[1]);
-        __syncthreads();
         LaneDot<MODE, P> Lb, Lt;
         Lb.init();
         Lt.init();
-        for (long long i = (long long)R.s0 * 64 + threadIdx.x; i < i1; i += blockDim.x) {
-            const long long g = r0 + i;
-            const double ri = __builtin_fma(-rho, a.w[g], a.r[g]);    // S4
-            const double zi = a.dinv[g] * ri;                         // S5
-            a.r[g] = ri;
-            a.z[g] = zi;
-            Lb.add(zi, ri, sh.acc[0], ee, capture);                   // S6
-            Lt.add(ri, ri, sh.acc[1], ee, capture);                   // S8
+        while (i < i1) {
+            const long long cur = i;
+            double ri[2], zi[2];
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                ri[r] = __builtin_fma(-rho, wn[r], rn[r]);                 // S4
+                zi[r] = qn[r] * ri[r];                                     // S5
+            }
+            i += 2 * blockDim.x;
+            load_rows<2>(wn, wp, i, i1);
+            load_rows<2>(rn, (const double *)rp, i, i1);
+            load_rows<2>(qn, qp, i, i1);
+            store_rows(rp, ri, cur, i1);
+            store_rows(zp, zi, cur, i1);
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+                if (cur + r < i1) {
+                    Lb.add(zi[r], ri[r], sh.acc[0], ee, capture);          // S6
+                    Lt.add(ri[r], ri[r], sh.acc[1], ee, capture);          // S8
+                }
         }
-        block_finish_pair<MODE, P>(Lb, sh.acc[0], wb, Lt, sh.acc[1], wt, R.slot, ee, capture, &st->flags, sh);
+        const DotWs wb = batch_dot(a, R.sys, S, 1), wt = batch_dot(a, R.sys, S, 2);
+        block_publish<MODE, P, 2, false>({&Lb, &Lt}, {sh.acc[0], sh.acc[1]}, {&wb, &wt}, R.slot - S.slot0, ee, capture,
+                                         &st->flags, sh);
     }
 }
 
-// K3: beta, tau of the run's system merged; stopping test of Fig. 1; gamma =
-// beta / beta_old; S3 and (unless the system stops) S7.
+// K3: beta, tau of the run's system merged (by its first two wavefronts);
+// stopping test of Fig. 1; gamma = beta / beta_old; S3 and (unless the system
+// stops) S7, BATCH_DIR row pairs per thread loaded at a time, the first while
+// the dots are merged.
+constexpr int BATCH_DIR = 4;
 template <int MODE, int P>
-__global__ void __launch_bounds__(MAX_BLOCK) k_batch_direction(BatchArgs a, SlotView wb, SlotView wt, bool ee,
-                                                               bool capture)
+__global__ void __launch_bounds__(MAX_BLOCK) k_batch_direction(BatchArgs a, bool capture)
 {
     __shared__ RedShared sh;
     for (int ri = a.wg_run[blockIdx.x]; ri < a.wg_run[blockIdx.x + 1]; ++ri) {
         const BatchRun R = a.runs[ri];
         PcgState *st = a.st + R.sys;
-        const int it = st->it_cur;
-        if (wg_read_int(&st->ended, sh) <= it) continue;
         const BatchSys S = a.sys[R.sys];
         const bool lead = R.s0 == 0;
+        const int i1 = (int)min((long long)R.s1 * 64, (long long)S.n);
+        const long long step = 2 * blockDim.x;
+        long long i = (long long)R.s0 * 64 + 2 * threadIdx.x;
+        double *__restrict__ dp = a.d + S.row0, *__restrict__ xp = a.x + S.row0;
+        const double *__restrict__ zp = a.z + S.row0;
+        double dv[BATCH_DIR][2], zv[BATCH_DIR][2], xv[BATCH_DIR][2];
+        auto load = [&](long long at) {
+#pragma unroll
+            for (int j = 0; j < BATCH_DIR; ++j) {
+                load_rows<2>(dv[j], (const double *)dp, at + j * step, i1);
+                load_rows<2>(zv[j], zp, at + j * step, i1);
+                load_rows<2>(xv[j], (const double *)xp, at + j * step, i1);
+            }
+        };
+        load(i);
+        const int it = st->it_cur, maxit = st->maxit;
+        const double beta_old = st->beta_par[it & 1], thr = st->thr;
+        const double rho = st->rho; // K2's rho of this iteration
         const int G = S.slot1 - S.slot0;
-        long long eb = 0, et = 0;
-        const double beta = merge_slots<MODE, P>(batch_slots<MODE>(wb, S.slot0), G, ee, capture, sh.acc[0], &eb,
-                                                 &st->flags, sh, 0);
-        const double tau = merge_slots<MODE, P>(batch_slots<MODE>(wt, S.slot0), G, ee, capture, sh.acc[1], &et,
-                                                &st->flags, sh, 1);
-        const bool bad = (batch_flags(st) & FLAG_NONFINITE) || !is_finite_bits(beta) || !is_finite_bits(tau);
-        const bool stop = bad || tau <= st->thr || it + 1 >= st->maxit;
-        const double beta_old = st->beta_par[it & 1];
+        __syncthreads(); // the previous run has read sh
+        const int wv = wave_id();
+        if (wv == 0) {
+            const int ended = coherent_int(&st->ended) <= it, flags = coherent_int(&st->flags);
+            long long esc;
+            const double b = wave_merge<MODE>(batch_dot(a, R.sys, S, 1), G, &esc);
+            if (lane_id() == 0) {
+                sh.flag = ended;
+                sh.rng[0] = flags;
+                sh.val[0] = b;
+                sh.red_ll[0] = esc;
+            }
+        }
+        if (wv == (num_waves() > 1 ? 1 : 0)) {
+            long long esc;
+            const double t = wave_merge<MODE>(batch_dot(a, R.sys, S, 2), G, &esc);
+            if (lane_id() == 0) {
+                sh.val[1] = t;
+                sh.red_ll[1] = esc;
+            }
+        }
+        __syncthreads();
+        if (sh.flag) continue;
+        const double beta = sh.val[0], tau = sh.val[1];
+        const bool bad = (sh.rng[0] & FLAG_NONFINITE) || !is_finite_bits(beta) || !is_finite_bits(tau);
+        const bool stop = bad || tau <= thr || it + 1 >= maxit;
+        const double gamma = beta / beta_old;
+        if (MODE != MODE_PLAIN && lead) clear_dot(batch_dot(a, R.sys, S, 0)); // K2 has read it
         if (lead && threadIdx.x == 0) {
-            st->escapes += eb + et;
-            if (capture) st->fallbacks += (eb > 0) + (et > 0);
+            const long long eb = sh.red_ll[0], et = sh.red_ll[1];
+            if (eb + et) st->escapes += eb + et;
+            if (capture && eb + et) st->fallbacks += (eb > 0) + (et > 0);
             if (bad) {
                 st->status = -6;
             } else {
-                st->gamma = beta / beta_old;
+                st->gamma = gamma;
                 st->beta = beta;
                 st->beta_par[(it + 1) & 1] = beta;
                 st->tau = tau;
@@ -167,29 +234,33 @@ __global__ void __launch_bounds__(MAX_BLOCK) k_batch_direction(BatchArgs a, Slot
                 atomicSub(a.active, 1);
             }
         }
-        const double rho = st->rho; // K2's rho of this iteration
-        const double gamma = beta / beta_old;
-        const long long i1 = min((long long)R.s1 * 64, (long long)S.n);
-        for (long long i = (long long)R.s0 * 64 + threadIdx.x; i < i1; i += blockDim.x) {
-            const long long g = S.row0 + i;
-            const double di = a.d[g];
-            a.x[g] = __builtin_fma(rho, di, a.x[g]);                   // S3
-            if (!stop) a.d[g] = __builtin_fma(gamma, di, a.z[g]);      // S7
+        while (i < i1) {
+#pragma unroll
+            for (int j = 0; j < BATCH_DIR; ++j) {
+                const long long c = i + j * step;
+#pragma unroll
+                for (int r = 0; r < 2; ++r) {
+                    xv[j][r] = __builtin_fma(rho, dv[j][r], xv[j][r]);      // S3
+                    dv[j][r] = __builtin_fma(gamma, dv[j][r], zv[j][r]);    // S7
+                }
+                store_rows(xp, xv[j], c, i1);
+                if (!stop) store_rows(dp, dv[j], c, i1);
+            }
+            i += BATCH_DIR * step;
+            if (i < i1) load(i);
         }
     }
 }
 
-hipError_t launch_batch_iteration(int mode, int layout, const BatchArgs &a, int grid, int block, const DotWs *ws3,
-                                  int stride, const LaunchCfg &c)
+hipError_t launch_batch_iteration(int mode, int layout, const BatchArgs &a, int grid, int block, const LaunchCfg &c)
 {
-    SlotView s0{ws3[0], stride}, s1{ws3[1], stride}, s2{ws3[2], stride};
     dispatch(mode, c.fpe_size, [&](auto m, auto p) {
         constexpr int M = decltype(m)::value, PP = decltype(p)::value;
         dispatch_layout(layout, [&](auto lay) {
-            k_batch_spmv_dot<M, PP, decltype(lay)::value><<<grid, block, 0, c.stream>>>(a, s0, c.early_exit, c.fallback);
+            k_batch_spmv_dot<M, PP, decltype(lay)::value><<<grid, block, 0, c.stream>>>(a, c.early_exit, c.fallback);
         });
-        k_batch_update<M, PP><<<grid, block, 0, c.stream>>>(a, s0, s1, s2, c.early_exit, c.fallback);
-        k_batch_direction<M, PP><<<grid, block, 0, c.stream>>>(a, s1, s2, c.early_exit, c.fallback);
+        k_batch_update<M, PP><<<grid, block, 0, c.stream>>>(a, c.early_exit, c.fallback);
+        k_batch_direction<M, PP><<<grid, block, 0, c.stream>>>(a, c.fallback);
     });
     return hipGetLastError();
 }

@@ -5,11 +5,13 @@
 
 namespace rpcg {
 
-__global__ void k_batch_state_init(BatchArgs a, int maxit)
+// State of every system; its dots emptied (one workgroup per system).
+__global__ void __launch_bounds__(256) k_batch_state_init(BatchArgs a, int maxit)
 {
-    const int sys = blockIdx.x * blockDim.x + threadIdx.x;
+    const int sys = blockIdx.x;
+    for (int d = 0; d < 3; ++d) clear_dot(batch_dot(a, sys, a.sys[sys], d));
+    if (threadIdx.x != 0) return;
     if (sys == 0) *a.active = a.nsys;
-    if (sys >= a.nsys) return;
     PcgState z = {};
     z.maxit = maxit;
     z.ended = 0x7FFFFFFF;
@@ -19,15 +21,15 @@ __global__ void k_batch_state_init(BatchArgs a, int maxit)
 // The setup runs once per solve: its block partials go through an
 // out-of-line call, which keeps the inlined copies (and compile time) down.
 template <int MODE, int P>
-__device__ __noinline__ void batch_setup_finish(LaneDot<MODE, P> &L, long long *acc, const SlotView &sv, int g,
-                                                bool ee, bool capture, int *gflags, RedShared &sh)
+__device__ __noinline__ void batch_setup_publish(LaneDot<MODE, P> &L, long long *acc, const DotWs &w, int g, bool ee,
+                                                 bool capture, int *gflags, RedShared &sh)
 {
-    block_finish<MODE, P>(L, acc, sv, g, ee, capture, gflags, sh);
+    block_publish<MODE, P, 1, false>({&L}, {acc}, {&w}, g, ee, capture, gflags, sh);
 }
 
 template <int MODE, int P, int LAY>
 __global__ void __launch_bounds__(MAX_BLOCK)
-k_batch_setup(BatchArgs a, SlotView w0, SlotView w1, SlotView w2, bool ee, bool capture)
+k_batch_setup(BatchArgs a, bool ee, bool capture)
 {
     __shared__ RedShared sh;
     const int lane = lane_id();
@@ -77,40 +79,39 @@ k_batch_setup(BatchArgs a, SlotView w0, SlotView w1, SlotView w2, bool ee, bool 
         });
         if (flags) atomicOr(&a.st[R.sys].flags, flags);
         int *gf = &a.st[R.sys].flags;
-        batch_setup_finish<MODE, P>(Lb, sh.acc[0], w0, R.slot, ee, capture, gf, sh);
-        batch_setup_finish<MODE, P>(Lt, sh.acc[1], w1, R.slot, ee, capture, gf, sh);
-        batch_setup_finish<MODE, P>(Lbb, sh.acc[2], w2, R.slot, ee, capture, gf, sh);
+        const int g = R.slot - S.slot0;
+        batch_setup_publish<MODE, P>(Lb, sh.acc[0], batch_dot(a, R.sys, S, 0), g, ee, capture, gf, sh);
+        batch_setup_publish<MODE, P>(Lt, sh.acc[1], batch_dot(a, R.sys, S, 1), g, ee, capture, gf, sh);
+        batch_setup_publish<MODE, P>(Lbb, sh.acc[2], batch_dot(a, R.sys, S, 2), g, ee, capture, gf, sh);
     }
 }
 
-template <int MODE, int P>
-__device__ __noinline__ double batch_setup_merge(const SlotView &sv, int G, bool ee, bool capture, long long *acc,
-                                                 long long *esc_out, int *flags_out, RedShared &sh, int slot_val)
-{
-    return merge_slots<MODE, P>(sv, G, ee, capture, acc, esc_out, flags_out, sh, slot_val);
-}
-
-// One workgroup per system: beta0, tau0, <b,b>, thr = RN(RN(tol*tol) <b,b>), stopping test.
-template <int MODE, int P>
-__global__ void __launch_bounds__(256)
-k_batch_fin_setup(BatchArgs a, SlotView w0, SlotView w1, SlotView w2, double tol, bool ee, bool capture)
+// One workgroup per system, a dot per wavefront: beta0, tau0, <b,b>, thr =
+// RN(RN(tol*tol) <b,b>), stopping test. Leaves the dots empty.
+template <int MODE>
+__global__ void __launch_bounds__(256) k_batch_fin_setup(BatchArgs a, double tol, bool capture)
 {
     __shared__ RedShared sh;
     const int sys = blockIdx.x;
     PcgState *st = a.st + sys;
     const BatchSys S = a.sys[sys];
-    const int G = S.slot1 - S.slot0;
-    long long e0, e1, e2;
-    const double beta = batch_setup_merge<MODE, P>(batch_slots<MODE>(w0, S.slot0), G, ee, capture, sh.acc[0], &e0,
-                                                   &st->flags, sh, 0);
-    const double tau = batch_setup_merge<MODE, P>(batch_slots<MODE>(w1, S.slot0), G, ee, capture, sh.acc[1], &e1,
-                                                  &st->flags, sh, 1);
-    const double bb = batch_setup_merge<MODE, P>(batch_slots<MODE>(w2, S.slot0), G, ee, capture, sh.acc[2], &e2,
-                                                 &st->flags, sh, 2);
+    const int wv = wave_id();
+    if (wv < 3) {
+        long long esc;
+        const double d = wave_merge<MODE>(batch_dot(a, sys, S, wv), S.slot1 - S.slot0, &esc);
+        if (lane_id() == 0) {
+            sh.val[wv] = d;
+            sh.red_ll[wv] = esc;
+        }
+    }
+    __syncthreads();
+    for (int d = 0; d < 3; ++d) clear_dot(batch_dot(a, sys, S, d));
+    const double beta = sh.val[0], tau = sh.val[1], bb = sh.val[2];
+    const long long e0 = sh.red_ll[0], e1 = sh.red_ll[1], e2 = sh.red_ll[2];
     if (threadIdx.x == 0) {
         st->escapes += e0 + e1 + e2;
         if (capture) st->fallbacks += (e0 > 0) + (e1 > 0) + (e2 > 0);
-        const int f = batch_flags(st);
+        const int f = coherent_int(&st->flags);
         st->beta = beta;
         st->beta_par[0] = beta;
         st->tau = tau;
@@ -133,18 +134,16 @@ k_batch_fin_setup(BatchArgs a, SlotView w0, SlotView w1, SlotView w2, double tol
     }
 }
 
-hipError_t launch_batch_setup(int mode, int layout, const BatchArgs &a, int grid, int block, const DotWs *ws3,
-                              int stride, double tol, int maxit, const LaunchCfg &c)
+hipError_t launch_batch_setup(int mode, int layout, const BatchArgs &a, int grid, int block, double tol, int maxit,
+                              const LaunchCfg &c)
 {
-    SlotView s0{ws3[0], stride}, s1{ws3[1], stride}, s2{ws3[2], stride};
-    k_batch_state_init<<<(a.nsys + 63) / 64, 64, 0, c.stream>>>(a, maxit);
+    k_batch_state_init<<<a.nsys, 256, 0, c.stream>>>(a, maxit);
     dispatch(mode, c.fpe_size, [&](auto m, auto p) {
         constexpr int M = decltype(m)::value, PP = decltype(p)::value;
         dispatch_layout(layout, [&](auto lay) {
-            k_batch_setup<M, PP, decltype(lay)::value><<<grid, block, 0, c.stream>>>(a, s0, s1, s2, c.early_exit,
-                                                                                     c.fallback);
+            k_batch_setup<M, PP, decltype(lay)::value><<<grid, block, 0, c.stream>>>(a, c.early_exit, c.fallback);
         });
-        k_batch_fin_setup<M, PP><<<a.nsys, 256, 0, c.stream>>>(a, s0, s1, s2, tol, c.early_exit, c.fallback);
+        k_batch_fin_setup<M><<<a.nsys, 256, 0, c.stream>>>(a, tol, c.fallback);
     });
     return hipGetLastError();
 }

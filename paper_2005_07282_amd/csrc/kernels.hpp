@@ -331,8 +331,8 @@ hipError_t launch_fac_update(int mode, int l, int n, const FacPre &P, const PcgV
 
 // Per-system constants of a batch. Rows of system s sit at [row0, row0 + n)
 // of the concatenated vectors, its slices at [slice0, slice0 + nslices) of
-// the concatenated sliced-ELL copy (slices never span systems), and its
-// dot partials in slots [slot0, slot1).
+// the concatenated sliced-ELL copy (slices never span systems), and its runs
+// are numbered slot0, ..., slot1 - 1.
 struct BatchSys {
     long long row0;   // multiple of 128
     long long slice0; // row0 / 64
@@ -344,7 +344,7 @@ struct BatchSys {
 };
 
 // One run of work: slices [s0, s1) of system `sys`, processed by one
-// workgroup, whose dot partials go to slot `slot`.
+// workgroup, number `slot` of all runs (those of a system are consecutive).
 struct BatchRun {
     int sys;
     int s0;
@@ -370,18 +370,20 @@ struct BatchArgs {
     const double *b;
     double *x, *r, *z, *d, *w, *dinv;
     PcgState *st;          // [nsys]
+    long long *acc;        // [nsys][3][DOT_COPIES][DOT_PITCH] accumulators of each system's dots
+    double *part;          // [3][part_cap] workgroup sums (plain), by slot
+    int part_cap;
     double *const *hist;   // [nsys] tau histories (maxit + 1 each, entries may be null), or null
     int *active;           // number of systems not done
 };
 
-// Setup of every system (state, partials of <z,r>, <r,r>, <b,b> into ws3,
-// one workgroup per system to merge them).
-hipError_t launch_batch_setup(int mode, int layout, const BatchArgs &a, int grid, int block, const DotWs *ws3,
-                              int stride, double tol, int maxit, const LaunchCfg &cfg);
-// One iteration of every system not done: SpMV + <d,w> partials (ws[0]),
-// per-system rho, updates + <z,r>, <r,r> partials (ws[1], ws[2]), per-system
-// stopping test and gamma, direction update.
-hipError_t launch_batch_iteration(int mode, int layout, const BatchArgs &a, int grid, int block, const DotWs *ws3,
-                                  int stride, const LaunchCfg &cfg);
+// Setup of every system (state, <z,r>, <r,r>, <b,b>, one workgroup per system
+// to merge them; the dots are left empty).
+hipError_t launch_batch_setup(int mode, int layout, const BatchArgs &a, int grid, int block, double tol, int maxit,
+                              const LaunchCfg &cfg);
+// One iteration of every system not done: SpMV + <d,w> (dot 0), per-system
+// rho, updates + <z,r>, <r,r> (dots 1, 2), per-system stopping test and gamma,
+// iterate and direction update. Emptied as in the single solver.
+hipError_t launch_batch_iteration(int mode, int layout, const BatchArgs &a, int grid, int block, const LaunchCfg &cfg);
 
 } // namespace rpcg

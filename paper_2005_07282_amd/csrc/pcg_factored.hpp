@@ -39,7 +39,7 @@ k_fac_z(int n, FacPre Pr, PcgVecs<double> v, const double *__restrict__ t, PcgSt
         if (SETUP) v.d[i] = zi;
         Lb.add(zi, ri, sh.acc[0], ee, capture);
     }
-    block_publish<MODE, P, 1, false>({&Lb}, {sh.acc[0]}, {&wb}, ee, capture, &st->flags, sh);
+    block_publish<MODE, P, 1, false>({&Lb}, {sh.acc[0]}, {&wb}, blockIdx.x, ee, capture, &st->flags, sh);
 }
 
 } // namespace rpcg

@@ -75,7 +75,7 @@ k_fac_update(int l, int n, FacPre Pr, PcgVecs<double> v, const double *__restric
         }
         t[i] = ti;
     }
-    block_publish<MODE, P, 1, false>({&Lt}, {sh.acc[1]}, {&wt}, ee, capture, &st->flags, sh);
+    block_publish<MODE, P, 1, false>({&Lt}, {sh.acc[1]}, {&wt}, blockIdx.x, ee, capture, &st->flags, sh);
 }
 
 hipError_t launch_fac_update(int mode, int l, int n, const FacPre &Pr, const PcgVecs<double> &v, double *r_new,

@@ -10,7 +10,7 @@ template <int MODE, int P>
 __device__ __noinline__ void fac_publish(LaneDot<MODE, P> &L, long long *acc, const DotWs &w, bool ee, bool capture,
                                          int *gflags, RedShared &sh)
 {
-    block_publish<MODE, P, 1, false>({&L}, {acc}, {&w}, ee, capture, gflags, sh);
+    block_publish<MODE, P, 1, false>({&L}, {acc}, {&w}, blockIdx.x, ee, capture, gflags, sh);
 }
 
 static __global__ void k_fac_state_init(PcgState *st, int maxit, DotWs w0, DotWs w1, DotWs w2)

@@ -14,7 +14,7 @@ template <int MODE, int P>
 __device__ __noinline__ void setup_publish(LaneDot<MODE, P> &L, long long *acc, const DotWs &w, bool ee, bool capture,
                                            int *gflags, RedShared &sh)
 {
-    block_publish<MODE, P, 1, false>({&L}, {acc}, {&w}, ee, capture, gflags, sh);
+    block_publish<MODE, P, 1, false>({&L}, {acc}, {&w}, blockIdx.x, ee, capture, gflags, sh);
 }
 
 // State of a new solve; the dots' accumulators emptied (one workgroup).

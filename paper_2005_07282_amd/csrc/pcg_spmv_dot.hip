@@ -36,7 +36,7 @@ k_pcg_spmv_dot(SellMat<T> A, PcgVecs<T> v, PcgState *st, DotWs wd, DotWs wb, Dot
         for (int r = 0; r < R; ++r)
             if (i + r < A.n) L.add(di[r], sum[r], acc, ee, capture);
     });
-    block_publish<MODE, P, 1, false>({&L}, {acc}, {&wd}, ee, capture, &st->flags, sh);
+    block_publish<MODE, P, 1, false>({&L}, {acc}, {&wd}, blockIdx.x, ee, capture, &st->flags, sh);
 }
 
 template <typename T>

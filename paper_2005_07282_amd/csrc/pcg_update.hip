@@ -82,7 +82,7 @@ k_pcg_update(int l, int n, PcgVecs<T> v, PcgState *st, DotWs wd, int Gd, DotWs w
         Lb.add(zi, ri, sh.acc[0], ee, capture);           // S6
         Lt.add(ri, ri, sh.acc[1], ee, capture);           // S8
     }
-    block_publish<MODE, P, 2, false>({&Lb, &Lt}, {sh.acc[0], sh.acc[1]}, {&wb, &wt}, ee, capture, &st->flags, sh);
+    block_publish<MODE, P, 2, false>({&Lb, &Lt}, {sh.acc[0], sh.acc[1]}, {&wb, &wt}, blockIdx.x, ee, capture, &st->flags, sh);
 }
 
 // Elements per thread whose operands K3 loads before merging the dots, so

@@ -876,16 +876,18 @@ __device__ __forceinline__ T merge_slots(const SlotView &sv, int G, bool ee, boo
 // latency in every workgroup. PLAIN keeps the slots (its sum order is fixed).
 
 // Add the workgroup accumulators of D dots (LDS) to their global copies, after
-// the lanes' expansions have gone in; escapes and flags too. All threads call.
+// the lanes' expansions have gone in; escapes and flags too. g: the workgroup's
+// number among those that add to these dots. All threads call.
 template <int MODE, int P, int D, bool ADAPT>
 __device__ __forceinline__ void block_publish(LaneDot<MODE, P, ADAPT> *const (&L)[D], long long *const (&acc)[D],
-                                              const DotWs *const (&w)[D], bool ee, bool capture, int *gflags, RedShared &sh)
+                                              const DotWs *const (&w)[D], int g, bool ee, bool capture, int *gflags,
+                                              RedShared &sh)
 {
     if constexpr (MODE == MODE_PLAIN) {
 #pragma unroll
         for (int d = 0; d < D; ++d) {
             const double t = block_sum_d(L[d]->s, sh);
-            if (threadIdx.x == 0) w[d]->part[blockIdx.x] = t;
+            if (threadIdx.x == 0) w[d]->part[g] = t;
         }
     } else {
         int fl = 0;
@@ -907,7 +909,7 @@ __device__ __forceinline__ void block_publish(LaneDot<MODE, P, ADAPT> *const (&L
 #pragma unroll
         for (int d = 0; d < D; ++d) fl |= L[d]->flags;
         __syncthreads();
-        const int copy = blockIdx.x % DOT_COPIES;
+        const int copy = g % DOT_COPIES;
         for (int q = threadIdx.x; q < D * ACC_DIGITS; q += blockDim.x) {
             const int d = D == 1 ? 0 : q / ACC_DIGITS, k = q - d * ACC_DIGITS;
             // one carry step keeps every word below 2^33 in magnitude, so the
