@@ -235,7 +235,7 @@ __global__ void __launch_bounds__(256) k_sell_spmv(SellMat<double> A, const doub
                                                    double *__restrict__ y, int parts)
 {
     const int lane = lane_of();
-    for_slices<double, LAY, false>(A, wave_slices(A.nslices, parts), lane, [&](long long i, auto &&rows) {
+    for_slices<double, LAY, false>(A, wave_slices(A.nslices, LAY == LAY_DIAG ? parts : 1), lane, [&](long long i, auto &&rows) {
         double sum[lane_rows<LAY>()];
         rows(x, sum, nullptr, nullptr);
         store_rows(y, sum, i, A.n);

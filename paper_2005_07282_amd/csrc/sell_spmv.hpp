@@ -199,11 +199,13 @@ __device__ __forceinline__ SliceRange wave_slices(int nslices, int parts)
 {
     const int W = blockDim.x >> 6;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int idx = __builtin_amdgcn_readfirstlane((int)(blockIdx.x / parts));
+    if (parts == 1) return {(long long)blockIdx.x * W + wave, nslices, (long long)gridDim.x * W};
+    const int idx = __builtin_amdgcn_readfirstlane((int)(blockIdx.x / (unsigned)parts));
     const int part = (int)blockIdx.x - idx * parts;
-    const int groups = __builtin_amdgcn_readfirstlane((int)((gridDim.x - part + parts - 1) / parts));
-    const long long lo = uniform_ll((long long)nslices * part / parts);
-    return {lo + (long long)idx * W + wave, uniform_ll((long long)nslices * (part + 1) / parts), (long long)groups * W};
+    const int groups = __builtin_amdgcn_readfirstlane((int)((gridDim.x - part + parts - 1) / (unsigned)parts));
+    const long long chunk = __builtin_amdgcn_readfirstlane((int)(((unsigned)nslices + parts - 1) / (unsigned)parts));
+    const long long lo = chunk * part, hi = lo + chunk < nslices ? lo + chunk : nslices;
+    return {lo + (long long)idx * W + wave, hi, (long long)groups * W};
 }
 
 // Rows a lane owns per slice.
