@@ -401,78 +401,122 @@ __device__ __forceinline__ double dpp_f64(double v)
     return __builtin_bit_cast(double, dpp_i64<CTRL, ROW_MASK>(__builtin_bit_cast(long long, v)));
 }
 
-// Sum over the wavefront in every lane; the caller makes sure every partial
-// sum is exact.
-__device__ __forceinline__ double wave_sum_f64_all(double v)
+// Wavefront sums of four values at once, each row of 16 lanes left with one of
+// them in all its lanes: row r holds the sum of s[row_sum_of(r)]. The caller
+// makes sure every partial sum is exact. The halves, then the rows, of two values
+// are swapped and added (permlane swaps), so a step serves two values.
+__device__ __forceinline__ int row_sum_of(int row) { return ((row & 1) << 1) | (row >> 1); }
+template <bool HALVES>
+__device__ __forceinline__ double swap_add(double x, double y)
 {
-    v += dpp_f64<0x111>(v);
-    v += dpp_f64<0x112>(v);
-    v += dpp_f64<0x114>(v);
-    v += dpp_f64<0x118>(v);
-    v += dpp_f64<0x142, 0xA>(v);
-    v += dpp_f64<0x143, 0xC>(v);
-    return __builtin_bit_cast(double, wave_i64_of(__builtin_bit_cast(long long, v), 63));
+    const unsigned long long bx = __builtin_bit_cast(unsigned long long, x), by = __builtin_bit_cast(unsigned long long, y);
+    auto sw = [](unsigned u, unsigned v) {
+        if constexpr (HALVES) return __builtin_amdgcn_permlane32_swap(u, v, false, false);
+        else return __builtin_amdgcn_permlane16_swap(u, v, false, false);
+    };
+    const auto lo = sw((unsigned)bx, (unsigned)by), hi = sw((unsigned)(bx >> 32), (unsigned)(by >> 32));
+    return __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]) +
+           __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
+}
+__device__ __forceinline__ double wave_row_sums(const double (&s)[4])
+{
+    double v = swap_add<false>(swap_add<true>(s[0], s[1]), swap_add<true>(s[2], s[3]));
+    v += dpp_f64<0x128>(v); // row_ror:8, 4, 2, 1
+    v += dpp_f64<0x124>(v);
+    v += dpp_f64<0x122>(v);
+    v += dpp_f64<0x121>(v);
+    return v;
 }
 
-// Exact sums of the lanes' expansions of one wavefront, D dots at once, added
-// to their long accumulators. The components are cut from the top into digits
+// Exact sums of the lanes' terms of one wavefront, D dots at once, added
+// to their long accumulators. The terms are cut from the top into digits
 // of 40 bits at the same places in every lane: t = (a + c) - c with c = 1.5
 // 2^(p + 52) is a rounded to a multiple of 2^p, exactly what a then loses,
-// and the sum of t over P <= 8 components and 64 lanes stays below 2^(p + 50), so the binary64
-// sums of a digit are exact in any order. Lane j keeps digit j's sum; all are
-// added to the accumulator together at the end. Adding the components' 32-bit chunks
-// word by word took about 80 instructions a word for some eight words; a digit
-// takes about 30 for some four or five (32 k rows: update kernel 8.3 -> 6.0 us,
-// SpMV + dot 8.3 -> 6.3 us; 4.1 M rows: 33.3 -> 30.2 and 34.1 -> 32.0 us).
+// and the sum of t over P <= 8 terms and 64 lanes stays below 2^(p + 50), so the binary64
+// sums of a digit are exact in any order. Four digits (two of each of two dots) are
+// summed over the wavefront together, one in each row of 16 lanes; block k's sums stay in lanes
+// k of the rows, and all are added to the accumulators together at the end. What
+// bounds it is the instruction count: adding the terms' 32-bit chunks word by word
+// took about 80 a word for some eight words, a digit summed by itself about 50
+// for some five, and so about 30 (32 k rows: update kernel 8.3 -> 6.0 -> 5.0 us,
+// SpMV + dot 8.3 -> 6.3 -> 6.15 us; 4.1 M rows: 33.3 -> 30.2 -> 29.3 and 34.1 -> 32.0 -> 31.6 us).
 constexpr int FLUSH_DIGIT = 40;
 template <int P, int D>
 __device__ __forceinline__ void wave_flush_dots(double (&a)[D][P], long long *const (&acc)[D], int *const (&flags)[D])
 {
-    double mx = 0.0;
+    static_assert(D == 1 || D == 2, "rows of a wavefront");
+    constexpr int Q = 4 / D; // digits per block
+    auto top = [&]() { // largest biased exponent of the wavefront
+        int m = 0;
 #pragma unroll
-    for (int d = 0; d < D; ++d)
+        for (int d = 0; d < D; ++d)
 #pragma unroll
-        for (int i = 0; i < P; ++i) {
-            if (!is_finite_bits(a[d][i])) {
-                *flags[d] |= FLAG_NONFINITE;
-                a[d][i] = 0.0;
-            }
-            mx = fmax(mx, __builtin_fabs(a[d][i]));
-        }
-    constexpr int NONE = -2000;
-    const int E = wave_minmax_i32_all<true>(mx > 0.0 ? __builtin_amdgcn_frexp_exp(mx) : NONE); // |a| < 2^E
-    if (E == NONE) return;
+            for (int i = 0; i < P; ++i)
+                m = max(m, (int)(__builtin_bit_cast(unsigned long long, a[d][i]) >> 32) & 0x7FFFFFFF);
+        return wave_minmax_i32_all<true>(m) >> 20;
+    };
+    int be = top();
+    if (be == 0x7FF) {
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+#pragma unroll
+            for (int i = 0; i < P; ++i)
+                if (!is_finite_bits(a[d][i])) {
+                    *flags[d] |= FLAG_NONFINITE;
+                    a[d][i] = 0.0;
+                }
+        be = top();
+    }
+    if (be == 0) { // zeros and subnormals
+        bool any = false;
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+#pragma unroll
+            for (int i = 0; i < P; ++i) any = any || a[d][i] != 0.0;
+        if (__ballot(any) == 0) return;
+    }
+    const int E = be - 1022; // |a| < 2^E
     if (E > 1011) { // the constants below would overflow
 #pragma unroll
         for (int d = 0; d < D; ++d) wave_flush_words<P>(a[d], acc[d]);
         return;
     }
-    double mine[D];
-#pragma unroll
-    for (int d = 0; d < D; ++d) mine[d] = 0.0;
     const int l = lane_id();
-    int j = 0;
-    for (int pos = E - FLUSH_DIGIT;; pos -= FLUSH_DIGIT, ++j) { // at most 53 digits
-        const int p = max(pos, -1074); // every component is a multiple of 2^-1074
-        const double c = __builtin_bit_cast(double, ((unsigned long long)(p + 52 + 1023) << 52) | (1ull << 51));
+    // of two dots, the odd rows hold the second (an offset: a chosen pointer would lose its address space)
+    long long *const to = acc[0] + ((l & 16) ? acc[D - 1] - acc[0] : 0);
+    double mine = 0.0;
+    int pos = E, k = 0, unused = 0;
+    for (;;) {
+        double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            pos -= FLUSH_DIGIT;
+            const int p = max(pos, -1074); // every term is a multiple of 2^-1074
+            const double c = __builtin_bit_cast(double, ((unsigned long long)(p + 52 + 1023) << 52) | (1ull << 51));
+#pragma unroll
+            for (int d = 0; d < D; ++d)
+#pragma unroll
+                for (int i = 0; i < P; ++i) {
+                    const double t = (a[d][i] + c) - c;
+                    a[d][i] -= t;
+                    s[d * Q + q] += t;
+                }
+        }
         bool left = false;
 #pragma unroll
-        for (int d = 0; d < D; ++d) {
-            double s = 0.0;
+        for (int d = 0; d < D; ++d)
 #pragma unroll
-            for (int i = 0; i < P; ++i) {
-                const double t = (a[d][i] + c) - c;
-                a[d][i] -= t;
-                s += t;
-                left = left || a[d][i] != 0.0;
-            }
-            s = wave_sum_f64_all(s);
-            mine[d] = l == j ? s : mine[d];
-        }
+            for (int i = 0; i < P; ++i) left = left || a[d][i] != 0.0;
+        const double v = wave_row_sums(s);
+        mine = (l & 15) == k ? v : mine;
         if (__ballot(left) == 0) break;
+        if (++k == 16) {
+            acc_add_lds(to, mine, unused);
+            mine = 0.0;
+            k = 0;
+        }
     }
-#pragma unroll
-    for (int d = 0; d < D; ++d) acc_add_lds(acc[d], mine[d], *flags[d]);
+    acc_add_lds(to, mine, unused);
 }
 
 template <int P>
@@ -891,19 +935,28 @@ __device__ __forceinline__ void block_publish(LaneDot<MODE, P, ADAPT> *const (&L
         }
     } else {
         int fl = 0;
-        if constexpr (MODE == MODE_EXBLAS && D == 2) {
-            wave_flush_exact2<P>(L[0]->a, acc[0], L[0]->flags, L[1]->a, acc[1], L[1]->flags);
+        bool together = D == 2; // both dots' digits in one pass
+        if constexpr (MODE == MODE_FPE) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                L[d]->esc += fpe_sum_capture<P>(L[d]->a, L[d]->e, ee, capture, acc[d], L[d]->flags);
+                if (D == 2) together = together && wave_fpe_merge_is_exact<P>(L[d]->a);
+            }
+        }
+        if (together) {
+            wave_flush_exact2<P>(L[0]->a, acc[0], L[0]->flags, L[D - 1]->a, acc[D - 1], L[D - 1]->flags);
         } else {
 #pragma unroll
             for (int d = 0; d < D; ++d) {
-                if constexpr (MODE == MODE_EXBLAS) {
-                    wave_flush_exact<P>(L[d]->a, acc[d], L[d]->flags);
-                } else {
-                    L[d]->esc += fpe_sum_capture<P>(L[d]->a, L[d]->e, ee, capture, acc[d], L[d]->flags);
-                    wave_fpe_finish<P>(L[d]->a, L[d]->esc, ee, capture, acc[d], L[d]->flags);
-                    const long long esc = wave_sum_i64_all(L[d]->esc);
-                    if (lane_id() == 0 && esc) atomicAdd((unsigned long long *)&w[d]->acc[DOT_ESC], (unsigned long long)esc);
-                }
+                if constexpr (MODE == MODE_EXBLAS) wave_flush_exact<P>(L[d]->a, acc[d], L[d]->flags);
+                else wave_fpe_finish<P>(L[d]->a, L[d]->esc, ee, capture, acc[d], L[d]->flags);
+            }
+        }
+        if constexpr (MODE == MODE_FPE) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                const long long esc = wave_sum_i64_all(L[d]->esc);
+                if (lane_id() == 0 && esc) atomicAdd((unsigned long long *)&w[d]->acc[DOT_ESC], (unsigned long long)esc);
             }
         }
 #pragma unroll
