@@ -4,6 +4,7 @@
 #include "lp_common.hpp"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace rpcg {
 
@@ -197,96 +198,174 @@ __global__ void __launch_bounds__(64 * CONV_LINES) k_lp_conv(int nb, int N, cons
 // the tap, channel l%16 (B). A workgroup is three wavefronts, one per dz,
 // each holding the nine tap tiles of its plane, and walks its items (system,
 // z-run, y-line, 32-cell x-segment) one z-plane at a time. Per plane it
-// stages, with 16-byte loads, the dout row of the plane and the three input
-// rows y - 1 .. y + 1 of the next plane into a ring of three planes in LDS
-// (zeros outside the grid), so every input row is loaded once and read by
-// the three wavefronts (dz = -1, 0, +1 read the planes z - 1, z, z + 1); the
-// loads of the next plane go to registers under the current plane's
-// products and are written to LDS at the start of the next step. The
-// operands are then gathered from LDS as 16-bit values: per input row a lane
-// reads the ten cells x - 1 .. x + 8 around its eight and forms the three dx
-// fragments from them. Every eighth staged cell is followed by a gap of one
-// cell (16 channels), so the four k-groups of a gather fall in different
-// banks. Each wavefront writes its nine taps to the workgroup's slot; the
-// slots are summed in a fixed order later.
+// stages the dout row of the plane and the three input rows y - 1 .. y + 1 of the
+// next plane into LDS (zeros outside the grid), so every input row is loaded
+// once and read by the three wavefronts (dz = -1, 0, +1 read the planes z - 1,
+// z, z + 1); the loads of the next DW_PF planes are in flight in registers under
+// the current plane's products. Four input planes and two dout rows are held, so
+// a plane needs one barrier: what is staged beside the products is read after it.
+//
+// The operands run along cells, the activations along channels: the rows are
+// turned while they are staged. A thread takes a pair of cells of eight (or
+// all four) channels and writes one 32-bit word of two cells per channel; the
+// operand of dx = -1 is then one 16-byte read, that of dx = +1 the same words one
+// on, and dx = 0 between them the words shifted by a cell. Gathering each operand
+// value with a 16-bit read of its own (38 a lane and plane instead of 7) and
+// packing them bounded this kernel: 2.1 M cells, 16 -> 4, 16 -> 16 and 4 -> 16
+// channels 86, 86 and 99 -> 47, 48 and 46 us (one plane in flight: 76, 74 and 63 us), now bound by
+// the chain of a step (LDS writes, barrier, LDS reads, products) on four
+// workgroups a CU. Rows past a layer's four channels repeat them; nothing
+// reads their sums.
 constexpr int DW_SEG = 32; // cells along x per item (the K of one product)
 constexpr int DW_ZR = 64;  // z-planes per item
-constexpr int DW_XC = DW_SEG + 2; // staged input cells per row
+constexpr int DW_XP = DW_SEG / 2 + 1; // staged pairs of input cells per row (x0 - 1 .. x0 + 32)
+// words of a channel's row: 16-byte units, and 16 channels of a unit in 64 different banks
+constexpr int DW_CS = 20;
+constexpr int DW_PF = 4;  // planes in flight
+constexpr unsigned DW_OUT = 0xFFFFFFF0u; // past every buffer
 
-// Byte offset of staged cell c in a row of cells of C channels.
+// A staged unit: two cells of eight channels (or of all four), one word of two
+// cells per channel when written.
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+typedef unsigned v2u __attribute__((ext_vector_type(2)));
 template <int C>
-__host__ __device__ constexpr int dw_cell(int c) { return C == 16 ? (c + (c >> 3)) * 32 : c * 8; }
-template <int C>
-__host__ __device__ constexpr int dw_row_bytes(int cells) { return dw_cell<C>(cells); }
-
-// Stage `cells` cells of row (Z, Y) from x = X0 on (zeros outside the grid)
-// at dst, with all threads of the workgroup; 16-byte units (8 channels), or
-// one 8-byte unit per cell for 4 channels.
-template <int C>
-__device__ __forceinline__ void dw_stage_row(unsigned char *dst, const bf16_t *__restrict__ src, int N, int Z, int Y,
-                                             int X0, int cells, int first, int stride)
-{
-    constexpr int UPC = C == 16 ? 2 : 1;
-    const bool row_in = Z >= 0 && Z < N && Y >= 0 && Y < N;
-    for (int u = first; u < cells * UPC; u += stride) {
-        const int c = u / UPC, q = u % UPC, X = X0 + c;
-        const bool in = row_in && X >= 0 && X < N;
-        const long long cell = ((long long)Z * N + Y) * N + X;
+struct DwUnit {
+    typedef typename std::conditional<C == 16, v4u, v2u>::type word_t;
+    word_t a, b;
+    // the two cells at byte offsets o0, o1 (past the buffer: zeros)
+    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rs, unsigned o0, unsigned o1)
+    {
         if constexpr (C == 16) {
-            v8s v = {0, 0, 0, 0, 0, 0, 0, 0};
-            if (in) v = *(const v8s *)(src + cell * 16 + 8 * q);
-            *(v8s *)(dst + dw_cell<16>(c) + 16 * q) = v;
+            a = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)o0, 0, 0));
+            b = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)o1, 0, 0));
         } else {
-            v4s v = {0, 0, 0, 0};
-            if (in) v = *(const v4s *)(src + cell * 4);
-            *(v4s *)(dst + dw_cell<4>(c)) = v;
+            a = __builtin_bit_cast(v2u, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)o0, 0, 0));
+            b = __builtin_bit_cast(v2u, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)o1, 0, 0));
         }
     }
-}
-
-// The same staging in two halves: dw_load_row reads the units thread
-// `first` owns (at most K of them) into registers, dw_store_row writes them
-// to LDS, so the loads of the next plane can run under the current plane's
-// products.
-template <int C, int K>
-__device__ __forceinline__ void dw_load_row(v8s (&reg)[K], const bf16_t *__restrict__ src, int N, int Z, int Y, int X0,
-                                            int cells, int first, int stride)
-{
-    constexpr int UPC = C == 16 ? 2 : 1;
-    const bool row_in = Z >= 0 && Z < N && Y >= 0 && Y < N;
+    __device__ __forceinline__ void store(unsigned *dst) // dst: word of the first channel's row
+    {
+        asm volatile("" : "+v"(a), "+v"(b)); // not taken up, and so waited for, before this place
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const int u = first + k * stride;
-        const int c = u / UPC, q = u % UPC, X = X0 + c;
-        const bool in = row_in && u < cells * UPC && X >= 0 && X < N;
-        const long long cell = ((long long)Z * N + Y) * N + X;
-        v8s v = {0, 0, 0, 0, 0, 0, 0, 0};
-        if constexpr (C == 16) {
-            if (in) v = *(const v8s *)(src + cell * 16 + 8 * q);
-        } else {
-            if (in) {
-                const v4s w = *(const v4s *)(src + cell * 4);
-                v[0] = w[0]; v[1] = w[1]; v[2] = w[2]; v[3] = w[3];
+        for (int w = 0; w < (C == 16 ? 4 : 2); ++w) {
+            dst[(2 * w) * DW_CS] = __builtin_amdgcn_perm(b[w], a[w], 0x05040100);
+            dst[(2 * w + 1) * DW_CS] = __builtin_amdgcn_perm(b[w], a[w], 0x07060302);
+        }
+    }
+};
+
+template <int CIN, int COUT>
+struct DwShared {
+    unsigned ring[4][3][CIN][DW_CS]; // input [plane][dy][channel][cell pair]
+    unsigned drow[2][COUT][DW_CS];   // dout [plane][channel][cell pair]
+    unsigned nowhere[64 + 7 * DW_CS]; // what threads without a unit write
+};
+
+// The items of one wavefront: DZ = 0, 1, 2 for dz = -1, 0, +1. The first two
+// stage the input, the third dout, the middle one sums the bias gradient. Each role
+// has a loop of its own: with branches in it, a wait would have to assume
+// the loads of the other side too and so wait for the newest.
+template <int CIN, int COUT, int DZ>
+__device__ __forceinline__ void dw_items(int nb, int N, long long slot, long long slots, const bf16_t *__restrict__ in,
+                                         const bf16_t *__restrict__ dout, v4f (&acc)[9], float &bsum,
+                                         DwShared<CIN, COUT> &sh)
+{
+    constexpr bool ISD = DZ == 2;
+    constexpr int C = ISD ? COUT : CIN;
+    constexpr int UPC = C == 16 ? 2 : 1;                                    // channel groups per cell
+    constexpr int ROW = ISD ? DW_SEG / 2 : DW_XP, UNITS = (ISD ? 1 : 3) * ROW * UPC; // staged units per plane
+    static_assert(UNITS <= (ISD ? 64 : 128), "a unit per thread");
+    const int lane = threadIdx.x & 63, kb = lane >> 4, c16 = lane & 15;
+    const int segs = (N + DW_SEG - 1) / DW_SEG, runs = (N + DW_ZR - 1) / DW_ZR;
+    const long long items = (long long)nb * runs * N * segs;
+    const long long NN = (long long)N * N, N3 = NN * N;
+    // this thread's unit: cell pair up of row ur, channels 8 uq ..
+    const int un = ISD ? lane : (int)threadIdx.x;
+    const bool mine = un < UNITS;
+    const int uq = mine ? un % UPC : 0, up = mine ? un / UPC % ROW : 0, ur = mine ? un / (UPC * ROW) : 0;
+    for (long long it = slot; it < items; it += slots) { // workgroup-uniform
+        const int seg = (int)(it % segs);
+        long long r = it / segs;
+        const int y = (int)(r % N);
+        r /= N;
+        const int zr = (int)(r % runs);
+        const long long b = r / runs;
+        const int x0 = seg * DW_SEG;
+        const int z0 = zr * DW_ZR, z1 = min(z0 + DW_ZR, N);
+        // byte offsets of the unit's cells in plane zb, the first that the item reads
+        const int zb = max(z0 - 1, 0), ze = min(z1 + 1, N);
+        const int X = ISD ? x0 + 2 * up : x0 - 1 + 2 * up, Y = ISD ? y : y + ur - 1;
+        const bool row_in = mine && Y >= 0 && Y < N;
+        const bool in0 = row_in && X >= 0 && X < N, in1 = row_in && X + 1 < N; // X >= -1
+        const unsigned plane = (unsigned)(NN * C * 2);
+        const unsigned cell = (unsigned)(((long long)Y * N + X) * C * 2 + 16 * uq);
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            (void *)((ISD ? dout : in) + (b * N3 + zb * NN) * C), 0, (int)((ze - zb) * plane), 0x00027000);
+        // the input is staged one plane ahead of dout: step z stages input z + 1 and dout z
+        auto load = [&](DwUnit<C> &u, int z) { // plane z, zeros outside the grid
+            const bool zin = z >= zb && z < ze;
+            const unsigned o = (unsigned)(z - zb) * plane + cell;
+            u.load(rs, in0 && zin ? o : DW_OUT, in1 && zin ? o + 2u * C : DW_OUT);
+        };
+        auto store = [&](DwUnit<C> &u, int z) {
+            unsigned *dst = ISD ? &sh.drow[z & 1][8 * uq][up] : &sh.ring[z & 3][ur][8 * uq][up];
+            u.store(mine ? dst : &sh.nowhere[lane]);
+        };
+        constexpr int LEAD = ISD ? 0 : 1;
+        DwUnit<C> pre[DW_PF];
+        __syncthreads(); // the previous item's readers are done
+        if constexpr (!ISD) {
+            DwUnit<C> u0, u1;
+            load(u0, z0 - 1);
+            load(u1, z0);
+            store(u0, z0 - 1);
+            store(u1, z0);
+        }
+#pragma unroll
+        for (int u = 0; u < DW_PF; ++u) load(pre[u], z0 + LEAD + u);
+        auto step = [&](DwUnit<C> &u, int z) {
+            store(u, z + LEAD);
+            load(u, z + LEAD + DW_PF);
+            __syncthreads(); // a wavefront that is ahead stages other planes than the others read
+            // A: dout at cells 8 kb + j of channel c16; B: of the three rows of plane z + dz the
+            // staged cells 8 kb .. 8 kb + 9 = x - 1 .. x + 8 of channel c16
+            v4u a = *(const v4u *)&sh.drow[z & 1][c16 & (COUT - 1)][4 * kb], w[3];
+            unsigned last[3];
+#pragma unroll
+            for (int dyi = 0; dyi < 3; ++dyi) {
+                const unsigned *row = sh.ring[(z + DZ + 3) & 3][dyi][c16 & (CIN - 1)] + 4 * kb;
+                w[dyi] = *(const v4u *)row;
+                last[dyi] = row[4];
             }
-        }
-        reg[k] = v;
-    }
-}
-
-template <int C, int K>
-__device__ __forceinline__ void dw_store_row(unsigned char *dst, const v8s (&reg)[K], int cells, int first, int stride)
-{
-    constexpr int UPC = C == 16 ? 2 : 1;
+            // all reads in flight at once, and none again for another register tuple
+            asm volatile("" : "+v"(a), "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(last[0]), "+v"(last[1]), "+v"(last[2]));
+            if constexpr (DZ == 1) {
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const int u = first + k * stride;
-        if (u >= cells * UPC) break;
-        const int c = u / UPC, q = u % UPC;
-        if constexpr (C == 16) {
-            *(v8s *)(dst + dw_cell<16>(c) + 16 * q) = reg[k];
-        } else {
-            *(v4s *)(dst + dw_cell<4>(c)) = (v4s){reg[k][0], reg[k][1], reg[k][2], reg[k][3]};
-        }
+                for (int j = 0; j < 4; ++j) {
+                    bsum += bf16_to_f32((bf16_t)a[j]);
+                    bsum += bf16_to_f32((bf16_t)(a[j] >> 16));
+                }
+            }
+            const v8bf av = __builtin_bit_cast(v8bf, a);
+#pragma unroll
+            for (int dyi = 0; dyi < 3; ++dyi) {
+                const v4u &q = w[dyi];
+                const v4u mid = {__builtin_amdgcn_alignbit(q[1], q[0], 16), __builtin_amdgcn_alignbit(q[2], q[1], 16),
+                                 __builtin_amdgcn_alignbit(q[3], q[2], 16), __builtin_amdgcn_alignbit(last[dyi], q[3], 16)};
+                const v4u bq[3] = {q, mid, {q[1], q[2], q[3], last[dyi]}};
+#pragma unroll
+                for (int dxi = 0; dxi < 3; ++dxi)
+                    acc[3 * dyi + dxi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(v8bf, bq[dxi]),
+                                                                                acc[3 * dyi + dxi], 0, 0, 0);
+            }
+        };
+        int z = z0;
+        for (; z + DW_PF <= z1; z += DW_PF)
+#pragma unroll
+            for (int u = 0; u < DW_PF; ++u) step(pre[u], z + u);
+#pragma unroll
+        for (int u = 0; u < DW_PF - 1; ++u)
+            if (z + u < z1) step(pre[u], z + u);
     }
 }
 
@@ -295,83 +374,20 @@ __global__ void __launch_bounds__(192) k_lp_conv_dw(int nb, int N, const bf16_t 
                                                     const bf16_t *__restrict__ dout, float *__restrict__ pw,
                                                     float *__restrict__ pb)
 {
-    constexpr int RB = dw_row_bytes<CIN>(DW_XC), DB = dw_row_bytes<COUT>(DW_SEG);
-    __shared__ __attribute__((aligned(16))) unsigned char ring[3][3][RB]; // [plane slot][dy][row]
-    __shared__ __attribute__((aligned(16))) unsigned char drow[DB];
-    const int lane = threadIdx.x & 63, kb = lane >> 4, c16 = lane & 15;
-    const int dzi = threadIdx.x >> 6;
-    const int segs = (N + DW_SEG - 1) / DW_SEG, runs = (N + DW_ZR - 1) / DW_ZR;
-    const long long items = (long long)nb * runs * N * segs;
-    const long long N3 = (long long)N * N * N;
+    __shared__ __attribute__((aligned(16))) DwShared<CIN, COUT> sh;
+    const int dzi = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    // each XCD takes a contiguous range of the slots (neighbouring rows share its L2)
+    const unsigned slot = gridDim.x % 8 == 0 ? blockIdx.x % 8 * (gridDim.x / 8) + blockIdx.x / 8 : blockIdx.x;
     v4f acc[9];
 #pragma unroll
     for (int t = 0; t < 9; ++t) acc[t] = (v4f){0.f, 0.f, 0.f, 0.f};
     float bsum = 0.f;
-    for (long long it = blockIdx.x; it < items; it += gridDim.x) { // workgroup-uniform
-        const int seg = (int)(it % segs);
-        long long r = it / segs;
-        const int y = (int)(r % N);
-        r /= N;
-        const int zr = (int)(r % runs);
-        const long long b = r / runs;
-        const int x0 = seg * DW_SEG;
-        const bf16_t *__restrict__ Db = dout + b * N3 * COUT;
-        const bf16_t *__restrict__ Ib = in + b * N3 * CIN;
-        const int z0 = zr * DW_ZR, z1 = min(z0 + DW_ZR, N);
-        __syncthreads(); // the previous item's readers are done
-        for (int p = z0 - 1; p <= z0; ++p)
-            for (int dy = 0; dy < 3; ++dy)
-                dw_stage_row<CIN>(ring[(p + 3) % 3][dy], Ib, N, p, y + dy - 1, x0 - 1, DW_XC, threadIdx.x, 192);
-        // registers for the next plane's input rows and dout row (loaded one plane ahead)
-        constexpr int KI = (DW_XC * (CIN == 16 ? 2 : 1) + 191) / 192, KD = (DW_SEG * (COUT == 16 ? 2 : 1) + 191) / 192;
-        v8s ri[3][KI], rd[KD];
-#pragma unroll
-        for (int dy = 0; dy < 3; ++dy) dw_load_row<CIN, KI>(ri[dy], Ib, N, z0 + 1, y + dy - 1, x0 - 1, DW_XC, threadIdx.x, 192);
-        dw_load_row<COUT, KD>(rd, Db, N, z0, y, x0, DW_SEG, threadIdx.x, 192);
-        for (int z = z0; z < z1; ++z) {
-#pragma unroll
-            for (int dy = 0; dy < 3; ++dy) dw_store_row<CIN, KI>(ring[(z + 4) % 3][dy], ri[dy], DW_XC, threadIdx.x, 192);
-            dw_store_row<COUT, KD>(drow, rd, DW_SEG, threadIdx.x, 192);
-            if (z + 1 < z1) {
-#pragma unroll
-                for (int dy = 0; dy < 3; ++dy)
-                    dw_load_row<CIN, KI>(ri[dy], Ib, N, z + 2, y + dy - 1, x0 - 1, DW_XC, threadIdx.x, 192);
-                dw_load_row<COUT, KD>(rd, Db, N, z + 1, y, x0, DW_SEG, threadIdx.x, 192);
-            }
-            __syncthreads();
-            // A: dout at cells 8 kb + j of channel c16
-            v8s a = {0, 0, 0, 0, 0, 0, 0, 0};
-            if (c16 < COUT) {
-#pragma unroll
-                for (int j = 0; j < 8; ++j) a[j] = *(const short *)(drow + dw_cell<COUT>(8 * kb + j) + 2 * c16);
-            }
-            if (dzi == 1) {
-#pragma unroll
-                for (int j = 0; j < 8; ++j) bsum += bf16_to_f32((bf16_t)a[j]);
-            }
-            const v8bf av = __builtin_bit_cast(v8bf, a);
-            const unsigned char(*pl)[RB] = ring[(z + dzi + 2) % 3]; // plane z + dz
-#pragma unroll
-            for (int dyi = 0; dyi < 3; ++dyi) {
-                // staged cells 8 kb .. 8 kb + 9 = x - 1 .. x + 8 of channel c16
-                short v[10];
-#pragma unroll
-                for (int m = 0; m < 10; ++m)
-                    v[m] = c16 < CIN ? *(const short *)(pl[dyi] + dw_cell<CIN>(8 * kb + m) + 2 * c16) : (short)0;
-#pragma unroll
-                for (int dxi = 0; dxi < 3; ++dxi) {
-                    v8s bq;
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) bq[j] = v[j + dxi];
-                    acc[3 * dyi + dxi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(v8bf, bq),
-                                                                                acc[3 * dyi + dxi], 0, 0, 0);
-                }
-            }
-            __syncthreads(); // readers done before the next plane is staged
-        }
-    }
+    if (dzi == 0) dw_items<CIN, COUT, 0>(nb, N, slot, gridDim.x, in, dout, acc, bsum, sh);
+    else if (dzi == 1) dw_items<CIN, COUT, 1>(nb, N, slot, gridDim.x, in, dout, acc, bsum, sh);
+    else dw_items<CIN, COUT, 2>(nb, N, slot, gridDim.x, in, dout, acc, bsum, sh);
+    const int lane = threadIdx.x & 63, kb = lane >> 4, c16 = lane & 15;
     // lane l holds dW[9 dzi + t][co = 4(l/16) + j][ci = l%16]
-    float *__restrict__ dst = pw + ((long long)blockIdx.x * LP_TAPS + 9 * dzi) * 256;
+    float *__restrict__ dst = pw + ((long long)slot * LP_TAPS + 9 * dzi) * 256;
 #pragma unroll
     for (int t = 0; t < 9; ++t)
 #pragma unroll
@@ -380,7 +396,7 @@ __global__ void __launch_bounds__(192) k_lp_conv_dw(int nb, int N, const bf16_t 
         // lane (co, kb) holds the bias partial of cells 8 kb .. 8 kb + 7: sum over kb in order
         const float p1 = __shfl(bsum, c16 + 16, 64), p2 = __shfl(bsum, c16 + 32, 64), p3 = __shfl(bsum, c16 + 48, 64);
         const float tot = ((bsum + p1) + p2) + p3;
-        if (kb == 0) pb[blockIdx.x * 16 + c16] = tot;
+        if (kb == 0) pb[slot * 16 + c16] = tot;
     }
 }
 
