@@ -30,7 +30,7 @@ struct rpcg_lpnet {
     static constexpr int DW_GRID = 1024; // slots of the weight-gradient sums (fixed: fixed order)
     Buffer params, grad, am, av, w1, w2, w3, w2t, w3t;
     Buffer feat, s, h1, h2, o, dob, d2, d1, pw, pb;
-    Buffer g_rp, g_col, gt_rp, gt_col, g_val, gt_val, scal;
+    Buffer g_rp, gt_rp, scal;
     // loss over (instance, probe) pairs: v, y, r, q per pair, the exact-dot
     // slots and results, and the matrix / probe pointer table
     Buffer lvec, lws, dots, tab;
@@ -80,18 +80,31 @@ int lp_prep(rpcg_lpnet *L, hipStream_t s)
     return RPCG_OK;
 }
 
-// Forward pass of nb systems: features, three convolutions; the outputs go to
+// The loss's operands on the device: the probes' pointers, the matrices
+// (for the products of a number of probes that the feature kernel does not
+// form), the vectors v, y, r, q per pair.
+struct LpLoss {
+    int nu = 0;
+    const double *const *ut = nullptr;
+    const LpMat *mA = nullptr;
+    double *v = nullptr, *y = nullptr, *r = nullptr, *q = nullptr;
+};
+
+// Forward pass of nb systems: features (with the products v = A u of a loss
+// that follows, where they go in one pass), three convolutions; the outputs go to
 // out (device, [nb][N^3][4]) if given, else to the network's own buffer.
 // Waits for completion (the diagonal check).
-int lp_forward(rpcg_lpnet *L, int nb, const rpcg_csr *A, float *out, hipStream_t s)
+int lp_forward(rpcg_lpnet *L, int nb, const rpcg_csr *A, float *out, const LpLoss *ls, hipStream_t s)
 {
     const int gen = L->gen = (L->gen % 0x3FFFFFFF) + 1;
+    const bool products = ls && lp_fused_nu(ls->nu);
     for (int k0 = 0; k0 < nb; k0 += LP_MAT_ARGS) {
         LpMatSet set{};
         const int m = std::min(LP_MAT_ARGS, nb - k0);
         for (int j = 0; j < m; ++j) set.m[j] = LpMat{A[k0 + j].row_ptr, A[k0 + j].col_idx, A[k0 + j].val};
         RPCG_TRY(launch_lp_features(L->N, m, set, (bf16_t *)L->feat.p + k0 * L->n * 4, (float *)L->s.p + k0 * L->n,
-                                    L->bad, gen, s));
+                                    L->bad, gen, products ? ls->nu : 0, products ? ls->ut + (long long)k0 * ls->nu : nullptr,
+                                    products ? ls->v + k0 * L->n * ls->nu : nullptr, s));
     }
     const float *p = (const float *)L->params.p;
     RPCG_TRY(launch_lp_conv(4, 16, EPI_RELU, nb, L->N, (const bf16_t *)L->feat.p, (const bf16_t *)L->w1.p,
@@ -136,54 +149,73 @@ int lp_ensure_dot_ws(rpcg_lpnet *L, int slots)
     return RPCG_OK;
 }
 
-// Loss and dL/do (bfloat16 into dob, binary64 into dout if given) over the
-// cached forward pass, for the nb x nu (instance, probe) pairs at once.
-int lp_loss_grad(rpcg_lpnet *L, int nb, const rpcg_csr *A, const double *const *u, int nu, double eps, double *loss,
-                 double *dout, hipStream_t s)
+// What the loss over nb x nu (instance, probe) pairs needs before the
+// forward pass: its vectors and the pointer table.
+int lp_loss_prepare(rpcg_lpnet *L, int nb, const rpcg_csr *A, const double *const *u, int nu, LpLoss *ls, hipStream_t s)
 {
     const long long n = L->n;
     const long long P = (long long)nb * nu;
-    if (P > 65535) return RPCG_ERR_INVALID; // pairs index the second grid dimension
     RPCG_TRY(L->lvec.ensure(sizeof(double) * 4 * n * P));
     RPCG_TRY(L->dots.ensure(sizeof(double) * 2 * P));
     int rc = lp_ensure_dot_ws(L, (int)(P * LP_DOT_CHUNKS));
     if (rc != RPCG_OK) return rc;
-    // pointer table: A, G, G^T of each instance, then the probe of each pair
-    const size_t mat_bytes = sizeof(LpMat) * 3 * nb, tab_bytes = mat_bytes + sizeof(double *) * P;
+    // pointer table: A of each instance, then the probe of each pair
+    const size_t mat_bytes = sizeof(LpMat) * nb, tab_bytes = mat_bytes + sizeof(double *) * P;
     RPCG_TRY(L->tab.ensure(tab_bytes));
     L->tab_host.resize(tab_bytes);
     LpMat *hm = (LpMat *)L->tab_host.data();
     const double **hu = (const double **)(L->tab_host.data() + mat_bytes);
-    double *G = (double *)L->g_val.p, *Gt = (double *)L->gt_val.p;
-    const int *grp = (const int *)L->g_rp.p, *gcol = (const int *)L->g_col.p;
-    const int *gtrp = (const int *)L->gt_rp.p, *gtcol = (const int *)L->gt_col.p;
-    for (int k = 0; k < nb; ++k) {
-        hm[k] = LpMat{A[k].row_ptr, A[k].col_idx, A[k].val};
-        hm[nb + k] = LpMat{grp, gcol, G + (long long)k * L->gnnz};
-        hm[2 * nb + k] = LpMat{gtrp, gtcol, Gt + (long long)k * L->gnnz};
-    }
+    for (int k = 0; k < nb; ++k) hm[k] = LpMat{A[k].row_ptr, A[k].col_idx, A[k].val};
     for (long long p = 0; p < P; ++p) hu[p] = u[p];
     RPCG_TRY(hipMemcpyAsync(L->tab.p, L->tab_host.data(), tab_bytes, hipMemcpyHostToDevice, s));
-    const LpMat *mA = (const LpMat *)L->tab.p, *mG = mA + nb, *mGt = mA + 2 * nb;
-    const double *const *ut = (const double *const *)((const char *)L->tab.p + mat_bytes);
+    ls->nu = nu;
+    ls->mA = (const LpMat *)L->tab.p;
+    ls->ut = (const double *const *)((const char *)L->tab.p + mat_bytes);
     // v, y, r, q: the nu vectors of an instance interleaved ([instance][cell][vector])
-    double *v = (double *)L->lvec.p, *y = v + P * n, *r = y + P * n, *q = r + P * n;
+    ls->v = (double *)L->lvec.p;
+    ls->y = ls->v + P * n;
+    ls->r = ls->y + P * n;
+    ls->q = ls->r + P * n;
+    return RPCG_OK;
+}
+
+// Loss and dL/do (bfloat16 into dob, binary64 into dout if given) over the
+// cached forward pass, for all pairs at once.
+int lp_loss_grad(rpcg_lpnet *L, int nb, const LpLoss &ls, double eps, double *loss, double *dout, hipStream_t s)
+{
+    const int nu = ls.nu, P = nb * nu;
     int *flags = (int *)((double *)L->scal.p + 4); // exact-dot flags of the loss (not reported)
-    const double scale = 1.0 / (double)P;
-    RPCG_TRY(launch_lp_factor(L->N, nb, (const float *)L->o.p, (const float *)L->s.p, grp, gtrp, G, Gt, L->gnnz, s));
-    RPCG_TRY(launch_lp_mv(n, nb, nu, mA, ut, nullptr, v, s));                                      // v = A u
-    RPCG_TRY(launch_lp_mv(n, nb, nu, mGt, nullptr, v, y, s));                                      // y = G^T v
-    RPCG_TRY(launch_lp_resid_dots(n, nb, nu, eps, mG, ut, y, v, r, L->wu, L->wr, L->lws_slots, flags, s)); // r
-    RPCG_TRY(launch_lp_dots_merge((int)P, L->wu, L->wr, L->lws_slots, (double *)L->dots.p, flags, s));
-    RPCG_TRY(launch_lp_mv(n, nb, nu, mGt, nullptr, r, q, s));                                      // q = G^T r
-    RPCG_TRY(launch_lp_dodg_all(L->N, nb, nu, scale, (const double *)L->dots.p, (const float *)L->o.p,
-                                (const float *)L->s.p, mG, r, y, v, q, dout, (bf16_t *)L->dob.p,
-                                (double *)L->scal.p + 2, s));
+    const float *o = (const float *)L->o.p, *sc = (const float *)L->s.p;
+    double *dots = (double *)L->dots.p;
+    int chunks = 0;
+    if (!lp_fused_nu(nu)) RPCG_TRY(launch_lp_mv(L->n, nb, nu, ls.mA, ls.ut, ls.v, s));              // v = A u
+    RPCG_TRY(launch_lp_gt(L->N, nb, nu, o, sc, ls.v, ls.y, s));                                     // y = G^T v
+    RPCG_TRY(launch_lp_resid_dots(L->N, nb, nu, eps, o, sc, ls.ut, ls.y, ls.v, ls.r, L->wu, L->wr, L->lws_slots, flags,
+                                  &chunks, s));                                                     // r
+    RPCG_TRY(launch_lp_dots_merge(P, chunks, L->wu, L->wr, L->lws_slots, dots, flags, s));
+    RPCG_TRY(launch_lp_gt(L->N, nb, nu, o, sc, ls.r, ls.q, s));                                     // q = G^T r
+    RPCG_TRY(launch_lp_dodg_all(L->N, nb, nu, 1.0 / (double)P, dots, o, sc, ls.r, ls.y, ls.v, ls.q, dout,
+                                (bf16_t *)L->dob.p, (double *)L->scal.p + 2, s));
     if (loss) {
         RPCG_TRY(hipMemcpyAsync(loss, (double *)L->scal.p + 2, sizeof(double), hipMemcpyDeviceToHost, s));
         RPCG_TRY(hipStreamSynchronize(s));
     }
     return RPCG_OK;
+}
+
+// Forward pass, then the loss and its gradient.
+int lp_forward_loss(rpcg_lpnet *L, int nb, const rpcg_csr *A, const double *const *u, int nu, double eps, double *loss,
+                    double *dout, hipStream_t s)
+{
+    if ((long long)nb * nu > 65535) { // pairs index the second grid dimension
+        const int rc = lp_forward(L, nb, A, nullptr, nullptr, s);
+        return rc != RPCG_OK ? rc : RPCG_ERR_INVALID;
+    }
+    LpLoss ls;
+    int rc = lp_loss_prepare(L, nb, A, u, nu, &ls, s);
+    if (rc == RPCG_OK) rc = lp_forward(L, nb, A, nullptr, &ls, s);
+    if (rc == RPCG_OK) rc = lp_loss_grad(L, nb, ls, eps, loss, dout, s);
+    return rc;
 }
 
 // Parameter gradient from the output gradient (bfloat16, in dob) over the cached forward pass.
@@ -232,17 +264,11 @@ int lp_create_body(rpcg_lpnet *L)
     RPCG_TRY(L->pb.ensure(sizeof(float) * rpcg_lpnet::DW_GRID * 16));
     RPCG_TRY(L->g_rp.ensure(sizeof(int) * (L->n + 1)));
     RPCG_TRY(L->gt_rp.ensure(sizeof(int) * (L->n + 1)));
-    RPCG_TRY(L->g_col.ensure(sizeof(int) * nz));
-    RPCG_TRY(L->gt_col.ensure(sizeof(int) * nz));
-    RPCG_TRY(L->g_val.ensure(sizeof(double) * nz * L->max_batch));
-    RPCG_TRY(L->gt_val.ensure(sizeof(double) * nz * L->max_batch));
     RPCG_TRY(L->scal.ensure(sizeof(double) * 8));
     std::vector<int32_t> grp(L->n + 1), gcol(nz), gtrp(L->n + 1), gtcol(nz);
     lp_pattern_host(L->N, grp.data(), gcol.data(), gtrp.data(), gtcol.data());
     RPCG_TRY(hipMemcpy(L->g_rp.p, grp.data(), sizeof(int) * (L->n + 1), hipMemcpyHostToDevice));
     RPCG_TRY(hipMemcpy(L->gt_rp.p, gtrp.data(), sizeof(int) * (L->n + 1), hipMemcpyHostToDevice));
-    RPCG_TRY(hipMemcpy(L->g_col.p, gcol.data(), sizeof(int) * nz, hipMemcpyHostToDevice));
-    RPCG_TRY(hipMemcpy(L->gt_col.p, gtcol.data(), sizeof(int) * nz, hipMemcpyHostToDevice));
     RPCG_TRY(hipHostMalloc((void **)&L->bad, sizeof(int), hipHostMallocDefault));
     *L->bad = 0;
     RPCG_TRY(hipMemset(L->params.p, 0, sizeof(float) * LP_NPARAMS));
@@ -274,7 +300,7 @@ void rpcg_lp_destroy(rpcg_lpnet *L)
     (void)hipDeviceSynchronize();
     for (Buffer *b : {&L->params, &L->grad, &L->am, &L->av, &L->w1, &L->w2, &L->w3, &L->w2t, &L->w3t, &L->feat, &L->s,
                       &L->h1, &L->h2, &L->o, &L->dob, &L->d2, &L->d1, &L->pw, &L->pb,
-                      &L->g_rp, &L->g_col, &L->gt_rp, &L->gt_col, &L->g_val, &L->gt_val, &L->scal, &L->lvec,
+                      &L->g_rp, &L->gt_rp, &L->scal, &L->lvec,
                       &L->lws, &L->dots, &L->tab})
         b->release();
     if (L->bad) (void)hipHostFree(L->bad);
@@ -329,7 +355,7 @@ int rpcg_lp_forward(rpcg_lpnet *L, int32_t nb, const rpcg_csr *A, float *o, void
     if (rc != RPCG_OK) return rc;
     RPCG_TRY(hipSetDevice(L->ctx->device));
     hipStream_t s = (hipStream_t)stream;
-    return lp_forward(L, nb, A, o, s);
+    return lp_forward(L, nb, A, o, nullptr, s);
 }
 
 int rpcg_lp_factor(rpcg_lpnet *L, int32_t nb, const rpcg_csr *A, rpcg_csr *G, rpcg_csr *Gt, void *stream)
@@ -342,7 +368,7 @@ int rpcg_lp_factor(rpcg_lpnet *L, int32_t nb, const rpcg_csr *A, rpcg_csr *G, rp
             return RPCG_ERR_INVALID;
     RPCG_TRY(hipSetDevice(L->ctx->device));
     hipStream_t s = (hipStream_t)stream;
-    rc = lp_forward(L, nb, A, nullptr, s);
+    rc = lp_forward(L, nb, A, nullptr, nullptr, s);
     if (rc != RPCG_OK) return rc;
     for (int k = 0; k < nb; ++k) {
         rc = lp_factor_one(L, k, (double *)G[k].val, (double *)Gt[k].val, s);
@@ -360,9 +386,7 @@ int rpcg_lp_loss_grad(rpcg_lpnet *L, int32_t nb, const rpcg_csr *A, const double
     if (rc != RPCG_OK) return rc;
     RPCG_TRY(hipSetDevice(L->ctx->device));
     hipStream_t s = (hipStream_t)stream;
-    rc = lp_forward(L, nb, A, nullptr, s);
-    if (rc != RPCG_OK) return rc;
-    rc = lp_loss_grad(L, nb, A, u, nu, eps, loss, dout, s);
+    rc = lp_forward_loss(L, nb, A, u, nu, eps, loss, dout, s);
     if (rc != RPCG_OK) return rc;
     RPCG_TRY(hipStreamSynchronize(s));
     return RPCG_OK;
@@ -375,7 +399,7 @@ int rpcg_lp_backward(rpcg_lpnet *L, int32_t nb, const rpcg_csr *A, const double 
     if (rc != RPCG_OK) return rc;
     RPCG_TRY(hipSetDevice(L->ctx->device));
     hipStream_t s = (hipStream_t)stream;
-    rc = lp_forward(L, nb, A, nullptr, s);
+    rc = lp_forward(L, nb, A, nullptr, nullptr, s);
     if (rc != RPCG_OK) return rc;
     RPCG_TRY(launch_lp_to_bf16(4 * L->n * nb, dout, (bf16_t *)L->dob.p, s));
     rc = lp_backward(L, nb, s);
@@ -393,9 +417,7 @@ int rpcg_lp_train_step(rpcg_lpnet *L, int32_t nb, const rpcg_csr *A, const doubl
     if (rc != RPCG_OK) return rc;
     RPCG_TRY(hipSetDevice(L->ctx->device));
     hipStream_t s = (hipStream_t)stream;
-    rc = lp_forward(L, nb, A, nullptr, s);
-    if (rc != RPCG_OK) return rc;
-    rc = lp_loss_grad(L, nb, A, u, nu, eps, nullptr, nullptr, s);
+    rc = lp_forward_loss(L, nb, A, u, nu, eps, nullptr, nullptr, s);
     if (rc != RPCG_OK) return rc;
     rc = lp_backward(L, nb, s);
     if (rc != RPCG_OK) return rc;
