@@ -14,8 +14,8 @@
 // loads; their lane masks go to the execution mask, so a masked product costs
 // one fma instead of an fma and two selects.
 // Measured (SpMV + dot of the solver): 160^3 27-point 235 us in the general layout
-// (1.29 GB), 70 us with one row per lane, 36 us now; binary32 200^3 249 us and 51 us;
-// 64 variable-coefficient 7-point systems together 313 us and 174 us (stored values).
+// (1.29 GB), 70 us with one row per lane, 30.5 us now; binary32 200^3 249 us and 40.4 us;
+// 64 variable-coefficient 7-point systems together 313 us and 168 us (stored values).
 #pragma once
 
 #include "kernels.hpp"
@@ -35,27 +35,54 @@ template <> struct Pair<float> { typedef float t __attribute__((ext_vector_type(
 template <typename T>
 using pair_t = typename Pair<T>::t;
 
-// sum = fma(a, g, sum) in the lanes of mask m; every lane of the wavefront is
-// active here (the loops over slices are uniform). The execution mask is set
-// and restored within the block, which is volatile so that it is not moved
-// under a condition.
-__device__ __forceinline__ void masked_fma(double &sum, double a, double g, unsigned long long m)
+// sum[r] = fma(a[u][r], g[u][r], sum[r]) in the lanes of mask m[u][r], for records
+// u = 0, .. in order and the lane's two rows r; every lane of the wavefront is
+// active here (the loops over slices are uniform). The execution mask is set for
+// each product and restored once per block: scalar instructions are the
+// largest part of a constant slice's, and a restore after every product took
+// one in four of them (SpMV + dot, 27 points: binary32 200^3 45.8 -> 40.4 us, binary64 160^3
+// 31.6 -> 30.5 us). The block is volatile so that it is not moved under a
+// condition. S: the factors, one for both rows, are in scalar registers.
+#define RPCG_MFMA(BITS, M, R, A, G) "s_mov_b64 exec, %" #M "\n\tv_fmac_f" #BITS " %" #R ", %" #A ", %" #G "\n\t"
+#define RPCG_MFMA_END "s_mov_b64 exec, -1"
+template <bool S, int K, typename T>
+__device__ __forceinline__ void masked_fma(T (&sum)[2], const T (*a)[2], const T (*g)[2], const unsigned long long (*m)[2])
 {
-    asm volatile("s_mov_b64 exec, %3\n\tv_fmac_f64 %0, %1, %2\n\ts_mov_b64 exec, -1" : "+v"(sum) : "v"(a), "v"(g), "s"(m));
+    static_assert(K == 1 || K == 3, "records per block");
+#define RPCG_SUMS "+&v"(sum[0]), "+&v"(sum[1])
+#define RPCG_REC(u) "v"(g[u][0]), "v"(g[u][1]), "s"(m[u][0]), "s"(m[u][1])
+    if constexpr (S && K == 1) {
+#define RPCG_BODY(B) RPCG_MFMA(B, 4, 0, 6, 2) RPCG_MFMA(B, 5, 1, 6, 3) RPCG_MFMA_END
+        if constexpr (sizeof(T) == 8) asm volatile(RPCG_BODY(64) : RPCG_SUMS : RPCG_REC(0), "s"(a[0][0]));
+        else asm volatile(RPCG_BODY(32) : RPCG_SUMS : RPCG_REC(0), "s"(a[0][0]));
+#undef RPCG_BODY
+    } else if constexpr (S) {
+#define RPCG_BODY(B) RPCG_MFMA(B, 4, 0, 14, 2) RPCG_MFMA(B, 5, 1, 14, 3) RPCG_MFMA(B, 8, 0, 15, 6) RPCG_MFMA(B, 9, 1, 15, 7) \
+    RPCG_MFMA(B, 12, 0, 16, 10) RPCG_MFMA(B, 13, 1, 16, 11) RPCG_MFMA_END
+        if constexpr (sizeof(T) == 8)
+            asm volatile(RPCG_BODY(64) : RPCG_SUMS : RPCG_REC(0), RPCG_REC(1), RPCG_REC(2), "s"(a[0][0]), "s"(a[1][0]), "s"(a[2][0]));
+        else
+            asm volatile(RPCG_BODY(32) : RPCG_SUMS : RPCG_REC(0), RPCG_REC(1), RPCG_REC(2), "s"(a[0][0]), "s"(a[1][0]), "s"(a[2][0]));
+#undef RPCG_BODY
+    } else if constexpr (K == 1) {
+#define RPCG_BODY(B) RPCG_MFMA(B, 4, 0, 6, 2) RPCG_MFMA(B, 5, 1, 7, 3) RPCG_MFMA_END
+        if constexpr (sizeof(T) == 8) asm volatile(RPCG_BODY(64) : RPCG_SUMS : RPCG_REC(0), "v"(a[0][0]), "v"(a[0][1]));
+        else asm volatile(RPCG_BODY(32) : RPCG_SUMS : RPCG_REC(0), "v"(a[0][0]), "v"(a[0][1]));
+#undef RPCG_BODY
+    } else {
+#define RPCG_BODY(B) RPCG_MFMA(B, 4, 0, 14, 2) RPCG_MFMA(B, 5, 1, 15, 3) RPCG_MFMA(B, 8, 0, 16, 6) RPCG_MFMA(B, 9, 1, 17, 7) \
+    RPCG_MFMA(B, 12, 0, 18, 10) RPCG_MFMA(B, 13, 1, 19, 11) RPCG_MFMA_END
+#define RPCG_FACTORS "v"(a[0][0]), "v"(a[0][1]), "v"(a[1][0]), "v"(a[1][1]), "v"(a[2][0]), "v"(a[2][1])
+        if constexpr (sizeof(T) == 8) asm volatile(RPCG_BODY(64) : RPCG_SUMS : RPCG_REC(0), RPCG_REC(1), RPCG_REC(2), RPCG_FACTORS);
+        else asm volatile(RPCG_BODY(32) : RPCG_SUMS : RPCG_REC(0), RPCG_REC(1), RPCG_REC(2), RPCG_FACTORS);
+#undef RPCG_FACTORS
+#undef RPCG_BODY
+    }
+#undef RPCG_SUMS
+#undef RPCG_REC
 }
-__device__ __forceinline__ void masked_fma(float &sum, float a, float g, unsigned long long m)
-{
-    asm volatile("s_mov_b64 exec, %3\n\tv_fmac_f32 %0, %1, %2\n\ts_mov_b64 exec, -1" : "+v"(sum) : "v"(a), "v"(g), "s"(m));
-}
-// The same with the factor a in scalar registers.
-__device__ __forceinline__ void masked_fma_s(double &sum, double a, double g, unsigned long long m)
-{
-    asm volatile("s_mov_b64 exec, %3\n\tv_fmac_f64 %0, %1, %2\n\ts_mov_b64 exec, -1" : "+v"(sum) : "s"(a), "v"(g), "s"(m));
-}
-__device__ __forceinline__ void masked_fma_s(float &sum, float a, float g, unsigned long long m)
-{
-    asm volatile("s_mov_b64 exec, %3\n\tv_fmac_f32 %0, %1, %2\n\ts_mov_b64 exec, -1" : "+v"(sum) : "s"(a), "v"(g), "s"(m));
-}
+#undef RPCG_MFMA
+#undef RPCG_MFMA_END
 
 template <typename T>
 __device__ __forceinline__ T rec_value(cptr<DiagEnt> e)
@@ -114,28 +141,28 @@ __device__ __forceinline__ void diag_batch(cptr<DiagEnt> e, int k0, int width, c
 #pragma unroll
     for (int u0 = 0; u0 < R; u0 += H) {
         unsigned long long m[H][2];
-        T c[H];
+        T c[H][2];
         int o[H];
 #pragma unroll
         for (int u = 0; u < H; ++u) {
             m[u][0] = e[k0 + u0 + u].mask[0];
             m[u][1] = e[k0 + u0 + u].mask[1];
-            if constexpr (CONSTV) c[u] = rec_value<T>(e + k0 + u0 + u);
+            if constexpr (CONSTV) c[u][0] = c[u][1] = rec_value<T>(e + k0 + u0 + u);
             if constexpr (DIAG) o[u] = e[k0 + u0 + u].off;
         }
+        constexpr int K = H % 3 == 0 ? 3 : 1;
 #pragma unroll
-        for (int u = 0; u < H; ++u)
+        for (int u = 0; u < H; u += K) masked_fma<CONSTV, K>(sum, CONSTV ? c + u : a + u0 + u, g + u0 + u, m + u);
+        if constexpr (DIAG) {
 #pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                if constexpr (CONSTV) masked_fma_s(sum[r], c[u], g[u0 + u][r], m[u][r]);
-                else masked_fma(sum[r], a[u0 + u][r], g[u0 + u][r], m[u][r]);
-                if constexpr (DIAG) {
+            for (int u = 0; u < H; ++u)
+#pragma unroll
+                for (int r = 0; r < 2; ++r)
                     if (o[u] == 0 && ((m[u][r] >> lane) & 1ull)) {
-                        aii[r] = CONSTV ? c[u] : a[u0 + u][r];
+                        aii[r] = CONSTV ? c[u][r] : a[u0 + u][r];
                         found[r] = true;
                     }
-                }
-            }
+        }
     }
 }
 
