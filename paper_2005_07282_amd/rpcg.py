@@ -201,8 +201,16 @@ def context(device: int | None = None):
     return _ctx[device]
 
 
-def _stream(dev: torch.device):
-    return ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
+# The current stream's handle without a Stream object around it (a small call's
+# time is host time: 8 k row product 6.2 -> 4.0 us, 10 k element dot 21 -> 19.5 us with this
+# and the default options copied instead of asked for).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream(dev: torch.device) -> int:
+    if _raw_stream is not None and dev.index is not None:
+        return _raw_stream(dev.index)
+    return torch.cuda.current_stream(dev).cuda_stream
 
 
 def _check(t: torch.Tensor, dtype, name: str):
@@ -214,9 +222,16 @@ def _check(t: torch.Tensor, dtype, name: str):
         raise ValueError(f"{name} must be contiguous")
 
 
+_opts_default = None  # the library's defaults, as bytes
+
+
 def _opts(**kw) -> _Opts:
-    o = _Opts()
-    lib().rpcg_opts_default(ctypes.byref(o))
+    global _opts_default
+    if _opts_default is None:
+        o = _Opts()
+        lib().rpcg_opts_default(ctypes.byref(o))
+        _opts_default = bytes(o)
+    o = _Opts.from_buffer_copy(_opts_default)
     for k, v in kw.items():
         if v is None:
             continue
