@@ -260,9 +260,9 @@ __global__ void k_acc_round(const long long *digits, double *out)
 // SpMV on CSR (Section 4.3): y_i = fold over the stored entries of row i, in
 // storage order, of acc = fma(a_ik, x[col_k], acc), acc from +0.
 //
-// A workgroup owns SPMV_R consecutive rows (one per thread); their entries
+// A workgroup owns R consecutive rows (one per thread); their entries
 // form one contiguous range of the CSR arrays. The range is staged through
-// LDS in chunks of SPMV_E entries: consecutive threads load consecutive
+// LDS in chunks of E entries: consecutive threads load consecutive
 // values and columns (coalesced, streamed once) and gather the x entries;
 // then every thread continues its own row's fma chain over the part of the
 // row inside the chunk, reading LDS. The accumulator stays in the row's
@@ -272,14 +272,8 @@ __global__ void k_acc_round(const long long *digits, double *out)
 // chains and its x entries gathered right after them, so rows longer than a
 // chunk's share no longer leave the memory idle while their chains run.
 
-#ifndef RPCG_SPMV_R
-#define RPCG_SPMV_R 512
-#endif
-#ifndef RPCG_SPMV_E
-#define RPCG_SPMV_E 2048
-#endif
-constexpr int SPMV_R = RPCG_SPMV_R; // rows per workgroup (= threads)
-constexpr int SPMV_E = RPCG_SPMV_E; // chunk of entries staged at a time
+constexpr int SPMV_E = 2048;  // chunk of entries staged at a time
+constexpr int SPMV_CUS = 256; // CUs of the device
 
 template <int R, int E>
 __global__ void __launch_bounds__(R)
@@ -375,15 +369,28 @@ hipError_t launch_spmv_csr(int n, long long nnz, const int *row_ptr, const int *
                            const double *x, double *y, hipStream_t s)
 {
     if (n == 0) return hipSuccess;
-    const long long blocks = ((long long)n + SPMV_R - 1) / SPMV_R;
-    const unsigned g = (unsigned)std::min<long long>(blocks, 65536);
-    // short rows (under 32 entries on average) fill a chunk with many rows:
-    // half-size chunks keep more workgroups per CU (measured 160^3: 0.58
-    // against 0.56 of 8 TB/s); long rows need the full chunk
-    if (nnz < 32ll * n)
-        hipLaunchKernelGGL((k_spmv_csr<SPMV_R, SPMV_E / 2>), dim3(g), dim3(SPMV_R), 0, s, n, row_ptr, col, val, x, y);
-    else
-        hipLaunchKernelGGL((k_spmv_csr<SPMV_R, SPMV_E>), dim3(g), dim3(SPMV_R), 0, s, n, row_ptr, col, val, x, y);
+    auto run = [&](auto rows) {
+        constexpr int R = decltype(rows)::value;
+        const unsigned g = (unsigned)std::min<long long>(((long long)n + R - 1) / R, 65536);
+        // short rows (under 32 entries on average) fill a chunk with many rows:
+        // half-size chunks keep more workgroups per CU (measured 160^3: 0.58
+        // against 0.56 of 8 TB/s); long rows need the full chunk
+        if (nnz < 32ll * n)
+            hipLaunchKernelGGL((k_spmv_csr<R, SPMV_E / 2>), dim3(g), dim3(R), 0, s, n, row_ptr, col, val, x, y);
+        else
+            hipLaunchKernelGGL((k_spmv_csr<R, SPMV_E>), dim3(g), dim3(R), 0, s, n, row_ptr, col, val, x, y);
+    };
+    // Rows per workgroup: the most that leave enough workgroups for every CU. A
+    // workgroup's entries come chunk after chunk, each behind the last one's
+    // latency, so a matrix that is cut into few workgroups waits on them with the
+    // memory idle (us with 512 rows everywhere, and now: 201-wide band of 20 k rows 203
+    // and 41, of 100 k 188 and 72, of 200 k 204 and 131; 27 points on 22 k rows 15.0 and 6.4,
+    // on 64 k 16.4 and 7.7, on 216 k 20.1 and 16.7). Large matrices keep 512: 4.1 M
+    // rows of 27 points 272 us against 282 us with 256, the band of 1 M rows 504 and 524 us.
+    if (n >= 512 * 3 * SPMV_CUS) run(std::integral_constant<int, 512>{});
+    else if (n >= 256 * 2 * SPMV_CUS) run(std::integral_constant<int, 256>{});
+    else if (n >= 128 * 2 * SPMV_CUS) run(std::integral_constant<int, 128>{});
+    else run(std::integral_constant<int, 64>{});
     return hipGetLastError();
 }
 
