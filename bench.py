@@ -28,13 +28,22 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-def k1_bytes(n, nnz):
-    """Algorithmic bytes of one SpMV+dot launch: val and col (12 per entry),
+def csr_bytes(n, nnz):
+    """Bytes of one SpMV+dot on the caller's CSR: val and col (12 per entry),
     row pointers 4(n+1), the direction vector read once (8n), w written (8n)."""
     return 12 * nnz + 4 * (n + 1) + 16 * n
 
 
-K1_SOURCES = ("pcg_spmv_dot.hip", "sell_spmv.hpp", "reduce.hpp", "numerics.hpp", "kernels.hpp")
+def k1_bytes(n):
+    """Bytes one SpMV+dot launch of the solver cannot do without: the direction
+    vector read and w written. The solver's copy of a constant-coefficient
+    stencil holds offsets, values and row masks per slice pattern and nothing per
+    row or entry (a few MB for any grid, mostly in cache), so the
+    matrix's own bytes are not part of it."""
+    return 16 * n
+
+
+K1_SOURCES = ("pcg_spmv_dot.hip", "diag_row.hpp", "sell_spmv.hpp", "reduce.hpp", "numerics.hpp", "kernels.hpp")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "pcg_160cube_hbm_traffic.md")
 # the timed loop brackets the SpMV+dot launch of every 4th iteration with HIP
 # events (the kernel's mean duration over those launches; fewer events in the loop)
@@ -67,10 +76,9 @@ def k1_traffic():
 
 def time_spmv(rpcg, torch, Ad, n, nnz, reps=20, prepared=False):
     """The exported SpMV on the caller's CSR (rpcg_spmv), or with
-    prepared=True on a prepared sliced-ELL copy (rpcg_smat_spmv; the copy's
+    prepared=True on a prepared copy (rpcg_smat_spmv; the copy's
     creation timed once, apart): median of reps event-timed calls against
-    the CSR algorithmic bytes 12 nnz + 4 (n+1) + 8 n (x read once) + 8 n (y
-    written)."""
+    the bytes of the CSR, x read once and y written (prepared: of x and y)."""
     import numpy as np
     dev = Ad.row_ptr.device
     x = torch.ones(n, dtype=torch.float64, device=dev)
@@ -99,18 +107,18 @@ def time_spmv(rpcg, torch, Ad, n, nnz, reps=20, prepared=False):
     if M is not None:
         M.close()
     tm = float(np.median(times))
-    byt = 12 * nnz + 4 * (n + 1) + 16 * n
+    byt = k1_bytes(n) if prepared else csr_bytes(n, nnz)
     gbs = byt / (tm * 1e-3) / 1e9
     del x, y
     return {"kernel": name, "ms": round(tm, 5), "bytes": byt, "GB_s": round(gbs, 1),
             "hbm_frac": round(gbs / HBM_PEAK_GBS, 4), **extra}
 
 
-def iteration_bytes(n, nnz):
-    """Algorithmic bytes of one fused PCG iteration (three kernels): K1, then
+def iteration_bytes(n):
+    """Bytes of one fused PCG iteration (three kernels): K1, then
     K2 reading w, r, dinv and writing r, z (40 n), then K3 reading d, z, x
-    and writing d, x (40 n): 12 nnz + 4 (n+1) + 96 n."""
-    return k1_bytes(n, nnz) + 40 * n + 40 * n
+    and writing d, x (40 n): 96 n."""
+    return k1_bytes(n) + 40 * n + 40 * n
 
 
 def measure_stream_read(torch, dev, nbytes=2 << 30, reps=10):
@@ -189,7 +197,7 @@ def run_mixed_precision(N, rpcg, torch, dev):
     xs_d = torch.from_numpy(xs).to(dev)
     inner_it = max(1, it["k_launches"])
     k1_32 = it["k_spmv_dot_ms"] / inner_it
-    k1_32_bytes = 8 * nnz + 4 * (n + 1) + 8 * n  # CSR with binary32 values: val + col, row pointers, d, w
+    k1_32_bytes = 8 * n  # d, w in binary32 (see k1_bytes)
     out["refinement"] = {
         "outer": info["outer"], "inner_iterations": info["inner_iterations"],
         "solve_ms": round(info["total_ms"], 2), "setup_ms": round(info["setup_ms"], 2),
@@ -254,8 +262,8 @@ def run_batched(seed, rpcg, torch, dev):
         same += int(i1["iterations"] == infos[k]["iterations"] and torch.equal(x1, xs[k]))
     B.close()
     row_it = sum(r * i["iterations"] for r, i in zip(rows, infos))
-    # algorithmic bytes of one iteration of a system (as for the single solve): 12 nnz + 4 (n+1) + 104 n
-    it_bytes = sum((12 * z + 4 * (r + 1) + 104 * r) * i["iterations"] for r, z, i in zip(rows, nnz, infos))
+    # bytes of one iteration of a system: the stored values and the vectors, 8 nnz + 96 n
+    it_bytes = sum((8 * z + 96 * r) * i["iterations"] for r, z, i in zip(rows, nnz, infos))
     out = {
         "workload": f"64 systems, 7-point diffusion with exp(N(0,1)) face coefficients on N^3 grids, N uniform "
                     f"in 16..96 (seed {seed}; n = {sum(rows)}, nnz = {sum(nnz)} in total), b ~ U[-1,1), "
@@ -324,7 +332,7 @@ def run_stress(n, w, n_ill, w_ill, rpcg, torch, dev):
         xs[mode], info, runs[mode] = solve(Ad, bd, mode, p)
         hs[mode] = info["hist"]
         log(f"[bench]   {mode}: {runs[mode]['iterations']} it, {runs[mode]['ms_per_iteration']} ms/it")
-    k1_bytes_band = 10 * nnz + 4 * (n + 1) + 16 * n  # 16-bit codes + values, row pointers, d, w (SELL-64)
+    k1_bytes_band = k1_bytes(n)
     spmv_band = time_spmv(rpcg, torch, Ad, n, nnz)
     log(f"[bench]   rpcg_spmv on the band: {spmv_band['ms']} ms, {spmv_band['GB_s']} GB/s")
     smat_band = time_spmv(rpcg, torch, Ad, n, nnz, prepared=True)
@@ -739,8 +747,8 @@ def main():
     k1_ms = ex["k_spmv_dot_ms"] / max(1, ex["k_launches"])
     k2_ms = inst["k_update_ms"] / max(1, inst["k_launches"])
     k3_ms = inst["k_direction_ms"] / max(1, inst["k_launches"])
-    k1_gbs = k1_bytes(n, nnz) / (k1_ms * 1e-3) / 1e9
-    it_gbs = iteration_bytes(n, nnz) / (ms_per_step * 1e-3) / 1e9
+    k1_gbs = k1_bytes(n) / (k1_ms * 1e-3) / 1e9
+    it_gbs = iteration_bytes(n) / (ms_per_step * 1e-3) / 1e9
     per_it = {m: res[m]["loop_ms"] / res[m]["iterations"] for m in res}
 
     # full solve to 1e-8 (the paper's stopping rule) for the iteration count
@@ -815,8 +823,9 @@ def main():
             "unit": "GB/s",
             "frac": round(k1_gbs / HBM_PEAK_GBS, 4),
             "traffic": traffic,
-            "kernel": "k_pcg_spmv_dot<exblas, 4, 16-bit column codes, binary64>",
-            "bytes_per_launch": k1_bytes(n, nnz),
+            "kernel": "k_pcg_spmv_dot<exblas, 4, diagonal-aligned slices, binary64>",
+            "bytes_per_launch": k1_bytes(n),
+            "csr_bytes_per_launch": csr_bytes(n, nnz),
             "stream_read": {"GB_s": round(stream_gbs, 1), "frac": round(k1_gbs / stream_gbs, 4),
                             "kernel": "torch.sum over a 2 GiB binary64 vector (fastest of 10)"},
         },
