@@ -70,6 +70,16 @@ static LaunchCfg make_vec_cfg(const rpcg_ctx *c, const rpcg_opts &o, long long n
     return cfg;
 }
 
+// General copies of few slices: a workgroup of so many wavefronts that every
+// CU has one, as a slice's gathers keep its CU's texture path busy (31.7 k
+// unstructured rows 27.2 us an iteration with four, 24.8 us with two; 12 k
+// rows 23.7 and, with one, 21.6 us; 60 k rows 30.5 us with four, 31.1 us with two).
+// Diagonal-aligned slices do not gain (32 k rows 17.05 us with one to four).
+static int general_waves(long long nslices, int num_cus)
+{
+    return (int)std::min(4ll, std::max(1ll, (nslices + num_cus - 1) / num_cus));
+}
+
 // SpMV kernel: one wavefront per slice at a time; own overrides. The binary32
 // kernel keeps fewer bytes in flight per wavefront and wants twice the
 // workgroups of the binary64 one. Over diagonal-aligned slices the loop waits
@@ -81,7 +91,9 @@ static LaunchCfg make_spmv_cfg(const rpcg_ctx *c, const rpcg_opts &o, long long 
     rpcg_opts q = o;
     q.block_size = o.spmv_block_size;
     q.grid_size = o.spmv_grid_size;
-    LaunchCfg cfg = make_cfg(c, q, std::max(1ll, nslices * 64), diag && nslices > 4ll * c->num_cus ? 512 : 256, s);
+    const int waves = general_waves(nslices, c->num_cus);
+    const int block = diag ? (nslices > 4ll * c->num_cus ? 512 : 256) : 64 * waves;
+    LaunchCfg cfg = make_cfg(c, q, std::max(1ll, nslices * 64), block, s);
     const long long cap = (!diag && f32 ? 4ll : 2ll) * c->num_cus;
     if (!q.grid_size) cfg.grid = (int)std::max(1ll, std::min((nslices * 64 + cfg.block - 1) / cfg.block, cap));
     return cfg;
@@ -900,11 +912,12 @@ int rpcg_smat_spmv(rpcg_smat *M, const double *x, double *y, void *stream)
     if (M->n == 0) return RPCG_OK;
     RPCG_TRY(hipSetDevice(M->device));
     const SellMat<double> A = sell_mat<double>(M->B, M->B.val64, M->n, (const int *)M->rp.p);
-    // one workgroup of four wavefronts per four slices; at most two per CU, four
-    // over diagonal-aligned slices (they wait on gathers, not on the matrix stream)
-    const long long want = ((long long)M->B.nslices + 3) / 4;
+    // a wavefront per slice, four a workgroup but for general copies of few slices; at most two
+    // workgroups per CU, four over diagonal-aligned slices (they wait on gathers, not on the matrix stream)
+    const int waves = M->B.ds ? 4 : general_waves(M->B.nslices, M->num_cus);
+    const long long want = ((long long)M->B.nslices + waves - 1) / waves;
     const int grid = (int)std::max(1ll, std::min(want, (M->B.ds ? 4ll : 2ll) * M->num_cus));
-    RPCG_TRY(launch_sell_spmv(A, x, y, grid, (hipStream_t)stream));
+    RPCG_TRY(launch_sell_spmv(A, x, y, grid, waves, (hipStream_t)stream));
     return RPCG_OK;
 }
 

@@ -239,8 +239,8 @@ hipError_t launch_diag_fill(int n, const int *row_ptr, const double *val64, cons
 hipError_t launch_sell_fill(int n, const int *row_ptr, const int *col, const double *val64_in,
                             const float *val32_in, int vec, const long long *off, double *sval64, float *sval32,
                             int *scol, unsigned short *scol16, int *cfirst, unsigned char *len8, hipStream_t s);
-// y = A x on a binary64 sliced-ELL copy (grid workgroups of 256 threads).
-hipError_t launch_sell_spmv(const SellMat<double> &A, const double *x, double *y, int grid, hipStream_t s);
+// y = A x on a binary64 copy (grid workgroups of `waves` wavefronts, at most four).
+hipError_t launch_sell_spmv(const SellMat<double> &A, const double *x, double *y, int grid, int waves, hipStream_t s);
 
 template <typename T>
 struct PcgVecs {

@@ -255,13 +255,13 @@ hipError_t launch_csr_scan(int n, int nnz, const int *row_ptr, const int *col, i
     return hipGetLastError();
 }
 
-hipError_t launch_sell_spmv(const SellMat<double> &A, const double *x, double *y, int grid, hipStream_t s)
+hipError_t launch_sell_spmv(const SellMat<double> &A, const double *x, double *y, int grid, int waves, hipStream_t s)
 {
     if (A.nslices == 0) return hipSuccess;
-    if (grid < 1) return hipErrorInvalidValue;
+    if (grid < 1 || waves < 1 || waves > 4) return hipErrorInvalidValue;
     const int parts = A.ds && grid >= 64 ? NUM_XCDS : 1;
     dispatch_layout(A.layout(), [&](auto lay) {
-        k_sell_spmv<decltype(lay)::value><<<grid, 256, 0, s>>>(A, x, y, parts);
+        k_sell_spmv<decltype(lay)::value><<<grid, 64 * waves, 0, s>>>(A, x, y, parts);
     });
     return hipGetLastError();
 }
