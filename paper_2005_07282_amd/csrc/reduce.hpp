@@ -402,10 +402,9 @@ __device__ __forceinline__ double dpp_f64(double v)
 }
 
 // Wavefront sums of four values at once, each row of 16 lanes left with one of
-// them in all its lanes: row r holds the sum of s[row_sum_of(r)]. The caller
-// makes sure every partial sum is exact. The halves, then the rows, of two values
-// are swapped and added (permlane swaps), so a step serves two values.
-__device__ __forceinline__ int row_sum_of(int row) { return ((row & 1) << 1) | (row >> 1); }
+// them in all its lanes: rows 0, 1, 2, 3 hold the sums of s[0], s[2], s[1], s[3].
+// The caller makes sure every partial sum is exact. The halves, then the rows, of two
+// values are swapped and added (permlane swaps), so a step serves two values.
 template <bool HALVES>
 __device__ __forceinline__ double swap_add(double x, double y)
 {
