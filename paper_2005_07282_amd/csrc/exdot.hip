@@ -36,9 +36,11 @@ __device__ __forceinline__ long long coherent_ll(const long long *p)
 // Every vector memory operation of this wavefront, atomics included, has completed.
 __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// Spread (in binades) of the products' exponents over a wavefront's first
-// loads above which a lane starts in the direct mode: the expansions hold about 53 P bits, so
-// most products would leave a remainder. It only moves work between two exact paths.
+// EXBLAS mode: spread (in binades) of the products' exponents over a wavefront's
+// first loads above which its lanes start in the direct mode, as the
+// expansions of the default length would soon overflow. There it moves work
+// between two exact paths that nobody can tell apart. In FPE mode what goes direct counts as
+// escaped, so a lane goes direct only once its own expansions have kept overflowing.
 constexpr int EX_WIDE = 128;
 
 __device__ __forceinline__ void exponent_span(double x, double y, int &lo, int &hi)
@@ -93,7 +95,7 @@ k_exdot(long long n, const double *__restrict__ x, const double *__restrict__ y,
 
     LaneDot<MODE, P, MODE != MODE_PLAIN> L;
     L.init();
-    if (MODE == MODE_EXBLAS || (MODE == MODE_FPE && capture)) {
+    if constexpr (MODE == MODE_EXBLAS) {
         int lo = 1 << 20, hi = -1;
         if (i < n2) {
             exponent_span(a[0].x, b[0].x, lo, hi);
