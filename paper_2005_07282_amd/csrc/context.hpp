@@ -120,16 +120,23 @@ inline int resolve_fpe_size(int p, int mode)
 // thread, at most eight workgroups per CU. The exact modes: one workgroup up to
 // EXDOT_ALONE elements (it needs no atomics and no tickets); then four elements
 // a thread up to one workgroup per CU, as each costs the accumulator's setup and
-// partial (2^20 pairs: 11.9 us on 256 workgroups, 13.9 us on 128, 14.3 us on 512); two per CU
-// where a thread has 32 elements or more (2^22 pairs in FPE mode: 22.6 us on
-// 256, 29.5 us on 512; 2^24 and up want 512, and no more: the next pairs are prefetched).
+// partial (2^20 pairs: 11.9 us on 256 workgroups, 13.9 us on 128, 14.3 us on 512). More per
+// CU from so many elements a thread on (us for narrow, +-30 and +-200 binades):
+// EXBLAS two from 32 (2^24 pairs 49, 76, 51 on 256, 53, 69, 52 on 512), three from 512 (2^27 pairs
+// 359, 504, 371 on 512, 364, 469, 368 on 768; 2^28 720, 1017, 728 and 712, 950, 724; the next pairs
+// are prefetched). FPE two from 512, as every workgroup pays the merges of its wavefronts'
+// expansions and every lane its first measurement window (2^22 pairs 19, 34, 46 on 256, 23,
+// 42, 57 on 512; 2^26 168, 235, 255 and 184, 227, 281; 2^27 332, 454, 514 and 352, 435, 453), four from
+// 1024 (2^28 pairs 705, 856, 902 on 512, 761, 845, 866 on 1024).
 constexpr int64_t EXDOT_ALONE = 8192;
 inline int exdot_grid(int mode, int64_t n, int block, int cus)
 {
     if (mode == rpcg::MODE_PLAIN)
         return (int)std::max<int64_t>(1, std::min<int64_t>((n + 8ll * block - 1) / (8ll * block), 8ll * cus));
     if (n <= EXDOT_ALONE) return 1;
-    const int64_t per_cu = n / ((int64_t)cus * block) >= 32 ? 2 : 1;
+    const int64_t each = n / ((int64_t)cus * block); // elements a thread, with one workgroup per CU
+    const int64_t per_cu = mode == rpcg::MODE_FPE ? (each >= 1024 ? 4 : (each >= 512 ? 2 : 1))
+                                                  : (each >= 512 ? 3 : (each >= 32 ? 2 : 1));
     return (int)std::max<int64_t>(1, std::min<int64_t>((n + 4ll * block - 1) / (4ll * block), per_cu * cus));
 }
 

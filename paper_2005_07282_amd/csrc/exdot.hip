@@ -26,7 +26,12 @@ namespace rpcg {
 constexpr int EX_COPIES = 4;
 constexpr int EX_PITCH = ACC_DIGITS; // 136 dwords: copies 8 banks apart
 constexpr int EX_ONE_LEVEL = 64;     // workgroups up to which the tickets take one level (one round trip less)
-constexpr int EX_UNROLL = 2;         // 16-byte pairs of each vector a thread loads together
+// 16-byte pairs of each vector a thread loads together. FPE: one, as its two
+// expansions and two pairs (with the next two in flight) took 76 registers and left one 1024-thread
+// workgroup a CU (four terms, 59 registers now; us for narrow, +-30 and +-200 binades: 2^24 pairs
+// 61, 95, 134 -> 48, 76, 125, 2^28 pairs 772, 928, 976 -> 705, 856, 902).
+template <int MODE>
+constexpr int ex_unroll() { return MODE == MODE_FPE ? 1 : 2; }
 
 __device__ __forceinline__ long long coherent_ll(const long long *p)
 {
@@ -71,10 +76,11 @@ k_exdot(long long n, const double *__restrict__ x, const double *__restrict__ y,
     long long *acc = sh.acc[0];
     const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     const long long stride = (long long)gridDim.x * blockDim.x;
+    constexpr int EX_UNROLL = ex_unroll<MODE>();
     typedef pair_t<double> pr; // 16-byte loads at any 8-byte alignment
     const long long n2 = n >> 1;
     pr a[EX_UNROLL], b[EX_UNROLL];
-    // the loads past the end repeat the thread's first pair or, where it has none, nothing
+    // past the end nothing is loaded and the pair keeps what it held (it is not used)
     auto load = [&](long long i) {
 #pragma unroll
         for (int u = 0; u < EX_UNROLL; ++u) {

@@ -55,3 +55,12 @@ def test_short_dots_count_the_same_with_the_fallback(R, n, span):
     dropped = _dot(R, x, y, False, fpe_size=4, fpe_fallback=0)[1]
     assert kept["fpe_escapes"] == dropped["fpe_escapes"] > 0
     assert kept["fallbacks"] == 1 and kept["status"] == 0 and dropped["status"] == 2  # expansions inexact
+
+
+@pytest.mark.parametrize("n", [1 << 23, (1 << 24) + 1, 1 << 26])
+def test_one_workgroup_per_cu(R, orc, n):
+    """Up to 2^27 pairs a second workgroup per CU costs more merges and windows than it hides latency."""
+    x = torch.ones(n, dtype=torch.float64, device="cuda")
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    out, info = R.exdot(x, x, mode="fpe")
+    assert out.item() == n and info["grid_size"] == cus and info["fpe_escapes"] == 0
