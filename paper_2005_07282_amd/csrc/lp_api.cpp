@@ -207,7 +207,10 @@ int lp_loss_grad(rpcg_lpnet *L, int nb, const LpLoss &ls, double eps, double *lo
 int lp_forward_loss(rpcg_lpnet *L, int nb, const rpcg_csr *A, const double *const *u, int nu, double eps, double *loss,
                     double *dout, hipStream_t s)
 {
-    if ((long long)nb * nu > 65535) { // pairs index the second grid dimension
+    // pairs index the second grid dimension; a missing probe is found before the feature kernel reads it
+    bool ok = (long long)nb * nu <= 65535;
+    for (long long p = 0; ok && p < (long long)nb * nu; ++p) ok = u[p] != nullptr;
+    if (!ok) {
         const int rc = lp_forward(L, nb, A, nullptr, nullptr, s);
         return rc != RPCG_OK ? rc : RPCG_ERR_INVALID;
     }

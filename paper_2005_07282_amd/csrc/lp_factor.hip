@@ -49,18 +49,20 @@ __device__ __forceinline__ void lp_feature_row(const LpGrid &grid, long long i, 
             if (c == nb[d]) a[d] = w;
     };
     for (int j0 = 0; j0 < len; j0 += LPF_BATCH) {
-        int c[LPF_BATCH];
+        int c[LPF_BATCH], at[LPF_BATCH];
         double w[LPF_BATCH], g[LPF_BATCH][NU ? NU : 1];
 #pragma unroll
         for (int j = 0; j < LPF_BATCH; ++j) {
             const int e = j0 + j < len ? j0 + j : 0;
             c[j] = col[e];
             w[j] = val[e];
+            // the diagonal check of the same pass has not refused the matrix yet: nothing is read past a probe
+            at[j] = (unsigned)c[j] < (unsigned)(N * N * N) ? c[j] : 0;
         }
 #pragma unroll
         for (int j = 0; j < LPF_BATCH; ++j)
 #pragma unroll
-            for (int m = 0; m < NU; ++m) g[j][m] = u[m][c[j]];
+            for (int m = 0; m < NU; ++m) g[j][m] = u[m][at[j]];
 #pragma unroll
         for (int j = 0; j < LPF_BATCH; ++j)
             if (j0 + j < len) {
