@@ -161,6 +161,8 @@ int rpcg_create(rpcg_ctx **out, int device)
     if (rc == RPCG_OK) rc = hip_status(c->dot_blocks.ensure(sizeof(long long) * DOT_BLOCKS * DOT_COPIES * DOT_PITCH));
     if (rc == RPCG_OK) rc = hip_status(hipMemset(c->dot_blocks.p, 0, c->dot_blocks.bytes));
     if (rc == RPCG_OK) rc = ensure_ws(c, 8 * c->num_cus);
+    // the memory is clear before a call on any stream uses it (the dot's blocks are not cleared again)
+    if (rc == RPCG_OK) rc = hip_status(hipDeviceSynchronize());
     if (rc != RPCG_OK) { rpcg_destroy(c); return rc; }
     *out = c;
     return RPCG_OK;
