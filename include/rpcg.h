@@ -156,9 +156,14 @@ void rpcg_destroy(rpcg_ctx *ctx);
  * (no expansion overflows); a product below 2^-969 gives
  * RPCG_WARN_FPE_INEXACT, an inf/NaN input or an overflow gives
  * RPCG_ERR_NONFINITE with out = NaN.
- * `res` (host, may be NULL): when given, the call waits for the stream and
- * fills status, fpe_escapes and fallbacks; when NULL the call is fully
- * asynchronous and returns RPCG_OK after enqueueing. `opts` may be NULL. */
+ * `res` (host, may be NULL): when given, the call waits until the dot is done
+ * (and with it everything enqueued on the stream before) and fills status,
+ * fpe_escapes and fallbacks: x and y have been read, out is in place for every
+ * stream and the host, the results of the earlier work too. It waits for the kernel's own record in host
+ * memory, polled by this thread for up to 1 ms and then through the stream, so
+ * hipStreamQuery may report the stream busy for some microseconds after it
+ * returns. When NULL the call is fully asynchronous and returns RPCG_OK after
+ * enqueueing. `opts` may be NULL. */
 int rpcg_exdot(rpcg_ctx *ctx, rpcg_mode mode, int64_t n, const double *x, const double *y,
                double *out, const rpcg_opts *opts, rpcg_result *res, void *stream);
 
@@ -175,8 +180,8 @@ int rpcg_exdot(rpcg_ctx *ctx, rpcg_mode mode, int64_t n, const double *x, const 
  * streams or host threads) race and give undefined results; calls ordered
  * on one stream are safe. The counters are cleared by a small kernel at the
  * start of each call (no memset node, so the call can be captured into a
- * graph when res is NULL). res: as rpcg_exdot (when given, the call waits
- * for the stream, which a capturing caller must avoid). */
+ * graph when res is NULL). res: filled as by rpcg_exdot (when given, the call
+ * waits for the stream, which a capturing caller must avoid). */
 #define RPCG_NOALLOC_MAX_GROUPS 2048
 int rpcg_exdot_noalloc(rpcg_mode mode, int64_t n, const double *x, const double *y, double *out,
                        const rpcg_opts *opts, rpcg_result *res, void *stream);

@@ -281,7 +281,9 @@ class CSR:
 
 def exdot(x: torch.Tensor, y: torch.Tensor, mode: str = "exblas", out: torch.Tensor | None = None,
           sync: bool = True, **opts):
-    """<x, y> on the GPU. Returns (out tensor of one double, info dict or None if sync=False)."""
+    """<x, y> on the GPU. Returns (out tensor of one double, info dict or None if sync=False).
+    With sync the result, and that of earlier work on the stream, is in place when the call returns;
+    the stream itself may report completion some microseconds later."""
     _check(x, torch.float64, "x")
     _check(y, torch.float64, "y")
     if x.numel() != y.numel() or x.device != y.device:
