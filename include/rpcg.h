@@ -222,6 +222,15 @@ int rpcg_smat_create(rpcg_ctx *ctx, const rpcg_csr *A /* host struct */, rpcg_sm
  * handle is only read). */
 int rpcg_smat_spmv(rpcg_smat *M, const double *x, double *y, void *stream);
 
+/* Which copy a prepared matrix holds: one of the values below (the solvers
+ * decide alike), or RPCG_ERR_INVALID for NULL. */
+enum {
+    RPCG_LAYOUT_COL32 = 0,  /* sliced-ELL, 32-bit columns */
+    RPCG_LAYOUT_COL16 = 1,  /* sliced-ELL, 16-bit column codes */
+    RPCG_LAYOUT_ALIGNED = 2 /* rows lined up by their column offsets: no column data */
+};
+int rpcg_smat_layout(const rpcg_smat *M);
+
 /* Frees the copy (NULL is ignored). No product with it may be pending. */
 void rpcg_smat_destroy(rpcg_smat *M);
 

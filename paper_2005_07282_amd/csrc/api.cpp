@@ -923,6 +923,14 @@ int rpcg_smat_spmv(rpcg_smat *M, const double *x, double *y, void *stream)
     return RPCG_OK;
 }
 
+int rpcg_smat_layout(const rpcg_smat *M)
+{
+    if (!M) return RPCG_ERR_INVALID;
+    static_assert(RPCG_LAYOUT_COL32 == LAY_COL32 && RPCG_LAYOUT_COL16 == LAY_COL16 && RPCG_LAYOUT_ALIGNED == LAY_DIAG,
+                  "layout names");
+    return M->B.ds ? LAY_DIAG : (M->B.col16 ? LAY_COL16 : LAY_COL32);
+}
+
 void rpcg_smat_destroy(rpcg_smat *M)
 {
     if (!M) return;

@@ -115,6 +115,8 @@ def lib():
         L.rpcg_smat_create.restype = ctypes.c_int
         L.rpcg_smat_spmv.argtypes = [P, P, P, P]
         L.rpcg_smat_spmv.restype = ctypes.c_int
+        L.rpcg_smat_layout.argtypes = [P]
+        L.rpcg_smat_layout.restype = ctypes.c_int
         L.rpcg_smat_destroy.argtypes = [P]
         L.rpcg_smat_destroy.restype = None
         L.rpcg_pcg_solve.argtypes = [P, ctypes.c_int, ctypes.POINTER(_Csr), P, P, ctypes.POINTER(_Opts),
@@ -177,7 +179,7 @@ def lib():
 
 EXPORTED = ["rpcg_opts_default", "rpcg_status_string", "rpcg_create", "rpcg_destroy", "rpcg_exdot", "rpcg_exdot_noalloc",
             "rpcg_fpe_size_auto",
-            "rpcg_spmv", "rpcg_smat_create", "rpcg_smat_spmv", "rpcg_smat_destroy", "rpcg_pcg_solve", "rpcg_pcg_solve_factored", "rpcg_pcg_solve_f32", "rpcg_ir_opts_default", "rpcg_ir_solve",
+            "rpcg_spmv", "rpcg_smat_create", "rpcg_smat_spmv", "rpcg_smat_layout", "rpcg_smat_destroy", "rpcg_pcg_solve", "rpcg_pcg_solve_factored", "rpcg_pcg_solve_f32", "rpcg_ir_opts_default", "rpcg_ir_solve",
             "rpcg_batch_create", "rpcg_batch_destroy", "rpcg_batch_get_tuning", "rpcg_batch_set_tuning",
             "rpcg_batch_tune", "rpcg_batch_solve", "rpcg_lp_pattern_nnz", "rpcg_lp_pattern", "rpcg_lp_create",
             "rpcg_lp_destroy", "rpcg_lp_set_params", "rpcg_lp_get_params", "rpcg_lp_forward", "rpcg_lp_factor",
@@ -360,8 +362,11 @@ def spmv(A: CSR, x: torch.Tensor, y: torch.Tensor | None = None) -> torch.Tensor
     return y
 
 
+LAYOUTS = ("col32", "col16", "aligned")  # rpcg_smat_layout
+
+
 class PreparedMatrix:
-    """A CSR matrix copied into the sliced-ELL layout for repeated products
+    """A CSR matrix copied into the solver's layout for repeated products
     (rpcg_smat_*); products are bit-identical to spmv(). The copy does not
     refer to the CSR arrays afterwards."""
 
@@ -375,6 +380,11 @@ class PreparedMatrix:
         if rc != 0:
             raise RpcgError(rc, "rpcg_smat_create")
         self._h = h
+
+    @property
+    def layout(self) -> str:
+        """Which copy the matrix is held in (one of LAYOUTS)."""
+        return LAYOUTS[lib().rpcg_smat_layout(self._h)]
 
     def spmv(self, x: torch.Tensor, y: torch.Tensor | None = None) -> torch.Tensor:
         _check(x, torch.float64, "x")
