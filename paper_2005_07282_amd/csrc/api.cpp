@@ -369,7 +369,7 @@ static int build_sell(rpcg_ctx *c, const SellBufs &bf, int n, int nnz, const int
         DiagSlice *ds = (DiagSlice *)bf.ds->p;
         DiagEnt *de = (DiagEnt *)bf.de->p;
         RPCG_TRY(hipMemsetAsync(table, 0xFF, sizeof(int) * DIAG_TABLE, s));
-        RPCG_TRY(launch_diag_align(n, 0, rp, col, v64, v32, off, de, ds, w, table, c->info, s));
+        RPCG_TRY(launch_diag_align(n, 0, rp, col, v64, v32, off, de, ds, w, table, c->info, c->num_cus, s));
         RPCG_TRY(hipMemcpyAsync(&scan_info, c->info, sizeof scan_info, hipMemcpyDeviceToHost, s));
         RPCG_TRY(hipStreamSynchronize(s));
         if (!scan_info.diag_fail && diag_worth_it(scan_info.diag_total, scan_info.diag_values, nnz)) {

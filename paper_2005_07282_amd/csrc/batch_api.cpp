@@ -461,7 +461,8 @@ static int batch_create_body(rpcg_batch *B, const rpcg_csr *A, hipStream_t calle
         for (int q = 0; q < B->nsys; ++q) {
             const BatchSys &S = B->sys[q];
             RPCG_TRY(launch_diag_align(S.n, S.slice0 / 2, A[q].row_ptr, A[q].col_idx, A[q].val, nullptr,
-                                       off + S.slice0, de, ds + S.slice0 / 2, w + S.slice0 / 2, table, c->info, B->gs));
+                                       off + S.slice0, de, ds + S.slice0 / 2, w + S.slice0 / 2, table, c->info,
+                                       c->num_cus, B->gs));
         }
         RPCG_TRY(hipMemcpyAsync(&inf, c->info, sizeof inf, hipMemcpyDeviceToHost, B->gs));
         RPCG_TRY(hipStreamSynchronize(B->gs));

@@ -1,12 +1,19 @@
 // Diagonal-aligned slices: the matrix copy of the solvers for operators whose
 // rows share their column offsets (stencils, bands). Layout with DiagSlice.
 //
-// A slice's 64 rows are merged by column offset (column - row): each step
+// A slice's 128 rows are merged by column offset (column - row): each step
 // takes the smallest head offset over the rows and emits one entry record for
 // every row whose next entry sits there, so a row's entries keep their storage
 // order whatever that order is. The merge gives up on a matrix whose rows do
-// not line up (more than 1.5 times the longest row plus 8 records in a slice);
-// the caller then builds the general sliced-ELL copy.
+// not line up (more records in a slice than the longest rows of its two halves
+// together, plus 8); the caller then builds the general sliced-ELL copy.
+//
+// What bounds the merge and the pass before it is what its wavefronts say to
+// the whole device: a device-scope atomic on one address takes about 10 ns however many
+// CUs wait for it. So a workgroup adds its totals once, as many workgroups as fit walk all slices, and a
+// wavefront claims a record list's table slot only where it has not just seen it claimed
+// (1 M rows of three entries: widths 62 -> 7 us, merge 288 -> 53 us; 512 k rows of 27
+// 60 -> 4 and 174 -> 76 us).
 #include "kernels.hpp"
 
 #include <algorithm>
@@ -18,10 +25,13 @@ namespace rpcg {
 __global__ void __launch_bounds__(256) k_row_widths(int n, int nnz, int nslices, const int *__restrict__ rp,
                                                     int *__restrict__ w, int *bad, int *max_len)
 {
+    __shared__ int top;
     const int lane = threadIdx.x & 63;
     const long long nwaves = ((long long)gridDim.x * blockDim.x) >> 6;
     int wmax = 0;
     bool ok = true;
+    if (threadIdx.x == 0) top = 0;
+    __syncthreads();
     for (long long s = ((long long)blockIdx.x * blockDim.x + threadIdx.x) >> 6; s < nslices; s += nwaves) {
         const long long i = s * 64 + lane;
         int a = 0, b = 0;
@@ -37,8 +47,10 @@ __global__ void __launch_bounds__(256) k_row_widths(int n, int nnz, int nslices,
         wmax = max(wmax, len);
     }
     if (__ballot(!ok) != 0 && lane == 0) atomicOr(bad, 1);
-    if (lane == 0 && __hip_atomic_load(max_len, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < wmax)
-        atomicMax(max_len, wmax);
+    if (lane == 0) atomicMax(&top, wmax);
+    __syncthreads();
+    if (threadIdx.x == 0 && __hip_atomic_load(max_len, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < top)
+        atomicMax(max_len, top);
 }
 
 // out[j * stride] = 64 sum(len[0..j)) for j < m, and out[m * stride] too when
@@ -147,16 +159,23 @@ k_diag_align(int n, int nslices, long long sbase, const int *__restrict__ rp, co
 {
     __shared__ int cwin[DW_WAVES][DIAG_ROWS * DW_PITCH];
     __shared__ TIN vwin[DW_WAVES][DIAG_ROWS * DW_PITCH];
+    __shared__ unsigned long long sums[2]; // records, and those whose values must be stored
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (threadIdx.x < 2) sums[threadIdx.x] = 0;
+    __syncthreads();
     int *cw = cwin[wv] + 2 * lane * DW_PITCH; // this lane's two rows
     TIN *vw = vwin[wv] + 2 * lane * DW_PITCH;
     unsigned long long tot = 0, totv = 0;
     bool failed = false, cbad = false;
+    int claimed = -1, seen = 0; // the table slot last found claimed; slices since the last look at the others
     const long long step = (long long)gridDim.x * DW_WAVES;
     for (long long s = (long long)blockIdx.x * DW_WAVES + wv; s < nslices; s += step) {
-        if (__builtin_amdgcn_readfirstlane(__hip_atomic_load(&info->diag_fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
-            break;
+        if (++seen == 4) {
+            seen = 0;
+            if (__builtin_amdgcn_readfirstlane(__hip_atomic_load(&info->diag_fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
+                break;
+        }
         const long long i = s * DIAG_ROWS + 2 * lane;
         int a[2], rem[2], p[2] = {0, 0}; // rem: entries from the window's start, p: consumed within the window
         a[0] = i < n ? rp[i] : 0;
@@ -222,14 +241,18 @@ k_diag_align(int n, int nslices, long long sbase, const int *__restrict__ rp, co
             }
         }
         if (failed) break;
+        if (cst) h ^= hv;
+        const int slot = (int)((h ^ (h >> 32)) & (DIAG_TABLE - 1)); // wavefront-uniform
+        if (slot != claimed) { // the first slice of a slot represents it
+            if (lane == 0 && __hip_atomic_load(&table[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == -1)
+                atomicCAS(&table[slot], -1, (int)(s + sbase));
+            claimed = slot;
+        }
         if (lane < DIAG_PAD) de[mpos + u + lane] = DiagEnt{0.0, {0ull, 0ull}, 0, 0.0f};
         if (lane == 0) {
             const long long s128 = s * DIAG_ROWS;
             // the loops read up to two elements past a record's rows
             const bool clamp = s128 + omin < 0 || s128 + DIAG_ROWS + 2 + omax >= n;
-            if (cst) h ^= hv;
-            const int slot = (int)((h ^ (h >> 32)) & (DIAG_TABLE - 1));
-            atomicCAS(&table[slot], -1, (int)(s + sbase)); // the first slice of a slot represents it
             ds[s].vpos = slot; // until the values are placed
             ds[s].mpos = mpos;
             ds[s].width = u;
@@ -242,8 +265,13 @@ k_diag_align(int n, int nslices, long long sbase, const int *__restrict__ rp, co
     if (__ballot(cbad) != 0 && lane == 0) atomicOr(&info->flags, 1);
     if (lane == 0) {
         if (failed) atomicOr(&info->diag_fail, 1);
-        if (tot) atomicAdd(&info->diag_total, tot);
-        if (totv) atomicAdd(&info->diag_values, totv);
+        if (tot) atomicAdd(&sums[0], tot);
+        if (totv) atomicAdd(&sums[1], totv);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        if (sums[0]) atomicAdd(&info->diag_total, sums[0]);
+        if (sums[1]) atomicAdd(&info->diag_values, sums[1]);
     }
 }
 
@@ -325,7 +353,7 @@ hipError_t launch_row_widths(int n, int nnz, const int *row_ptr, int *w, int *ba
 {
     const int nslices = (n + DIAG_ROWS - 1) / DIAG_ROWS * 2;
     if (nslices == 0) return hipSuccess;
-    const int grid = (int)std::min<long long>((nslices + 3) / 4, 2048);
+    const int grid = (int)std::min<long long>((nslices + 3) / 4, 1024);
     k_row_widths<<<grid, 256, 0, s>>>(n, nnz, nslices, row_ptr, w, bad, max_len);
     return hipGetLastError();
 }
@@ -339,12 +367,13 @@ hipError_t launch_scan_len(const int *len, int m, long long *out, int stride, bo
 
 hipError_t launch_diag_align(int n, long long sbase, const int *row_ptr, const int *col, const double *val64,
                              const float *val32, const long long *off, DiagEnt *de, DiagSlice *ds, int *ulen,
-                             int *table, DotInfo *info, hipStream_t s)
+                             int *table, DotInfo *info, int num_cus, hipStream_t s)
 {
     const int nslices = (n + DIAG_ROWS - 1) / DIAG_ROWS;
     if (nslices == 0) return hipSuccess;
     if ((val64 == nullptr) == (val32 == nullptr)) return hipErrorInvalidValue;
-    const int grid = (int)std::min<long long>((nslices + DW_WAVES - 1) / DW_WAVES, 4096);
+    // three workgroups a CU: what their windows leave room for
+    const int grid = (int)std::min<long long>((nslices + DW_WAVES - 1) / DW_WAVES, 3ll * num_cus);
     if (val64)
         k_diag_align<double><<<grid, 64 * DW_WAVES, 0, s>>>(n, nslices, sbase, row_ptr, col, val64, off, de, ds, ulen,
                                                                table, info);

@@ -227,7 +227,7 @@ hipError_t launch_csr_scan(int n, int nnz, const int *row_ptr, const int *col, i
 // that need them.
 hipError_t launch_diag_align(int n, long long sbase, const int *row_ptr, const int *col, const double *val64,
                              const float *val32, const long long *off, DiagEnt *de, DiagSlice *ds, int *ulen,
-                             int *table, DotInfo *info, hipStream_t s);
+                             int *table, DotInfo *info, int num_cus, hipStream_t s);
 hipError_t launch_diag_share(int nslices, const DiagEnt *de, DiagSlice *ds, const int *table, hipStream_t s);
 hipError_t launch_diag_fill(int n, const int *row_ptr, const double *val64, const float *val32, const DiagEnt *de,
                             const DiagSlice *ds, double *sval64, float *sval32, hipStream_t s);
