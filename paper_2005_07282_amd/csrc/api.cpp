@@ -363,13 +363,14 @@ static int build_sell(rpcg_ctx *c, const SellBufs &bf, int n, int nnz, const int
     RPCG_TRY(hipMemcpyAsync(&scan_info, c->info, sizeof scan_info, hipMemcpyDeviceToHost, s));
     RPCG_TRY(hipStreamSynchronize(s));
     if (scan_info.flags) return RPCG_ERR_INVALID;
-    if (!no_col16 && padded > 0 && scan_info.max_len <= DIAG_MAX_ROW) {
+    if (!no_col16 && diag_to_try(n, scan_info.max_len)) {
         RPCG_TRY(bf.ds->ensure(sizeof(DiagSlice) * nd));
         RPCG_TRY(bf.de->ensure(sizeof(DiagEnt) * (size_t)diag_mpos(padded, nd)));
         DiagSlice *ds = (DiagSlice *)bf.ds->p;
         DiagEnt *de = (DiagEnt *)bf.de->p;
         RPCG_TRY(hipMemsetAsync(table, 0xFF, sizeof(int) * DIAG_TABLE, s));
-        RPCG_TRY(launch_diag_align(n, 0, rp, col, v64, v32, off, de, ds, w, table, c->info, c->num_cus, s));
+        RPCG_TRY(launch_diag_align(n, 0, rp, col, v64, v32, off, de, ds, w, table, c->info,
+                                   diag_max_stored(nd, c->num_cus), c->num_cus, s));
         RPCG_TRY(hipMemcpyAsync(&scan_info, c->info, sizeof scan_info, hipMemcpyDeviceToHost, s));
         RPCG_TRY(hipStreamSynchronize(s));
         if (!scan_info.diag_fail && diag_worth_it(scan_info.diag_total, scan_info.diag_values, nnz)) {

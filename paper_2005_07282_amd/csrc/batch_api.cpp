@@ -449,7 +449,7 @@ static int batch_create_body(rpcg_batch *B, const rpcg_csr *A, hipStream_t calle
     if (inf.flags) return RPCG_ERR_INVALID;
     const long long padded = B->off_host[B->total_slices];
     bool aligned = false;
-    if (padded > 0 && inf.max_len <= DIAG_MAX_ROW) { // diagonal-aligned slices, as for a single system
+    if (inf.max_len > 0 && inf.max_len <= DIAG_MAX_ROW) { // diagonal-aligned slices, as for a single system
         const int nd = ns / 2;
         long long nnz = 0;
         for (int q = 0; q < B->nsys; ++q) nnz += A[q].nnz;
@@ -462,7 +462,7 @@ static int batch_create_body(rpcg_batch *B, const rpcg_csr *A, hipStream_t calle
             const BatchSys &S = B->sys[q];
             RPCG_TRY(launch_diag_align(S.n, S.slice0 / 2, A[q].row_ptr, A[q].col_idx, A[q].val, nullptr,
                                        off + S.slice0, de, ds + S.slice0 / 2, w + S.slice0 / 2, table, c->info,
-                                       c->num_cus, B->gs));
+                                       diag_max_stored(nd, c->num_cus), c->num_cus, B->gs));
         }
         RPCG_TRY(hipMemcpyAsync(&inf, c->info, sizeof inf, hipMemcpyDeviceToHost, B->gs));
         RPCG_TRY(hipStreamSynchronize(B->gs));

@@ -150,12 +150,14 @@ __device__ __forceinline__ void stage_rows(TV *win, const TV *__restrict__ src, 
 // Pass 2: the merge, one wavefront per 128-row slice (grid-stride). Writes the
 // entry records and DiagSlice (vpos excepted), ulen[s] (records whose values
 // must be stored: 0 for a constant slice), the column check, and the totals of
-// the matrix. Once a slice has failed the others stop.
+// the matrix. Once a slice has failed, or more than max_stored of all slices
+// need stored values, the others stop.
 template <typename TIN>
 __global__ void __launch_bounds__(64 * DW_WAVES)
 k_diag_align(int n, int nslices, long long sbase, const int *__restrict__ rp, const int *__restrict__ col,
              const TIN *__restrict__ val, const long long *__restrict__ off, DiagEnt *__restrict__ de,
-             DiagSlice *__restrict__ ds, int *__restrict__ ulen, int *__restrict__ table, DotInfo *info)
+             DiagSlice *__restrict__ ds, int *__restrict__ ulen, int *__restrict__ table, DotInfo *info,
+             int max_stored)
 {
     __shared__ int cwin[DW_WAVES][DIAG_ROWS * DW_PITCH];
     __shared__ TIN vwin[DW_WAVES][DIAG_ROWS * DW_PITCH];
@@ -168,13 +170,16 @@ k_diag_align(int n, int nslices, long long sbase, const int *__restrict__ rp, co
     TIN *vw = vwin[wv] + 2 * lane * DW_PITCH;
     unsigned long long tot = 0, totv = 0;
     bool failed = false, cbad = false;
+    const bool few = max_stored != DIAG_ANY; // slices that need stored values are counted as they are met
+    auto given_up = [&]() {
+        return __builtin_amdgcn_readfirstlane(__hip_atomic_load(&info->diag_fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != 0;
+    };
     int claimed = -1, seen = 0; // the table slot last found claimed; slices since the last look at the others
     const long long step = (long long)gridDim.x * DW_WAVES;
     for (long long s = (long long)blockIdx.x * DW_WAVES + wv; s < nslices; s += step) {
         if (++seen == 4) {
             seen = 0;
-            if (__builtin_amdgcn_readfirstlane(__hip_atomic_load(&info->diag_fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
-                break;
+            if (given_up()) break;
         }
         const long long i = s * DIAG_ROWS + 2 * lane;
         int a[2], rem[2], p[2] = {0, 0}; // rem: entries from the window's start, p: consumed within the window
@@ -219,7 +224,14 @@ k_diag_align(int n, int nslices, long long sbase, const int *__restrict__ rp, co
                 const unsigned hi = __builtin_amdgcn_readlane((unsigned)(mine_first >> 32), f);
                 const unsigned long long fb = ((unsigned long long)hi << 32) | lo;
                 vv = __builtin_bit_cast(double, fb);
-                if (__ballot((in[0] && b0 != fb) || (in[1] && b1 != fb)) != 0) cst = false;
+                if (__ballot((in[0] && b0 != fb) || (in[1] && b1 != fb)) != 0) {
+                    cst = false;
+                    if (few) {
+                        int before = 0;
+                        if (lane == 0) before = atomicAdd(&info->diag_stored, 1);
+                        if (__builtin_amdgcn_readfirstlane(before) >= max_stored) { failed = true; break; }
+                    }
+                }
             }
             if (lane == 0) de[mpos + u] = DiagEnt{vv, {m[0], m[1]}, om, (float)vv};
             h = (h ^ (unsigned)om ^ (m[0] * 0x9E3779B97F4A7C15ull)) * 0xBF58476D1CE4E5B9ull;
@@ -236,6 +248,7 @@ k_diag_align(int n, int nslices, long long sbase, const int *__restrict__ rp, co
             if (__ballot((p[0] == DW_WIN && p[0] < rem[0]) || (p[1] == DW_WIN && p[1] < rem[1])) != 0) {
 #pragma unroll
                 for (int r = 0; r < 2; ++r) { a[r] += p[r]; rem[r] -= p[r]; p[r] = 0; }
+                if (few && given_up()) { failed = true; break; }
                 stage_rows(cwin[wv], col, a, rem, lane, range);
                 staged = false; // the value window follows when it is next needed
             }
@@ -367,7 +380,7 @@ hipError_t launch_scan_len(const int *len, int m, long long *out, int stride, bo
 
 hipError_t launch_diag_align(int n, long long sbase, const int *row_ptr, const int *col, const double *val64,
                              const float *val32, const long long *off, DiagEnt *de, DiagSlice *ds, int *ulen,
-                             int *table, DotInfo *info, int num_cus, hipStream_t s)
+                             int *table, DotInfo *info, int max_stored, int num_cus, hipStream_t s)
 {
     const int nslices = (n + DIAG_ROWS - 1) / DIAG_ROWS;
     if (nslices == 0) return hipSuccess;
@@ -376,10 +389,10 @@ hipError_t launch_diag_align(int n, long long sbase, const int *row_ptr, const i
     const int grid = (int)std::min<long long>((nslices + DW_WAVES - 1) / DW_WAVES, 3ll * num_cus);
     if (val64)
         k_diag_align<double><<<grid, 64 * DW_WAVES, 0, s>>>(n, nslices, sbase, row_ptr, col, val64, off, de, ds, ulen,
-                                                               table, info);
+                                                               table, info, max_stored);
     else
         k_diag_align<float><<<grid, 64 * DW_WAVES, 0, s>>>(n, nslices, sbase, row_ptr, col, val32, off, de, ds, ulen,
-                                                               table, info);
+                                                               table, info, max_stored);
     return hipGetLastError();
 }
 

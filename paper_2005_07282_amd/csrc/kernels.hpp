@@ -46,8 +46,8 @@ struct DotInfo {
     int pad1;
     long long max_delta; // column-code range (SELL construction scratch)
     // construction scratch of the diagonal-aligned copy
-    int diag_fail;                // nonzero: some slice's rows do not line up
-    int pad2;
+    int diag_fail;                // nonzero: the rows do not line up, or too many slices need stored values
+    int diag_stored;              // slices that need stored values, counted where there may be too many
     unsigned long long diag_total;  // entry records of all slices
     unsigned long long diag_values; // those whose values must be stored
 };
@@ -153,8 +153,27 @@ __host__ constexpr bool diag_worth_it(unsigned long long records, unsigned long 
 {
     return 4 * DIAG_ROWS * values <= 5 * (unsigned long long)nnz && DIAG_ROWS * records <= 2 * (unsigned long long)nnz;
 }
+// The rows that an aligned copy is tried for: those of a matrix wider than twice its
+// longest row (nearly every slice of others is at an end, where the gathers are clamped one by
+// one: binary32 solver, 1000 rows, constant band of 1001 67 us an iteration
+// in general slices, 77 us aligned), none longer than DIAG_MAX_ROW (the merge
+// walks a row entry by entry).
+constexpr int DIAG_MAX_ROW = 1024;
+__host__ constexpr bool diag_to_try(int n, int max_len) { return max_len > 0 && max_len <= DIAG_MAX_ROW && 2ll * max_len <= n; }
+// Slices (of all nslices) whose values may have to be stored, or DIAG_ANY. Two rows a lane
+// give stored values half the wavefronts of the general copy, each with one
+// batch of loads in flight: less HBM traffic, but more latency, and up to five slices
+// a CU it is latency that counts (prepared product, general and aligned, us: 20 k rows of 31
+// 4.5 and 7.3, of 201 16.6 and 33.6; 100 k rows of 21 6.1 and 7.3, of 101 20.8 and
+// 27.9; 150 k rows 9.3 and 9.2, 32.6 and 36.0; 200 k rows 10.6 and 8.1, 39.4 and 28.9; 512 k rows of 27
+// 28.2 and 19.3; rows of up to seven about alike). A few stored slices among constant ones, which
+// are faster aligned at any size, do no harm.
+constexpr int DIAG_ANY = 2147483647;
+__host__ constexpr int diag_max_stored(long long nslices, int num_cus)
+{
+    return nslices >= 5ll * num_cus ? DIAG_ANY : (int)(nslices / 16);
+}
 constexpr int DIAG_TABLE = 8192; // hash slots of record lists, a power of two (see k_diag_share)
-constexpr int DIAG_MAX_ROW = 1024; // longer rows keep the general layout (the merge walks a row entry by entry)
 
 // Column layouts of the solvers' matrix copies.
 enum { LAY_COL32 = 0, LAY_COL16 = 1, LAY_DIAG = 2 };
@@ -221,13 +240,14 @@ hipError_t launch_csr_scan(int n, int nnz, const int *row_ptr, const int *col, i
                            long long *max_delta, hipStream_t s);
 // Diagonal-aligned slices from a CSR whose row_ptr has been checked: the merge
 // (records, DiagSlice without vpos, ulen, column check, totals or diag_fail in
-// info; values from exactly one of val64 and val32; sbase = slices before this
+// info; values from exactly one of val64 and val32; max_stored: slices, of all
+// matrices of an info, whose values may vary, else diag_fail; sbase = slices before this
 // matrix in de, in 128-row slices; off: 64 times the widths of the 64-row slices before; table: DIAG_TABLE ints set to -1), the sharing of equal record
 // lists (over all matrices of a table), and the stored values of the slices
 // that need them.
 hipError_t launch_diag_align(int n, long long sbase, const int *row_ptr, const int *col, const double *val64,
                              const float *val32, const long long *off, DiagEnt *de, DiagSlice *ds, int *ulen,
-                             int *table, DotInfo *info, int num_cus, hipStream_t s);
+                             int *table, DotInfo *info, int max_stored, int num_cus, hipStream_t s);
 hipError_t launch_diag_share(int nslices, const DiagEnt *de, DiagSlice *ds, const int *table, hipStream_t s);
 hipError_t launch_diag_fill(int n, const int *row_ptr, const double *val64, const float *val32, const DiagEnt *de,
                             const DiagSlice *ds, double *sval64, float *sval32, hipStream_t s);

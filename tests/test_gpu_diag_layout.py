@@ -6,7 +6,7 @@ so those cases have more than the 1280 slices of 128 rows that 256 CUs ask for."
 import numpy as np
 import pytest
 
-from rpcg_workloads import CSRHost, stencil27_csr, stencil7_varcoef_csr, uniform_pm1
+from rpcg_workloads import CSRHost, band_csr, stencil27_csr, stencil7_varcoef_csr, uniform_pm1
 from test_gpu_diag import CASES as SMALL, _offsets_csr
 
 pytestmark = pytest.mark.gpu
@@ -55,6 +55,27 @@ def test_smallest_aligned(R, orc, n, aligned):
     _product(R, orc, _offsets_csr(n, [0], 1, True), "aligned" if aligned else "col16")
 
 
+@pytest.mark.parametrize("case,layout", [("n129", "col16"), ("far", "col16"), ("unsorted", "col32"), ("holes", "col16"),
+                                         ("band17", "col16"), ("stencil27_var", "col16"), ("stencil7", "col16"),
+                                         ("first_scaled", "aligned")])
+def test_few_slices_of_varying_values(R, orc, case, layout):
+    """They are faster in the general copy; one slice in sixteen may vary among constant ones."""
+    print(f"layout {case}", flush=True)
+    _product(R, orc, SMALL[case](), layout)
+
+
+@pytest.mark.parametrize("n,w,layout", [(1000, 249, "aligned"), (1000, 250, "col16"), (2053, 130, "aligned")])
+def test_bands_against_the_size(R, orc, n, w, layout):
+    _product(R, orc, band_csr(n, w), layout)
+
+
+def test_slices_that_varying_values_need(R, orc):
+    rows = 128 * 5 * torch.cuda.get_device_properties(0).multi_processor_count
+    for n, layout in ((rows, "aligned"), (rows - 128, "col16")):
+        _product(R, orc, _offsets_csr(n, [-1, 0, 1], 9, False), layout)
+        _product(R, orc, _offsets_csr(n, [-1, 0, 1], 9, True), "aligned")
+
+
 def _big(kind):
     if kind == "stencil7":
         return stencil7_varcoef_csr(56, 4)  # 175 616 rows
@@ -85,6 +106,37 @@ def test_solves_over_varying_values(R, orc, kind, mode):
         x, info = R.pcg_solve(Ad, bd, mode=mode, tol=1e-8, maxit=6, raise_on_error=False, **kw)
         assert info["iterations"] == ref["iters"]
         assert np.array_equal(_bits(x.cpu().numpy()), _bits(ref["x"]))
+
+
+def test_binary32_and_refinement_over_varying_values(R, orc):
+    A = _big("stencil7")
+    b = orc.spmv(A, uniform_pm1(15, A.n))
+    b32 = b.astype(np.float32)
+    ref = orc.pcg_f32(A, b32, tol=1e-6, maxit=5)
+    x, info = R.pcg_solve_f32(R.CSR.from_host(A, dtype=torch.float32), torch.from_numpy(b32).cuda(), tol=1e-6, maxit=5,
+                              raise_on_error=False)
+    assert info["iterations"] == ref["iters"]
+    assert np.array_equal(x.cpu().numpy().view(np.uint32), ref["x"].view(np.uint32))
+    ref = orc.ir(A, b, tol=1e-10, maxit_out=2, maxit_in=5)
+    x, info = R.ir_solve(R.CSR.from_host(A), torch.from_numpy(b).cuda(), maxit=2, maxit_inner=5, raise_on_error=False)
+    assert info["outer"] == 2
+    assert np.array_equal(_bits(x.cpu().numpy()), _bits(ref["x"]))
+
+
+def test_batch_over_varying_values(R, orc):
+    """1300 slices in all, and as many less one system: aligned and general give each system's own bits."""
+    systems = [stencil7_varcoef_csr(N, 90 + N) for N in (40, 3, 41, 17)]  # 501, 1, 539, 39 slices
+    systems.append(stencil7_varcoef_csr(31, 7))                           # 233
+    bs = [orc.spmv(A, uniform_pm1(30 + k, A.n)) for k, A in enumerate(systems)]
+    refs = [orc.pcg(A, b, tol=1e-9, maxit=12) for A, b in zip(systems, bs)]
+    for keep in (5, 4):
+        for mode in ("exblas", "fpe"):
+            B = R.Batch([R.CSR.from_host(A) for A in systems[:keep]], mode=mode, tol=1e-9, maxit=12)
+            xs, infos, _ = B.solve([torch.from_numpy(b).cuda() for b in bs[:keep]], raise_on_error=False)
+            for x, i, r in zip(xs, infos, refs):
+                assert i["iterations"] == r["iters"]
+                assert np.array_equal(_bits(x.cpu().numpy()), _bits(r["x"]))
+            B.close()
 
 
 def test_layout_of_nothing(R):
