@@ -84,18 +84,24 @@ static int general_waves(long long nslices, int num_cus)
 // kernel keeps fewer bytes in flight per wavefront and wants twice the
 // workgroups of the binary64 one. Over diagonal-aligned slices the loop waits
 // on gathers, not on the matrix stream, and wants every wavefront the
-// registers allow (16 per CU).
-static LaunchCfg make_spmv_cfg(const rpcg_ctx *c, const rpcg_opts &o, long long nslices, bool diag, hipStream_t s,
-                               bool f32 = false)
+// registers allow (16 per CU). With stored values and few slices a CU, workgroups
+// of four wavefronts that divide evenly over the CUs: with eight, some CUs have a workgroup more
+// than the others and the kernel waits for them (us with eight and with four wavefronts: 300 k rows of 21
+// 22.5 and 16.8, of 101 75.8 and 52.0, of 201 139 and 101; 600 k rows of 101 94 and 84; 1 M rows of
+// 21 36.5 and 35.9; two a CU up to eight slices a CU, 250 k rows of 101 49.0 and 39.6, three 40.7).
+static LaunchCfg make_spmv_cfg(const rpcg_ctx *c, const rpcg_opts &o, long long nslices, bool diag, bool stored,
+                               hipStream_t s, bool f32 = false)
 {
     rpcg_opts q = o;
     q.block_size = o.spmv_block_size;
     q.grid_size = o.spmv_grid_size;
     const int waves = general_waves(nslices, c->num_cus);
-    const int block = diag ? (nslices > 4ll * c->num_cus ? 512 : 256) : 64 * waves;
+    const bool even = diag && stored && nslices < 32ll * c->num_cus;
+    const int block = diag ? (nslices > 4ll * c->num_cus && !even ? 512 : 256) : 64 * waves;
     LaunchCfg cfg = make_cfg(c, q, std::max(1ll, nslices * 64), block, s);
-    const long long cap = (!diag && f32 ? 4ll : 2ll) * c->num_cus;
-    if (!q.grid_size) cfg.grid = (int)std::max(1ll, std::min((nslices * 64 + cfg.block - 1) / cfg.block, cap));
+    const long long per_cu = even ? (nslices <= 8ll * c->num_cus ? 2 : 3) : (!diag && f32 ? 4 : 2);
+    if (!q.grid_size)
+        cfg.grid = (int)std::max(1ll, std::min((nslices * 64 + cfg.block - 1) / cfg.block, per_cu * c->num_cus));
     return cfg;
 }
 
@@ -318,6 +324,7 @@ struct SellBuilt {
     const unsigned char *len8 = nullptr;
     const DiagSlice *ds = nullptr; // diagonal-aligned slices instead of off, col, ...
     const DiagEnt *de = nullptr;
+    bool stored = false; // most records of the diagonal-aligned slices have stored values
 };
 
 // Device buffers a sliced-ELL copy is built into (the context's for the
@@ -386,6 +393,7 @@ static int build_sell(rpcg_ctx *c, const SellBufs &bf, int n, int nnz, const int
                 RPCG_TRY(launch_diag_fill(n, rp, v64, v32, de, ds, s64, s32, s));
             }
             out->nslices = nd;
+            out->stored = 2 * scan_info.diag_values > scan_info.diag_total;
             out->val64 = s64;
             out->val32 = s32;
             out->ds = ds;
@@ -633,7 +641,7 @@ static int pcg_solve_any(rpcg_ctx *c, int mode, int n, int nnz, const int *rp, c
     int rc = build_sell(c, ctx_sell_bufs(c), n, nnz, rp, col, v64, v32, !F32, F32, o.no_col16 != 0, s, &B);
     if (rc != RPCG_OK) return rc;
     LaunchCfg cfg_rows = make_vec_cfg(c, o, std::max(1, n), s);
-    LaunchCfg cfg_sl = make_spmv_cfg(c, o, B.nslices, B.ds != nullptr, s, F32);
+    LaunchCfg cfg_sl = make_spmv_cfg(c, o, B.nslices, B.ds != nullptr, B.stored, s, F32);
     // EXBLAS results do not depend on the lane expansion length. With the
     // default, the binary64 SpMV kernel (and the setup) keep four terms: its
     // <d, w> lanes then flush to the long accumulator less often, while the
@@ -743,7 +751,7 @@ static int ir_body(rpcg_ctx *c, int mode, const rpcg_csr *A, const double *b, do
     int rc = build_sell(c, ctx_sell_bufs(c), n, A->nnz, A->row_ptr, A->col_idx, A->val, nullptr, true, true,
                         o.no_col16 != 0, s, &B);
     if (rc != RPCG_OK) return rc;
-    LaunchCfg cfg_sl = make_spmv_cfg(c, o, B.nslices, B.ds != nullptr, s, true);
+    LaunchCfg cfg_sl = make_spmv_cfg(c, o, B.nslices, B.ds != nullptr, B.stored, s, true);
     LaunchCfg cfg_res = make_res_cfg(c, nslices, s);
     rpcg_opts dflt;
     rpcg_opts_default(&dflt);
