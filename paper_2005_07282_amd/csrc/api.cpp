@@ -324,6 +324,7 @@ struct SellBuilt {
     const unsigned char *len8 = nullptr;
     const DiagSlice *ds = nullptr; // diagonal-aligned slices instead of off, col, ...
     const DiagEnt *de = nullptr;
+    size_t records = 0;  // extent of de
     bool stored = false; // most records of the diagonal-aligned slices have stored values
 };
 
@@ -363,21 +364,27 @@ static int build_sell(rpcg_ctx *c, const SellBufs &bf, int n, int nnz, const int
     RPCG_TRY(c->widths.ensure(sizeof(int) * ((size_t)nw + DIAG_TABLE)));
     long long *off = (long long *)bf.off->p;
     int *table = (int *)c->widths.p, *w = table + DIAG_TABLE;
-    RPCG_TRY(launch_row_widths(n, nnz, rp, w, &c->info->flags, &c->info->max_len, s));
+    const int max_stored = diag_max_stored(nd, c->num_cus);
+    const bool sample = max_stored != DIAG_ANY && !no_col16;
+    const DiagCsr<double> m64{rp, col, v64, n, nnz, 0};
+    const DiagCsr<float> m32{rp, col, v32, n, nnz, 0};
+    auto of_type = [&](auto &&f) { return v64 ? f(m64, (const DiagCsr<double> *)nullptr) : f(m32, (const DiagCsr<float> *)nullptr); };
+    RPCG_TRY(of_type([&](auto &m, auto none) { return launch_row_widths(m, none, 1, nw, sample, w, table, c->info, s); }));
     RPCG_TRY(launch_scan_len(w, nw, off, 1, true, s));
     padded = 0;
     if (nw > 0) RPCG_TRY(hipMemcpyAsync(&padded, off + nw, sizeof padded, hipMemcpyDeviceToHost, s));
     RPCG_TRY(hipMemcpyAsync(&scan_info, c->info, sizeof scan_info, hipMemcpyDeviceToHost, s));
     RPCG_TRY(hipStreamSynchronize(s));
     if (scan_info.flags) return RPCG_ERR_INVALID;
-    if (!no_col16 && diag_to_try(n, scan_info.max_len)) {
+    if (!no_col16 && diag_to_try(n, scan_info.max_len) && scan_info.varying / 2 <= max_stored) {
         RPCG_TRY(bf.ds->ensure(sizeof(DiagSlice) * nd));
-        RPCG_TRY(bf.de->ensure(sizeof(DiagEnt) * (size_t)diag_mpos(padded, nd)));
+        out->records = (size_t)diag_mpos(padded, nd);
+        RPCG_TRY(bf.de->ensure(sizeof(DiagEnt) * out->records));
         DiagSlice *ds = (DiagSlice *)bf.ds->p;
         DiagEnt *de = (DiagEnt *)bf.de->p;
-        RPCG_TRY(hipMemsetAsync(table, 0xFF, sizeof(int) * DIAG_TABLE, s));
-        RPCG_TRY(launch_diag_align(n, 0, rp, col, v64, v32, off, de, ds, w, table, c->info,
-                                   diag_max_stored(nd, c->num_cus), c->num_cus, s));
+        RPCG_TRY(of_type([&](auto &m, auto none) {
+            return launch_diag_align(m, none, 1, nd, off, de, ds, w, table, c->info, max_stored, c->num_cus, s);
+        }));
         RPCG_TRY(hipMemcpyAsync(&scan_info, c->info, sizeof scan_info, hipMemcpyDeviceToHost, s));
         RPCG_TRY(hipStreamSynchronize(s));
         if (!scan_info.diag_fail && diag_worth_it(scan_info.diag_total, scan_info.diag_values, nnz)) {
@@ -390,7 +397,7 @@ static int build_sell(rpcg_ctx *c, const SellBufs &bf, int n, int nnz, const int
                 if (out64) { RPCG_TRY(bf.val->ensure(sizeof(double) * nv)); s64 = (double *)bf.val->p; }
                 if (out32) { RPCG_TRY(bf.val32->ensure(sizeof(float) * nv)); s32 = (float *)bf.val32->p; }
                 RPCG_TRY(launch_scan_len(w, nd, &ds->vpos, sizeof(DiagSlice) / sizeof(long long), false, s));
-                RPCG_TRY(launch_diag_fill(n, rp, v64, v32, de, ds, s64, s32, s));
+                RPCG_TRY(of_type([&](auto &m, auto none) { return launch_diag_fill(m, none, 1, nd, de, ds, s64, s32, s); }));
             }
             out->nslices = nd;
             out->stored = 2 * scan_info.diag_values > scan_info.diag_total;
@@ -879,14 +886,31 @@ struct rpcg_smat {
     SellBuilt B;
 };
 
+// `need` bytes of the context's scratch into a handle's own memory: the buffer
+// itself where it is not much larger, else a copy (a buffer made and freed for a copy that
+// turns out general cost 0.1 to 0.3 ms).
+static int take_scratch(rpcg_host::Buffer &own, rpcg_host::Buffer &scratch, size_t need, hipStream_t s)
+{
+    if (scratch.bytes <= need + need / 4) {
+        std::swap(own, scratch);
+        return RPCG_OK;
+    }
+    RPCG_TRY(own.ensure(need));
+    RPCG_TRY(hipMemcpyAsync(own.p, scratch.p, need, hipMemcpyDeviceToDevice, s));
+    return RPCG_OK;
+}
+
 static int smat_build(rpcg_ctx *c, const rpcg_csr *A, rpcg_smat *M, hipStream_t s)
 {
-    const SellBufs bf{&M->off, &M->val, &M->val32, &M->col, &M->cfirst, &M->len, &M->ds, &M->de};
+    const SellBufs bf{&M->off, &M->val, &M->val32, &M->col, &M->cfirst, &M->len, &c->diag_ds, &c->diag_de};
     int rc = build_sell(c, bf, A->n, A->nnz, A->row_ptr, A->col_idx, A->val, nullptr, true, false, false, s, &M->B);
     if (rc != RPCG_OK) return rc;
-    if (!M->B.ds) { // the merge's scratch is not kept
-        M->ds.release();
-        M->de.release();
+    if (M->B.ds) {
+        rc = take_scratch(M->ds, c->diag_ds, sizeof(DiagSlice) * (size_t)M->B.nslices, s);
+        if (rc == RPCG_OK) rc = take_scratch(M->de, c->diag_de, sizeof(DiagEnt) * M->B.records, s);
+        if (rc != RPCG_OK) return rc;
+        M->B.ds = (const DiagSlice *)M->ds.p;
+        M->B.de = (const DiagEnt *)M->de.p;
     }
     if (!M->B.len8 && !M->B.ds) { // rows of 256 or more entries: the row lengths come from a copy of row_ptr
         RPCG_TRY(M->rp.ensure(sizeof(int) * ((size_t)A->n + 1)));

@@ -20,25 +20,64 @@
 
 namespace rpcg {
 
-// Pass 1: slice widths (longest row), the longest row of the matrix, and the
-// check of row_ptr (0 at the start, nnz at the end, non-decreasing).
-__global__ void __launch_bounds__(256) k_row_widths(int n, int nnz, int nslices, const int *__restrict__ rp,
-                                                    int *__restrict__ w, int *bad, int *max_len)
+// The matrix of slice s (wavefront-uniform; UNIT: 64-row slices per slice of s): of
+// several the last that starts at or before it.
+template <int UNIT, typename TIN>
+__device__ __forceinline__ DiagCsr<TIN> matrix_of(const DiagCsr<TIN> &one, const DiagCsr<TIN> *__restrict__ mats, int nmats,
+                                                  long long s)
 {
-    __shared__ int top;
+    if (nmats <= 1) return one;
+    int lo = 0, hi = nmats - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) / 2;
+        if (mats[mid].slice0 <= UNIT * s) lo = mid;
+        else hi = mid - 1;
+    }
+    return mats[lo];
+}
+
+// Pass 1: slice widths (longest row), the longest row of the matrix, and the
+// check of row_ptr (0 at the start, nnz at the end, non-decreasing), over the slices of one
+// matrix or of all systems of a batch (mats in device memory). The merge's table is
+// emptied on the way. SAMPLE: info->varying counts the slices in which first entries at one
+// offset differ, so that a matrix of few slices whose values plainly vary is not tried
+// at all (a failed try costs 20 to 40 us).
+template <typename TIN, bool SAMPLE>
+__global__ void __launch_bounds__(256) k_row_widths(DiagCsr<TIN> one, const DiagCsr<TIN> *__restrict__ mats, int nmats,
+                                                    int nslices, int *__restrict__ w, int *__restrict__ table, DotInfo *info)
+{
+    __shared__ int top, vary;
+    if (blockIdx.x == 0)
+        for (int k = threadIdx.x; k < DIAG_TABLE; k += blockDim.x) table[k] = -1;
     const int lane = threadIdx.x & 63;
     const long long nwaves = ((long long)gridDim.x * blockDim.x) >> 6;
-    int wmax = 0;
+    int wmax = 0, differ = 0;
     bool ok = true;
-    if (threadIdx.x == 0) top = 0;
+    if (threadIdx.x == 0) top = vary = 0;
     __syncthreads();
-    for (long long s = ((long long)blockIdx.x * blockDim.x + threadIdx.x) >> 6; s < nslices; s += nwaves) {
-        const long long i = s * 64 + lane;
+    for (long long s = __builtin_amdgcn_readfirstlane((int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6)); s < nslices;
+         s += nwaves) {
+        const DiagCsr<TIN> M = matrix_of<1>(one, mats, nmats, s);
+        const long long i = (s - M.slice0) * 64 + lane;
         int a = 0, b = 0;
-        if (i < n) {
-            a = rp[i];
-            b = rp[i + 1];
-            ok = ok && a >= 0 && a <= b && b <= nnz && (i != 0 || a == 0) && (i != n - 1 || b == nnz);
+        bool good = true;
+        if (i < M.n) {
+            a = M.rp[i];
+            b = M.rp[i + 1];
+            good = a >= 0 && a <= b && b <= M.nnz;
+            ok = ok && good && (i != 0 || a == 0) && (i != M.n - 1 || b == M.nnz);
+        }
+        if constexpr (SAMPLE) {
+            const bool has = good && b > a;
+            const unsigned off = has ? (unsigned)M.col[a] - (unsigned)i : 0u;
+            const unsigned long long v = has ? __builtin_bit_cast(unsigned long long, (double)M.val[a]) : 0ull;
+            const unsigned long long m = __ballot(has);
+            if (m) {
+                const int f = (int)__builtin_ctzll(m);
+                const unsigned of = __builtin_amdgcn_readlane(off, f);
+                const unsigned v0 = __builtin_amdgcn_readlane((unsigned)v, f), v1 = __builtin_amdgcn_readlane((unsigned)(v >> 32), f);
+                differ += __ballot(has && off == of && v != (((unsigned long long)v1 << 32) | v0)) != 0;
+            }
         }
         int len = max(0, b - a);
 #pragma unroll
@@ -46,11 +85,16 @@ __global__ void __launch_bounds__(256) k_row_widths(int n, int nnz, int nslices,
         if (lane == 0) w[s] = len;
         wmax = max(wmax, len);
     }
-    if (__ballot(!ok) != 0 && lane == 0) atomicOr(bad, 1);
-    if (lane == 0) atomicMax(&top, wmax);
+    if (__ballot(!ok) != 0 && lane == 0) atomicOr(&info->flags, 1);
+    if (lane == 0) {
+        atomicMax(&top, wmax);
+        if (SAMPLE && differ) atomicAdd(&vary, differ);
+    }
     __syncthreads();
-    if (threadIdx.x == 0 && __hip_atomic_load(max_len, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < top)
-        atomicMax(max_len, top);
+    if (threadIdx.x == 0) {
+        if (__hip_atomic_load(&info->max_len, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < top) atomicMax(&info->max_len, top);
+        if (SAMPLE && vary) atomicAdd(&info->varying, vary);
+    }
 }
 
 // out[j * stride] = 64 sum(len[0..j)) for j < m, and out[m * stride] too when
@@ -154,10 +198,9 @@ __device__ __forceinline__ void stage_rows(TV *win, const TV *__restrict__ src, 
 // need stored values, the others stop.
 template <typename TIN>
 __global__ void __launch_bounds__(64 * DW_WAVES)
-k_diag_align(int n, int nslices, long long sbase, const int *__restrict__ rp, const int *__restrict__ col,
-             const TIN *__restrict__ val, const long long *__restrict__ off, DiagEnt *__restrict__ de,
-             DiagSlice *__restrict__ ds, int *__restrict__ ulen, int *__restrict__ table, DotInfo *info,
-             int max_stored)
+k_diag_align(DiagCsr<TIN> one, const DiagCsr<TIN> *__restrict__ mats, int nmats, int nslices,
+             const long long *__restrict__ off, DiagEnt *__restrict__ de, DiagSlice *__restrict__ ds,
+             int *__restrict__ ulen, int *__restrict__ table, DotInfo *info, int max_stored)
 {
     __shared__ int cwin[DW_WAVES][DIAG_ROWS * DW_PITCH];
     __shared__ TIN vwin[DW_WAVES][DIAG_ROWS * DW_PITCH];
@@ -181,7 +224,12 @@ k_diag_align(int n, int nslices, long long sbase, const int *__restrict__ rp, co
             seen = 0;
             if (given_up()) break;
         }
-        const long long i = s * DIAG_ROWS + 2 * lane;
+        const DiagCsr<TIN> M = matrix_of<2>(one, mats, nmats, s);
+        const int n = M.n;
+        const int *__restrict__ rp = M.rp, *__restrict__ col = M.col;
+        const TIN *__restrict__ val = M.val;
+        const long long s128 = (s - M.slice0 / 2) * DIAG_ROWS;
+        const long long i = s128 + 2 * lane;
         int a[2], rem[2], p[2] = {0, 0}; // rem: entries from the window's start, p: consumed within the window
         a[0] = i < n ? rp[i] : 0;
         a[1] = i + 1 < n ? rp[i + 1] : 0;
@@ -189,7 +237,7 @@ k_diag_align(int n, int nslices, long long sbase, const int *__restrict__ rp, co
         rem[1] = i + 1 < n ? rp[i + 2] - a[1] : 0;
         const long long W = off[2 * s];
         const int limit = (int)((off[2 * s + 2] - W) >> 6) + 8;
-        const long long mpos = diag_mpos(W, s + sbase);
+        const long long mpos = diag_mpos(W, s);
         int u = 0, omin = 0, omax = 0, oprev = 0;
         bool cst = true, tri = true;
         unsigned long long h = 0, hv = 0; // hashes of the offsets and masks, and of the values
@@ -258,12 +306,11 @@ k_diag_align(int n, int nslices, long long sbase, const int *__restrict__ rp, co
         const int slot = (int)((h ^ (h >> 32)) & (DIAG_TABLE - 1)); // wavefront-uniform
         if (slot != claimed) { // the first slice of a slot represents it
             if (lane == 0 && __hip_atomic_load(&table[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == -1)
-                atomicCAS(&table[slot], -1, (int)(s + sbase));
+                atomicCAS(&table[slot], -1, (int)s);
             claimed = slot;
         }
         if (lane < DIAG_PAD) de[mpos + u + lane] = DiagEnt{0.0, {0ull, 0ull}, 0, 0.0f};
         if (lane == 0) {
-            const long long s128 = s * DIAG_ROWS;
             // the loops read up to two elements past a record's rows
             const bool clamp = s128 + omin < 0 || s128 + DIAG_ROWS + 2 + omax >= n;
             ds[s].vpos = slot; // until the values are placed
@@ -318,8 +365,7 @@ __global__ void __launch_bounds__(256) k_diag_share(int nslices, const DiagEnt *
 // (lanes without the entry store 0; they are masked out of the chain).
 template <typename TIN>
 __global__ void __launch_bounds__(64 * DW_WAVES)
-k_diag_fill(int n, int nslices, const int *__restrict__ rp, const TIN *__restrict__ val,
-            const DiagEnt *__restrict__ de, const DiagSlice *__restrict__ ds, double *__restrict__ sval64,
+k_diag_fill(DiagCsr<TIN> one, const DiagCsr<TIN> *__restrict__ mats, int nmats, int nslices, const DiagEnt *__restrict__ de, const DiagSlice *__restrict__ ds, double *__restrict__ sval64,
             float *__restrict__ sval32)
 {
     __shared__ TIN vwin[DW_WAVES][DIAG_ROWS * DW_PITCH];
@@ -332,7 +378,11 @@ k_diag_fill(int n, int nslices, const int *__restrict__ rp, const TIN *__restric
         const DiagSlice S = ds[s];
         if (S.flags & DIAG_CONST) continue;
         const int width = __builtin_amdgcn_readfirstlane(S.width);
-        const long long i = s * DIAG_ROWS + 2 * lane;
+        const DiagCsr<TIN> M = matrix_of<2>(one, mats, nmats, s);
+        const int n = M.n;
+        const int *__restrict__ rp = M.rp;
+        const TIN *__restrict__ val = M.val;
+        const long long i = (s - M.slice0 / 2) * DIAG_ROWS + 2 * lane;
         int a[2], rem[2], p[2] = {0, 0};
         a[0] = i < n ? rp[i] : 0;
         a[1] = i + 1 < n ? rp[i + 1] : 0;
@@ -362,15 +412,16 @@ k_diag_fill(int n, int nslices, const int *__restrict__ rp, const TIN *__restric
 // ---------------------------------------------------------------------------
 // Launch functions
 
-hipError_t launch_row_widths(int n, int nnz, const int *row_ptr, int *w, int *bad, int *max_len, hipStream_t s)
+template <typename TIN>
+hipError_t launch_row_widths(const DiagCsr<TIN> &one, const DiagCsr<TIN> *mats, int nmats, int nslices, bool sample, int *w,
+                             int *table, DotInfo *info, hipStream_t s)
 {
-    const int nslices = (n + DIAG_ROWS - 1) / DIAG_ROWS * 2;
     if (nslices == 0) return hipSuccess;
-    const int grid = (int)std::min<long long>((nslices + 3) / 4, 1024);
-    k_row_widths<<<grid, 256, 0, s>>>(n, nnz, nslices, row_ptr, w, bad, max_len);
+    const int grid = (int)std::min<long long>(((long long)nslices + 3) / 4, 1024);
+    if (sample) k_row_widths<TIN, true><<<grid, 256, 0, s>>>(one, mats, nmats, nslices, w, table, info);
+    else k_row_widths<TIN, false><<<grid, 256, 0, s>>>(one, mats, nmats, nslices, w, table, info);
     return hipGetLastError();
 }
-
 hipError_t launch_scan_len(const int *len, int m, long long *out, int stride, bool total, hipStream_t s)
 {
     if (m == 0) return hipSuccess;
@@ -378,21 +429,15 @@ hipError_t launch_scan_len(const int *len, int m, long long *out, int stride, bo
     return hipGetLastError();
 }
 
-hipError_t launch_diag_align(int n, long long sbase, const int *row_ptr, const int *col, const double *val64,
-                             const float *val32, const long long *off, DiagEnt *de, DiagSlice *ds, int *ulen,
-                             int *table, DotInfo *info, int max_stored, int num_cus, hipStream_t s)
+template <typename TIN>
+hipError_t launch_diag_align(const DiagCsr<TIN> &one, const DiagCsr<TIN> *mats, int nmats, int nslices, const long long *off,
+                             DiagEnt *de, DiagSlice *ds, int *ulen, int *table, DotInfo *info, int max_stored, int num_cus,
+                             hipStream_t s)
 {
-    const int nslices = (n + DIAG_ROWS - 1) / DIAG_ROWS;
     if (nslices == 0) return hipSuccess;
-    if ((val64 == nullptr) == (val32 == nullptr)) return hipErrorInvalidValue;
     // three workgroups a CU: what their windows leave room for
-    const int grid = (int)std::min<long long>((nslices + DW_WAVES - 1) / DW_WAVES, 3ll * num_cus);
-    if (val64)
-        k_diag_align<double><<<grid, 64 * DW_WAVES, 0, s>>>(n, nslices, sbase, row_ptr, col, val64, off, de, ds, ulen,
-                                                               table, info, max_stored);
-    else
-        k_diag_align<float><<<grid, 64 * DW_WAVES, 0, s>>>(n, nslices, sbase, row_ptr, col, val32, off, de, ds, ulen,
-                                                               table, info, max_stored);
+    const int grid = (int)std::min<long long>(((long long)nslices + DW_WAVES - 1) / DW_WAVES, 3ll * num_cus);
+    k_diag_align<TIN><<<grid, 64 * DW_WAVES, 0, s>>>(one, mats, nmats, nslices, off, de, ds, ulen, table, info, max_stored);
     return hipGetLastError();
 }
 
@@ -403,18 +448,25 @@ hipError_t launch_diag_share(int nslices, const DiagEnt *de, DiagSlice *ds, cons
     return hipGetLastError();
 }
 
-hipError_t launch_diag_fill(int n, const int *row_ptr, const double *val64, const float *val32, const DiagEnt *de,
+template <typename TIN>
+hipError_t launch_diag_fill(const DiagCsr<TIN> &one, const DiagCsr<TIN> *mats, int nmats, int nslices, const DiagEnt *de,
                             const DiagSlice *ds, double *sval64, float *sval32, hipStream_t s)
 {
-    const int nslices = (n + DIAG_ROWS - 1) / DIAG_ROWS;
     if (nslices == 0) return hipSuccess;
-    if ((val64 == nullptr) == (val32 == nullptr)) return hipErrorInvalidValue;
-    const int grid = (int)std::min<long long>((nslices + DW_WAVES - 1) / DW_WAVES, 8192);
-    if (val64)
-        k_diag_fill<double><<<grid, 64 * DW_WAVES, 0, s>>>(n, nslices, row_ptr, val64, de, ds, sval64, sval32);
-    else
-        k_diag_fill<float><<<grid, 64 * DW_WAVES, 0, s>>>(n, nslices, row_ptr, val32, de, ds, sval64, sval32);
+    const int grid = (int)std::min<long long>(((long long)nslices + DW_WAVES - 1) / DW_WAVES, 8192);
+    k_diag_fill<TIN><<<grid, 64 * DW_WAVES, 0, s>>>(one, mats, nmats, nslices, de, ds, sval64, sval32);
     return hipGetLastError();
 }
+
+#define RPCG_DIAG_LAUNCHERS(TIN)                                                                                            \
+    template hipError_t launch_row_widths<TIN>(const DiagCsr<TIN> &, const DiagCsr<TIN> *, int, int, bool, int *, int *,    \
+                                               DotInfo *, hipStream_t);                                                     \
+    template hipError_t launch_diag_align<TIN>(const DiagCsr<TIN> &, const DiagCsr<TIN> *, int, int, const long long *,     \
+                                               DiagEnt *, DiagSlice *, int *, int *, DotInfo *, int, int, hipStream_t);     \
+    template hipError_t launch_diag_fill<TIN>(const DiagCsr<TIN> &, const DiagCsr<TIN> *, int, int, const DiagEnt *,        \
+                                              const DiagSlice *, double *, float *, hipStream_t);
+RPCG_DIAG_LAUNCHERS(double)
+RPCG_DIAG_LAUNCHERS(float)
+#undef RPCG_DIAG_LAUNCHERS
 
 } // namespace rpcg

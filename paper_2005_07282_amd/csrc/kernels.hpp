@@ -40,7 +40,7 @@ constexpr int DOT_COPIES = 8, DOT_PITCH = 72, DOT_ESC = 70;
 
 // Scalars of a matrix copy's construction (device memory).
 struct DotInfo {
-    unsigned pad0;
+    int varying;         // slices whose first entries show that their values vary (see launch_row_widths)
     int flags;
     int max_len;         // longest row (SELL construction scratch)
     int pad1;
@@ -175,6 +175,15 @@ __host__ constexpr int diag_max_stored(long long nslices, int num_cus)
 }
 constexpr int DIAG_TABLE = 8192; // hash slots of record lists, a power of two (see k_diag_share)
 
+// A CSR matrix whose slices of 64 rows start at slice0.
+template <typename TIN>
+struct DiagCsr {
+    const int *rp, *col;
+    const TIN *val;
+    int n, nnz;
+    long long slice0;
+};
+
 // Column layouts of the solvers' matrix copies.
 enum { LAY_COL32 = 0, LAY_COL16 = 1, LAY_DIAG = 2 };
 
@@ -228,9 +237,13 @@ hipError_t launch_exp_range(long long n, const double *v, int *emin, int *emax, 
 hipError_t launch_spmv_csr(int n, long long nnz, const int *row_ptr, const int *col, const double *val,
                            const double *x, double *y, hipStream_t s);
 
-// Slice widths (longest row of each 64 rows, an even number of slices: the
-// last may be empty), longest row, and the check of row_ptr (*bad set if malformed).
-hipError_t launch_row_widths(int n, int nnz, const int *row_ptr, int *w, int *bad, int *max_len, hipStream_t s);
+// Slice widths (longest row of each 64 rows) into w, longest row, and the
+// check of row_ptr (info->flags set if malformed), of one matrix (slice0 = 0) or, with
+// nmats > 1, of all in mats (device memory, in order, each from an even slice0 on); rows past a matrix's
+// last are empty. table (DIAG_TABLE ints) is set to -1. sample: info->varying, a lower bound for twice the 128-row slices whose values vary.
+template <typename TIN>
+hipError_t launch_row_widths(const DiagCsr<TIN> &one, const DiagCsr<TIN> *mats, int nmats, int nslices, bool sample, int *w,
+                             int *table, DotInfo *info, hipStream_t s);
 // out[j stride] = 64 sum(len[0..j)), j < m (and j = m with `total`).
 hipError_t launch_scan_len(const int *len, int m, long long *out, int stride, bool total, hipStream_t s);
 // CSR structural check (*bad set if malformed), longest row, and the range of
@@ -238,18 +251,19 @@ hipError_t launch_scan_len(const int *len, int m, long long *out, int stride, bo
 // wavefront per 64-row slice.
 hipError_t launch_csr_scan(int n, int nnz, const int *row_ptr, const int *col, int *bad, int *max_len,
                            long long *max_delta, hipStream_t s);
-// Diagonal-aligned slices from a CSR whose row_ptr has been checked: the merge
-// (records, DiagSlice without vpos, ulen, column check, totals or diag_fail in
-// info; values from exactly one of val64 and val32; max_stored: slices, of all
-// matrices of an info, whose values may vary, else diag_fail; sbase = slices before this
-// matrix in de, in 128-row slices; off: 64 times the widths of the 64-row slices before; table: DIAG_TABLE ints set to -1), the sharing of equal record
-// lists (over all matrices of a table), and the stored values of the slices
-// that need them.
-hipError_t launch_diag_align(int n, long long sbase, const int *row_ptr, const int *col, const double *val64,
-                             const float *val32, const long long *off, DiagEnt *de, DiagSlice *ds, int *ulen,
-                             int *table, DotInfo *info, int max_stored, int num_cus, hipStream_t s);
+// Diagonal-aligned slices (nslices of 128 rows in all) from CSRs whose row_ptr have been
+// checked, matrices as above: the merge (records, DiagSlice without vpos, ulen, column check,
+// totals or diag_fail in info; max_stored: slices whose values may vary, else
+// diag_fail; off: 64 times the widths of the 64-row slices before; table: as
+// launch_row_widths leaves it), the sharing of equal record lists (over all matrices),
+// and the stored values of the slices that need them.
+template <typename TIN>
+hipError_t launch_diag_align(const DiagCsr<TIN> &one, const DiagCsr<TIN> *mats, int nmats, int nslices, const long long *off,
+                             DiagEnt *de, DiagSlice *ds, int *ulen, int *table, DotInfo *info, int max_stored, int num_cus,
+                             hipStream_t s);
 hipError_t launch_diag_share(int nslices, const DiagEnt *de, DiagSlice *ds, const int *table, hipStream_t s);
-hipError_t launch_diag_fill(int n, const int *row_ptr, const double *val64, const float *val32, const DiagEnt *de,
+template <typename TIN>
+hipError_t launch_diag_fill(const DiagCsr<TIN> &one, const DiagCsr<TIN> *mats, int nmats, int nslices, const DiagEnt *de,
                             const DiagSlice *ds, double *sval64, float *sval32, hipStream_t s);
 
 // Fill the sliced-ELL arrays from the CSR. The source values are binary64
