@@ -412,7 +412,7 @@ static int batch_create_body(rpcg_batch *B, const rpcg_csr *A, hipStream_t calle
     RPCG_TRY(hipEventCreateWithFlags(&B->stage_ev[1], hipEventDisableTiming));
     // layout: each system's rows start at a multiple of 128, its slices after the previous system's
     B->sys.resize(B->nsys);
-    long long row0 = 0, slice0 = 0;
+    long long row0 = 0, slice0 = 0, words = 0; // words: the dots' accumulators
     for (int q = 0; q < B->nsys; ++q) {
         BatchSys &S = B->sys[q];
         S.row0 = row0;
@@ -421,6 +421,9 @@ static int batch_create_body(rpcg_batch *B, const rpcg_csr *A, hipStream_t calle
         S.nslices = (A[q].n + 63) / 64;
         S.slot0 = S.slot1 = 0;
         S.row_ptr = A[q].row_ptr;
+        S.acc0 = words;
+        S.copies = batch_copies(S.nslices);
+        words += 3 * S.copies * DOT_PITCH;
         slice0 += (S.nslices + 1) / 2 * 2; // an even number of 64-row slices: whole 128-row slices
         row0 = 64 * slice0;
     }
@@ -510,7 +513,7 @@ static int batch_create_body(rpcg_batch *B, const rpcg_csr *A, hipStream_t calle
     RPCG_TRY(B->vecs.ensure(sizeof(double) * 7 * (size_t)B->total_rows));
     RPCG_TRY(hipMemsetAsync(B->vecs.p, 0, sizeof(double) * 7 * (size_t)B->total_rows, B->gs));
     RPCG_TRY(B->st.ensure(sizeof(PcgState) * B->nsys));
-    RPCG_TRY(B->acc.ensure(sizeof(long long) * 3 * DOT_COPIES * DOT_PITCH * (size_t)B->nsys));
+    RPCG_TRY(B->acc.ensure(sizeof(long long) * (size_t)words));
     RPCG_TRY(B->hist_ptrs.ensure(sizeof(double *) * B->nsys));
     RPCG_TRY(B->active.ensure(sizeof(int)));
     B->host_st.resize(B->nsys);

@@ -48,11 +48,12 @@ __device__ __forceinline__ SlotView batch_slots(const SlotView &v, int g0)
     return o;
 }
 
-// Dot d of system `sys` (S its record).
-__device__ __forceinline__ DotWs batch_dot(const BatchArgs &a, int sys, const BatchSys &S, int d)
+// Dot d of system S, and the copies of its accumulators (uniform).
+__device__ __forceinline__ int batch_dot_copies(const BatchSys &S) { return __builtin_amdgcn_readfirstlane((int)S.copies); }
+__device__ __forceinline__ DotWs batch_dot(const BatchArgs &a, const BatchSys &S, int d)
 {
     DotWs w{};
-    w.acc = a.acc + ((long long)sys * 3 + d) * (DOT_COPIES * DOT_PITCH);
+    w.acc = a.acc + S.acc0 + (long long)d * batch_dot_copies(S) * DOT_PITCH;
     w.part = a.part + (long long)d * a.part_cap + S.slot0;
     return w;
 }

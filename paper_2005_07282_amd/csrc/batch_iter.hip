@@ -39,13 +39,14 @@ __global__ void __launch_bounds__(MAX_BLOCK) k_batch_spmv_dot(BatchArgs a, bool 
         if (R.s0 == 0 && threadIdx.x == 0) st->it_cur = st->iter;
         if (st->done) continue;
         const BatchSys S = a.sys[R.sys];
+        const int copies = batch_dot_copies(S);
         const SellMat<double> M = batch_mat(a, S);
         const double *__restrict__ d = a.d + S.row0;
         double *__restrict__ w = a.w + S.row0;
-        const DotWs wd = batch_dot(a, R.sys, S, 0);
+        const DotWs wd = batch_dot(a, S, 0);
         if (MODE != MODE_PLAIN && R.s0 == 0) { // the direction kernel has read them
-            clear_dot(batch_dot(a, R.sys, S, 1));
-            clear_dot(batch_dot(a, R.sys, S, 2));
+            clear_dot(batch_dot(a, S, 1), copies);
+            clear_dot(batch_dot(a, S, 2), copies);
         }
         __syncthreads(); // the previous run's accumulator has been published before it is reused
         zero_acc(sh.acc[0]);
@@ -62,7 +63,7 @@ __global__ void __launch_bounds__(MAX_BLOCK) k_batch_spmv_dot(BatchArgs a, bool 
             for (int r = 0; r < NR; ++r)
                 if (i + r < M.n) L.add(di[r], sum[r], sh.acc[0], ee, capture);
         });
-        block_publish<MODE, P, 1, false>({&L}, {sh.acc[0]}, {&wd}, R.slot - S.slot0, ee, capture, &st->flags, sh);
+        block_publish<MODE, P, 1, false>({&L}, {sh.acc[0]}, {&wd}, R.slot - S.slot0, ee, capture, &st->flags, sh, copies);
     }
 }
 
@@ -77,6 +78,7 @@ __global__ void __launch_bounds__(MAX_BLOCK) k_batch_update(BatchArgs a, bool ee
         const BatchRun R = a.runs[ri];
         PcgState *st = a.st + R.sys;
         const BatchSys S = a.sys[R.sys];
+        const int copies = batch_dot_copies(S);
         const bool lead = R.s0 == 0;
         const int i1 = (int)min((long long)R.s1 * 64, (long long)S.n);
         long long i = (long long)R.s0 * 64 + 2 * threadIdx.x;
@@ -92,7 +94,7 @@ __global__ void __launch_bounds__(MAX_BLOCK) k_batch_update(BatchArgs a, bool ee
         if (wave_id() == 0) {
             const int done = coherent_int(&st->done), flags = coherent_int(&st->flags);
             long long esc;
-            const double d = wave_merge<MODE>(batch_dot(a, R.sys, S, 0), S.slot1 - S.slot0, &esc);
+            const double d = wave_merge<MODE>(batch_dot(a, S, 0), S.slot1 - S.slot0, &esc, copies);
             if (lane_id() == 0) {
                 sh.flag = done; // set in this kernel only by a breakdown every run sees
                 sh.rng[0] = flags;
@@ -147,9 +149,9 @@ __global__ void __launch_bounds__(MAX_BLOCK) k_batch_update(BatchArgs a, bool ee
                     Lt.add(ri[r], ri[r], sh.acc[1], ee, capture);          // S8
                 }
         }
-        const DotWs wb = batch_dot(a, R.sys, S, 1), wt = batch_dot(a, R.sys, S, 2);
+        const DotWs wb = batch_dot(a, S, 1), wt = batch_dot(a, S, 2);
         block_publish<MODE, P, 2, false>({&Lb, &Lt}, {sh.acc[0], sh.acc[1]}, {&wb, &wt}, R.slot - S.slot0, ee, capture,
-                                         &st->flags, sh);
+                                         &st->flags, sh, copies);
     }
 }
 
@@ -166,6 +168,7 @@ __global__ void __launch_bounds__(MAX_BLOCK) k_batch_direction(BatchArgs a, bool
         const BatchRun R = a.runs[ri];
         PcgState *st = a.st + R.sys;
         const BatchSys S = a.sys[R.sys];
+        const int copies = batch_dot_copies(S);
         const bool lead = R.s0 == 0;
         const int i1 = (int)min((long long)R.s1 * 64, (long long)S.n);
         const long long step = 2 * blockDim.x;
@@ -191,7 +194,7 @@ __global__ void __launch_bounds__(MAX_BLOCK) k_batch_direction(BatchArgs a, bool
         if (wv == 0) {
             const int ended = coherent_int(&st->ended) <= it, flags = coherent_int(&st->flags);
             long long esc;
-            const double b = wave_merge<MODE>(batch_dot(a, R.sys, S, 1), G, &esc);
+            const double b = wave_merge<MODE>(batch_dot(a, S, 1), G, &esc, copies);
             if (lane_id() == 0) {
                 sh.flag = ended;
                 sh.rng[0] = flags;
@@ -201,7 +204,7 @@ __global__ void __launch_bounds__(MAX_BLOCK) k_batch_direction(BatchArgs a, bool
         }
         if (wv == (num_waves() > 1 ? 1 : 0)) {
             long long esc;
-            const double t = wave_merge<MODE>(batch_dot(a, R.sys, S, 2), G, &esc);
+            const double t = wave_merge<MODE>(batch_dot(a, S, 2), G, &esc, copies);
             if (lane_id() == 0) {
                 sh.val[1] = t;
                 sh.red_ll[1] = esc;
@@ -213,7 +216,7 @@ __global__ void __launch_bounds__(MAX_BLOCK) k_batch_direction(BatchArgs a, bool
         const bool bad = (sh.rng[0] & FLAG_NONFINITE) || !is_finite_bits(beta) || !is_finite_bits(tau);
         const bool stop = bad || tau <= thr || it + 1 >= maxit;
         const double gamma = beta / beta_old;
-        if (MODE != MODE_PLAIN && lead) clear_dot(batch_dot(a, R.sys, S, 0)); // K2 has read it
+        if (MODE != MODE_PLAIN && lead) clear_dot(batch_dot(a, S, 0), copies); // K2 has read it
         if (lead && threadIdx.x == 0) {
             const long long eb = sh.red_ll[0], et = sh.red_ll[1];
             if (eb + et) st->escapes += eb + et;

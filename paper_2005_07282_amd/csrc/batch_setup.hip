@@ -9,7 +9,8 @@ namespace rpcg {
 __global__ void __launch_bounds__(256) k_batch_state_init(BatchArgs a, int maxit)
 {
     const int sys = blockIdx.x;
-    for (int d = 0; d < 3; ++d) clear_dot(batch_dot(a, sys, a.sys[sys], d));
+    const BatchSys S = a.sys[sys];
+    for (int d = 0; d < 3; ++d) clear_dot(batch_dot(a, S, d), batch_dot_copies(S));
     if (threadIdx.x != 0) return;
     if (sys == 0) *a.active = a.nsys;
     PcgState z = {};
@@ -22,9 +23,9 @@ __global__ void __launch_bounds__(256) k_batch_state_init(BatchArgs a, int maxit
 // out-of-line call, which keeps the inlined copies (and compile time) down.
 template <int MODE, int P>
 __device__ __noinline__ void batch_setup_publish(LaneDot<MODE, P> &L, long long *acc, const DotWs &w, int g, bool ee,
-                                                 bool capture, int *gflags, RedShared &sh)
+                                                 bool capture, int *gflags, RedShared &sh, int copies)
 {
-    block_publish<MODE, P, 1, false>({&L}, {acc}, {&w}, g, ee, capture, gflags, sh);
+    block_publish<MODE, P, 1, false>({&L}, {acc}, {&w}, g, ee, capture, gflags, sh, copies);
 }
 
 template <int MODE, int P, int LAY>
@@ -79,10 +80,10 @@ k_batch_setup(BatchArgs a, bool ee, bool capture)
         });
         if (flags) atomicOr(&a.st[R.sys].flags, flags);
         int *gf = &a.st[R.sys].flags;
-        const int g = R.slot - S.slot0;
-        batch_setup_publish<MODE, P>(Lb, sh.acc[0], batch_dot(a, R.sys, S, 0), g, ee, capture, gf, sh);
-        batch_setup_publish<MODE, P>(Lt, sh.acc[1], batch_dot(a, R.sys, S, 1), g, ee, capture, gf, sh);
-        batch_setup_publish<MODE, P>(Lbb, sh.acc[2], batch_dot(a, R.sys, S, 2), g, ee, capture, gf, sh);
+        const int g = R.slot - S.slot0, copies = batch_dot_copies(S);
+        batch_setup_publish<MODE, P>(Lb, sh.acc[0], batch_dot(a, S, 0), g, ee, capture, gf, sh, copies);
+        batch_setup_publish<MODE, P>(Lt, sh.acc[1], batch_dot(a, S, 1), g, ee, capture, gf, sh, copies);
+        batch_setup_publish<MODE, P>(Lbb, sh.acc[2], batch_dot(a, S, 2), g, ee, capture, gf, sh, copies);
     }
 }
 
@@ -98,14 +99,14 @@ __global__ void __launch_bounds__(256) k_batch_fin_setup(BatchArgs a, double tol
     const int wv = wave_id();
     if (wv < 3) {
         long long esc;
-        const double d = wave_merge<MODE>(batch_dot(a, sys, S, wv), S.slot1 - S.slot0, &esc);
+        const double d = wave_merge<MODE>(batch_dot(a, S, wv), S.slot1 - S.slot0, &esc, batch_dot_copies(S));
         if (lane_id() == 0) {
             sh.val[wv] = d;
             sh.red_ll[wv] = esc;
         }
     }
     __syncthreads();
-    for (int d = 0; d < 3; ++d) clear_dot(batch_dot(a, sys, S, d));
+    for (int d = 0; d < 3; ++d) clear_dot(batch_dot(a, S, d), batch_dot_copies(S));
     const double beta = sh.val[0], tau = sh.val[1], bb = sh.val[2];
     const long long e0 = sh.red_ll[0], e1 = sh.red_ll[1], e2 = sh.red_ll[2];
     if (threadIdx.x == 0) {

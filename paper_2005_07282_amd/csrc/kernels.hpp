@@ -375,7 +375,20 @@ struct BatchSys {
     int slot0;
     int slot1;
     const int *row_ptr; // the caller's CSR row pointers of the system
+    long long acc0;     // first word of its dots' accumulators
+    long long copies;   // copies of each (see batch_copies)
 };
+
+// Accumulator copies of a system's dots: one per run that its size allows at a time
+// (runs have 16 slices on average, or more, but for hand-set tiles). Eight for every system made
+// batches of thousands of small ones clear and read more accumulators than
+// vectors (4096 systems of 64 rows 200 us an iteration and 13.8 KB a system, now
+// 179 us with the same schedule and 1.7 KB; 20 000 of 27 rows 658 and 553 us).
+__host__ constexpr int batch_copies(int nslices)
+{
+    const int c = (nslices + 15) / 16;
+    return c < 1 ? 1 : (c < DOT_COPIES ? c : DOT_COPIES);
+}
 
 // One run of work: slices [s0, s1) of system `sys`, processed by one
 // workgroup, number `slot` of all runs (those of a system are consecutive).
@@ -404,7 +417,7 @@ struct BatchArgs {
     const double *b;
     double *x, *r, *z, *d, *w, *dinv;
     PcgState *st;          // [nsys]
-    long long *acc;        // [nsys][3][DOT_COPIES][DOT_PITCH] accumulators of each system's dots
+    long long *acc;        // accumulators of the systems' dots: [3][copies][DOT_PITCH] from acc0 on
     double *part;          // [3][part_cap] workgroup sums (plain), by slot
     int part_cap;
     double *const *hist;   // [nsys] tau histories (maxit + 1 each, entries may be null), or null

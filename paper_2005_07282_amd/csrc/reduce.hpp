@@ -920,11 +920,11 @@ __device__ __forceinline__ T merge_slots(const SlotView &sv, int G, bool ee, boo
 
 // Add the workgroup accumulators of D dots (LDS) to their global copies, after
 // the lanes' expansions have gone in; escapes and flags too. g: the workgroup's
-// number among those that add to these dots. All threads call.
+// number among those that add to these dots. A batch's systems have fewer copies. All threads call.
 template <int MODE, int P, int D, bool ADAPT>
 __device__ __forceinline__ void block_publish(LaneDot<MODE, P, ADAPT> *const (&L)[D], long long *const (&acc)[D],
                                               const DotWs *const (&w)[D], int g, bool ee, bool capture, int *gflags,
-                                              RedShared &sh)
+                                              RedShared &sh, int copies = DOT_COPIES)
 {
     if constexpr (MODE == MODE_PLAIN) {
 #pragma unroll
@@ -961,7 +961,7 @@ __device__ __forceinline__ void block_publish(LaneDot<MODE, P, ADAPT> *const (&L
 #pragma unroll
         for (int d = 0; d < D; ++d) fl |= L[d]->flags;
         __syncthreads();
-        const int copy = g % DOT_COPIES;
+        const int copy = g % copies;
         for (int q = threadIdx.x; q < D * ACC_DIGITS; q += blockDim.x) {
             const int d = D == 1 ? 0 : q / ACC_DIGITS, k = q - d * ACC_DIGITS;
             // one carry step keeps every word below 2^33 in magnitude, so the
@@ -980,7 +980,7 @@ __device__ __forceinline__ void block_publish(LaneDot<MODE, P, ADAPT> *const (&L
 // The scalar of one dot, by one full wavefront: rounded once (every lane
 // returns it), escapes into *esc. PLAIN: the G workgroup sums in a fixed order.
 template <int MODE, typename T = double>
-__device__ __forceinline__ T wave_merge(const DotWs &w, int G, long long *esc)
+__device__ __forceinline__ T wave_merge(const DotWs &w, int G, long long *esc, int copies = DOT_COPIES)
 {
     const int l = lane_id();
     *esc = 0;
@@ -998,7 +998,10 @@ __device__ __forceinline__ T wave_merge(const DotWs &w, int G, long long *esc)
         if (l < DOT_PITCH / 2) {
             longlong2 q[DOT_COPIES];
 #pragma unroll
-            for (int c = 0; c < DOT_COPIES; ++c) q[c] = ((const longlong2 *)(w.acc + c * DOT_PITCH))[l];
+            for (int c = 0; c < DOT_COPIES; ++c) {
+                q[c] = longlong2{0, 0};
+                if (c < copies) q[c] = ((const longlong2 *)(w.acc + c * DOT_PITCH))[l];
+            }
 #pragma unroll
             for (int c = 0; c < DOT_COPIES; ++c) { a += q[c].x; b += q[c].y; }
         }
@@ -1009,9 +1012,9 @@ __device__ __forceinline__ T wave_merge(const DotWs &w, int G, long long *esc)
 }
 
 // Empty a dot's accumulators (one workgroup, for adds of a later kernel).
-__device__ __forceinline__ void clear_dot(const DotWs &w)
+__device__ __forceinline__ void clear_dot(const DotWs &w, int copies = DOT_COPIES)
 {
-    for (int k = threadIdx.x; k < DOT_COPIES * DOT_PITCH; k += blockDim.x) w.acc[k] = 0;
+    for (int k = threadIdx.x; k < copies * DOT_PITCH; k += blockDim.x) w.acc[k] = 0;
 }
 
 template <int V>
