@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "rpcg.h"
+#include "batch_tuning.hpp"
 #include "context.hpp"
 #include "kernels.hpp"
 
@@ -60,20 +61,6 @@ bool valid_tuning(const rpcg_batch_tuning &t)
     return (t.policy == 0 || t.policy == 1) && t.tile_slices >= 1 && t.grid_size >= 1 && t.grid_size <= 65536 &&
            t.block_size >= 64 && t.block_size <= MAX_BLOCK && t.block_size % 64 == 0 && t.graph_iterations >= 1 &&
            t.graph_iterations <= 64;
-}
-
-rpcg_batch_tuning default_tuning(const rpcg_ctx *c, long long slices)
-{
-    rpcg_batch_tuning t{};
-    t.policy = 0;
-    t.tile_slices = 16;
-    // two workgroups of 512 a CU where they have work for it (64 systems of
-    // 16^3 to 96^3: 115 ms; 121 ms with 256 threads; 4 of 60^3 to 70^3: 13.0 ms
-    // against 14.7 ms with one), one for small batches (60 of 16^3 to 30^3: 4.9 ms against 5.3 ms)
-    t.grid_size = (slices >= 32ll * 2 * c->num_cus ? 2 : 1) * c->num_cus;
-    t.block_size = 512;
-    t.graph_iterations = 8;
-    return t;
 }
 
 // The workgroup sums of the plain mode, by slot (the exact modes' accumulators are per system).
@@ -518,7 +505,7 @@ static int batch_create_body(rpcg_batch *B, const rpcg_csr *A, hipStream_t calle
     RPCG_TRY(B->active.ensure(sizeof(int)));
     B->host_st.resize(B->nsys);
     auto it = c->batch_tunings.find(B->signature);
-    B->tuning = it != c->batch_tunings.end() ? it->second : default_tuning(c, B->total_slices);
+    B->tuning = it != c->batch_tunings.end() ? it->second : default_tuning(c->num_cus, B->total_slices, B->nsys);
     int rc = build_schedule(B);
     if (rc != RPCG_OK) return rc;
     RPCG_TRY(hipStreamSynchronize(B->gs));
@@ -578,24 +565,8 @@ int rpcg_batch_tune(rpcg_batch *B, const double *const *b, int32_t trial_iterati
     RPCG_TRY(hipEventRecord(B->ev_in, (hipStream_t)stream));
     RPCG_TRY(hipStreamWaitEvent(B->gs, B->ev_in, 0));
     const int cu = B->ctx->num_cus;
-    std::vector<rpcg_batch_tuning> cand;
-    auto mk = [&](int policy, int tile, int grid, int block) {
-        rpcg_batch_tuning t{};
-        t.policy = policy;
-        t.tile_slices = tile;
-        t.grid_size = grid;
-        t.block_size = block;
-        t.graph_iterations = B->tuning.graph_iterations;
-        cand.push_back(t);
-    };
-    mk(0, 16, cu, 256);
-    mk(0, 16, 2 * cu, 256);
-    mk(0, 16, 4 * cu, 256);
-    mk(0, 16, 2 * cu, 512);
-    mk(0, 16, cu, 1024);
-    mk(1, 16, 2 * cu, 256);
-    mk(1, 64, 2 * cu, 256);
-    mk(1, 256, cu, 512);
+    std::vector<rpcg_batch_tuning> cand =
+        tuning_candidates(default_tuning(cu, B->total_slices, B->nsys), cu, B->tuning.graph_iterations);
     const rpcg_batch_tuning keep = B->tuning;
     // two rounds over the candidates, each keeping its faster trial: one
     // short trial per candidate left the choice to run-to-run noise
