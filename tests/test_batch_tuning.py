@@ -47,3 +47,24 @@ def test_the_default_is_a_candidate(tmp_path):
     for line in lines:
         cus, slices, nsys, same, twice, valid = map(int, line.split())
         assert same == 1 and twice == 0 and valid == 1, line
+
+
+def test_small_systems_get_a_workgroup_each(tmp_path):
+    """Workgroups of one or two wavefronts where a system has no slices for more."""
+    src, exe = tmp_path / "t.cpp", tmp_path / "t"
+    src.write_text(r"""
+#include "batch_tuning.hpp"
+#include <cstdio>
+int main()
+{
+    for (long long per : {1ll, 2ll, 8ll, 16ll, 43ll, 64ll, 1000ll}) {
+        const rpcg_batch_tuning d = rpcg_host::default_tuning(256, per * 4096, 4096);
+        std::printf("%lld %d %d\n", per, d.block_size, d.grid_size);
+    }
+}
+""")
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I",
+                    os.path.join(ROOT, "paper_2005_07282_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    got = [tuple(map(int, x.split())) for x in subprocess.run([str(exe)], capture_output=True, text=True, check=True).stdout.split("\n")[:-1]]
+    for per, block, grid in got:
+        assert block // 64 <= max(1, per) and block * grid >= 256 * 512, (per, block, grid)
