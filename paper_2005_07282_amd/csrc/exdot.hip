@@ -280,8 +280,7 @@ __global__ void k_acc_round(const long long *digits, double *out)
 // chains and its x entries gathered right after them, so rows longer than a
 // chunk's share no longer leave the memory idle while their chains run.
 
-constexpr int SPMV_E = 2048;  // chunk of entries staged at a time
-constexpr int SPMV_CUS = 256; // CUs of the device
+constexpr int SPMV_E = 2048; // chunk of entries staged at a time
 
 template <int R, int E>
 __global__ void __launch_bounds__(R)
@@ -374,7 +373,7 @@ hipError_t launch_acc_round(const long long *digits, double *out, hipStream_t s)
 }
 
 hipError_t launch_spmv_csr(int n, long long nnz, const int *row_ptr, const int *col, const double *val,
-                           const double *x, double *y, hipStream_t s)
+                           const double *x, double *y, int num_cus, hipStream_t s)
 {
     if (n == 0) return hipSuccess;
     auto run = [&](auto rows) {
@@ -395,9 +394,9 @@ hipError_t launch_spmv_csr(int n, long long nnz, const int *row_ptr, const int *
     // and 41, of 100 k 188 and 72, of 200 k 204 and 131; 27 points on 22 k rows 15.0 and 6.4,
     // on 64 k 16.4 and 7.7, on 216 k 20.1 and 16.7). Large matrices keep 512: 4.1 M
     // rows of 27 points 272 us against 282 us with 256, the band of 1 M rows 504 and 524 us.
-    if (n >= 512 * 3 * SPMV_CUS) run(std::integral_constant<int, 512>{});
-    else if (n >= 256 * 2 * SPMV_CUS) run(std::integral_constant<int, 256>{});
-    else if (n >= 128 * 2 * SPMV_CUS) run(std::integral_constant<int, 128>{});
+    if (n >= 512ll * 3 * num_cus) run(std::integral_constant<int, 512>{});
+    else if (n >= 256ll * 2 * num_cus) run(std::integral_constant<int, 256>{});
+    else if (n >= 128ll * 2 * num_cus) run(std::integral_constant<int, 128>{});
     else run(std::integral_constant<int, 64>{});
     return hipGetLastError();
 }

@@ -232,10 +232,10 @@ hipError_t launch_exdot_partial(long long n, const double *x, const double *y, l
 hipError_t launch_acc_round(const long long *digits, double *out, hipStream_t s);
 // Exponent range (floor(log2 |v|)) of the nonzero finite entries of v, merged into *emin, *emax.
 hipError_t launch_exp_range(long long n, const double *v, int *emin, int *emax, hipStream_t s);
-// CSR SpMV (nnz = row_ptr[n]): workgroups of 512 rows, one per row block;
-// the staging chunk is chosen by the average row length.
+// CSR SpMV (nnz = row_ptr[n]): workgroups of 64 to 512 rows by the number that
+// n leaves for num_cus CUs; the staging chunk is chosen by the average row length.
 hipError_t launch_spmv_csr(int n, long long nnz, const int *row_ptr, const int *col, const double *val,
-                           const double *x, double *y, hipStream_t s);
+                           const double *x, double *y, int num_cus, hipStream_t s);
 
 // Slice widths (longest row of each 64 rows) into w, longest row, and the
 // check of row_ptr (info->flags set if malformed), of one matrix (slice0 = 0) or, with
