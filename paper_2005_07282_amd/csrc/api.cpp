@@ -763,7 +763,8 @@ static int ir_body(rpcg_ctx *c, int mode, const rpcg_csr *A, const double *b, do
     rpcg_opts dflt;
     rpcg_opts_default(&dflt);
     dflt.fpe_size = 3;
-    LaunchCfg cfg_dot = make_cfg(c, dflt, std::max(1, (n + 7) / 8), 256, s);
+    LaunchCfg cfg_dot = make_cfg(c, dflt, std::max(1, n), 1024, s); // the shape of a standalone dot
+    cfg_dot.grid = exdot_grid(MODE_EXBLAS, n, cfg_dot.block, c->num_cus);
     rc = ensure_ws(c, std::max(std::max(cfg_rows.grid, cfg_sl.grid), std::max(cfg_res.grid, cfg_dot.grid)));
     if (rc != RPCG_OK) return rc;
     SellMat<float> M = sell_mat<float>(B, B.val32, n, A->row_ptr);
