@@ -24,23 +24,18 @@ static int ensure_ws(rpcg_ctx *c, int groups)
 {
     if (groups <= c->ws_groups) return RPCG_OK;
     const size_t acc_bytes = DOT_COPIES * DOT_PITCH * sizeof(long long);
-    size_t per = (size_t)groups * (ACC_WORDS * sizeof(long long) + 2 * sizeof(int) +
-                                   MAX_FPE * sizeof(double) + sizeof(int));
-    per = acc_bytes + (per + 255) / 256 * 256;
-    RPCG_TRY(c->ws_mem.ensure(3 * per));
-    char *base = (char *)c->ws_mem.p;
-    for (int i = 0; i < 3; ++i) {
-        char *b = base + i * per;
-        c->ws[i].acc = (long long *)b;
-        b += acc_bytes;
-        c->ws[i].digits = (long long *)b;
-        b += (size_t)groups * ACC_WORDS * sizeof(long long);
-        c->ws[i].part = (double *)b;
-        b += (size_t)groups * MAX_FPE * sizeof(double);
-        c->ws[i].range = (int *)b;
-        b += (size_t)groups * 2 * sizeof(int);
-        c->ws[i].esc = (int *)b;
+    const size_t per = acc_bytes + ((size_t)groups * sizeof(double) + 255) / 256 * 256;
+    const size_t digits = (size_t)groups * ACC_WORDS * sizeof(long long);
+    c->ws_groups = 0; // nothing is usable if the allocation fails
+    RPCG_TRY(c->ws_mem.ensure(3 * per + digits + (size_t)groups * 2 * sizeof(int)));
+    char *b = (char *)c->ws_mem.p;
+    for (DotWs &w : c->ws) {
+        w.acc = (long long *)b;
+        w.part = (double *)(b + acc_bytes);
+        b += per;
     }
+    c->slots.digits = (long long *)b;
+    c->slots.range = (int *)(b + digits);
     c->ws_groups = groups;
     return RPCG_OK;
 }
@@ -796,9 +791,9 @@ static int ir_body(rpcg_ctx *c, int mode, const rpcg_csr *A, const double *b, do
         auto to = std::chrono::steady_clock::now();
         hipEvent_t *ev = timing ? &c->ir_events[2 * (size_t)k] : nullptr;
         if (ev) RPCG_TRY(hipEventRecord(ev[0], s));
-        RPCG_TRY(launch_ir_residual(M, b, x, r, ist, c->ws[0], stride, cfg_res));
+        RPCG_TRY(launch_ir_residual(M, b, x, r, ist, c->slots, stride, cfg_res));
         if (ev) RPCG_TRY(hipEventRecord(ev[1], s));
-        RPCG_TRY(launch_ir_prepare(k, io.maxit, io.tol, n, r, rf, cv, io.rr_history, ist, c->ws[0], cfg_res.grid,
+        RPCG_TRY(launch_ir_prepare(k, io.maxit, io.tol, n, r, rf, cv, io.rr_history, ist, c->slots, cfg_res.grid,
                                    stride, cfg_rows));
         RPCG_TRY(hipMemcpyAsync(H, ist, sizeof(IrState), hipMemcpyDeviceToHost, s));
         RPCG_TRY(hipStreamSynchronize(s));

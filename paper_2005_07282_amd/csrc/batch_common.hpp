@@ -1,5 +1,5 @@
 // Helpers shared by the batched-solve kernels: the per-system view of the
-// concatenated matrix copy and of the dot-partial slots.
+// concatenated matrix copy and of its dots.
 #pragma once
 
 #include "reduce.hpp"
@@ -34,18 +34,6 @@ __device__ __forceinline__ SliceRange batch_slices(const BatchRun &R, int wave, 
     const int s0 = __builtin_amdgcn_readfirstlane(R.s0), s1 = __builtin_amdgcn_readfirstlane(R.s1);
     if constexpr (LAY == LAY_DIAG) return {s0 / 2 + wave, (s1 + 1) / 2, W};
     else return {s0 + wave, s1, W};
-}
-
-// Slots [g0, ...) of a workspace seen as slots [0, ...).
-template <int MODE>
-__device__ __forceinline__ SlotView batch_slots(const SlotView &v, int g0)
-{
-    SlotView o = v;
-    o.ws.digits += g0;
-    o.ws.range += 2 * g0;
-    o.ws.part += (MODE == MODE_PLAIN) ? (long long)g0 : (long long)g0 * MAX_FPE;
-    o.ws.esc += g0;
-    return o;
 }
 
 // Dot d of system S, and the copies of its accumulators (uniform).

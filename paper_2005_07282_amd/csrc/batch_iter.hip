@@ -160,7 +160,7 @@ __global__ void __launch_bounds__(MAX_BLOCK) k_batch_update(BatchArgs a, bool ee
 // stops) S7, BATCH_DIR row pairs per thread loaded at a time, the first while
 // the dots are merged.
 constexpr int BATCH_DIR = 4;
-template <int MODE, int P>
+template <int MODE>
 __global__ void __launch_bounds__(MAX_BLOCK) k_batch_direction(BatchArgs a, bool capture)
 {
     __shared__ RedShared sh;
@@ -263,7 +263,7 @@ hipError_t launch_batch_iteration(int mode, int layout, const BatchArgs &a, int 
             k_batch_spmv_dot<M, PP, decltype(lay)::value><<<grid, block, 0, c.stream>>>(a, c.early_exit, c.fallback);
         });
         k_batch_update<M, PP><<<grid, block, 0, c.stream>>>(a, c.early_exit, c.fallback);
-        k_batch_direction<M, PP><<<grid, block, 0, c.stream>>>(a, c.fallback);
+        k_batch_direction<M><<<grid, block, 0, c.stream>>>(a, c.fallback);
     });
     return hipGetLastError();
 }

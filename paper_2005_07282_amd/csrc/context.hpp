@@ -43,8 +43,9 @@ struct rpcg_ctx {
     int device = 0;
     int num_cus = 256;
     int ws_groups = 0;        // capacity of the dot workspaces, in workgroups
-    rpcg_host::Buffer ws_mem; // 3 dot workspaces
+    rpcg_host::Buffer ws_mem; // 3 dot workspaces, the refinement's slots
     rpcg::DotWs ws[3];
+    rpcg::SlotWs slots{};
     rpcg_host::Buffer scalars; // DotInfo + PcgState + IrState
     rpcg::DotInfo *info = nullptr;
     rpcg::PcgState *st = nullptr;

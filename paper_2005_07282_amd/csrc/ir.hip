@@ -138,7 +138,7 @@ k_ir_residual(SellMat<float> A, const double *__restrict__ b, const double *__re
         }
     }
     if (flags) atomicOr(&ist->flags, flags);
-    block_finish<MODE_EXBLAS, IR_DOT_P>(L, sh.acc[0], sv, blockIdx.x, true, true, &ist->flags, sh);
+    block_finish<IR_DOT_P>(L, sh.acc[0], sv, blockIdx.x, &ist->flags, sh);
 }
 
 // floor(log2 v) of a positive finite double (subnormals included).
@@ -162,9 +162,7 @@ k_ir_prepare(int k, int maxit, double tol, int n, const double *__restrict__ r, 
 {
     __shared__ RedShared sh;
     if (wg_read_flag(&ist->stop, sh)) return;
-    long long esc = 0;
-    const double rr = merge_slots<MODE_EXBLAS, IR_DOT_P, double>(sv, G, true, true, sh.acc[0], &esc, &ist->flags,
-                                                                 sh, 0);
+    const double rr = merge_slots(sv, G, sh.acc[0], sh, 0);
     const double thr = (tol * tol) * ist->bb;
     const bool bad = (ist->flags & FLAG_NONFINITE) || !is_finite_bits(rr);
     const bool conv = !bad && rr <= thr;
@@ -205,7 +203,7 @@ __global__ void k_ir_update(int n, double *__restrict__ x, const float *__restri
 }
 
 hipError_t launch_ir_residual(const SellMat<float> &A, const double *b, const double *x, double *r, IrState *ist,
-                              const DotWs &ws, int stride, const LaunchCfg &c)
+                              const SlotWs &ws, int stride, const LaunchCfg &c)
 {
     if ((!A.val64 && !A.ds) || sell_vec<float>() != 1) return hipErrorInvalidValue;
     SlotView sv{ws, stride};
@@ -216,7 +214,7 @@ hipError_t launch_ir_residual(const SellMat<float> &A, const double *b, const do
 }
 
 hipError_t launch_ir_prepare(int k, int maxit, double tol, int n, const double *r, float *rf, float *cvec,
-                             double *rr_hist, IrState *ist, const DotWs &ws, int G, int stride, const LaunchCfg &c)
+                             double *rr_hist, IrState *ist, const SlotWs &ws, int G, int stride, const LaunchCfg &c)
 {
     SlotView sv{ws, stride};
     k_ir_prepare<<<c.grid, c.block, 0, c.stream>>>(k, maxit, tol, n, r, rf, cvec, rr_hist, ist, sv, G);

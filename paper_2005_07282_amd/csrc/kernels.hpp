@@ -23,16 +23,19 @@ constexpr int MAX_FPE = 8;
 constexpr int NUM_XCDS = 8; // accelerator dies, each with its own L2; workgroups are dealt to them round-robin
 constexpr int ACC_WORDS = 68; // same as ACC_DIGITS in numerics.hpp
 
-// Per-dot reduction workspace for up to `gmax` workgroups (slots).
+// Workspace of one of the solvers' dots.
 struct DotWs {
-    long long *digits; // [ACC_WORDS][gmax] workgroup accumulator words, word-major
-    int *range;        // [gmax][2] nonzero word range of each workgroup accumulator
-    double *part;      // [gmax][MAX_FPE] workgroup expansions (fpe) or partial sums (plain)
-    int *esc;          // [gmax] escape counts (fpe)
-    long long *acc;    // [DOT_COPIES][DOT_PITCH] accumulators the single solver's workgroups add to
+    double *part;   // [workgroups] partial sums (plain)
+    long long *acc; // [DOT_COPIES][DOT_PITCH] accumulators the workgroups add to (exact modes)
 };
 
-// The single solver's exact dots: workgroups add the words of their
+// Slots of the exact partials of up to `gmax` workgroups.
+struct SlotWs {
+    long long *digits; // [ACC_WORDS][gmax] workgroup accumulator words, word-major
+    int *range;        // [gmax][2] nonzero word range of each workgroup accumulator
+};
+
+// The solvers' exact dots: workgroups add the words of their
 // accumulators into one of DOT_COPIES copies (integers, any order), the next
 // kernel sums the copies. Eight copies keep the adds to one address few
 // enough to drain with the kernel; the escape count sits behind the words of copy 0.
@@ -328,11 +331,11 @@ struct IrState {
 // the sliced-ELL copy), and the workgroup partials of <r, r> into ws (exact
 // dot, expansion length 3).
 hipError_t launch_ir_residual(const SellMat<float> &A, const double *b, const double *x, double *r, IrState *ist,
-                              const DotWs &ws, int stride, const LaunchCfg &cfg);
+                              const SlotWs &ws, int stride, const LaunchCfg &cfg);
 // Merge <r, r> (G slots), record rr_hist[k], decide whether to stop, and for
 // a further correction the inner right-hand side rf = RN32(r 2^-s) and c = 0.
 hipError_t launch_ir_prepare(int k, int maxit, double tol, int n, const double *r, float *rf, float *c,
-                             double *rr_hist, IrState *ist, const DotWs &ws, int G, int stride, const LaunchCfg &cfg);
+                             double *rr_hist, IrState *ist, const SlotWs &ws, int G, int stride, const LaunchCfg &cfg);
 // x = RN(x + c 2^s).
 hipError_t launch_ir_update(int n, double *x, const float *c, const IrState *ist, const LaunchCfg &cfg);
 

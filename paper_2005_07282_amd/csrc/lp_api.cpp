@@ -35,7 +35,7 @@ struct rpcg_lpnet {
     // slots and results, and the matrix / probe pointer table
     Buffer lvec, lws, dots, tab;
     int lws_slots = 0;
-    DotWs wu{}, wr{};
+    SlotWs wu{}, wr{};
     std::vector<unsigned char> tab_host;
 };
 
@@ -130,19 +130,12 @@ int lp_factor_one(rpcg_lpnet *L, int k, double *g_val, double *gt_val, hipStream
 int lp_ensure_dot_ws(rpcg_lpnet *L, int slots)
 {
     if (slots <= L->lws_slots) return RPCG_OK;
-    const size_t per = (size_t)slots * (ACC_WORDS * sizeof(long long) + MAX_FPE * sizeof(double) +
-                                        2 * sizeof(int) + sizeof(int));
+    const size_t per = (size_t)slots * (ACC_WORDS * sizeof(long long) + 2 * sizeof(int));
     RPCG_TRY(L->lws.ensure(2 * per));
     char *base = (char *)L->lws.p;
-    for (DotWs *w : {&L->wu, &L->wr}) {
-        char *b = base;
-        w->digits = (long long *)b;
-        b += (size_t)slots * ACC_WORDS * sizeof(long long);
-        w->part = (double *)b;
-        b += (size_t)slots * MAX_FPE * sizeof(double);
-        w->range = (int *)b;
-        b += (size_t)slots * 2 * sizeof(int);
-        w->esc = (int *)b;
+    for (SlotWs *w : {&L->wu, &L->wr}) {
+        w->digits = (long long *)base;
+        w->range = (int *)(base + (size_t)slots * ACC_WORDS * sizeof(long long));
         base += per;
     }
     L->lws_slots = slots;
@@ -192,7 +185,7 @@ int lp_loss_grad(rpcg_lpnet *L, int nb, const LpLoss &ls, double eps, double *lo
     RPCG_TRY(launch_lp_gt(L->N, nb, nu, o, sc, ls.v, ls.y, s));                                     // y = G^T v
     RPCG_TRY(launch_lp_resid_dots(L->N, nb, nu, eps, o, sc, ls.ut, ls.y, ls.v, ls.r, L->wu, L->wr, L->lws_slots, flags,
                                   &chunks, s));                                                     // r
-    RPCG_TRY(launch_lp_dots_merge(P, chunks, L->wu, L->wr, L->lws_slots, dots, flags, s));
+    RPCG_TRY(launch_lp_dots_merge(P, chunks, L->wu, L->wr, L->lws_slots, dots, s));
     RPCG_TRY(launch_lp_gt(L->N, nb, nu, o, sc, ls.r, ls.q, s));                                     // q = G^T r
     RPCG_TRY(launch_lp_dodg_all(L->N, nb, nu, 1.0 / (double)P, dots, o, sc, ls.r, ls.y, ls.v, ls.q, dout,
                                 (bf16_t *)L->dob.p, (double *)L->scal.p + 2, s));

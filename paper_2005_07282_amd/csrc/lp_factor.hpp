@@ -88,10 +88,10 @@ hipError_t launch_lp_gt(int N, int nb, int nu, const float *o, const float *s, c
 // stride >= nb nu LP_DOT_CHUNKS).
 hipError_t launch_lp_resid_dots(int N, int nb, int nu, double eps, const float *o, const float *s,
                                 const double *const *utab, const double *y, const double *v, double *r,
-                                const DotWs &wu, const DotWs &wr, int stride, int *flags, int *chunks, hipStream_t st);
+                                const SlotWs &wu, const SlotWs &wr, int stride, int *flags, int *chunks, hipStream_t st);
 // dots[2p] = <u_p, u_p>, dots[2p + 1] = <r_p, r_p>, each correctly rounded.
-hipError_t launch_lp_dots_merge(int npairs, int chunks, const DotWs &wu, const DotWs &wr, int stride, double *dots,
-                                int *flags, hipStream_t st);
+hipError_t launch_lp_dots_merge(int npairs, int chunks, const SlotWs &wu, const SlotWs &wr, int stride, double *dots,
+                                hipStream_t st);
 // dL/do of every instance (bfloat16 into dob; binary64 into do64 unless null)
 // and the loss, from the interleaved R, Y, V, Q.
 hipError_t launch_lp_dodg_all(int N, int nb, int nu, double scale, const double *dots, const float *o, const float *s,

@@ -12,7 +12,7 @@
 // rounded), and every sum over m and over the pairs runs in a fixed order, so
 // the loss and the gradient are bit-reproducible.
 #include "lp_factor.hpp"
-#include "batch_common.hpp"
+#include "reduce.hpp"
 
 namespace rpcg {
 
@@ -193,8 +193,7 @@ __global__ void __launch_bounds__(LPL_BLOCK) k_lp_dots(long long n, int nu, cons
         Lu.add(ui, ui, sh.acc[0], true, true);
         Lr.add(ri, ri, sh.acc[1], true, true);
     }
-    block_finish_pair<MODE_EXBLAS, P>(Lu, sh.acc[0], su, Lr, sh.acc[1], sr, p * gridDim.x + blockIdx.x, true, true,
-                                      flags, sh);
+    block_finish_pair<P>(Lu, sh.acc[0], su, Lr, sh.acc[1], sr, p * gridDim.x + blockIdx.x, flags, sh);
 }
 
 // R and those partials in one pass, NU = 1, 2 or 4: a lane takes one vector of
@@ -254,9 +253,7 @@ __global__ void __launch_bounds__(LPL_BLOCK) k_lp_resid_dots(LpGrid grid, double
         const int c = q % ACC_DIGITS, d = q / ACC_DIGITS % 2, p = q / (2 * ACC_DIGITS);
         const SlotView &sv = d ? sr : su;
         const int g = (k * NU + p) * gridDim.x + blockIdx.x;
-        // one carry step, as in block_finish_pair
-        const long long a = acc[p][d][c], cin = c ? (acc[p][d][c - 1] >> 32) : 0;
-        const long long out = (c == ACC_DIGITS - 1) ? a + cin : (a & 0xFFFFFFFFll) + cin;
+        const long long out = carried_word(acc[p][d], c);
         sv.ws.digits[(long long)c * sv.stride + g] = out;
         if (out != 0) {
             atomicMin(&rng[p][d][0], c);
@@ -272,19 +269,23 @@ __global__ void __launch_bounds__(LPL_BLOCK) k_lp_resid_dots(LpGrid grid, double
     if (fl) atomicOr(flags, fl);
 }
 
+// Slots [g0, ...) of a workspace seen as slots [0, ...).
+__device__ __forceinline__ SlotView slots_from(const SlotView &v, int g0)
+{
+    SlotView o = v;
+    o.ws.digits += g0;
+    o.ws.range += 2 * g0;
+    return o;
+}
+
 // dots[2p] = <u_p, u_p>, dots[2p + 1] = <r_p, r_p> from the slots of pair p
 // (one workgroup per pair).
-template <int P>
-__global__ void __launch_bounds__(LPL_BLOCK) k_lp_dots_merge(int chunks, SlotView su, SlotView sr, double *dots,
-                                                             int *flags)
+__global__ void __launch_bounds__(LPL_BLOCK) k_lp_dots_merge(int chunks, SlotView su, SlotView sr, double *dots)
 {
     __shared__ RedShared sh;
     const int p = blockIdx.x;
-    long long esc;
-    const double uu = merge_slots<MODE_EXBLAS, P>(batch_slots<MODE_EXBLAS>(su, p * chunks), chunks, true, true,
-                                                  sh.acc[0], &esc, flags, sh, 0);
-    const double rr = merge_slots<MODE_EXBLAS, P>(batch_slots<MODE_EXBLAS>(sr, p * chunks), chunks, true, true,
-                                                  sh.acc[1], &esc, flags, sh, 1);
+    const double uu = merge_slots(slots_from(su, p * chunks), chunks, sh.acc[0], sh, 0);
+    const double rr = merge_slots(slots_from(sr, p * chunks), chunks, sh.acc[1], sh, 1);
     if (threadIdx.x == 0) {
         dots[2 * p] = uu;
         dots[2 * p + 1] = rr;
@@ -385,7 +386,7 @@ hipError_t launch_lp_gt(int N, int nb, int nu, const float *o, const float *s, c
 
 hipError_t launch_lp_resid_dots(int N, int nb, int nu, double eps, const float *o, const float *s,
                                 const double *const *utab, const double *y, const double *v, double *r,
-                                const DotWs &wu, const DotWs &wr, int stride, int *flags, int *chunks, hipStream_t st)
+                                const SlotWs &wu, const SlotWs &wr, int stride, int *flags, int *chunks, hipStream_t st)
 {
     SlotView su{wu, stride}, sr{wr, stride};
     const long long n = (long long)N * N * N;
@@ -406,11 +407,11 @@ hipError_t launch_lp_resid_dots(int N, int nb, int nu, double eps, const float *
     return hipGetLastError();
 }
 
-hipError_t launch_lp_dots_merge(int npairs, int chunks, const DotWs &wu, const DotWs &wr, int stride, double *dots,
-                                int *flags, hipStream_t st)
+hipError_t launch_lp_dots_merge(int npairs, int chunks, const SlotWs &wu, const SlotWs &wr, int stride, double *dots,
+                                hipStream_t st)
 {
     SlotView su{wu, stride}, sr{wr, stride};
-    hipLaunchKernelGGL(k_lp_dots_merge<LP_DOT_P>, dim3(npairs), dim3(LPL_BLOCK), 0, st, chunks, su, sr, dots, flags);
+    hipLaunchKernelGGL(k_lp_dots_merge, dim3(npairs), dim3(LPL_BLOCK), 0, st, chunks, su, sr, dots);
     return hipGetLastError();
 }
 

@@ -63,9 +63,9 @@ k_fac_setup_r(SellMat<double> A, PcgVecs<double> v, PcgState *st, DotWs wt, DotW
 // One workgroup of FIN_BLOCK threads, a dot per wavefront: beta0, tau0, <b,b>,
 // threshold, stopping test. Leaves the accumulators empty.
 constexpr int FIN_BLOCK = 256;
-template <int MODE, int P>
+template <int MODE>
 __global__ void __launch_bounds__(FIN_BLOCK)
-k_fac_fin_setup(int G, PcgVecs<double> v, PcgState *st, DotWs w0, DotWs w1, DotWs w2, double tol, bool ee, bool capture)
+k_fac_fin_setup(int G, PcgVecs<double> v, PcgState *st, DotWs w0, DotWs w1, DotWs w2, double tol, bool capture)
 {
     __shared__ RedShared sh;
     const int wv = wave_id();
@@ -120,8 +120,7 @@ hipError_t launch_fac_setup(int mode, const SellMat<double> &A, const FacPre &Pr
         });
         k_fac_gt<<<c.grid, c.block, 0, c.stream>>>(A.n, Pr, v.r, t, st);
         k_fac_z<M, PP, true><<<c.grid, c.block, 0, c.stream>>>(A.n, Pr, v, t, st, s0, c.early_exit, c.fallback);
-        k_fac_fin_setup<M, PP><<<1, FIN_BLOCK, 0, c.stream>>>(c.grid, v, st, s0, s1, s2, tol, c.early_exit,
-                                                              c.fallback);
+        k_fac_fin_setup<M><<<1, FIN_BLOCK, 0, c.stream>>>(c.grid, v, st, s0, s1, s2, tol, c.fallback);
     });
     return hipGetLastError();
 }

@@ -31,8 +31,8 @@ static __global__ void k_state_init(PcgState *st, int maxit, DotWs w0, DotWs w1,
 }
 
 // dinv = RN(1/a_ii), r = RN(b - A x0), z = RN(dinv r), d = z, and the
-// workgroup partials of <z,r>, <r,r>, <b,b>. One wavefront per 64-row slice
-// of the sliced-ELL copy, as in the iteration's SpMV.
+// workgroup partials of <z,r>, <r,r>, <b,b>. One wavefront per slice of the
+// matrix copy, as in the iteration's SpMV.
 template <int MODE, int P, int LAY, typename T>
 __global__ void __launch_bounds__(MAX_BLOCK)
 k_pcg_setup(SellMat<T> A, PcgVecs<T> v, PcgState *st, DotWs w0, DotWs w1, DotWs w2, bool ee, bool capture)
@@ -80,9 +80,9 @@ k_pcg_setup(SellMat<T> A, PcgVecs<T> v, PcgState *st, DotWs w0, DotWs w1, DotWs 
 // One workgroup of FIN_BLOCK threads, a dot per wavefront: beta0, tau0, <b,b>; thr = RN(RN(tol*tol)
 // <b,b>) in T with tol rounded to T; stopping test. Leaves the accumulators empty.
 constexpr int FIN_BLOCK = 256;
-template <int MODE, int P, typename T>
+template <int MODE, typename T>
 __global__ void __launch_bounds__(FIN_BLOCK)
-k_pcg_fin_setup(int G, PcgVecs<T> v, PcgState *st, DotWs w0, DotWs w1, DotWs w2, double tol, bool ee, bool capture)
+k_pcg_fin_setup(int G, PcgVecs<T> v, PcgState *st, DotWs w0, DotWs w1, DotWs w2, double tol, bool capture)
 {
     __shared__ RedShared sh;
     const int wv = wave_id();
@@ -138,8 +138,7 @@ hipError_t launch_pcg_setup(int mode, const SellMat<T> &A, const PcgVecs<T> &v, 
             k_pcg_setup<M, PP, decltype(lay)::value, T><<<c.grid, c.block, 0, c.stream>>>(A, v, st, ws3[0], ws3[1], ws3[2],
                                                                                           c.early_exit, c.fallback);
         });
-        k_pcg_fin_setup<M, PP, T><<<1, FIN_BLOCK, 0, c.stream>>>(c.grid, v, st, ws3[0], ws3[1], ws3[2], tol, c.early_exit,
-                                                                 c.fallback);
+        k_pcg_fin_setup<M, T><<<1, FIN_BLOCK, 0, c.stream>>>(c.grid, v, st, ws3[0], ws3[1], ws3[2], tol, c.fallback);
     });
     return hipGetLastError();
 }

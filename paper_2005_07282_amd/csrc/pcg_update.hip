@@ -92,9 +92,9 @@ constexpr int DIR_PREFETCH = 8;
 // S3: with S3 set (the Jacobi solver) this kernel also applies the iterate
 // update x = fma(rho, d, x) of iteration l; the factored solver's update
 // kernel applies it itself.
-template <int MODE, int P, typename T, bool S3>
+template <int MODE, typename T, bool S3>
 __global__ void __launch_bounds__(MAX_BLOCK)
-k_pcg_direction(int l, int n, PcgVecs<T> v, PcgState *st, DotWs wb, DotWs wt, DotWs wd, int G, bool ee, bool capture)
+k_pcg_direction(int l, int n, PcgVecs<T> v, PcgState *st, DotWs wb, DotWs wt, DotWs wd, int G, bool capture)
 {
     __shared__ RedShared sh;
     const long long i0 = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -194,14 +194,10 @@ template <typename T>
 hipError_t launch_pcg_direction(int mode, int l, int n, const PcgVecs<T> &v, PcgState *st, const DotWs *ws3, int G,
                                 const LaunchCfg &c, bool s3)
 {
-    dispatch(mode, c.fpe_size, [&](auto m, auto p) {
-        constexpr int M = decltype(m)::value, PP = decltype(p)::value;
-        if (s3)
-            k_pcg_direction<M, PP, T, true><<<c.grid, c.block, 0, c.stream>>>(l, n, v, st, ws3[1], ws3[2], ws3[0], G,
-                                                                              c.early_exit, c.fallback);
-        else
-            k_pcg_direction<M, PP, T, false><<<c.grid, c.block, 0, c.stream>>>(l, n, v, st, ws3[1], ws3[2], ws3[0], G,
-                                                                               c.early_exit, c.fallback);
+    dispatch_mode(mode, [&](auto m) {
+        constexpr int M = decltype(m)::value;
+        if (s3) k_pcg_direction<M, T, true><<<c.grid, c.block, 0, c.stream>>>(l, n, v, st, ws3[1], ws3[2], ws3[0], G, c.fallback);
+        else k_pcg_direction<M, T, false><<<c.grid, c.block, 0, c.stream>>>(l, n, v, st, ws3[1], ws3[2], ws3[0], G, c.fallback);
     });
     return hipGetLastError();
 }

@@ -4,17 +4,22 @@
 //
 // Reduction structure (Section 3.2 / 4.3 mapped onto one GPU): each lane
 // keeps its own accumulator (an expansion, or a plain sum); the lanes of a
-// workgroup combine into one workgroup partial written to a slot: a plain
-// sum in a fixed tree, or, in both exact modes, a long accumulator in LDS.
-// In EXBLAS mode each wavefront adds its lanes' expansions to it word by
-// word as exact integer sums; in FPE mode each wavefront's expansions are
-// first merged in a fixed lane tree whose escapes are counted (Section 4.3),
-// and the merged expansion is added exactly. The kernel that
-// needs the scalar next merges all slots in a fixed order at its start, in
-// every workgroup alike, and rounds once; the kernel boundary makes the slots
-// visible, so no device-scope fence or atomic ticket is needed inside the
-// producing kernel (on multi-XCD gfx950 a per-workgroup release fence writes
-// back the XCD's L2 and serialises the workgroups). This replaces the paper's
+// workgroup combine into one workgroup partial: a plain sum in a fixed tree
+// written to a slot, or, in both exact modes, a long accumulator in LDS. In
+// EXBLAS mode each wavefront sums its lanes' expansions in digits of 40 bits
+// (wave_flush_dots) and adds the digits to it; in FPE mode the wavefront's
+// expansions are merged in a fixed lane tree whose escapes are counted (Section
+// 4.3), and the merged expansion is added, but for wavefronts whose merge provably leaves no
+// escape: their expansions go in as in EXBLAS mode, the same exact sum.
+// The solvers' workgroups then add the words of their accumulators to a few copies in
+// device memory with device-scope integer atomics (block_publish); the kernel that
+// needs the scalar next sums the copies at its start, in every workgroup alike,
+// by one wavefront, and rounds once (wave_merge). The kernel boundary makes the
+// sums visible, so no fence or ticket is needed inside the producing kernel
+// (on multi-XCD gfx950 a per-workgroup release fence writes back the XCD's L2 and
+// serialises the workgroups); the standalone dot, one kernel, takes tickets with
+// atomics alone. The refinement's residual and the training loss keep one slot per
+// workgroup, merged in the same way. This replaces the paper's
 // MPI_Reduce + Round + MPI_Bcast: every consumer computes the same rounded
 // scalar from the same integers.
 #pragma once
@@ -597,19 +602,6 @@ __device__ inline double block_sum_d(double v, RedShared &sh)
     return t;
 }
 
-// Workgroup sum of an integer into thread 0.
-__device__ inline long long block_sum_ll(long long v, RedShared &sh)
-{
-    v = wave_sum_down(v);
-    if (lane_id() == 0) sh.red_ll[wave_id()] = v;
-    __syncthreads();
-    long long t = 0;
-    if (threadIdx.x == 0)
-        for (int w = 0; w < num_waves(); ++w) t += sh.red_ll[w];
-    __syncthreads();
-    return t;
-}
-
 // FPE: the lanes' expansions of a wavefront into the long accumulator, escapes
 // of the wavefront merge counted. Where the merge provably has none, the
 // expansions go in word by word instead: the same exact sum without the merge's
@@ -629,97 +621,72 @@ __device__ __forceinline__ void wave_fpe_finish(double (&a)[P], int &esc, bool e
 }
 
 // ---------------------------------------------------------------------------
-// Slots: one workgroup partial per producing workgroup. Long-accumulator
+// Slots (exact mode): one workgroup partial per producing workgroup, for the
+// refinement's residual and the training loss. Long-accumulator
 // words are stored word-major (word k of slot g at digits[k * stride + g]) so
 // that the merge reads each word of all slots as one coalesced run.
 
 struct SlotView {
-    DotWs ws;
+    SlotWs ws;
     int stride; // slot capacity (words of one index are `stride` apart)
 };
 
-// Write the workgroup partial of one dot into slot g. All threads call.
-template <int MODE, int P, bool ADAPT>
-__device__ __forceinline__ void block_finish(LaneDot<MODE, P, ADAPT> &L, long long *acc, const SlotView &sv, int g,
-                                             bool ee, bool capture, int *gflags, RedShared &sh)
+// Word k of a workgroup's accumulator after one carry step, which keeps every
+// word below 2^33 in magnitude, so the integer sum over workgroups cannot overflow.
+__device__ __forceinline__ long long carried_word(const long long *acc, int k)
 {
-    if constexpr (MODE == MODE_PLAIN) {
-        double t = block_sum_d(L.s, sh);
-        if (threadIdx.x == 0) sv.ws.part[g] = t;
-        return;
-    } else {
-        if constexpr (MODE == MODE_EXBLAS) {
-            // the lanes' expansions go into the accumulator word by word, one
-            // atomic per word and wavefront
-            wave_flush_exact<P>(L.a, acc, L.flags);
-        } else {
-            // each lane merges its result and error expansions, the
-            // wavefront merges its lanes' expansions (fixed tree, escapes
-            // counted), and the wavefront's expansion is added exactly to the
-            // long accumulator, which already holds whatever escaped on the
-            // way: the slot is the exact workgroup partial, merged across
-            // workgroups like exblas
-            L.esc += fpe_sum_capture<P>(L.a, L.e, ee, capture, acc, L.flags);
-            wave_fpe_finish<P>(L.a, L.esc, ee, capture, acc, L.flags);
-            const long long esc = block_sum_ll(L.esc, sh);
-            if (threadIdx.x == 0) sv.ws.esc[g] = (int)esc;
-        }
-        if (threadIdx.x == 0) { sh.rng[0] = ACC_DIGITS; sh.rng[1] = -1; }
-        __syncthreads();
-        // one carry step keeps every word below 2^33 in magnitude, so the
-        // integer sum over the slots cannot overflow
-        for (int k = threadIdx.x; k < ACC_DIGITS; k += blockDim.x) {
-            long long v = acc[k];
-            long long cin = k ? (acc[k - 1] >> 32) : 0;
-            long long o = (k == ACC_DIGITS - 1) ? v + cin : (v & 0xFFFFFFFFll) + cin;
-            sv.ws.digits[(long long)k * sv.stride + g] = o;
-            if (o != 0) { atomicMin(&sh.rng[0], k); atomicMax(&sh.rng[1], k); }
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) { sv.ws.range[2 * g] = sh.rng[0]; sv.ws.range[2 * g + 1] = sh.rng[1]; }
-        if (L.flags) atomicOr(gflags, L.flags);
+    const long long v = acc[k], cin = k ? (acc[k - 1] >> 32) : 0;
+    return (k == ACC_DIGITS - 1) ? v + cin : (v & 0xFFFFFFFFll) + cin;
+}
+
+// Write the workgroup partial of one dot into slot g. All threads call.
+template <int P>
+__device__ __forceinline__ void block_finish(LaneDot<MODE_EXBLAS, P> &L, long long *acc, const SlotView &sv, int g,
+                                             int *gflags, RedShared &sh)
+{
+    wave_flush_exact<P>(L.a, acc, L.flags);
+    if (threadIdx.x == 0) { sh.rng[0] = ACC_DIGITS; sh.rng[1] = -1; }
+    __syncthreads();
+    for (int k = threadIdx.x; k < ACC_DIGITS; k += blockDim.x) {
+        const long long o = carried_word(acc, k);
+        sv.ws.digits[(long long)k * sv.stride + g] = o;
+        if (o != 0) { atomicMin(&sh.rng[0], k); atomicMax(&sh.rng[1], k); }
     }
+    __syncthreads();
+    if (threadIdx.x == 0) { sv.ws.range[2 * g] = sh.rng[0]; sv.ws.range[2 * g + 1] = sh.rng[1]; }
+    if (L.flags) atomicOr(gflags, L.flags);
 }
 
 // The partials of two dots into slot g of sv0 and sv1 (as two block_finish
-// calls; in EXBLAS mode in one pass, the wavefront word sums of both dots
-// side by side and one carry step over both accumulators).
-template <int MODE, int P, bool ADAPT>
-__device__ __forceinline__ void block_finish_pair(LaneDot<MODE, P, ADAPT> &L0, long long *acc0, const SlotView &sv0,
-                                                  LaneDot<MODE, P, ADAPT> &L1, long long *acc1, const SlotView &sv1,
-                                                  int g, bool ee, bool capture, int *gflags, RedShared &sh)
+// calls, in one pass).
+template <int P>
+__device__ __forceinline__ void block_finish_pair(LaneDot<MODE_EXBLAS, P> &L0, long long *acc0, const SlotView &sv0,
+                                                  LaneDot<MODE_EXBLAS, P> &L1, long long *acc1, const SlotView &sv1,
+                                                  int g, int *gflags, RedShared &sh)
 {
-    if constexpr (MODE != MODE_EXBLAS) {
-        block_finish<MODE, P>(L0, acc0, sv0, g, ee, capture, gflags, sh);
-        block_finish<MODE, P>(L1, acc1, sv1, g, ee, capture, gflags, sh);
-    } else {
-        wave_flush_exact2<P>(L0.a, acc0, L0.flags, L1.a, acc1, L1.flags);
-        if (threadIdx.x == 0) { sh.rng[0] = ACC_DIGITS; sh.rng[1] = -1; sh.rng2[0] = ACC_DIGITS; sh.rng2[1] = -1; }
-        __syncthreads();
-        for (int q = threadIdx.x; q < 2 * ACC_DIGITS; q += blockDim.x) {
-            const bool second = q >= ACC_DIGITS;
-            const int k = second ? q - ACC_DIGITS : q;
-            const long long *acc = second ? acc1 : acc0;
-            long long v = acc[k];
-            long long cin = k ? (acc[k - 1] >> 32) : 0;
-            long long o = (k == ACC_DIGITS - 1) ? v + cin : (v & 0xFFFFFFFFll) + cin;
-            (second ? sv1 : sv0).ws.digits[(long long)k * (second ? sv1 : sv0).stride + g] = o;
-            if (o != 0) {
-                int *rng = second ? sh.rng2 : sh.rng;
-                atomicMin(&rng[0], k);
-                atomicMax(&rng[1], k);
-            }
+    wave_flush_exact2<P>(L0.a, acc0, L0.flags, L1.a, acc1, L1.flags);
+    if (threadIdx.x == 0) { sh.rng[0] = ACC_DIGITS; sh.rng[1] = -1; sh.rng2[0] = ACC_DIGITS; sh.rng2[1] = -1; }
+    __syncthreads();
+    for (int q = threadIdx.x; q < 2 * ACC_DIGITS; q += blockDim.x) {
+        const bool second = q >= ACC_DIGITS;
+        const int k = second ? q - ACC_DIGITS : q;
+        const long long o = carried_word(second ? acc1 : acc0, k);
+        (second ? sv1 : sv0).ws.digits[(long long)k * (second ? sv1 : sv0).stride + g] = o;
+        if (o != 0) {
+            int *rng = second ? sh.rng2 : sh.rng;
+            atomicMin(&rng[0], k);
+            atomicMax(&rng[1], k);
         }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            sv0.ws.range[2 * g] = sh.rng[0];
-            sv0.ws.range[2 * g + 1] = sh.rng[1];
-            sv1.ws.range[2 * g] = sh.rng2[0];
-            sv1.ws.range[2 * g + 1] = sh.rng2[1];
-        }
-        const int fl = L0.flags | L1.flags;
-        if (fl) atomicOr(gflags, fl);
     }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        sv0.ws.range[2 * g] = sh.rng[0];
+        sv0.ws.range[2 * g + 1] = sh.rng[1];
+        sv1.ws.range[2 * g] = sh.rng2[0];
+        sv1.ws.range[2 * g + 1] = sh.rng2[1];
+    }
+    const int fl = L0.flags | L1.flags;
+    if (fl) atomicOr(gflags, fl);
 }
 
 // ---------------------------------------------------------------------------
@@ -828,8 +795,7 @@ __device__ inline T wave_acc_round(const long long *acc)
 // ---------------------------------------------------------------------------
 // Merge of the G slots of one dot, in every workgroup alike. All threads of
 // the workgroup call; the result is returned to every thread. `acc` is an
-// LDS accumulator the merge may overwrite. *esc_out (thread 0) receives the
-// escapes (FPE); flags seen on the way are or-ed into *flags_out.
+// LDS accumulator the merge may overwrite.
 
 // Sum of row[0..G) by one wavefront (result in every lane); eight independent
 // loads per lane are in flight at a time.
@@ -846,68 +812,35 @@ __device__ __forceinline__ long long sum_row(const long long *row, int G)
     return wave_sum_i64_all(t);
 }
 
-template <int MODE, int P, typename T = double>
-__device__ __forceinline__ T merge_slots(const SlotView &sv, int G, bool ee, bool capture, long long *acc,
-                              long long *esc_out, int *flags_out, RedShared &sh, int slot_val)
+__device__ __forceinline__ double merge_slots(const SlotView &sv, int G, long long *acc, RedShared &sh, int slot_val)
 {
-    *esc_out = 0;
-    T r;
-    if constexpr (MODE == MODE_PLAIN) {
-        // fixed order: wavefront 0 sums the slots lane-strided, then the tree
-        if (wave_id() == 0) {
-            double s[4] = {0.0, 0.0, 0.0, 0.0};
-            int g = lane_id();
-            for (; g + 3 * 64 < G; g += 4 * 64) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) s[j] += sv.ws.part[g + 64 * j];
-            }
-            for (; g < G; g += 64) s[0] += sv.ws.part[g];
-            double t = wave_sum_down((s[0] + s[1]) + (s[2] + s[3]));
-            if (lane_id() == 0) sh.val[slot_val] = t;
-        }
-        __syncthreads();
-        r = (T)sh.val[slot_val];
-        __syncthreads();
-        return r;
-    } else {
-        int flags = 0;
-        zero_acc(acc);
-        if (threadIdx.x == 0) { sh.rng[0] = ACC_DIGITS; sh.rng[1] = -1; }
-        __syncthreads();
-        // FPE: the slots are exact workgroup partials (expansion included);
-        // only the escape counts are summed here
-        if constexpr (MODE == MODE_FPE) {
-            long long esc_slots = 0;
-            for (int g = threadIdx.x; g < G; g += blockDim.x) esc_slots += sv.ws.esc[g];
-            long long esc_tot = block_sum_ll(esc_slots, sh);
-            if (threadIdx.x == 0) *esc_out = esc_tot;
-        }
-        // long-accumulator words: global nonzero range, then one word per wavefront
-        int kmin = ACC_DIGITS, kmax = -1;
-        for (int g = threadIdx.x; g < G; g += blockDim.x) {
-            kmin = min(kmin, sv.ws.range[2 * g]);
-            kmax = max(kmax, sv.ws.range[2 * g + 1]);
-        }
-        kmin = wave_minmax_i32_all<false>(kmin);
-        kmax = wave_minmax_i32_all<true>(kmax);
-        if (lane_id() == 0) { atomicMin(&sh.rng[0], kmin); atomicMax(&sh.rng[1], kmax); }
-        __syncthreads();
-        const int K0 = sh.rng[0], K1 = sh.rng[1];
-        for (int k = K0 + wave_id(); k <= K1; k += num_waves()) {
-            long long s = sum_row(sv.ws.digits + (long long)k * sv.stride, G);
-            if (lane_id() == 0) atomicAdd((unsigned long long *)&acc[k], (unsigned long long)s);
-        }
-        __syncthreads();
-        if (flags) atomicOr(flags_out, flags);
-        if (wave_id() == 0) {
-            T v = wave_acc_round<T>(acc);
-            if (lane_id() == 0) sh.val[slot_val] = (double)v;
-        }
-        __syncthreads();
-        r = (T)sh.val[slot_val];
-        __syncthreads();
-        return r;
+    zero_acc(acc);
+    if (threadIdx.x == 0) { sh.rng[0] = ACC_DIGITS; sh.rng[1] = -1; }
+    __syncthreads();
+    // long-accumulator words: global nonzero range, then one word per wavefront
+    int kmin = ACC_DIGITS, kmax = -1;
+    for (int g = threadIdx.x; g < G; g += blockDim.x) {
+        kmin = min(kmin, sv.ws.range[2 * g]);
+        kmax = max(kmax, sv.ws.range[2 * g + 1]);
     }
+    kmin = wave_minmax_i32_all<false>(kmin);
+    kmax = wave_minmax_i32_all<true>(kmax);
+    if (lane_id() == 0) { atomicMin(&sh.rng[0], kmin); atomicMax(&sh.rng[1], kmax); }
+    __syncthreads();
+    const int K0 = sh.rng[0], K1 = sh.rng[1];
+    for (int k = K0 + wave_id(); k <= K1; k += num_waves()) {
+        const long long s = sum_row(sv.ws.digits + (long long)k * sv.stride, G);
+        if (lane_id() == 0) atomicAdd((unsigned long long *)&acc[k], (unsigned long long)s);
+    }
+    __syncthreads();
+    if (wave_id() == 0) {
+        const double v = wave_acc_round(acc);
+        if (lane_id() == 0) sh.val[slot_val] = v;
+    }
+    __syncthreads();
+    const double r = sh.val[slot_val];
+    __syncthreads();
+    return r;
 }
 
 // ---------------------------------------------------------------------------
@@ -964,12 +897,7 @@ __device__ __forceinline__ void block_publish(LaneDot<MODE, P, ADAPT> *const (&L
         const int copy = g % copies;
         for (int q = threadIdx.x; q < D * ACC_DIGITS; q += blockDim.x) {
             const int d = D == 1 ? 0 : q / ACC_DIGITS, k = q - d * ACC_DIGITS;
-            // one carry step keeps every word below 2^33 in magnitude, so the
-            // integer sum over the workgroups cannot overflow
-            const long long *a = D == 1 || d == 0 ? acc[0] : acc[D - 1];
-            const long long v = a[k];
-            const long long cin = k ? (a[k - 1] >> 32) : 0;
-            const long long o = (k == ACC_DIGITS - 1) ? v + cin : (v & 0xFFFFFFFFll) + cin;
+            const long long o = carried_word(D == 1 || d == 0 ? acc[0] : acc[D - 1], k);
             long long *dst = (D == 1 || d == 0 ? w[0] : w[D - 1])->acc;
             if (o != 0) atomicAdd((unsigned long long *)&dst[copy * DOT_PITCH + k], (unsigned long long)o);
         }
@@ -1034,6 +962,15 @@ inline void dispatch_p(int p, F &&f)
     case 7: f(IC<M>{}, IC<7>{}); break;
     default: f(IC<M>{}, IC<8>{}); break;
     }
+}
+
+// f(IC<mode>) for kernels that do not depend on the expansion length.
+template <typename F>
+inline void dispatch_mode(int mode, F &&f)
+{
+    if (mode == MODE_PLAIN) f(IC<MODE_PLAIN>{});
+    else if (mode == MODE_FPE) f(IC<MODE_FPE>{});
+    else f(IC<MODE_EXBLAS>{});
 }
 
 template <typename F>
