@@ -359,8 +359,7 @@ static int build_sell(rpcg_ctx *c, const SellBufs &bf, int n, int nnz, const int
     RPCG_TRY(c->widths.ensure(sizeof(int) * ((size_t)nw + DIAG_TABLE)));
     long long *off = (long long *)bf.off->p;
     int *table = (int *)c->widths.p, *w = table + DIAG_TABLE;
-    const int max_stored = diag_max_stored(nd, c->num_cus);
-    const bool sample = max_stored != DIAG_ANY && !no_col16;
+    const bool sample = diag_few(nd, c->num_cus) && !no_col16;
     const DiagCsr<double> m64{rp, col, v64, n, nnz, 0};
     const DiagCsr<float> m32{rp, col, v32, n, nnz, 0};
     auto of_type = [&](auto &&f) { return v64 ? f(m64, (const DiagCsr<double> *)nullptr) : f(m32, (const DiagCsr<float> *)nullptr); };
@@ -371,6 +370,7 @@ static int build_sell(rpcg_ctx *c, const SellBufs &bf, int n, int nnz, const int
     RPCG_TRY(hipMemcpyAsync(&scan_info, c->info, sizeof scan_info, hipMemcpyDeviceToHost, s));
     RPCG_TRY(hipStreamSynchronize(s));
     if (scan_info.flags) return RPCG_ERR_INVALID;
+    const int max_stored = diag_max_stored(nd, scan_info.max_len, c->num_cus);
     if (!no_col16 && diag_to_try(n, scan_info.max_len) && scan_info.varying / 2 <= max_stored) {
         RPCG_TRY(bf.ds->ensure(sizeof(DiagSlice) * nd));
         out->records = (size_t)diag_mpos(padded, nd);

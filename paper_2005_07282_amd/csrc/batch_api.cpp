@@ -430,12 +430,11 @@ static int batch_create_body(rpcg_batch *B, const rpcg_csr *A, hipStream_t calle
     std::vector<DiagCsr<double>> tab(B->nsys);
     for (int q = 0; q < B->nsys; ++q)
         tab[q] = DiagCsr<double>{A[q].row_ptr, A[q].col_idx, A[q].val, A[q].n, A[q].nnz, B->sys[q].slice0};
-    const int max_stored = diag_max_stored(ns / 2, c->num_cus);
     RPCG_TRY(hipMemcpyAsync(dtab, tab.data(), sizeof(DiagCsr<double>) * B->nsys, hipMemcpyHostToDevice, B->gs));
     RPCG_TRY(hipMemsetAsync(off, 0, sizeof(long long), B->gs));
     RPCG_TRY(hipMemsetAsync(c->info, 0, sizeof(DotInfo), B->gs));
     // every pass takes all systems in one launch (creation with launches for each: 1024 systems of 1000 rows 25.6 ms, now 6.8 ms)
-    RPCG_TRY(launch_row_widths(tab[0], dtab, B->nsys, ns, max_stored != DIAG_ANY, w, table, c->info, B->gs));
+    RPCG_TRY(launch_row_widths(tab[0], dtab, B->nsys, ns, diag_few(ns / 2, c->num_cus), w, table, c->info, B->gs));
     RPCG_TRY(launch_scan_len(w, ns, off, 1, true, B->gs));
     B->off_host.resize(B->total_slices + 1);
     DotInfo inf;
@@ -445,6 +444,7 @@ static int batch_create_body(rpcg_batch *B, const rpcg_csr *A, hipStream_t calle
     RPCG_TRY(hipStreamSynchronize(B->gs));
     if (inf.flags) return RPCG_ERR_INVALID;
     const long long padded = B->off_host[B->total_slices];
+    const int max_stored = diag_max_stored(ns / 2, inf.max_len, c->num_cus);
     bool aligned = false;
     if (inf.max_len > 0 && inf.max_len <= DIAG_MAX_ROW && inf.varying / 2 <= max_stored) {
         // diagonal-aligned slices, as for a single system

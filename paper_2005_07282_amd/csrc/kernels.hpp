@@ -169,12 +169,15 @@ __host__ constexpr bool diag_to_try(int n, int max_len) { return max_len > 0 && 
 // a CU it is latency that counts (prepared product, general and aligned, us: 20 k rows of 31
 // 4.5 and 7.3, of 201 16.6 and 33.6; 100 k rows of 21 6.1 and 7.3, of 101 20.8 and
 // 27.9; 150 k rows 9.3 and 9.2, 32.6 and 36.0; 200 k rows 10.6 and 8.1, 39.4 and 28.9; 512 k rows of 27
-// 28.2 and 19.3; rows of up to seven about alike). A few stored slices among constant ones, which
-// are faster aligned at any size, do no harm.
+// 28.2 and 19.3). Rows of one batch only cross at half of that (solves of 7-point operators: 64 k
+// rows 2.38 and 2.55 ms; factored, 85 k rows 2.94 and 2.90 ms, 157 k rows 4.57 and 4.43 ms). A few
+// stored slices among constant ones, which are faster aligned at any size, do no harm.
 constexpr int DIAG_ANY = 2147483647;
-__host__ constexpr int diag_max_stored(long long nslices, int num_cus)
+__host__ constexpr bool diag_few(long long nslices, int num_cus) { return nslices < 5ll * num_cus; }
+__host__ constexpr int diag_max_stored(long long nslices, int max_len, int num_cus)
 {
-    return nslices >= 5ll * num_cus ? DIAG_ANY : (int)(nslices / 16);
+    const bool enough = !diag_few(max_len <= DIAG_BATCH ? 2 * nslices : nslices, num_cus);
+    return enough ? DIAG_ANY : (int)(nslices / 16);
 }
 constexpr int DIAG_TABLE = 8192; // hash slots of record lists, a power of two (see k_diag_share)
 
@@ -243,7 +246,7 @@ hipError_t launch_spmv_csr(int n, long long nnz, const int *row_ptr, const int *
 // Slice widths (longest row of each 64 rows) into w, longest row, and the
 // check of row_ptr (info->flags set if malformed), of one matrix (slice0 = 0) or, with
 // nmats > 1, of all in mats (device memory, in order, each from an even slice0 on); rows past a matrix's
-// last are empty. table (DIAG_TABLE ints) is set to -1. sample: info->varying, a lower bound for twice the 128-row slices whose values vary.
+// last are empty. table (DIAG_TABLE ints) is set to -1. sample (for diag_few): info->varying, a lower bound for twice the 128-row slices whose values vary.
 template <typename TIN>
 hipError_t launch_row_widths(const DiagCsr<TIN> &one, const DiagCsr<TIN> *mats, int nmats, int nslices, bool sample, int *w,
                              int *table, DotInfo *info, hipStream_t s);
