@@ -609,6 +609,11 @@ def run_learned(n_eval, rpcg, torch, dev):
     return out
 
 
+def head(table, *keys):
+    """The named entries of a table of results (None stays None)."""
+    return None if table is None else {k: table[k] for k in keys if k in table}
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -778,6 +783,11 @@ def main():
     traffic = k1_traffic() if N == 160 else None
     stream_gbs = measure_stream_read(torch, dev)
     log(f"[bench] stream read (torch.sum, 2 GiB binary64) {stream_gbs:.1f} GB/s")
+    # the tables behind the line's figures: lines of their own, so that the JSON line stays short
+    for name, table in (("exdot_grid", exgrid), ("mixed_precision", mixed), ("batched", batched),
+                        ("learned_preconditioner", learned_pc), ("stress", stress)):
+        if table is not None:
+            print(f"details {name}: {json.dumps(table)}", flush=True)
     line = {
         "metric": METRIC,
         "value": round(value, 2),
@@ -810,11 +820,13 @@ def main():
             "rpcg_smat_spmv": smat160,
             "exdot_n": ne,
             "exdot": exd,
-            "exdot_grid": exgrid,
-            "mixed_precision": mixed,
-            "batched": batched,
-            "learned_preconditioner": learned_pc,
-            "stress": stress,
+            "mixed_precision": head(mixed, "speedup_vs_fp64_plain", "speedup_vs_fp64_exblas"),
+            "batched": head(batched, "solve_ms", "iterations_total", "speedup_vs_solo", "algorithmic_GB_s",
+                            "systems_bit_identical_to_solo"),
+            "learned_preconditioner": head(learned_pc, "jacobi_solve_ms_mean", "learned_solve_ms_mean",
+                                           "train_step_ms_8_systems_4_vectors", "all_converged"),
+            "stress": {k: head(v, "exblas_over_plain", "fpe_over_plain", "exblas_fpe_identical")
+                       for k, v in (stress or {}).items()} or None,
         },
         "roofline": {
             "bound": "hbm",
