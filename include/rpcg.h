@@ -196,9 +196,10 @@ int rpcg_spmv(rpcg_ctx *ctx, const rpcg_csr *A /* host struct */, const double *
 
 /* A matrix prepared for repeated products (Section 4.3 SpMV): a device copy
  * in the solver's layout, owned by the handle. Where the rows line up by their
- * column offsets (stencils, bands) it holds 8 bytes per stored entry, or next
- * to nothing where the entries are also constant along the offsets; else a
- * sliced-ELL copy (binary64 values, 16-bit column codes where the columns
+ * column offsets (stencils, bands) and the entries are constant along the offsets
+ * it holds next to nothing; where they line up and vary, 8 bytes per stored
+ * entry (of matrices with enough rows to fill the device: about 80 k rows of
+ * up to seven entries, 160 k of longer ones); else a sliced-ELL copy (binary64 values, 16-bit column codes where the columns
  * allow them; about 10 bytes per stored entry plus 9 bytes per row). Products
  * with it are the same fma chains as rpcg_spmv, so y is bit-identical to
  * rpcg_spmv on the matrix it was made from, at the rate of the solver's own
@@ -250,8 +251,8 @@ int rpcg_fpe_size_auto(rpcg_ctx *ctx, const rpcg_csr *A /* host struct */, const
  * doubles, in: starting guess x^(0), out: final iterate. A must be SPD with a
  * positive stored diagonal entry in every row. The CSR structure is checked
  * on the device first (RPCG_ERR_INVALID if row_ptr or a column index is out
- * of range); the library then keeps a sliced-ELL copy of A for the
- * iteration (same rows, same entry order). Waits for completion; `res`
+ * of range); the library then keeps a copy of A for the iteration (same rows,
+ * same entry order; see rpcg_smat). Waits for completion; `res`
  * (host, may be NULL) receives iterations, tau, status and timings. The
  * returned status is also written to res->status. */
 int rpcg_pcg_solve(rpcg_ctx *ctx, rpcg_mode mode, const rpcg_csr *A /* host struct */,

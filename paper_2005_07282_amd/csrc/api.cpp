@@ -57,7 +57,7 @@ static LaunchCfg make_cfg(const rpcg_ctx *c, const rpcg_opts &o, long long work_
 }
 
 // Vector kernels (setup, K2, K3): 512-thread workgroups, at most two per CU,
-// so that the slot merges in the next kernel's prologue stay short.
+// as each costs its accumulators' setup and partials.
 static LaunchCfg make_vec_cfg(const rpcg_ctx *c, const rpcg_opts &o, long long n, hipStream_t s)
 {
     LaunchCfg cfg = make_cfg(c, o, n, 512, s);
@@ -343,7 +343,8 @@ static SellBufs ctx_sell_bufs(rpcg_ctx *c)
 // values: v64 or v32; kept as binary64 (out64) and/or rounded to binary32
 // (out32). The general copy's interleave is that of the solver's value type:
 // two entries for a binary64-only copy, one when binary32 values are kept.
-// no_col16 asks for 32-bit columns, that is the general copy. Waits for the stream.
+// no_col16 asks for 32-bit columns, that is the general copy. Waits for
+// the answers that choose the copy, not for its filling.
 static int build_sell(rpcg_ctx *c, const SellBufs &bf, int n, int nnz, const int *rp, const int *col,
                       const double *v64, const float *v32, bool out64, bool out32, bool no_col16, hipStream_t s,
                       SellBuilt *out)

@@ -17,10 +17,12 @@ namespace rpcg {
 // before each ticket had cost 2 to 14 times the whole dot). The tickets are in two levels: a thousand
 // workgroups that end together would otherwise queue on one address.
 // A call on one workgroup needs neither atomics nor tickets.
-// What bounds it: HBM from about 2^26 pairs on, for narrow and wide exponents
-// alike (2^26 narrow 250 -> 185 us, 5.8 TB/s; FPE on wide data 300 -> 210 us),
-// with the next pairs prefetched and the streamed loads marked non-temporal
-// (199 us without the mark). Short calls are latency: 10007 pairs took a memset, two
+// What bounds it: HBM from about 2^26 pairs on in the exact mode, for narrow and
+// wide exponents alike (2^26 pairs 188 and 222 -> 185 and 189 us, 5.7 TB/s), and in FPE mode
+// for narrow ones (198 -> 172 us, 6.2 TB/s); FPE over +-200 binades is bound by
+// its expansions and the LDS adds of what escapes them (285 -> 258 us, 4.2 TB/s; 2^28 pairs 890 -> 880 us,
+// 4.9 TB/s). The next pairs are prefetched and the streamed loads marked non-temporal
+// (2^26 narrow 199 us without the mark). Short calls are latency: 10007 pairs took a memset, two
 // kernels of 8.3 and 7.2 us and a copy, and take one kernel of 9.6 us.
 
 constexpr int EX_COPIES = 4;

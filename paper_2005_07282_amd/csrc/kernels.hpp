@@ -222,7 +222,7 @@ struct LaunchCfg {
 };
 
 // ---- launch functions (return hipError_t of the launch) ----
-// `stride` is the slot capacity of the dot workspaces (see DotWs).
+// `stride` is the slot capacity of a SlotWs.
 
 // Workspace of one standalone dot call.
 struct ExdotWs {
